@@ -523,8 +523,8 @@ hif8_status hif8_als_update(hif8_als_state* st, int found_overflow);
  * value is exact in bfloat16), so results agree with exact arithmetic to within
  * K * 2^-23 * sum_k |a b| * descale per element, and the summation order is fixed for a given
  * shape and tile variant.  NaN / Inf codes propagate by IEEE rules.
- * The matrix-core path needs K % 16 == 0 and 16-byte aligned operands; anything else takes a
- * plain one-element-per-lane kernel.  M, N, K < 2^31.
+ * Any K and any alignment; large products are fastest with K % 16 == 0 and 16-byte aligned
+ * operands.  M, N, K < 2^31.
  *   hif8_gemm_sqerr   no output matrix: *d_err += sum (out[m, n] - ref[m, n])^2 in fp64
  *                     (ref: [M, N] FP32; the caller clears *d_err) -- the "Quantization Error"
  *                     step of Algorithm 1.
@@ -585,7 +585,8 @@ hif8_status hif8_gemm_expanded_sqerr(const uint16_t* a, const uint16_t* b, const
  * hif8_gemm_* on code operands with a workspace: both code matrices are expanded to bfloat16 into the
  * workspace (hif8_expand_bf16) and multiplied by the expanded-operand kernel -- three launches on `stream`, and
  * for matrix-core-bound shapes about two thirds of the time of hif8_gemm_* (whose kernel expands the codes on
- * their way into LDS and is bound by that work).  Arguments, result and error bound as for hif8_gemm_* (the
+ * their way into LDS and is bound by that work).  Small products with up to 128 rows in one operand are taken
+ * straight from the codes instead, in one launch, and leave the workspace unused.  Arguments, result and error bound as for hif8_gemm_* (the
  * result equals that of hif8_gemm_expanded_* on the expanded operands bit for bit); any K and any alignment of
  * the code matrices.
  * workspace: device memory, 16-byte aligned, at least hif8_gemm_workspace_bytes(M, N, K) bytes

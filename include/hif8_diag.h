@@ -63,6 +63,8 @@ int hif8_get_tuning(int key); /* -1 for an unknown key */
  *                                              memory instructions placed one by one between the MFMAs (the choice
  *                                              from two rounds of tiles on); 11 = the same placement with 8
  *                                              wavefronts as 2 x 4 (the choice for a single round)
+ *   both:                                      12 = the small-tile kernel that few output tiles and unaligned code
+ *                                              operands take (its tile still follows the problem size)
  * 0 resets both choices.  Other values: HIF8_ERR_ARG.
  */
 hif8_status hif8_gemm_set_variant(int variant);

@@ -196,36 +196,6 @@ k_gemm_nt(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __
                         reinterpret_cast<double*>(As), wave, WM * WN);
 }
 
-// any K, any alignment: one output element per lane, codes expanded with the integer decoder
-template <int EPI>
-__global__ void __launch_bounds__(256)
-k_gemm_nt_simple(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __restrict__ out,
-                 const float* __restrict__ ref, double* __restrict__ err, uint32_t M, uint32_t N, uint32_t K,
-                 float descale) {
-  const size_t total = (size_t)M * N;
-  double e2 = 0.0;
-  for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (size_t)gridDim.x * blockDim.x) {
-    const uint32_t row = (uint32_t)(idx / N), col = (uint32_t)(idx - (size_t)row * N);
-    const uint8_t* a = A + (size_t)row * K;
-    const uint8_t* b = B + (size_t)col * K;
-    float s = 0.0f;
-    for (uint32_t k = 0; k < K; ++k) s = fmaf(__uint_as_float(decode_bits(a[k])), __uint_as_float(decode_bits(b[k])), s);
-    const float o = __fmul_rn(s, descale);
-    if constexpr (EPI == EPI_F32) reinterpret_cast<float*>(out)[idx] = o;
-    else if constexpr (EPI == EPI_BF16) reinterpret_cast<uint16_t*>(out)[idx] = (uint16_t)narrow_bf16(__float_as_uint(o));
-    else if constexpr (EPI == EPI_F16) reinterpret_cast<_Float16*>(out)[idx] = (_Float16)o;
-    else {
-      const double d = (double)o - (double)ref[idx];
-      e2 = fma(d, d, e2);
-    }
-  }
-  if constexpr (EPI == EPI_ERR) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) e2 += __shfl_xor(e2, off, 64);
-    if ((threadIdx.x & 63u) == 0u) unsafeAtomicAdd(err, e2);
-  }
-}
-
 // ====================================================================================
 // host side
 // ====================================================================================
@@ -305,11 +275,8 @@ static hif8_status gemm_dispatch(const uint8_t* A, const uint8_t* B, void* out, 
   if (s != HIF8_OK) return s;
   const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
   const bool fast = K != 0 && (K % 16) == 0 && aligned_to(A, 16) && aligned_to(B, 16);
-  if (!fast) {
-    hipLaunchKernelGGL(k_gemm_nt_simple<EPI>, dim3(grid_elem(M * N, cus)), dim3(256), 0, st, A, B, out, ref, err, m,
-                       n, k, descale);
-    return finish_launch();
-  }
+  if (!fast || g_gemm_variant == 12 || (g_gemm_variant == 0 && small_problem(M, N)))
+    return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st);
   int variant = g_gemm_variant;
   uint32_t split = 0;
   if (variant == 0 && ragged_round_split(M, N, (size_t)cus, &split)) {
@@ -347,6 +314,9 @@ static hif8_status gemm_ws(const uint8_t* A, const uint8_t* B, void* out, const 
   if (EPI == EPI_ERR ? (!ref || !err) : !out) return HIF8_ERR_NULL;
   if (ws_bytes < need || !aligned_to(ws, 16)) return HIF8_ERR_ARG;
   if (EPI == EPI_ERR && !aligned_to(err, 8)) return HIF8_ERR_ARG;
+  // few rows: straight from the codes, which gives the bits that the expanded operands would give (see small_plan)
+  if (expanded_variant() == 0 && (M < N ? M : N) <= kSmallCodesRows && small_problem(M, N))
+    return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st);
   const size_t ld = expanded_ld(K);
   uint16_t* xa = reinterpret_cast<uint16_t*>(ws);
   uint16_t* xb = xa + M * ld;  // M * ld * 2 bytes is a multiple of 128: still 16-byte aligned
@@ -432,10 +402,13 @@ using namespace hif8gemm;
 extern "C" {
 
 hif8_status hif8_gemm_set_variant(int variant) {
-  if (variant != 0 && variant != 5 && variant != 6 && (variant < 9 || variant > 11)) return HIF8_ERR_ARG;
+  if (variant != 0 && variant != 5 && variant != 6 && (variant < 9 || variant > 12)) return HIF8_ERR_ARG;
   if (variant == 0) {
     g_gemm_variant = 0;
     expanded_variant() = 0;
+  } else if (variant == 12) {
+    g_gemm_variant = 12;
+    expanded_variant() = 12;
   } else if (variant <= 6) {
     g_gemm_variant = variant;
   } else {

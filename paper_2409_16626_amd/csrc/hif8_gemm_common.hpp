@@ -103,7 +103,8 @@ inline size_t expanded_ld(size_t K) { return (K + kExpandK - 1) / kExpandK * kEx
 constexpr size_t kMaxLd = (size_t)1 << 22;
 
 // tile layout of the expanded-operand kernel: 0 = by problem size, 9 = 128 x 128 with 4 wavefronts,
-// 10 / 11 = 256 x 256 as 2 x 2 / 2 x 4 wavefronts with the hand-placed K step (set through hif8_gemm_set_variant)
+// 10 / 11 = 256 x 256 as 2 x 2 / 2 x 4 wavefronts with the hand-placed K step, 12 = the small-tile kernel (set through
+// hif8_gemm_set_variant)
 int& expanded_variant();
 
 hif8_status expand_rows(const uint8_t* codes, size_t rows, size_t K, uint16_t* dst, size_t ld, hipStream_t st);
@@ -113,5 +114,11 @@ hif8_status expand_cols(const uint8_t* codes, size_t rows, size_t cols, uint16_t
 template <int EPI>
 hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const float* ref, double* err, size_t M,
                           size_t N, size_t ld, float descale, hipStream_t st, const Batch& batch, uint32_t pairs);
+
+// ---- few output tiles, any K and alignment of code operands (hif8_gemm_s.hip) ----
+// out = (A x B^T) * descale; expanded: operands are bfloat16 of pitch K (a multiple of 64), else codes of pitch K
+template <int EPI>
+hif8_status gemm_small(const void* A, const void* B, bool expanded, void* out, const float* ref, double* err, size_t M,
+                       size_t N, size_t K, float descale, hipStream_t st);
 
 }  // namespace hif8gemm

@@ -1,0 +1,324 @@
+// Simulated HiF8 GEMM for problems with few output tiles (a handful of tokens against a weight matrix, small products)
+// and for code matrices of any K and any alignment.
+//
+// The tiled kernels (hif8_gemm.hip, hif8_gemm_x.hip) need a 128 x 128 output tile for every compute unit and 16-byte
+// aligned rows; with eight rows of activations their launch has one tile row, most of the chip idles and each
+// workgroup walks the whole of K alone, one memory round trip per step.  Here an output tile is small (16 TM x 16 TN)
+// and the wavefronts of a workgroup split K between them: no barrier in the K loop, a wavefront's loads only ever
+// wait for themselves, and the partial products meet in LDS once, added in wavefront order (the result does not
+// depend on timing).
+//
+// A wavefront reads 128 bytes of 8 rows with one load (8 lanes x 16 bytes a row: whole cache lines; fragments taken
+// straight from global memory, 16 rows in 16 neighbouring lanes, ran at half the speed on rows that are not 16-byte
+// aligned), passes them through its own 2 KiB of LDS per 16-row block, with the loads of the next 128 bytes in flight
+// meanwhile, and expands codes on their way from there into the fragments of v_mfma_f32_16x16x32_bf16 through a
+// 256-entry table in LDS.  That table look-up, one LDS read and three vector instructions per element, is what bounds
+// the code form: without it 8 x 11008 x 4096 takes 11 us, without the loads 14 us, as it is 14 us (45 MB: 7.5 us at
+// the memory's rate); the tiled kernel took 85 us.  Measured against the tiled kernels (us per call, codes / expanded
+// operands): 8 x 4096 x 4096 7.9 / 9.3 (80 / 55), 64 x 4096 x 4096 14.2 / 14.9 (84 / 55), 256 x 4096 x 4096 33 / 23
+// (85 / 55), 512 x 4096 x 11008 150 / 80 (231 / 143); odd K, 509 x 1003 x 2049: 18.6 (3810 with one output per lane).
+//
+// The element order of a K share is the same for both operand kinds, so that one product gives the same bits whether
+// its operands come as codes or expanded.
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+#include <cstdint>
+#include <cstring>
+
+#include "hif8.h"
+#include "hif8_device.hpp"
+#include "hif8_gemm_common.hpp"
+#include "hif8_host.hpp"
+
+namespace hif8gemm {
+
+using namespace hif8dev;
+using namespace hif8host;
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Operand kinds
+enum : int { OP_CODES = 0, OP_BF16 = 1 };
+
+constexpr uint32_t kUnitK = 128;  // K elements of the smallest share of a wavefront
+
+// 16 bytes from any address
+__device__ __forceinline__ u32x4 load16(const uint8_t* p) {
+  u32x4 v;
+  __builtin_memcpy(&v, p, 16);
+  return v;
+}
+
+// The 16 codes at k .. k + 15 of a row of K codes, zero codes past its end; reads inside the row only.
+__device__ __forceinline__ u32x4 load16_tail(const uint8_t* row, uint32_t k, uint32_t K) {
+  u32x4 v = {0u, 0u, 0u, 0u};
+  if (k >= K) return v;
+  const uint32_t rem = K - k;
+  if (rem >= 16u) return load16(row + k);
+  if (K >= 16u) {  // the last 16 codes of the row, moved down
+    unsigned __int128 x;
+    __builtin_memcpy(&x, row + (K - 16u), 16);
+    x >>= 8u * (16u - rem);
+    __builtin_memcpy(&v, &x, 16);
+    return v;
+  }
+  for (uint32_t j = 0; j < rem; ++j) v[j >> 2] |= (uint32_t)row[k + j] << (8u * (j & 3u));
+  return v;
+}
+
+// Position of a code in the table: bit 4 flipped for negative codes, so that the magnitudes a tensor uses most and
+// their negatives (codes 0x40.., 0x60.., 0xC0.., 0xE0.. of values above 2^4) sit in different LDS banks.
+__device__ __forceinline__ uint32_t table_slots(uint32_t w) { return w ^ ((w >> 3) & 0x10101010u); }
+
+// Two neighbouring elements.  The table is the first thing in the kernel's (only) dynamic LDS, at LDS address 0; with
+// the address formed here an index costs one shift of a selected byte.
+__device__ __forceinline__ uint32_t lookup2(uint32_t lo, uint32_t hi) {
+  typedef const __attribute__((address_space(3))) uint16_t* lds_u16;
+  return (uint32_t)*(lds_u16)(lo << 1) | ((uint32_t)*(lds_u16)(hi << 1) << 16);
+}
+
+// 8 codes -> one MFMA fragment
+__device__ __forceinline__ u32x4 expand8(uint32_t w0, uint32_t w1) {
+  w0 = table_slots(w0);
+  w1 = table_slots(w1);
+  return u32x4{lookup2(w0 & 0xFFu, (w0 >> 8) & 0xFFu), lookup2((w0 >> 16) & 0xFFu, w0 >> 24),
+               lookup2(w1 & 0xFFu, (w1 >> 8) & 0xFFu), lookup2((w1 >> 16) & 0xFFu, w1 >> 24)};
+}
+
+// 16 codes -> two fragments
+__device__ __forceinline__ void expand16(const u32x4& c, bf16x8 (&f)[2]) {
+  f[0] = __builtin_bit_cast(bf16x8, expand8(c[0], c[1]));
+  f[1] = __builtin_bit_cast(bf16x8, expand8(c[2], c[3]));
+}
+
+// Rows of a 16-row operand block are staged 128 bytes at a time: 128 codes or 64 bfloat16.
+constexpr uint32_t kRowStage = 128;
+
+// K: codes per row (OP_CODES) or row pitch, a multiple of 64 (OP_BF16).  HALF: at most 8 rows of A (codes): the lanes
+// of the upper eight rows expand the second half of a fragment pair for the lower eight, half the look-ups for A.
+template <int OP, int TM, int TN, int HALF, int EPI>
+__global__ void __launch_bounds__(TM * TN <= 4 ? 1024 : 512)
+k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __restrict__ out,
+         const float* __restrict__ ref, double* __restrict__ err, uint32_t M, uint32_t N, uint32_t K, float descale,
+         uint32_t tiles_m, uint32_t tiles_n) {
+  constexpr int kPitch = TN * 16 + 4;  // floats per row of the reduction buffer: the four lane groups start 16 banks apart
+  constexpr uint32_t kElem = OP == OP_CODES ? 1u : 2u, kBlocks = TM + TN, kPerUnit = OP == OP_CODES ? 1u : 2u;
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // [512] table, then one area per wavefront, reused by the reduction
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, threads = blockDim.x;
+  const uint32_t waves = threads >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t r16 = lane & 15u, q = lane >> 4;
+  uint8_t* const area = smem + 512 + wave * (kBlocks * 16u * kRowStage);
+  float* const red = reinterpret_cast<float*>(smem + 512);  // [wavefronts][16][kPitch]
+  if constexpr (OP == OP_CODES) {
+    if (tid < 256u) reinterpret_cast<uint16_t*>(smem)[table_slots(tid)] = (uint16_t)(decode_bits(tid) >> 16);  // at least 4 wavefronts
+  }
+  // this wavefront's share of K, in units of 128 elements for both operand kinds, as stages of kRowStage bytes per row
+  const uint32_t row_bytes = K * kElem, units = (K + kUnitK - 1u) / kUnitK, stages = (row_bytes + kRowStage - 1u) / kRowStage;
+  uint32_t s0 = (uint32_t)((uint64_t)units * wave / waves) * kPerUnit, s1 = (uint32_t)((uint64_t)units * (wave + 1u) / waves) * kPerUnit;
+  if (s1 > stages) s1 = stages;
+  const uint32_t full = row_bytes / kRowStage;
+  // staging: 8 lanes x 16 bytes per row, 8 rows per load; chunk c of row r sits at position c ^ ((r >> 1) & 7)
+  const uint32_t lrow = lane >> 3, lchunk = lane & 7u;
+  double e2 = 0.0;
+
+  const uint32_t total = tile_order_grid(tiles_m * tiles_n);
+  for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {  // gridDim.x is a multiple of the number of dies
+    uint32_t tile_m, tile_n;
+    if (!tile_order(b, tiles_m, tiles_n, &tile_m, &tile_n)) continue;  // the whole workgroup skips
+    const uint32_t m0 = tile_m * (16 * TM), n0 = tile_n * (16 * TN);
+    // rows past the edge repeat the last one; what they produce is not stored
+    const uint8_t* rows[kBlocks][2];
+#pragma unroll
+    for (int i = 0; i < (int)kBlocks; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t r = (i < TM ? m0 + i * 16u : n0 + (i - TM) * 16u) + h * 8u + lrow, last = (i < TM ? M : N) - 1u;
+        rows[i][h] = (i < TM ? A : B) + (size_t)(r < last ? r : last) * row_bytes;
+      }
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    u32x4 raw[kBlocks][2];
+    auto load_stage = [&](uint32_t s) {
+      const uint32_t at = s * kRowStage + lchunk * 16u;
+      if (s < full) {
+#pragma unroll
+        for (int i = 0; i < (int)kBlocks; ++i)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) raw[i][h] = load16(rows[i][h] + at);
+      } else {
+#pragma unroll
+        for (int i = 0; i < (int)kBlocks; ++i)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) raw[i][h] = load16_tail(rows[i][h], at, row_bytes);
+      }
+    };
+    auto stage_to_lds = [&]() {
+      // through the wavefront's own LDS: a wavefront's LDS operations run in order, so only the compiler needs fences
+#pragma unroll
+      for (int i = 0; i < (int)kBlocks; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t r = h * 8u + lrow;
+          *reinterpret_cast<u32x4*>(area + (i * 16u + r) * kRowStage + ((lchunk ^ ((r >> 1) & 7u)) * 16u)) = raw[i][h];
+        }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    };
+    auto compute_stage = [&]() {
+      auto frag = [&](int block, uint32_t chunk) {
+        return *reinterpret_cast<const u32x4*>(area + (block * 16u + r16) * kRowStage + ((chunk ^ ((r16 >> 1) & 7u)) * 16u));
+      };
+      // element order within a unit: 16 q + 0..7, 16 q + 8..15, then the same 64 further on
+#pragma unroll
+      for (int p = 0; p < (OP == OP_CODES ? 2 : 1); ++p) {
+        bf16x8 fa[TM][2], fb[2];
+        auto get = [&](int block, bf16x8 (&f)[2]) {
+          if constexpr (OP == OP_CODES) {
+            expand16(frag(block, p * 4 + q), f);
+          } else {
+            f[0] = __builtin_bit_cast(bf16x8, frag(block, 2 * q));
+            f[1] = __builtin_bit_cast(bf16x8, frag(block, 2 * q + 1));
+          }
+        };
+        if constexpr (HALF != 0) {
+          static_assert(OP == OP_CODES && TM == 1, "one row block of codes");
+          const uint32_t r8 = r16 & 7u;
+          const u32x4 c = *reinterpret_cast<const u32x4*>(area + r8 * kRowStage + (((p * 4 + q) ^ (r8 >> 1)) * 16u));
+          const u32x4 own = r16 < 8u ? expand8(c[0], c[1]) : expand8(c[2], c[3]);
+          u32x4 other;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) other[v] = __builtin_amdgcn_update_dpp(0, own[v], 0x128, 0xF, 0xF, true);  // row_ror:8
+          fa[0][0] = __builtin_bit_cast(bf16x8, own);
+          fa[0][1] = __builtin_bit_cast(bf16x8, other);
+        } else {
+#pragma unroll
+          for (int i = 0; i < TM; ++i) get(i, fa[i]);
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          get(TM + j, fb);
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][h], fb[h], acc[i][j], 0, 0, 0);
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    };
+    if (s0 < s1) load_stage(s0);
+    __syncthreads();  // table written; reduction buffer of the previous tile read
+    for (uint32_t s = s0; s < s1; ++s) {
+      stage_to_lds();
+      if (s + 1 < s1) load_stage(s + 1);
+      compute_stage();
+    }
+    __syncthreads();  // staging areas free: the reduction uses the same LDS
+
+    // the wavefronts' partial tiles, 16 rows at a time, added in wavefront order
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if (i > 0) __syncthreads();
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[(wave * 16u + q * 4u + v) * kPitch + j * 16 + r16] = acc[i][j][v];
+      __syncthreads();
+      for (uint32_t e = tid; e < 16u * (TN * 16); e += threads) {
+        const uint32_t r = e / (TN * 16), c = e % (TN * 16), row = m0 + i * 16u + r, col = n0 + c;
+        float sum = red[r * kPitch + c];
+        for (uint32_t w = 1; w < waves; ++w) sum += red[(w * 16u + r) * kPitch + c];
+        if (row < M && col < N) {
+          const float o = __fmul_rn(sum, descale);
+          if constexpr (EPI == EPI_ERR) {
+            const double d = (double)o - (double)ref[(size_t)row * N + col];
+            e2 = fma(d, d, e2);
+          } else {
+            store_one<EPI>(out, (size_t)row * N + col, o);
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if constexpr (EPI == EPI_ERR) {
+    double* scratch = reinterpret_cast<double*>(red);  // free: every tile ends with a barrier
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) e2 += __shfl_xor(e2, off, 64);
+    if (lane == 0) scratch[wave] = e2;
+    __syncthreads();
+    if (tid == 0) {
+      double t = 0.0;
+      for (uint32_t w = 0; w < waves; ++w) t += scratch[w];
+      unsafeAtomicAdd(err, t);
+    }
+  }
+}
+
+// ====================================================================================
+// host side
+// ====================================================================================
+template <int OP, int TM, int TN, int HALF, int EPI>
+static hif8_status launch_s(const void* A, const void* B, void* out, const float* ref, double* err, uint32_t M, uint32_t N,
+                            uint32_t K, float descale, uint32_t waves, hipStream_t st) {
+  const uint64_t tiles_m = ((uint64_t)M + 16 * TM - 1) / (16 * TM), tiles_n = ((uint64_t)N + 16 * TN - 1) / (16 * TN);
+  if (tiles_m * tiles_n > 0x7FFFFFF0ull) return HIF8_ERR_ARG;
+  const uint32_t total = tile_order_grid((uint32_t)(tiles_m * tiles_n)), most = 1u << 20;  // threads of a launch are counted in 32 bits
+  const size_t stage = (size_t)waves * (TM + TN) * 16 * kRowStage, red = (size_t)waves * 16 * (TN * 16 + 4) * 4;
+  const size_t smem = 512 + (stage > red ? stage : red);
+  if (smem > 65536) {
+    static bool attr_set[64] = {};
+    int dev = 0;
+    if (!hip_ok(hipGetDevice(&dev))) return HIF8_ERR_HIP;
+    if (dev < 0 || dev >= 64) return HIF8_ERR_ARG;
+    if (!attr_set[dev]) {
+      if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_s<OP, TM, TN, HALF, EPI>),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)))
+        return HIF8_ERR_HIP;
+      attr_set[dev] = true;
+    }
+  }
+  hipLaunchKernelGGL((k_gemm_s<OP, TM, TN, HALF, EPI>), dim3(total < most ? total : most), dim3(64 * waves), smem, st,
+                     reinterpret_cast<const uint8_t*>(A), reinterpret_cast<const uint8_t*>(B), out, ref, err, M, N, K, descale,
+                     (uint32_t)tiles_m, (uint32_t)tiles_n);
+  return finish_launch();
+}
+
+template <int OP, int EPI>
+static hif8_status gemm_small_op(const void* A, const void* B, void* out, const float* ref, double* err, size_t M, size_t N,
+                                 size_t K, float descale, hipStream_t st) {
+  const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
+  const SmallPlan p = small_plan(M, N, OP == OP_CODES);
+  switch (p.tm * 10 + p.tn) {
+    case 11:
+      if constexpr (OP == OP_CODES) {
+        if (M <= 8) return launch_s<OP, 1, 1, 1, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
+      }
+      return launch_s<OP, 1, 1, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
+    case 12: return launch_s<OP, 1, 2, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
+    case 22: return launch_s<OP, 2, 2, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
+    case 24: return launch_s<OP, 2, 4, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
+    default: return launch_s<OP, 4, 4, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
+  }
+}
+
+template <int EPI>
+hif8_status gemm_small(const void* A, const void* B, bool expanded, void* out, const float* ref, double* err, size_t M, size_t N,
+                       size_t K, float descale, hipStream_t st) {
+  return expanded ? gemm_small_op<OP_BF16, EPI>(A, B, out, ref, err, M, N, K, descale, st)
+                  : gemm_small_op<OP_CODES, EPI>(A, B, out, ref, err, M, N, K, descale, st);
+}
+
+template hif8_status gemm_small<EPI_F32>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t);
+template hif8_status gemm_small<EPI_BF16>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t);
+template hif8_status gemm_small<EPI_F16>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t);
+template hif8_status gemm_small<EPI_ERR>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t);
+
+}  // namespace hif8gemm

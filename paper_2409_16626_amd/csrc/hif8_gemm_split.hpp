@@ -20,6 +20,41 @@ inline bool ragged_round_split(size_t M, size_t N, size_t cus, uint32_t* split) 
   return true;
 }
 
+// Products with at most this many rows on one side run straight from the codes in hif8_gemm_ws_* when they go to the
+// small-tile kernel; above it expanding first is faster (128 x 11008 x 4096: 52 us against 55; 384 x 4096 x 4096:
+// 50 against 44; 512 x 4096 x 11008: 150 against 100).
+constexpr size_t kSmallCodesRows = 128;
+
+// Which problems go to the small-tile kernel (hif8_gemm_s.hip) although the tiled kernels could run them.  The tiled
+// kernels take a whole K walk (K = 4096: 85 us on codes, 55 us expanded) however few tiles there are, the small-tile
+// kernel's time goes with M N: at K = 4096 they meet between M N = 2.8 M (256 x 11008: codes 92 against 93 us,
+// expanded 54 against 58) and 4.2 M (384 x 11008: 135 / 120, 73 / 59; 1024 x 4096: 112 / 91, 59 / 56), at K = 11008
+// likewise (512 x 4096: 150 / 231, 80 / 143; 1024 x 4096: 278 / 232, 141 / 145).  With up to 32 rows on either side
+// three quarters of a tile would be padding, so such products stay with the small tiles whatever the other side is.
+inline bool small_problem(size_t M, size_t N) {
+  const size_t s = M < N ? M : N, l = M < N ? N : M;
+  return s <= 32 || l <= (size_t)3 * 1048576 / s;
+}
+
+// Tile (16 tm x 16 tn) and wavefronts per workgroup of the small-tile kernel.  The wavefronts split K, so a wavefront
+// count is part of the result's rounding: below 128 rows it is the same for code and for expanded operands (there
+// hif8_gemm_ws_* runs on the codes what hif8_gemm_expanded_* runs on expanded operands).  The smallest tiles win while
+// one operand has few rows (8 x 11008 x 4096 on codes: 1 x 1 14 us, 1 x 2 17, 2 x 4 20); more rows want the operand
+// reuse of larger ones, and fewer wavefronts once the tiles alone fill the chip (64 x 4096 x 4096: 2 x 2 with 16
+// wavefronts 14.2 us, with 8 16.2; 64 x 11008 x 4096: 4 wavefronts 33.6, 16 41.8).
+struct SmallPlan {
+  uint32_t tm, tn, waves;
+};
+inline SmallPlan small_plan(size_t M, size_t N, bool codes) {
+  auto tiles = [&](size_t tm, size_t tn) { return ((M + 16 * tm - 1) / (16 * tm)) * ((N + 16 * tn - 1) / (16 * tn)); };
+  const size_t s = M < N ? M : N;
+  if (s <= 16) return {1, 1, 8};
+  if (s <= 32) return tiles(2, 4) >= 128 ? SmallPlan{2, 4, 8} : SmallPlan{1, 2, 8};
+  if (s <= 64) return {2, 2, tiles(2, 2) <= 256 ? 16u : 4u};
+  if (s <= kSmallCodesRows || (codes && small_problem(M, N))) return {2, 4, tiles(2, 4) <= 256 ? 8u : 4u};
+  return {4, 4, !codes && tiles(4, 4) <= 256 ? 8u : 4u};
+}
+
 // Workgroup -> tile of the expanded-operand kernel.  The hardware deals consecutive workgroups round-robin over the
 // kXcds accelerator dies (XCDs), each with its own L2.  Workgroup b therefore takes tile number
 // (b % kXcds) * per_xcd + b / kXcds of a tile order that walks groups of kGroupM tile rows column by column: the

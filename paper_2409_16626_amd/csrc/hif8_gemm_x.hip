@@ -428,6 +428,8 @@ hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const
   // a single round, where the second wavefront per SIMD covers the start and the end of the tile.
   const size_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256) * (size_t)pairs;
   int variant = expanded_variant();
+  if (pairs == 1 && (variant == 12 || (variant == 0 && small_problem(M, N))))
+    return gemm_small<EPI>(A, B, true, out, ref, err, M, N, ld, descale, st);
   uint32_t split = 0;
   if (variant == 0 && pairs == 1 && ragged_round_split(M, N, (size_t)cus, &split)) {
     // complete rounds of 256 x 256 tiles, then the remaining columns in 128 x 128 tiles (second launch)

@@ -204,3 +204,25 @@ def test_gemm_tile_order_is_a_bijection_and_compact_per_die(dev):
         rows = {t // tn for t in tiles}
         cols = {t % tn for t in tiles}
         assert len(rows) <= 8 and len(cols) <= 5, (die, sorted(rows), sorted(cols))
+
+
+def test_small_gemm_plan(dev):
+    """Small-tile GEMM kernel: only the tiles that exist, 4 to 16 wavefronts (16 only with the tile whose kernel allows
+    them), tile areas within the 160 KiB of LDS, and below 129 rows the same K split for codes and expanded operands."""
+    dev.devfn_small_plan.restype = ctypes.c_uint32
+    dev.devfn_small_plan.argtypes = [ctypes.c_size_t, ctypes.c_size_t, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_uint32)]
+
+    def plan(M, N, codes, force=1):
+        w = ctypes.c_uint32(0)
+        return dev.devfn_small_plan(M, N, codes, force, ctypes.byref(w)), w.value
+
+    assert plan(8, 11008, 1, 0) == (110, 8) and plan(2048, 11008, 0, 0)[0] == 0 and plan(32, 1 << 30, 1, 0)[0] != 0
+    rng = np.random.default_rng(4)
+    for _ in range(3000):
+        M, N = (int(2.0 ** rng.uniform(0, 20)) for _ in range(2))
+        got = [plan(M, N, c) for c in (0, 1)]
+        for t, w in got:
+            assert t in (110, 120, 220, 240, 440) and w in (4, 8, 16) and (w <= 8 or t == 220)
+            assert 512 + w * (t // 100 + t // 10 % 10) * 16 * 128 <= 160 * 1024
+        if min(M, N) <= 128:
+            assert got[0][1] == got[1][1]

@@ -1,0 +1,105 @@
+"""GPU parity for the small-tile GEMM kernel (few output tiles, code matrices of any K and alignment) against the
+fp64 oracle, with the bound of test_gpu_gemm.py: K * 2^-23 * sum_k |a b| * descale per element."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import gemm_oracle as go
+from oracle import hif8_oracle as orc
+from gpu_util import dev
+from test_gpu_gemm import check, h, random_codes  # noqa: F401  (h is the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def on_gpu(codes, off=0):
+    buf = torch.zeros(codes.size + off + 1, dtype=torch.uint8, device=dev())
+    buf[off:off + codes.size] = torch.from_numpy(codes.reshape(-1)).to(dev())
+    return buf[off:off + codes.size]
+
+
+# every tile of the plan: 1 x 1 with and without the half-row form (8 / 9 / 16 rows), 1 x 2 and 2 x 4 (17 .. 32 rows), 2 x 2
+# with 16 and 4 wavefronts (33 .. 64), 2 x 4 with 8 and 4 (65 .. 128), 2 x 4 / 4 x 4 above; edges of the 16-row blocks;
+# K below, at and above one 128-element share, more and fewer shares than wavefronts, remainders of 1, 15, 16, 17
+SHAPES = [(1, 1, 1), (3, 2, 15), (8, 64, 128), (9, 65, 127), (16, 15, 129), (7, 8200, 144), (17, 33, 1025), (32, 8193, 17),
+          (33, 40, 2047), (64, 2100, 272), (64, 9000, 130), (65, 70, 1000), (128, 1024, 400), (100, 9000, 131), (129, 300, 513),
+          (300, 257, 2049), (2000, 2100, 33), (300, 12, 700), (5000, 3, 31)]
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+@pytest.mark.parametrize("off", [0, 1])
+def test_small_gemm_codes_match_oracle(h, M, N, K, off):
+    rng = np.random.default_rng(M + 5 * N + 11 * K + off)
+    for kind in ("cast_normal", "uniform_codes"):
+        ca, cb = random_codes(rng, (M, K), kind), random_codes(rng, (N, K), kind)
+        out = torch.full((M + 1, N), 7.0, dtype=torch.float32, device=dev())
+        h.hif8_gemm_set_variant(12 if off == 0 else 0)
+        h.hif8_gemm_f32(on_gpu(ca, off), on_gpu(cb, off), out, M, N, K, 2.0, 0.5)
+        torch.cuda.synchronize()
+        h.hif8_gemm_set_variant(0)
+        check(out[:M].cpu().numpy(), ca, cb, 2.0, 0.5)
+        assert torch.all(out[M] == 7.0)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 100, 100), (8, 4100, 300), (20, 70, 1001), (32, 9000, 65), (64, 2100, 272), (50, 9000, 257),
+                                   (128, 700, 900), (129, 700, 900), (256, 4096, 130), (700, 40, 1111)])
+def test_small_gemm_same_bits_from_codes_workspace_and_expanded(h, M, N, K):
+    """hif8_gemm_ws_* takes the codes directly below 129 rows and expands first above: the bits of the expanded form."""
+    rng = np.random.default_rng(M + N + K)
+    ca, cb = random_codes(rng, (M, K), "cast_normal"), random_codes(rng, (N, K), "cast_normal")
+    a, b, ld = on_gpu(ca), on_gpu(cb), h.hif8_expanded_ld(K)
+    ws = torch.empty(h.hif8_gemm_workspace_bytes(M, N, K), dtype=torch.uint8, device=dev())
+    xa, xb = (torch.empty(r, ld, dtype=torch.bfloat16, device=dev()) for r in (M, N))
+    h.hif8_expand_bf16(a, M, K, xa, ld)
+    h.hif8_expand_bf16(b, N, K, xb, ld)
+    one, two = (torch.empty(M, N, dtype=torch.float32, device=dev()) for _ in range(2))
+    h.hif8_gemm_ws_f32(a, b, one, M, N, K, ws, 8.0, 0.5)
+    h.hif8_gemm_expanded_f32(xa, xb, two, M, N, K, ld, 8.0, 0.5)
+    check(two.cpu().numpy(), ca, cb, 8.0, 0.5)
+    assert torch.equal(one.view(torch.int32), two.view(torch.int32))
+    if min(M, N) <= 128:
+        h.hif8_gemm_f32(a, b, one, M, N, K, 8.0, 0.5)
+        assert torch.equal(one.view(torch.int32), two.view(torch.int32))
+
+
+def test_small_gemm_16bit_outputs_and_squared_error(h):
+    rng = np.random.default_rng(21)
+    for M, N, K in ((8, 96, 333), (48, 130, 512), (200, 150, 257)):
+        ca, cb = random_codes(rng, (M, K), "cast_normal"), random_codes(rng, (N, K), "cast_normal")
+        a, b = on_gpu(ca), on_gpu(cb)
+        o32, o16 = (torch.empty(M, N, dtype=d, device=dev()) for d in (torch.float32, torch.bfloat16))
+        oh = torch.empty(M, N, dtype=torch.float16, device=dev())
+        for call, o in ((h.hif8_gemm_f32, o32), (h.hif8_gemm_bf16, o16), (h.hif8_gemm_f16, oh)):
+            call(a, b, o, M, N, K, 8.0, 8.0)
+        assert torch.equal(o16, o32.to(torch.bfloat16)) and torch.equal(oh, o32.to(torch.float16))
+        ref = (o32 * 1.01 + 0.5).contiguous()
+        err = torch.zeros(1, dtype=torch.float64, device=dev())
+        h.hif8_gemm_sqerr(a, b, ref, M, N, K, 8.0, 8.0, err)
+        want = float(((o32.double() - ref.double()) ** 2).sum())
+        assert abs(err.item() - want) <= 1e-12 * want
+
+
+def test_small_gemm_special_codes_follow_ieee(h):
+    rng = np.random.default_rng(22)
+    for M, N in ((7, 20), (40, 50)):
+        K = 150
+        ca, cb = random_codes(rng, (M, K), "cast_normal"), random_codes(rng, (N, K), "cast_normal")
+        ca[1, 5], ca[2, 149], ca[5, 140] = 0x6F, 0x80, 0xEF          # +Inf, NaN, -Inf (meeting a zero below)
+        cb[11, 140] = 0x00
+        out = torch.zeros(M, N, dtype=torch.float32, device=dev())
+        h.hif8_gemm_f32(on_gpu(ca), on_gpu(cb), out, M, N, K, 1.0, 1.0)
+        got, want = out.cpu().numpy(), go.gemm_hif8(ca, cb)
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.isnan(want[2]).all() and np.isnan(want[5, 11])
+        assert np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isneginf(got), np.isneginf(want))
+
+
+def test_small_gemm_more_tiles_than_workgroups(h):
+    """2^20 workgroups walk more tiles than that (a launch counts its threads in 32 bits)."""
+    M, N, K = (1 << 24) + 37, 2, 3
+    rng = np.random.default_rng(23)
+    vals = np.array([0x00, 0x08, 0x10, 0x14, 0x20, 0x88, 0x90], np.uint8)      # 0, 1, 2, 3, 4, -1, -2: sums exact
+    ca, cb = rng.choice(vals, size=(M, K)), rng.choice(vals, size=(N, K))
+    out = torch.empty(M, N, dtype=torch.float32, device=dev())
+    h.hif8_gemm_f32(on_gpu(ca), on_gpu(cb), out, M, N, K, 1.0, 1.0)
+    v = np.array([orc.decode_value(c) if np.isfinite(orc.decode_value(c)) else 0.0 for c in range(256)], np.float32)
+    assert np.array_equal(out.cpu().numpy(), v[ca] @ v[cb].T)
