@@ -58,11 +58,9 @@ int hif8_get_tuning(int key); /* -1 for an unknown key */
  *   code-operand kernel (hif8_gemm_*):         5 = 256 x 256 x 32 workgroup tile, 8 wavefronts as 4 x 2 (the
  *                                              choice when there is such a tile for every compute unit);
  *                                              6 = 128 x 128 x 32, 4 wavefronts, two workgroups per CU
- *   expanded-operand kernel (hif8_gemm_expanded_*): 9 = 128 x 128 x 64, 4 wavefronts (the choice below one large
- *                                              tile per compute unit); 10 = 256 x 256 x 64, 4 wavefronts as 2 x 2,
- *                                              memory instructions placed one by one between the MFMAs (the choice
- *                                              from two rounds of tiles on); 11 = the same placement with 8
- *                                              wavefronts as 2 x 4 (the choice for a single round)
+ *   expanded-operand kernel (hif8_gemm_expanded_*), 4 wavefronts as 2 x 2 each: 9 = 128 x 128 x 64, two workgroups
+ *                                              per CU; 10 = 256 x 256 x 64; 11 = 256 x 192 x 64 (the choice is the
+ *                                              one with the shortest sum of rounds)
  *   both:                                      12 = the small-tile kernel that few output tiles and unaligned code
  *                                              operands take (its tile still follows the problem size)
  * 0 resets both choices.  Other values: HIF8_ERR_ARG.

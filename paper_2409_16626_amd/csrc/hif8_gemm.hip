@@ -78,15 +78,7 @@ template <int WM, int WN, int TM, int TN, int BK, int EPI>
 __global__ void __launch_bounds__(64 * WM * WN)
 k_gemm_nt(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __restrict__ out,
           const float* __restrict__ ref, double* __restrict__ err, uint32_t M, uint32_t N, uint32_t K,
-          float descale, const uint16_t* __restrict__ g_lut, uint32_t tiles_n, uint32_t col_begin, Batch batch) {
-  // batched form (the scale search of Algorithm 1): blockIdx.y = pair (i, j) of code matrices
-  if (batch.nb != 0u) {
-    const uint32_t bi = blockIdx.y / batch.nb, bj = blockIdx.y - bi * batch.nb;
-    A += (size_t)bi * batch.a_stride;
-    B += (size_t)bj * batch.b_stride;
-    err += blockIdx.y;
-    descale = pow2f(-(batch.e_base + (int)bi + (int)bj));
-  }
+          float descale, const uint16_t* __restrict__ g_lut, uint32_t tiles_n, uint32_t col_begin) {
   constexpr int kThreads = 64 * WM * WN;
   constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
   constexpr int LDA = BK + kPad;                       // LDS row stride in bf16
@@ -171,7 +163,7 @@ k_gemm_nt(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
     }
     store_tiles(set, buf ^ 1);
     __syncthreads();
@@ -191,9 +183,10 @@ k_gemm_nt(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __
   }
   if (kt < nk) k_step(kt, 0, 1);
 
-  // the last K step ended with a barrier: the tile buffers (behind the table) are free for the error sums
-  epilogue<EPI, TM, TN>(acc, out, ref, err, M, N, m0 + wm * TM * 32, n0 + wn * TN * 32, lane, descale,
-                        reinterpret_cast<double*>(As), wave, WM * WN);
+  // the last K step ended with a barrier: the tile buffers (behind the table) are free for the epilogue
+  static_assert(WM * WN * epilogue_lds(2) <= 4 * (BM + BN) * LDA, "LDS of the epilogue");
+  epilogue<EPI, TM, TN, 2>(acc, out, ref, err, M, N, m0 + wm * TM * 32, n0 + wn * TN * 32, lane, descale,
+                           reinterpret_cast<uint8_t*>(As), wave, WM * WN);
 }
 
 // ====================================================================================
@@ -232,8 +225,7 @@ constexpr size_t smem_bytes() {
 template <int WM, int WN, int TM, int TN, int BK, int EPI>
 static hif8_status launch_tiled(const uint8_t* A, const uint8_t* B, void* out, const float* ref, double* err,
                                 uint32_t M, uint32_t N, uint32_t K, float descale, const uint16_t* lut,
-                                hipStream_t st, const Batch& batch = Batch{0u, 0, 0, 0}, uint32_t pairs = 1,
-                                uint32_t col_begin = 0, uint32_t col_end = 0xFFFFFFFFu) {
+                                hipStream_t st, uint32_t col_begin = 0, uint32_t col_end = 0xFFFFFFFFu) {
   if (col_end > N) col_end = N;
   if (col_begin >= col_end) return HIF8_OK;
   constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
@@ -249,8 +241,8 @@ static hif8_status launch_tiled(const uint8_t* A, const uint8_t* B, void* out, c
   }
   const uint32_t tiles_m = (M + BM - 1) / BM, tiles_n = (col_end - col_begin + BN - 1) / BN;
   if ((uint64_t)tiles_m * tiles_n > 0x7FFFFFFFull) return HIF8_ERR_ARG;
-  hipLaunchKernelGGL((k_gemm_nt<WM, WN, TM, TN, BK, EPI>), dim3(tiles_m * tiles_n, pairs), dim3(64 * WM * WN), smem, st,
-                     A, B, out, ref, err, M, N, K, descale, lut, tiles_n, col_begin, batch);
+  hipLaunchKernelGGL((k_gemm_nt<WM, WN, TM, TN, BK, EPI>), dim3(tiles_m * tiles_n), dim3(64 * WM * WN), smem, st,
+                     A, B, out, ref, err, M, N, K, descale, lut, tiles_n, col_begin);
   return finish_launch();
 }
 
@@ -281,9 +273,9 @@ static hif8_status gemm_dispatch(const uint8_t* A, const uint8_t* B, void* out, 
   uint32_t split = 0;
   if (variant == 0 && ragged_round_split(M, N, (size_t)cus, &split)) {
     // complete rounds of 256 x 256 tiles, then the remaining columns in 128 x 128 tiles (second launch)
-    s = launch_tiled<4, 2, 2, 4, 32, EPI>(A, B, out, ref, err, m, n, k, descale, lut, st, Batch{0u, 0, 0, 0}, 1u, 0u, split);
+    s = launch_tiled<4, 2, 2, 4, 32, EPI>(A, B, out, ref, err, m, n, k, descale, lut, st, 0u, split);
     if (s != HIF8_OK) return s;
-    return launch_tiled<2, 2, 2, 2, 32, EPI>(A, B, out, ref, err, m, n, k, descale, lut, st, Batch{0u, 0, 0, 0}, 1u, split, n);
+    return launch_tiled<2, 2, 2, 2, 32, EPI>(A, B, out, ref, err, m, n, k, descale, lut, st, split, n);
   }
   if (variant == 0)  // 256 x 256 tiles once there is one for every compute unit, else 128 x 128 (two workgroups per CU)
     variant = (((M + 255) / 256) * ((N + 255) / 256) >= (size_t)cus) ? 5 : 6;
@@ -324,7 +316,7 @@ static hif8_status gemm_ws(const uint8_t* A, const uint8_t* B, void* out, const 
   if (s != HIF8_OK) return s;
   s = expand_rows(B, N, K, xb, ld, st);
   if (s != HIF8_OK) return s;
-  return gemm_expanded<EPI>(xa, xb, out, ref, err, M, N, ld, descale, st, Batch{0u, 0, 0, 0}, 1u);
+  return gemm_expanded<EPI>(xa, xb, out, ref, err, M, N, ld, descale, st);
 }
 
 // position of the smallest finite entry of err[rows * cols] -> best[0] = e_row_lo + row,
@@ -384,9 +376,9 @@ static hif8_status calibrate_layer(const void* a, const void* w, const float* o_
     s = expand_rows(ws_codes, N, K, ws_w + w_elems * j, ld, st);
     if (s != HIF8_OK) return s;
   }
-  // all pairs in one launch: the grid's second dimension runs over the search square
-  const Batch batch{(uint32_t)ew_count, ea_lo + ew_lo, a_elems, w_elems};
-  s = gemm_expanded<EPI_ERR>(ws_a, ws_w, nullptr, o_ref, d_err, M, N, ld, 1.0f, st, batch, (uint32_t)(ea_count * ew_count));
+  // all pairs in one launch
+  const Batch batch{(uint32_t)ea_count, (uint32_t)ew_count, ea_lo + ew_lo, a_elems, w_elems};
+  s = gemm_expanded<EPI_ERR>(ws_a, ws_w, nullptr, o_ref, d_err, M, N, ld, 1.0f, st, batch);
   if (s != HIF8_OK) return s;
   if (d_best) {
     hipLaunchKernelGGL(k_argmin_pair, dim3(1), dim3(64), 0, st, d_err, ea_count, ew_count, ea_lo, ew_lo, d_best);

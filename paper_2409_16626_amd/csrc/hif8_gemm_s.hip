@@ -36,7 +36,6 @@ namespace hif8gemm {
 using namespace hif8dev;
 using namespace hif8host;
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Operand kinds

@@ -20,6 +20,37 @@ inline bool ragged_round_split(size_t M, size_t N, size_t cus, uint32_t* split) 
   return true;
 }
 
+// Tiles of the expanded-operand kernel: 256 x 256 or 256 x 192, one workgroup per compute unit, or 128 x 128, two.  A launch
+// takes as long as its rounds of resident workgroups, so the tile with the shortest sum of rounds is taken.  A round
+// costs, relative to each other, 13 (256 x 256), 10 (256 x 192), 7.6 (128 x 128, two per compute unit) or 6.2 (128 x 128,
+// one): measured 84, 63.8, 47.7 and 40.7 us at K = 4096.  The column split adds a launch (a twelfth of a large round).
+// Measured in us (256 x 256 / 256 x 192 / 128 x 128): 2048 x 11008 x 4096 151 / 128 / 138, 2048 x 4096 x 11008
+// 183 / 164 / 131, 11008 x 4096 x 2048 132 / 142 / 148, 4096^3 84 / 126 / 99.
+enum : int { TILE_256 = 0, TILE_192 = 1, TILE_128 = 2, TILE_SPLIT = 3 };
+inline uint64_t tile_cost(int tile, size_t M, size_t N, size_t pairs, size_t cus) {
+  const uint64_t bm = tile == TILE_128 ? 128 : 256, bn = tile == TILE_256 ? 256 : tile == TILE_192 ? 192 : 128;
+  const uint64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * (uint64_t)pairs;
+  if (tile != TILE_128) return (tiles + cus - 1) / cus * (tile == TILE_256 ? 130u : 100u);
+  const uint64_t rest = tiles % (2 * cus);
+  return tiles / (2 * cus) * 76u + (rest == 0 ? 0u : rest <= cus ? 62u : 76u);
+}
+inline int tile_plan(size_t M, size_t N, size_t pairs, size_t cus, uint32_t* split) {
+  int best = TILE_256;
+  uint64_t cost = tile_cost(TILE_256, M, N, pairs, cus);
+  for (int t = TILE_192; t <= TILE_128; ++t) {
+    const uint64_t c = tile_cost(t, M, N, pairs, cus);
+    if (c < cost) {
+      cost = c;
+      best = t;
+    }
+  }
+  // complete rounds of 256 x 256 tiles, then the remaining columns in 128 x 128 tiles
+  if (pairs == 1 && ragged_round_split(M, N, cus, split) &&
+      tile_cost(TILE_256, M, *split, 1, cus) + tile_cost(TILE_128, M, N - *split, 1, cus) + 10u < cost)
+    best = TILE_SPLIT;
+  return best;
+}
+
 // Products with at most this many rows on one side run straight from the codes in hif8_gemm_ws_* when they go to the
 // small-tile kernel; above it expanding first is faster (128 x 11008 x 4096: 52 us against 55; 384 x 4096 x 4096:
 // 50 against 44; 512 x 4096 x 11008: 150 against 100).

@@ -8,19 +8,20 @@
 //   expand:  X[r, k] = bf16(value(codes[r, k]))  for k < K,  0 for K <= k < ld,  ld = K rounded up to 64
 //   GEMM:    O[M, N] = (A[M, ld] x B[N, ld]^T) * descale
 //
-// Kernel design (gfx950): a workgroup of WM x WN wavefronts owns a (WM TM 32) x (WN TN 32) tile of O.
-// K advances in steps of 64 through two LDS stages.  Tiles go from global memory straight into LDS
-// (buffer_load_dwordx4 ... lds: 64 lanes x 16 bytes land contiguously), so the operands never pass
+// Kernel design (gfx950): a workgroup of 2 x 2 wavefronts owns a (32 TA) x (32 TB) tile of O, each wavefront TA x TB blocks
+// of v_mfma_f32_16x16x32_bf16.  K advances in steps of 64 through two LDS stages.  Tiles go from global memory straight
+// into LDS (buffer_load_dwordx4 ... lds: 64 lanes x 16 bytes land contiguously), so the operands never pass
 // through registers.  A tile row is 128 bytes = 8 chunks of 16 bytes; chunk position p of tile row r
 // holds k-chunk p ^ ((r >> 1) & 7).  LDS has 64 banks of 4 bytes and serves a 16-byte read 16 lanes
 // at a time: the 16 lanes of a fragment read touch 16 consecutive rows of one k-chunk, which the
 // permutation spreads over all 16 chunk slots of two adjacent rows -- no bank conflicts, no padding.
-// Fragments are double-buffered in registers, and the workgroup barrier sits before the last of
-// the four MFMA groups of a K step, so the first fragments of the next step are fetched under it.
+// Fragments are double-buffered in registers, and the workgroup barrier sits between the two halves of a K step, so
+// that the first fragments of the next step are fetched under the MFMAs of the second.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "hif8.h"
 #include "hif8_device.hpp"
@@ -37,218 +38,195 @@ constexpr int kRowBytes = kBK * 2;  // one tile row in LDS
 constexpr int kRowsPerLoad = 8;     // a wavefront-wide 16-byte load covers 8 tile rows
 
 // s_waitcnt immediates (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[15:14])
-constexpr int kWaitLgkm0 = 0xC07F;        // lgkmcnt(0)
 constexpr int kWaitVm0Lgkm0 = 0x0070;     // vmcnt(0) lgkmcnt(0)
 constexpr int kWaitVm0 = 0x0F70;          // vmcnt(0)
 constexpr int kRsrcFlags = 0x00020000;    // word 3 of a raw (unstructured, untyped) buffer descriptor on gfx9-family parts
 
-template <int WM, int WN, int TM, int TN, int EPI, int FINE = 0>
-__global__ void __launch_bounds__(64 * WM * WN)
+// The K loop of a 256 x 256 tile is bound by the matrix cores at the clock that the power limit leaves them, provided that
+// a wavefront (alone on its SIMD) never makes them wait:
+//   * v_mfma_f32_16x16x32_bf16 costs less power than the 32 x 32 x 16 shape on operands with HiF8's few mantissa bits
+//     (in registers only 1.97 PFLOP/s against 1.80), and with 16 cycles each there is a place for a memory instruction
+//     every 16 cycles.
+//   * One fragment read behind each of the first TA + TB MFMAs of a half step; a tile load behind every kLoadEvery-th
+//     MFMA of the half behind the barrier.  A compute unit's address path needs 16 cycles for each of them, times four
+//     wavefronts, which is what one load per four MFMAs leaves it: one per two stalls the issue of the MFMAs, and a load
+//     that waits for the next half step arrives too late for its barrier (8192^3: 667 us; one load per two MFMAs 684, half
+//     of the loads in the next half step 767).
+//   * MFMAs in inline assembly with the accumulator as one operand: built from the intrinsic, the loop moved 16 of the
+//     256 accumulator registers to and fro in every step and waited for MFMAs to do so (710 us).
+// Measured (us; with 32 x 32 x 16 MFMAs, all loads behind the last 16 of a K step / now): 8192^3 727 / 667, 4096^3 97 / 84,
+// 2048 x 4096 x 11008 in 128 x 128 tiles 140 / 131; the scale search of a 2048 x 4096 x 4096 layer 5820 / 4860.
+//
+// WALK: a workgroup takes tiles blockIdx.x, + gridDim.x, ... (as many workgroups as compute units) and requests the first
+// K step of the next tile before the epilogue of the current one, so that neither the launch of a workgroup nor its first
+// round trip to memory stands between two tiles.  For the squared error only: the stores of the other epilogues would
+// still be counted by the waits of the next tile's loads.
+template <int TA, int TB, int EPI, bool WALK>
+__global__ void __launch_bounds__(256, TA * TB <= 16 ? 2 : 1)
 k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* __restrict__ out,
          const float* __restrict__ ref, double* __restrict__ err, uint32_t M, uint32_t N, uint32_t ld,
-         float descale, uint32_t tiles_n, uint32_t col_begin, Batch batch) {
-  if (batch.nb != 0u) {
-    const uint32_t bi = blockIdx.y / batch.nb, bj = blockIdx.y - bi * batch.nb;
-    A += (size_t)bi * batch.a_stride;
-    B += (size_t)bj * batch.b_stride;
-    err += blockIdx.y;
-    descale = pow2f(-(batch.e_base + (int)bi + (int)bj));
-  }
-  constexpr int kWaves = WM * WN;
-  constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
-  constexpr int IA = BM / kRowsPerLoad / kWaves, IB = BN / kRowsPerLoad / kWaves;  // loads per wavefront and K step
-  static_assert(BM % (kRowsPerLoad * kWaves) == 0 && BN % (kRowsPerLoad * kWaves) == 0, "tile / wavefront mismatch");
+         float descale, uint32_t tiles_n, uint32_t tiles, uint32_t col_begin, Batch batch) {
+  constexpr int kWaves = 4, BM = 32 * TA, BN = 32 * TB;
+  constexpr int NL = TA + TB;  // tile loads per wavefront and K step (8 rows each)
   constexpr int kStageBytes = (BM + BN) * kRowBytes;
-  static_assert(kStageBytes == 65536 || kStageBytes == 32768, "stage size");
   extern __shared__ __attribute__((aligned(128))) uint8_t smem[];  // [2][BM + BN][128 bytes]
 
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: LDS destinations of the loads stay in SGPRs
-  const uint32_t wm = wave / WN, wn = wave % WN;
-  uint32_t tile_m, tile_n;  // in an order that keeps the workgroups of one die on neighbouring tiles
-  if (!tile_order(blockIdx.x, (M - 1u) / BM + 1u, tiles_n, &tile_m, &tile_n)) return;  // the whole workgroup leaves
-  const uint32_t m0 = tile_m * BM, n0 = col_begin + tile_n * BN;  // the launch covers columns from col_begin on
+  const uint32_t wm = wave >> 1, wn = wave & 1u;
 
   // Tile loads are buffer loads into LDS: one descriptor per operand panel of this workgroup (SGPRs), a
   // 32-bit byte offset per lane that never changes, and a scalar offset that advances along K -- no vector
   // ALU work per load.  The descriptor ends with the matrix, so rows past it read as zeros.
-  const size_t bytes_a = ((size_t)M - m0) * ld * 2u, bytes_b = ((size_t)N - n0) * ld * 2u;
-  const __amdgpu_buffer_rsrc_t res_a = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(A + (size_t)m0 * ld), 0, (int)(bytes_a > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)bytes_a), kRsrcFlags);
-  const __amdgpu_buffer_rsrc_t res_b = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(B + (size_t)n0 * ld), 0, (int)(bytes_b > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)bytes_b), kRsrcFlags);
+  uint32_t m0, n0;
+  __amdgpu_buffer_rsrc_t res_a, res_b;
+  double* tile_err;
+  float tile_descale;
+  auto take_tile = [&](uint32_t b) {
+    const uint32_t tiles_m = (M - 1u) / BM + 1u;
+    uint32_t tile_m, tile_n;  // in an order that keeps the workgroups of one die on neighbouring tiles
+    const uint16_t *a = A, *bb = B;
+    tile_err = err;
+    tile_descale = descale;
+    if (batch.na != 0u) {
+      if (!tile_order(b, tiles_m * batch.na, tiles_n * batch.nb, &tile_m, &tile_n)) return false;
+      const uint32_t i = tile_m % batch.na, j = tile_n % batch.nb;
+      tile_m /= batch.na;
+      tile_n /= batch.nb;
+      a += (size_t)i * batch.a_stride;
+      bb += (size_t)j * batch.b_stride;
+      tile_err += i * batch.nb + j;
+      tile_descale = pow2f(-(batch.e_base + (int)i + (int)j));
+    } else if (!tile_order(b, tiles_m, tiles_n, &tile_m, &tile_n)) {
+      return false;
+    }
+    m0 = tile_m * BM;
+    n0 = col_begin + tile_n * BN;  // the launch covers columns from col_begin on
+    const size_t bytes_a = ((size_t)M - m0) * ld * 2u, bytes_b = ((size_t)N - n0) * ld * 2u;
+    res_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a + (size_t)m0 * ld), 0,
+                                              (int)(bytes_a > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)bytes_a), kRsrcFlags);
+    res_b = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(bb + (size_t)n0 * ld), 0,
+                                              (int)(bytes_b > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)bytes_b), kRsrcFlags);
+    return true;
+  };
   // lane -> tile row 8 * (load index) + lane / 8, chunk position lane % 8 (which holds k-chunk position ^ ((row >> 1) & 7))
   const uint32_t lr = lane >> 3, lc = lane & 7u;
-  uint32_t off_a[IA], off_b[IB];
+  uint32_t off_a[TA], off_b[TB];  // < 2^32: the host limits ld
+  auto lane_offset = [&](uint32_t r) { return (r * ld + ((lc ^ ((r >> 1) & 7u)) * 8u)) * 2u; };
 #pragma unroll
-  for (int i = 0; i < IA; ++i) {
-    const uint32_t r = (wave * IA + i) * kRowsPerLoad + lr;
-    off_a[i] = (r * ld + ((lc ^ ((r >> 1) & 7u)) * 8u)) * 2u;  // < 2^32: the host limits ld
-  }
+  for (int i = 0; i < TA; ++i) off_a[i] = lane_offset((wave * TA + i) * kRowsPerLoad + lr);
 #pragma unroll
-  for (int i = 0; i < IB; ++i) {
-    const uint32_t r = (wave * IB + i) * kRowsPerLoad + lr;
-    off_b[i] = (r * ld + ((lc ^ ((r >> 1) & 7u)) * 8u)) * 2u;
-  }
-  uint32_t koff = 0;  // byte offset along K of the next tile to request
-  auto issue = [&](int stage) {
-    uint8_t* sa = smem + stage * kStageBytes + wave * IA * kRowsPerLoad * kRowBytes;
-    uint8_t* sb = smem + stage * kStageBytes + BM * kRowBytes + wave * IB * kRowsPerLoad * kRowBytes;
-#pragma unroll
-    for (int i = 0; i < IA; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(res_a, (__attribute__((address_space(3))) void*)(sa + i * kRowsPerLoad * kRowBytes),
-                                               16, (int)off_a[i], (int)koff, 0, 0);
-#pragma unroll
-    for (int i = 0; i < IB; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(res_b, (__attribute__((address_space(3))) void*)(sb + i * kRowsPerLoad * kRowBytes),
-                                               16, (int)off_b[i], (int)koff, 0, 0);
-    koff += kBK * 2;
-  };
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-  // MFMA operand of lane l: row l % 32 of the block, k elements 8 * (l / 32) .. + 7 of the 16-wide step.
-  // LDS address of the lane's A fragment of block row 0 for every (stage, step), computed once; the other
-  // block rows and the B fragments are constant offsets from it.
-  const uint32_t frow = lane & 31u, fk = lane >> 5;
-  const uint32_t swz = (frow >> 1) & 7u;  // block row offsets are multiples of 32: the permutation depends on frow only
-  uint32_t fbase[2][4];
-#pragma unroll
-  for (int st = 0; st < 2; ++st)
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-      fbase[st][s] = st * kStageBytes + (wm * TM * 32 + frow) * kRowBytes + ((((uint32_t)(s * 2) + fk) ^ swz) * 16u);
-  const uint32_t b_delta = BM * kRowBytes + (wn * TN * 32) * kRowBytes - (wm * TM * 32) * kRowBytes;  // scalar
-  bf16x8 fa[2][TM], fb[2][TN];
-  auto read_frags = [&](int buf, int stage, int s) {
-    const uint8_t* base = smem + fbase[stage][s];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) fa[buf][i] = *reinterpret_cast<const bf16x8*>(base + i * 32 * kRowBytes);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) fb[buf][j] = *reinterpret_cast<const bf16x8*>(base + b_delta + j * 32 * kRowBytes);
-  };
-  auto mfmas = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][i], fb[buf][j], acc[i][j], 0, 0, 0);
-  };
-
-  // One K step on LDS stage `cur` (a compile-time constant at both call sites).  The scheduling barriers
-  // pin "fetch the next fragments, then the MFMAs of the current ones"; each explicit wait sits where the
-  // reads it covers were issued a whole MFMA group earlier.
-  const uint32_t nk = ld / kBK;  // >= 1
-  auto k_step = [&](int cur, uint32_t kt) {
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-    read_frags(1, cur, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    mfmas(0);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-    read_frags(0, cur, 2);
-    __builtin_amdgcn_sched_barrier(0);
-    mfmas(1);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-    read_frags(1, cur, 3);
-    __builtin_amdgcn_sched_barrier(0);
-    mfmas(0);
-    __builtin_amdgcn_sched_barrier(0);
-    // this wavefront's part of tile kt + 1 has landed and its last fragments of tile kt are in registers;
-    // after the barrier that holds for the whole workgroup, so stage `cur` may be overwritten
-    __builtin_amdgcn_s_waitcnt(kWaitVm0Lgkm0);
-    __syncthreads();
-    if (kt + 2 < nk) issue(cur);
-    if (kt + 1 < nk) read_frags(0, cur ^ 1, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    mfmas(1);
-  };
-  // The same K step with every instruction placed by hand (FINE): one fragment read behind each of the first
-  // TM + TN MFMAs of a group, and the tile loads of the step after next spread over the last group, so that a
-  // wavefront that has its SIMD to itself never leaves the matrix core waiting behind a burst of memory
-  // instructions.  Used while two more tiles follow; the last steps run k_step.
-  auto read_one = [&](int buf, int stage, int s, int r) {
-    const uint8_t* base = smem + fbase[stage][s];
-    if (r < TM) fa[buf][r] = *reinterpret_cast<const bf16x8*>(base + r * 32 * kRowBytes);
-    else fb[buf][r - TM] = *reinterpret_cast<const bf16x8*>(base + b_delta + (r - TM) * 32 * kRowBytes);
-  };
-  auto issue_one = [&](int stage, int i) {
-    uint8_t* sa = smem + stage * kStageBytes + wave * IA * kRowsPerLoad * kRowBytes;
-    uint8_t* sb = smem + stage * kStageBytes + BM * kRowBytes + wave * IB * kRowsPerLoad * kRowBytes;
-    if (i < IA)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(res_a, (__attribute__((address_space(3))) void*)(sa + i * kRowsPerLoad * kRowBytes),
-                                               16, (int)off_a[i], (int)koff, 0, 0);
+  for (int i = 0; i < TB; ++i) off_b[i] = lane_offset((wave * TB + i) * kRowsPerLoad + lr);
+  // load i of the K step at byte offset k; stage: byte offset of an LDS stage
+  auto load = [&](uint32_t stage, int i, uint32_t k) {
+    if (i < TA)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          res_a, (__attribute__((address_space(3))) void*)(smem + stage + (wave * TA + i) * kRowsPerLoad * kRowBytes), 16, (int)off_a[i],
+          (int)k, 0, 0);
     else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(res_b, (__attribute__((address_space(3))) void*)(sb + (i - IA) * kRowsPerLoad * kRowBytes),
-                                               16, (int)off_b[i - IA], (int)koff, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          res_b, (__attribute__((address_space(3))) void*)(smem + stage + BM * kRowBytes + (wave * TB + i - TA) * kRowsPerLoad * kRowBytes),
+          16, (int)off_b[i - TA], (int)k, 0, 0);
   };
-  auto fine_step = [&](int cur) {
-    constexpr int NM = TM * TN, NR = TM + TN, NL = IA + IB;
-    static_assert(NR <= NM, "one fragment read per MFMA");
+  auto load_all = [&](uint32_t stage, uint32_t k) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int buf = s & 1;
+    for (int i = 0; i < NL; ++i) load(stage, i, k);
+  };
+
+  // MFMA operand of lane l: row l % 16 of the block, k elements 8 * (l / 16) .. + 7 of the half step
+  const uint32_t frow = lane & 15u, swz = (frow >> 1) & 7u;  // block offsets are multiples of 16 rows: the permutation depends on frow only
+  uint32_t fbase[2];  // LDS address of the lane's first A fragment of each half step; the others are constant offsets from it
+#pragma unroll
+  for (int s = 0; s < 2; ++s) fbase[s] = (wm * (16u * TA) + frow) * kRowBytes + ((((uint32_t)(s * 4) + (lane >> 4)) ^ swz) * 16u);
+  const uint32_t b_delta = BM * kRowBytes + (wn * (16u * TB)) * kRowBytes - (wm * (16u * TA)) * kRowBytes;  // scalar
+  f32x4 acc[TA][TB];
+  bf16x8 fa[2][TA], fb[2][TB];
+  auto read = [&](int buf, uint32_t stage, int s, int r) {
+    const uint8_t* base = smem + stage + fbase[s];
+    if (r < TA) fa[buf][r] = *reinterpret_cast<const bf16x8*>(base + r * 16 * kRowBytes);
+    else fb[buf][r - TA] = *reinterpret_cast<const bf16x8*>(base + b_delta + (r - TA) * 16 * kRowBytes);
+  };
+
+  // One K step on stage `cur`; LOADS: the K step after next, at byte offset k, follows into the same stage.  The scheduling
+  // barriers keep every instruction where it is written.  The last step of a tile reads fragments that nothing uses.
+  const uint32_t nk = ld / kBK;  // >= 1
+  auto k_step = [&](auto loads_c, uint32_t cur, uint32_t k) {
+    constexpr bool LOADS = decltype(loads_c)::value;
+    constexpr int NM = TA * TB, kLoadEvery = NM / NL;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
       __builtin_amdgcn_sched_barrier(0);
-      if (s == 3) {
-        // tile kt + 1 has landed and the last fragments of tile kt are in registers, for the whole workgroup
+      if (s == 1) {
+        // the next K step has landed and the last fragments of this one are in registers; behind the barrier that holds
+        // for the whole workgroup, so stage `cur` may be overwritten
         __builtin_amdgcn_s_waitcnt(kWaitVm0Lgkm0);
         __syncthreads();
-      } else {
-        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int idx = 0; idx < NM; ++idx) {
-        const int i = idx / TN, j = idx % TN;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][i], fb[buf][j], acc[i][j], 0, 0, 0);
+        const int i = idx / TB, j = idx % TB;
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fb[s][j]), "v"(fa[s][i]));
         __builtin_amdgcn_sched_barrier(0);  // the MFMA first: the memory instructions issue while it runs
-        if (idx < NR) {
-          if (s < 3) read_one(buf ^ 1, cur, s + 1, idx);
-          else read_one(buf ^ 1, cur ^ 1, 0, idx);
+        if (idx < NL) {  // first what the first MFMAs of the next half step use
+          const int r = idx == 0 ? 0 : idx <= TB ? TA + idx - 1 : idx - TB;
+          if (s == 0) read(1, cur, 1, r);
+          else read(0, cur ^ kStageBytes, 0, r);
         }
-        if (s == 3) {
-#pragma unroll
-          for (int l = idx * NL / NM; l < (idx + 1) * NL / NM; ++l) issue_one(cur, l);
-        }
+        if (LOADS && s == 1 && idx % kLoadEvery == 0 && idx / kLoadEvery < NL) load(cur, idx / kLoadEvery, k);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    koff += kBK * 2;
   };
-  issue(0);
-  __builtin_amdgcn_s_waitcnt(kWaitVm0);
-  __syncthreads();
-  if (nk > 1) issue(1);
-  read_frags(0, 0, 0);
-  uint32_t kt = 0;
-  if constexpr (FINE != 0) {
-    for (; kt + 3 < nk; kt += 2) {
-      fine_step(0);
-      fine_step(1);
-    }
-    // at most three steps are left, and kt is even
-    if (kt < nk) k_step(0, kt);
-    if (kt + 1 < nk) k_step(1, kt + 1);
-    if (kt + 2 < nk) k_step(0, kt + 2);
-  } else {
-    for (; kt + 1 < nk; kt += 2) {
-      k_step(0, kt);
-      k_step(1, kt + 1);
-    }
-    if (kt < nk) k_step(0, kt);
-  }
 
-  // every fragment of the last step was in registers before the last barrier, so the tile LDS is free
-  epilogue<EPI, TM, TN>(acc, out, ref, err, M, N, m0 + wm * TM * 32, n0 + wn * TN * 32, lane, descale,
-                        reinterpret_cast<double*>(smem), wave, kWaves);
+  uint32_t at = blockIdx.x;
+  if (!take_tile(at)) return;  // the whole workgroup leaves; WALK: every later number of its die's share lies further on
+  load_all(0, 0);
+  for (;;) {
+#pragma unroll
+    for (int i = 0; i < TA; ++i)
+#pragma unroll
+      for (int j = 0; j < TB; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    __syncthreads();
+    if (nk > 1) load_all(kStageBytes, kBK * 2);
+#pragma unroll
+    for (int r = 0; r < NL; ++r) read(0, 0, 0, r);
+    uint32_t cur = 0, k = 2 * kBK * 2;
+    for (uint32_t kt = 0; kt + 2 < nk; ++kt) {
+      k_step(std::true_type{}, cur, k);
+      cur ^= kStageBytes;
+      k += kBK * 2;
+    }
+    if (nk > 1) {
+      k_step(std::false_type{}, cur, 0);
+      cur ^= kStageBytes;
+    }
+    k_step(std::false_type{}, cur, 0);
+    // the compiler does not know the assembly for MFMAs: wait states before their results are read, and a use of every
+    // accumulator behind them
+    asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+    for (int i = 0; i < TA; ++i)
+#pragma unroll
+      for (int j = 0; j < TB; j += 2) asm volatile("" : "+a"(acc[i][j]), "+a"(acc[i][j + 1]));
+
+    // the fragments of the last half step were in registers before the last barrier, so the tile LDS is free; WALK: stage 0
+    // receives the next tile's first K step meanwhile
+    constexpr int TM = TA / 2, TN = TB / 2, CB = TN < 4 ? 2 : 4;
+    static_assert(TA % 2 == 0 && TB % 2 == 0, "whole 32 x 32 blocks");
+    const uint32_t row0 = m0 + wm * TM * 32, col0 = n0 + wn * TN * 32;
+    double* const e = tile_err;
+    const float ds = tile_descale;
+    bool more = false;
+    if constexpr (WALK) {
+      at += gridDim.x;
+      more = at < tiles && take_tile(at);
+      if (more) load_all(0, 0);
+    }
+    epilogue<EPI, TM, TN, CB>(acc, out, ref, e, M, N, row0, col0, lane, ds, smem + (WALK ? kStageBytes : 0), wave, kWaves);
+    if (!more) return;
+  }
 }
 
 // codes [rows, K] -> bf16 [rows, ld]; one 16-byte output chunk (8 elements) per lane and step
@@ -382,35 +360,43 @@ int& expanded_variant() {
   return v;
 }
 
-template <int WM, int WN, int TM, int TN, int EPI, int FINE = 0>
+template <int TA, int TB, int EPI>
 static hif8_status launch_x(const uint16_t* A, const uint16_t* B, void* out, const float* ref, double* err, uint32_t M,
-                            uint32_t N, uint32_t ld, float descale, hipStream_t st, const Batch& batch, uint32_t pairs,
+                            uint32_t N, uint32_t ld, float descale, hipStream_t st, int cus, const Batch& batch,
                             uint32_t col_begin = 0, uint32_t col_end = 0xFFFFFFFFu) {
   if (col_end > N) col_end = N;
-  constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
-  constexpr size_t smem = (size_t)2 * (BM + BN) * kRowBytes;
+  constexpr bool WALK = EPI == EPI_ERR && TA == 8 && TB == 8;
+  constexpr int BM = 32 * TA, BN = 32 * TB;
+  constexpr size_t stage = (size_t)(BM + BN) * kRowBytes, epi = 4 * (size_t)epilogue_lds(TB < 8 ? 2 : 4);
+  constexpr size_t smem = stage + (stage > epi ? stage : epi);  // WALK: the epilogue runs behind stage 0
   static bool attr_set[kMaxDevices] = {};
   int dev = 0;
   if (!hip_ok(hipGetDevice(&dev))) return HIF8_ERR_HIP;
   if (dev < 0 || dev >= kMaxDevices) return HIF8_ERR_ARG;
   if (!attr_set[dev]) {
-    if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_x<WM, WN, TM, TN, EPI, FINE>),
+    if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_x<TA, TB, EPI, WALK>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem)))
       return HIF8_ERR_HIP;
     attr_set[dev] = true;
   }
   if (col_begin >= col_end) return HIF8_OK;
   const uint32_t tiles_m = (M + BM - 1) / BM, tiles_n = (col_end - col_begin + BN - 1) / BN;
-  if ((uint64_t)tiles_m * tiles_n > 0x7FFFFFFFull || pairs == 0 || pairs > 65535u) return HIF8_ERR_ARG;
-  const uint32_t grid_x = tile_order_grid(tiles_m * tiles_n);  // a whole number of workgroups per die
-  hipLaunchKernelGGL((k_gemm_x<WM, WN, TM, TN, EPI, FINE>), dim3(grid_x, pairs), dim3(64 * WM * WN), smem, st, A, B,
-                     out, ref, err, M, N, ld, descale, tiles_n, col_begin, batch);
+  const uint64_t total = (uint64_t)tiles_m * tiles_n * (batch.na ? batch.na * batch.nb : 1u);
+  if (total > 0x7FFFFFF0ull) return HIF8_ERR_ARG;
+  const uint32_t tiles = tile_order_grid((uint32_t)total);  // a whole number of workgroups per die
+  uint32_t grid = tiles;
+  if (WALK) {
+    const uint32_t resident = tile_order_grid((uint32_t)cus);
+    if (grid > resident) grid = resident;
+  }
+  hipLaunchKernelGGL((k_gemm_x<TA, TB, EPI, WALK>), dim3(grid), dim3(256), smem, st, A, B, out, ref, err, M, N, ld, descale,
+                     tiles_n, tiles, col_begin, batch);
   return finish_launch();
 }
 
 template <int EPI>
 hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const float* ref, double* err, size_t M,
-                          size_t N, size_t ld, float descale, hipStream_t st, const Batch& batch, uint32_t pairs) {
+                          size_t N, size_t ld, float descale, hipStream_t st, const Batch& batch) {
   if (M == 0 || N == 0) return HIF8_OK;
   // 256 rows x ld x 2 bytes of a workgroup's operand panel must fit the 32-bit lane offsets of the tile loads
   if (M > 0x7FFFFFFFu || N > 0x7FFFFFFFu || ld > kMaxLd || ld == 0 || ld % kExpandK != 0) return HIF8_ERR_ARG;
@@ -418,43 +404,44 @@ hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const
   if (EPI == EPI_ERR ? (!ref || !err) : !out) return HIF8_ERR_NULL;
   if (!aligned_to(A, 16) || !aligned_to(B, 16)) return HIF8_ERR_ARG;
   if (EPI == EPI_ERR && !aligned_to(err, 8)) return HIF8_ERR_ARG;
-  if (batch.nb != 0u && ((batch.a_stride % 8) != 0 || (batch.b_stride % 8) != 0)) return HIF8_ERR_ARG;
+  if (batch.na != 0u && ((batch.a_stride % 8) != 0 || (batch.b_stride % 8) != 0)) return HIF8_ERR_ARG;
   int cus = 0;
   hif8_status s = ensure_init(&cus, nullptr);
   if (s != HIF8_OK) return s;
-  // 256 x 256 tiles once the launch has one for every compute unit, else 128 x 128 (4 wavefronts, two workgroups
-  // per compute unit).  The large tile runs the hand-placed K step: as 2 x 2 wavefronts of 128 x 128 each (a third
-  // fewer fragment reads per MFMA) when the launch lasts several rounds, as 2 x 4 wavefronts of 128 x 64 when it is
-  // a single round, where the second wavefront per SIMD covers the start and the end of the tile.
-  const size_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256) * (size_t)pairs;
+  const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)ld;
+  const size_t pairs = batch.na ? (size_t)batch.na * batch.nb : 1;
+  // tiles of a launch are counted in 32 bits: a search over a very large matrix goes row by row of its square
+  if (batch.na > 1u && (((uint64_t)M + 127) / 128) * (((uint64_t)N + 127) / 128) * pairs > 0x7FFFFFF0ull) {
+    for (uint32_t i = 0; i < batch.na; ++i) {
+      const Batch row{1u, batch.nb, batch.e_base + (int)i, batch.a_stride, batch.b_stride};
+      s = gemm_expanded<EPI>(A + i * batch.a_stride, B, out, ref, err + (size_t)i * batch.nb, M, N, ld, descale, st, row);
+      if (s != HIF8_OK) return s;
+    }
+    return HIF8_OK;
+  }
   int variant = expanded_variant();
-  if (pairs == 1 && (variant == 12 || (variant == 0 && small_problem(M, N))))
+  if (pairs == 1 && batch.na == 0u && (variant == 12 || (variant == 0 && small_problem(M, N))))
     return gemm_small<EPI>(A, B, true, out, ref, err, M, N, ld, descale, st);
   uint32_t split = 0;
-  if (variant == 0 && pairs == 1 && ragged_round_split(M, N, (size_t)cus, &split)) {
-    // complete rounds of 256 x 256 tiles, then the remaining columns in 128 x 128 tiles (second launch)
-    s = launch_x<2, 2, 4, 4, EPI, 1>(A, B, out, ref, err, (uint32_t)M, (uint32_t)N, (uint32_t)ld, descale, st, batch, pairs,
-                                     0u, split);
+  const int tile = variant == 9 ? TILE_128 : variant == 10 ? TILE_256 : variant == 11 ? TILE_192 : tile_plan(M, N, pairs, (size_t)cus, &split);
+  if (tile == TILE_SPLIT) {
+    s = launch_x<8, 8, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch, 0u, split);
     if (s != HIF8_OK) return s;
-    return launch_x<2, 2, 2, 2, EPI>(A, B, out, ref, err, (uint32_t)M, (uint32_t)N, (uint32_t)ld, descale, st, batch, pairs,
-                                     split, (uint32_t)N);
+    return launch_x<4, 4, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch, split, n);
   }
-  if (variant == 0) variant = big_tiles >= 2 * (size_t)cus ? 10 : big_tiles >= (size_t)cus ? 11 : 9;
-  if (variant == 10)
-    return launch_x<2, 2, 4, 4, EPI, 1>(A, B, out, ref, err, (uint32_t)M, (uint32_t)N, (uint32_t)ld, descale, st, batch, pairs);
-  if (variant == 11)
-    return launch_x<2, 4, 4, 2, EPI, 1>(A, B, out, ref, err, (uint32_t)M, (uint32_t)N, (uint32_t)ld, descale, st, batch, pairs);
-  return launch_x<2, 2, 2, 2, EPI>(A, B, out, ref, err, (uint32_t)M, (uint32_t)N, (uint32_t)ld, descale, st, batch, pairs);
+  if (tile == TILE_256) return launch_x<8, 8, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch);
+  if (tile == TILE_192) return launch_x<8, 6, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch);
+  return launch_x<4, 4, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch);
 }
 
 template hif8_status gemm_expanded<EPI_F32>(const uint16_t*, const uint16_t*, void*, const float*, double*, size_t, size_t,
-                                            size_t, float, hipStream_t, const Batch&, uint32_t);
+                                            size_t, float, hipStream_t, const Batch&);
 template hif8_status gemm_expanded<EPI_BF16>(const uint16_t*, const uint16_t*, void*, const float*, double*, size_t, size_t,
-                                             size_t, float, hipStream_t, const Batch&, uint32_t);
+                                            size_t, float, hipStream_t, const Batch&);
 template hif8_status gemm_expanded<EPI_F16>(const uint16_t*, const uint16_t*, void*, const float*, double*, size_t, size_t,
-                                            size_t, float, hipStream_t, const Batch&, uint32_t);
+                                            size_t, float, hipStream_t, const Batch&);
 template hif8_status gemm_expanded<EPI_ERR>(const uint16_t*, const uint16_t*, void*, const float*, double*, size_t, size_t,
-                                            size_t, float, hipStream_t, const Batch&, uint32_t);
+                                            size_t, float, hipStream_t, const Batch&);
 
 // descale = fl32(fl32(1 / scale_a) * fl32(1 / scale_b)), as in the code-operand GEMM
 static bool descale_of(float scale_a, float scale_b, float* out) {
@@ -472,7 +459,7 @@ static hif8_status gemm_expanded_abi(const uint16_t* a, const uint16_t* b, void*
   float descale = 1.0f;
   if (!descale_of(scale_a, scale_b, &descale)) return HIF8_ERR_SCALE;
   if (K == 0 || ld < K) return HIF8_ERR_ARG;
-  return gemm_expanded<EPI>(a, b, out, ref, err, M, N, ld, descale, st, Batch{0u, 0, 0, 0}, 1u);
+  return gemm_expanded<EPI>(a, b, out, ref, err, M, N, ld, descale, st);
 }
 
 }  // namespace hif8gemm

@@ -226,3 +226,36 @@ def test_small_gemm_plan(dev):
             assert 512 + w * (t // 100 + t // 10 % 10) * 16 * 128 <= 160 * 1024
         if min(M, N) <= 128:
             assert got[0][1] == got[1][1]
+
+
+def test_gemm_tile_plan(dev):
+    """Tile of the expanded-operand GEMM: none of the single tiles has a shorter sum of rounds than the plan's, and a split
+    lies on a tile column inside the matrix."""
+    dev.devfn_tile_plan.restype = ctypes.c_int
+    dev.devfn_tile_plan.argtypes = [ctypes.c_size_t] * 4 + [ctypes.POINTER(ctypes.c_uint32)]
+
+    def plan(M, N, pairs=1, cus=256):
+        s = ctypes.c_uint32(0)
+        return dev.devfn_tile_plan(M, N, pairs, cus, ctypes.byref(s)), s.value
+
+    def cost(t, M, N, pairs, cus):
+        bm, bn, each = ((256, 256, 130), (256, 192, 100), (128, 128, 0))[t]
+        tiles = -(-M // bm) * -(-N // bn) * pairs
+        if each:
+            return -(-tiles // cus) * each
+        rest = tiles % (2 * cus)
+        return tiles // (2 * cus) * 76 + (0 if rest == 0 else 62 if rest <= cus else 76)
+
+    assert plan(4096, 4096)[0] == 0 and plan(2048, 11008)[0] == 1 and plan(2048, 4096)[0] == 2
+    assert plan(8192, 11008) == (3, 40 * 256) and plan(2048, 4096, 100)[0] == 0 and plan(1, 1)[0] == 2
+    rng = np.random.default_rng(6)
+    for _ in range(2000):
+        M, N, pairs = int(2.0 ** rng.uniform(0, 16)), int(2.0 ** rng.uniform(0, 16)), int(rng.choice([1, 1, 16, 100]))
+        cus = int(rng.choice([64, 256, 304]))
+        t, split = plan(M, N, pairs, cus)
+        least = min(cost(c, M, N, pairs, cus) for c in range(3))
+        if t == 3:
+            assert pairs == 1 and split % 256 == 0 and 0 < split < N
+            assert cost(0, M, split, 1, cus) + cost(2, M, N - split, 1, cus) < least
+        else:
+            assert cost(t, M, N, pairs, cus) == least

@@ -1,0 +1,109 @@
+"""GPU tests of the expanded-operand GEMM's tiles: every tile shape on edge tiles and unaligned rows, in every output
+kind, against the fp64 oracle (bound of test_gpu_gemm.py: K * 2^-23 * sum_k |a b| * descale per element) and against its
+own binary32 result; launches with more tiles than workgroups; batched pairs over every tile."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import dev
+from oracle import hif8_oracle as orc
+from test_gpu_gemm import check, h, random_codes  # noqa: F401  (h is the fixture)
+from test_gpu_gemm_expanded import expand
+
+pytestmark = pytest.mark.gpu
+
+
+# K steps 1, 2, 3, 4 and more; rows that are not 16-byte aligned (N odd), shorter than a run of four or of eight columns, one
+# past and one below a block; one tile, edge tiles only, whole tiles and edge tiles
+@pytest.mark.parametrize("variant", [9, 10, 11])
+@pytest.mark.parametrize("M,N,K", [(5, 1, 64), (300, 3, 65), (257, 7, 130), (130, 191, 200), (511, 385, 256), (256, 192, 300), (514, 770, 400)])
+def test_tiles_every_output(h, variant, M, N, K):
+    rng = np.random.default_rng(variant + M + 3 * N + 7 * K)
+    ca, cb = random_codes(rng, (M, K), "cast_normal"), random_codes(rng, (N, K), "cast_normal")
+    (a, ld), (b, _) = expand(h, ca), expand(h, cb)
+    o32 = torch.full((M * N + 8,), 7.0, dtype=torch.float32, device=dev())
+    ob, oh = (torch.full((M * N + 8,), 7.0, dtype=d, device=dev()) for d in (torch.bfloat16, torch.float16))
+    h.hif8_gemm_set_variant(variant)
+    for call, o in ((h.hif8_gemm_expanded_f32, o32), (h.hif8_gemm_expanded_bf16, ob), (h.hif8_gemm_expanded_f16, oh)):
+        call(a, b, o, M, N, K, ld, 8.0, 8.0)
+        assert torch.all(o[M * N:] == 7.0)
+    out = o32[:M * N].view(M, N)
+    check(out.cpu().numpy(), ca, cb, 8.0, 8.0)
+    assert torch.equal(ob[:M * N].view(M, N), out.to(torch.bfloat16)) and torch.equal(oh[:M * N].view(M, N), out.to(torch.float16))
+    ref = (out * 1.01 + 0.5).contiguous()
+    err = torch.zeros(2, dtype=torch.float64, device=dev())
+    h.hif8_gemm_expanded_sqerr(a, b, ref, M, N, K, ld, 8.0, 8.0, err)
+    h.hif8_gemm_set_variant(0)
+    want = float(((out.double() - ref.double()) ** 2).sum())
+    assert err[1].item() == 0.0 and abs(err[0].item() - want) <= 1e-12 * want
+
+
+@pytest.mark.parametrize("variant", [9, 10, 11])
+def test_tiles_nan_and_inf(h, variant):
+    """A NaN of either operand reaches its row or column only, as 0x7FC0 in bfloat16, and nothing past the edge of a tile."""
+    rng = np.random.default_rng(3)
+    M, N, K = 300, 270, 128
+    ca, cb = random_codes(rng, (M, K), "cast_normal"), random_codes(rng, (N, K), "cast_normal")
+    ca[7, 3], cb[100, 70], cb[269, 5] = 0x80, 0x80, 0x6F
+    (a, ld), (b, _) = expand(h, ca), expand(h, cb)
+    o32, ob = (torch.zeros(M, N, dtype=d, device=dev()) for d in (torch.float32, torch.bfloat16))
+    ref, err = torch.zeros(M, N, device=dev()), torch.zeros(1, dtype=torch.float64, device=dev())
+    h.hif8_gemm_set_variant(variant)
+    h.hif8_gemm_expanded_f32(a, b, o32, M, N, K, ld, 1.0, 1.0)
+    h.hif8_gemm_expanded_bf16(a, b, ob, M, N, K, ld, 1.0, 1.0)
+    h.hif8_gemm_expanded_sqerr(a, b, ref, M, N, K, ld, 1.0, 1.0, err)
+    h.hif8_gemm_set_variant(0)
+    nan = torch.isnan(o32)
+    want = torch.zeros(M, N, dtype=torch.bool, device=dev())
+    want[7], want[:, 100] = True, True
+    want[torch.from_numpy(np.isin(ca[:, 5], [0x00])).to(dev()), 269] = True  # 0 * Inf
+    assert torch.equal(nan, want)
+    assert torch.all(ob.view(torch.int16)[nan] == 0x7FC0) and torch.isnan(err).item()
+
+
+def test_squared_error_of_more_tiles_than_workgroups(h):
+    """The workgroups of the squared error walk over tiles: 17 x 18 tiles of 256 x 256, edges on both sides."""
+    rng = np.random.default_rng(8)
+    M, N, K = 4200, 4503, 192
+    (a, ld), (b, _) = (expand(h, random_codes(rng, (r, K), "cast_normal")) for r in (M, N))
+    out = torch.empty(M, N, dtype=torch.float32, device=dev())
+    h.hif8_gemm_set_variant(10)
+    h.hif8_gemm_expanded_f32(a, b, out, M, N, K, ld, 2.0, 4.0)
+    ref = out + torch.randn(M, N, device=dev(), generator=torch.Generator(device=dev()).manual_seed(1))
+    err = torch.zeros(1, dtype=torch.float64, device=dev())
+    h.hif8_gemm_expanded_sqerr(a, b, ref, M, N, K, ld, 2.0, 4.0, err)
+    h.hif8_gemm_set_variant(0)
+    want = float(((out.double() - ref.double()) ** 2).sum())
+    assert abs(err.item() - want) <= 1e-12 * want
+
+
+@pytest.mark.parametrize("variant", [9, 10, 11])
+def test_scale_search_over_every_tile(h, variant):
+    """Every pair of a 10 x 7 search meets its own operands, scale and place in the table (edge tiles; with 256 x 256 tiles
+    420 tiles on at most 256 workgroups): each entry against the same product made alone."""
+    rng = np.random.default_rng(5)
+    M, N, K, na, nb = 300, 520, 130, 10, 7
+    x = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).to(dev())
+    w = torch.from_numpy((rng.standard_normal((N, K)) * 0.02).astype(np.float32)).to(dev())
+    ref = (x.double() @ w.double().t()).float()
+    ws = torch.empty(h.hif8_calibrate_workspace_bytes(M, N, K, na, nb), dtype=torch.uint8, device=dev())
+    err = torch.full((na, nb), -1.0, dtype=torch.float64, device=dev())
+    best = torch.zeros(2, dtype=torch.int32, device=dev())
+    h.hif8_gemm_set_variant(variant)
+    h.hif8_calibrate_layer_f32(x, w, ref, M, N, K, -3, na, -2, nb, orc.RM_TA, ws, ws.numel(), err, best)
+    one = torch.zeros(na, nb, dtype=torch.float64, device=dev())
+    ld = h.hif8_expanded_ld(K)
+    cast = []
+    for t, rows, lo, count in ((x, M, -3, na), (w, N, -2, nb)):
+        codes, xs = torch.empty(rows, K, dtype=torch.uint8, device=dev()), torch.zeros(count, rows, ld, dtype=torch.bfloat16, device=dev())
+        for i in range(count):
+            h.hif8_encode_f32(t, codes, rows * K, 2.0 ** (lo + i), orc.RM_TA)
+            h.hif8_expand_bf16(codes, rows, K, xs[i], ld)
+        cast.append(xs)
+    for i in range(na):
+        for j in range(nb):
+            h.hif8_gemm_expanded_sqerr(cast[0][i], cast[1][j], ref, M, N, K, ld, 2.0 ** (-3 + i), 2.0 ** (-2 + j), one[i, j:])
+    h.hif8_gemm_set_variant(0)
+    assert torch.all((err - one).abs() <= 1e-12 * one)
+    at = int(one.argmin())
+    assert best.tolist() == [-3 + at // nb, -2 + at % nb]
