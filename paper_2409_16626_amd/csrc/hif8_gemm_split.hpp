@@ -23,7 +23,8 @@ inline bool ragged_round_split(size_t M, size_t N, size_t cus, uint32_t* split) 
 // Tiles of the expanded-operand kernel: 256 x 256 or 256 x 192, one workgroup per compute unit, or 128 x 128, two.  A launch
 // takes as long as its rounds of resident workgroups, so the tile with the shortest sum of rounds is taken.  A round
 // costs, relative to each other, 13 (256 x 256), 10 (256 x 192), 7.6 (128 x 128, two per compute unit) or 6.2 (128 x 128,
-// one): measured 84, 63.8, 47.7 and 40.7 us at K = 4096.  The column split adds a launch (a twelfth of a large round).
+// one), 4.0 (128 x 128 on at most one per compute unit, with four LDS stages): measured 84, 63.8, 47.7, 40.7 and 25.7 us
+// at K = 4096.  The column split adds a launch (a twelfth of a large round).
 // Measured in us (256 x 256 / 256 x 192 / 128 x 128): 2048 x 11008 x 4096 151 / 128 / 138, 2048 x 4096 x 11008
 // 183 / 164 / 131, 11008 x 4096 x 2048 132 / 142 / 148, 4096^3 84 / 126 / 99.
 enum : int { TILE_256 = 0, TILE_192 = 1, TILE_128 = 2, TILE_SPLIT = 3 };
@@ -31,6 +32,7 @@ inline uint64_t tile_cost(int tile, size_t M, size_t N, size_t pairs, size_t cus
   const uint64_t bm = tile == TILE_128 ? 128 : 256, bn = tile == TILE_256 ? 256 : tile == TILE_192 ? 192 : 128;
   const uint64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * (uint64_t)pairs;
   if (tile != TILE_128) return (tiles + cus - 1) / cus * (tile == TILE_256 ? 130u : 100u);
+  if (tiles <= cus) return 40u;
   const uint64_t rest = tiles % (2 * cus);
   return tiles / (2 * cus) * 76u + (rest == 0 ? 0u : rest <= cus ? 62u : 76u);
 }
@@ -57,14 +59,17 @@ inline int tile_plan(size_t M, size_t N, size_t pairs, size_t cus, uint32_t* spl
 constexpr size_t kSmallCodesRows = 128;
 
 // Which problems go to the small-tile kernel (hif8_gemm_s.hip) although the tiled kernels could run them.  The tiled
-// kernels take a whole K walk (K = 4096: 85 us on codes, 55 us expanded) however few tiles there are, the small-tile
-// kernel's time goes with M N: at K = 4096 they meet between M N = 2.8 M (256 x 11008: codes 92 against 93 us,
-// expanded 54 against 58) and 4.2 M (384 x 11008: 135 / 120, 73 / 59; 1024 x 4096: 112 / 91, 59 / 56), at K = 11008
-// likewise (512 x 4096: 150 / 231, 80 / 143; 1024 x 4096: 278 / 232, 141 / 145).  With up to 32 rows on either side
-// three quarters of a tile would be padding, so such products stay with the small tiles whatever the other side is.
-inline bool small_problem(size_t M, size_t N) {
+// kernels take a whole K walk however few tiles there are (K = 4096: 85 us on codes, 25.7 us expanded), the small-tile
+// kernel's time goes with M N.  On codes they meet between M N = 2.8 M (256 x 11008 x 4096: 92 against 93 us) and 4.2 M
+// (384 x 11008 135 / 120, 1024 x 4096 112 / 91), at K = 11008 likewise (512 x 4096 150 / 231, 1024 x 4096 278 / 232).
+// On expanded operands (us, small tiles / 128 x 128): 256 x 4096 x 4096 19.6 / 25.7, 384 x 4096 x 4096 29.2 / 25.9, 64 x
+// 11008 x 4096 21.2 / 24.6, 100 x 11008 x 4096 29.1 / 25.4; K = 11008 256 x 4096 38 / 64, 512 x 4096 80 / 65; K = 2048 512 x
+// 2048 12.5 / 14.3; K = 1024 300 x 5000 12.6 / 9.5.  With up to 32 rows on either side three quarters of a tile would be
+// padding, so such products stay with the small tiles whatever the other side is.
+inline bool small_problem(size_t M, size_t N, bool codes) {
   const size_t s = M < N ? M : N, l = M < N ? N : M;
-  return s <= 32 || l <= (size_t)3 * 1048576 / s;
+  if (s <= 32) return true;
+  return codes ? l <= (size_t)3 * 1048576 / s : l <= (size_t)5 * 262144 / ((s + 31) / 32 * 32);
 }
 
 // Tile (16 tm x 16 tn) and wavefronts per workgroup of the small-tile kernel.  The wavefronts split K, so a wavefront
@@ -82,7 +87,7 @@ inline SmallPlan small_plan(size_t M, size_t N, bool codes) {
   if (s <= 16) return {1, 1, 8};
   if (s <= 32) return tiles(2, 4) >= 128 ? SmallPlan{2, 4, 8} : SmallPlan{1, 2, 8};
   if (s <= 64) return {2, 2, tiles(2, 2) <= 256 ? 16u : 4u};
-  if (s <= kSmallCodesRows || (codes && small_problem(M, N))) return {2, 4, tiles(2, 4) <= 256 ? 8u : 4u};
+  if (s <= kSmallCodesRows || (codes && small_problem(M, N, true))) return {2, 4, tiles(2, 4) <= 256 ? 8u : 4u};
   return {4, 4, !codes && tiles(4, 4) <= 256 ? 8u : 4u};
 }
 

@@ -40,6 +40,8 @@ constexpr int kRowsPerLoad = 8;     // a wavefront-wide 16-byte load covers 8 ti
 // s_waitcnt immediates (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[15:14])
 constexpr int kWaitVm0Lgkm0 = 0x0070;     // vmcnt(0) lgkmcnt(0)
 constexpr int kWaitVm0 = 0x0F70;          // vmcnt(0)
+// to add to an immediate with vmcnt(0): wait until n loads are in flight
+constexpr int wait_vm(int n) { return (n & 15) | (n >> 4) << 14; }
 constexpr int kRsrcFlags = 0x00020000;    // word 3 of a raw (unstructured, untyped) buffer descriptor on gfx9-family parts
 
 // The K loop of a 256 x 256 tile is bound by the matrix cores at the clock that the power limit leaves them, provided that
@@ -61,15 +63,19 @@ constexpr int kRsrcFlags = 0x00020000;    // word 3 of a raw (unstructured, unty
 // K step of the next tile before the epilogue of the current one, so that neither the launch of a workgroup nor its first
 // round trip to memory stands between two tiles.  For the squared error only: the stores of the other epilogues would
 // still be counted by the waits of the next tile's loads.
-template <int TA, int TB, int EPI, bool WALK>
-__global__ void __launch_bounds__(256, TA * TB <= 16 ? 2 : 1)
+//
+// ST: LDS stages.  With two, a K step lasts at least as long as its loads take to arrive, which two workgroups on a compute
+// unit hide from each other and the MFMAs of a large tile outlast; a 128 x 128 tile with the compute unit to itself
+// waited for them half of the time (768 x 4096 x 4096: 39 us) and takes four (27 us).
+template <int TA, int TB, int EPI, bool WALK, int ST>
+__global__ void __launch_bounds__(256, TA * TB <= 16 && ST == 2 ? 2 : 1)
 k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* __restrict__ out,
          const float* __restrict__ ref, double* __restrict__ err, uint32_t M, uint32_t N, uint32_t ld,
          float descale, uint32_t tiles_n, uint32_t tiles, uint32_t col_begin, Batch batch) {
   constexpr int kWaves = 4, BM = 32 * TA, BN = 32 * TB;
   constexpr int NL = TA + TB;  // tile loads per wavefront and K step (8 rows each)
   constexpr int kStageBytes = (BM + BN) * kRowBytes;
-  extern __shared__ __attribute__((aligned(128))) uint8_t smem[];  // [2][BM + BN][128 bytes]
+  extern __shared__ __attribute__((aligned(128))) uint8_t smem[];  // [ST][BM + BN][128 bytes]
 
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: LDS destinations of the loads stay in SGPRs
@@ -147,9 +153,11 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
     else fb[buf][r - TA] = *reinterpret_cast<const bf16x8*>(base + b_delta + (r - TA) * 16 * kRowBytes);
   };
 
-  // One K step on stage `cur`; LOADS: the K step after next, at byte offset k, follows into the same stage.  The scheduling
+  // One K step on stage `cur`; LOADS: the K step ST further on, at byte offset k, follows into the same stage.  The scheduling
   // barriers keep every instruction where it is written.  The last step of a tile reads fragments that nothing uses.
   const uint32_t nk = ld / kBK;  // >= 1
+  static_assert((ST == 2 || (ST * kStageBytes & (ST * kStageBytes - 1)) == 0) && (ST - 1) * NL < 64, "stages wrap by a mask, loads in flight are counted in 6 bits");
+  auto next_stage = [](uint32_t cur) { return ST == 2 ? cur ^ kStageBytes : (cur + kStageBytes) & (ST * kStageBytes - 1u); };
   auto k_step = [&](auto loads_c, uint32_t cur, uint32_t k) {
     constexpr bool LOADS = decltype(loads_c)::value;
     constexpr int NM = TA * TB, kLoadEvery = NM / NL;
@@ -159,7 +167,7 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
       if (s == 1) {
         // the next K step has landed and the last fragments of this one are in registers; behind the barrier that holds
         // for the whole workgroup, so stage `cur` may be overwritten
-        __builtin_amdgcn_s_waitcnt(kWaitVm0Lgkm0);
+        __builtin_amdgcn_s_waitcnt(kWaitVm0Lgkm0 + (LOADS ? wait_vm((ST - 2) * NL) : 0));
         __syncthreads();
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -171,7 +179,7 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
         if (idx < NL) {  // first what the first MFMAs of the next half step use
           const int r = idx == 0 ? 0 : idx <= TB ? TA + idx - 1 : idx - TB;
           if (s == 0) read(1, cur, 1, r);
-          else read(0, cur ^ kStageBytes, 0, r);
+          else read(0, next_stage(cur), 0, r);
         }
         if (LOADS && s == 1 && idx % kLoadEvery == 0 && idx / kLoadEvery < NL) load(cur, idx / kLoadEvery, k);
         __builtin_amdgcn_sched_barrier(0);
@@ -187,20 +195,32 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
     for (int i = 0; i < TA; ++i)
 #pragma unroll
       for (int j = 0; j < TB; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    __builtin_amdgcn_s_waitcnt(kWaitVm0);
-    __syncthreads();
-    if (nk > 1) load_all(kStageBytes, kBK * 2);
+    if constexpr (ST == 2) {
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+      __syncthreads();
+      if (nk > 1) load_all(kStageBytes, kBK * 2);
+    } else {
+#pragma unroll
+      for (uint32_t t = 1; t < (uint32_t)ST; ++t)
+        if (t < nk) load_all(t * kStageBytes, t * kBK * 2);
+      if (nk >= (uint32_t)ST) __builtin_amdgcn_s_waitcnt(kWaitVm0 + wait_vm((ST - 1) * NL));
+      else __builtin_amdgcn_s_waitcnt(kWaitVm0);
+      __syncthreads();
+    }
 #pragma unroll
     for (int r = 0; r < NL; ++r) read(0, 0, 0, r);
-    uint32_t cur = 0, k = 2 * kBK * 2;
-    for (uint32_t kt = 0; kt + 2 < nk; ++kt) {
+    uint32_t cur = 0, k = ST * kBK * 2;
+    for (uint32_t kt = ST; kt < nk; ++kt) {
       k_step(std::true_type{}, cur, k);
-      cur ^= kStageBytes;
+      cur = next_stage(cur);
       k += kBK * 2;
     }
-    if (nk > 1) {
-      k_step(std::false_type{}, cur, 0);
-      cur ^= kStageBytes;
+#pragma unroll
+    for (uint32_t t = ST - 1; t >= 1u; --t) {
+      if (nk > t) {
+        k_step(std::false_type{}, cur, 0);
+        cur = next_stage(cur);
+      }
     }
     k_step(std::false_type{}, cur, 0);
     // the compiler does not know the assembly for MFMAs: wait states before their results are read, and a use of every
@@ -360,7 +380,7 @@ int& expanded_variant() {
   return v;
 }
 
-template <int TA, int TB, int EPI>
+template <int TA, int TB, int EPI, int ST = 2>
 static hif8_status launch_x(const uint16_t* A, const uint16_t* B, void* out, const float* ref, double* err, uint32_t M,
                             uint32_t N, uint32_t ld, float descale, hipStream_t st, int cus, const Batch& batch,
                             uint32_t col_begin = 0, uint32_t col_end = 0xFFFFFFFFu) {
@@ -368,13 +388,13 @@ static hif8_status launch_x(const uint16_t* A, const uint16_t* B, void* out, con
   constexpr bool WALK = EPI == EPI_ERR && TA == 8 && TB == 8;
   constexpr int BM = 32 * TA, BN = 32 * TB;
   constexpr size_t stage = (size_t)(BM + BN) * kRowBytes, epi = 4 * (size_t)epilogue_lds(TB < 8 ? 2 : 4);
-  constexpr size_t smem = stage + (stage > epi ? stage : epi);  // WALK: the epilogue runs behind stage 0
+  constexpr size_t smem = stage + ((ST - 1) * stage > epi ? (ST - 1) * stage : epi);  // WALK: the epilogue runs behind stage 0
   static bool attr_set[kMaxDevices] = {};
   int dev = 0;
   if (!hip_ok(hipGetDevice(&dev))) return HIF8_ERR_HIP;
   if (dev < 0 || dev >= kMaxDevices) return HIF8_ERR_ARG;
   if (!attr_set[dev]) {
-    if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_x<TA, TB, EPI, WALK>),
+    if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_x<TA, TB, EPI, WALK, ST>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem)))
       return HIF8_ERR_HIP;
     attr_set[dev] = true;
@@ -389,7 +409,7 @@ static hif8_status launch_x(const uint16_t* A, const uint16_t* B, void* out, con
     const uint32_t resident = tile_order_grid((uint32_t)cus);
     if (grid > resident) grid = resident;
   }
-  hipLaunchKernelGGL((k_gemm_x<TA, TB, EPI, WALK>), dim3(grid), dim3(256), smem, st, A, B, out, ref, err, M, N, ld, descale,
+  hipLaunchKernelGGL((k_gemm_x<TA, TB, EPI, WALK, ST>), dim3(grid), dim3(256), smem, st, A, B, out, ref, err, M, N, ld, descale,
                      tiles_n, tiles, col_begin, batch);
   return finish_launch();
 }
@@ -420,7 +440,7 @@ hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const
     return HIF8_OK;
   }
   int variant = expanded_variant();
-  if (pairs == 1 && batch.na == 0u && (variant == 12 || (variant == 0 && small_problem(M, N))))
+  if (pairs == 1 && batch.na == 0u && (variant == 12 || (variant == 0 && small_problem(M, N, false))))
     return gemm_small<EPI>(A, B, true, out, ref, err, M, N, ld, descale, st);
   uint32_t split = 0;
   const int tile = variant == 9 ? TILE_128 : variant == 10 ? TILE_256 : variant == 11 ? TILE_192 : tile_plan(M, N, pairs, (size_t)cus, &split);
@@ -431,6 +451,9 @@ hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const
   }
   if (tile == TILE_256) return launch_x<8, 8, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch);
   if (tile == TILE_192) return launch_x<8, 6, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch);
+  // 128 x 128: four stages where every workgroup has a compute unit to itself
+  if (((M + 127) / 128) * ((N + 127) / 128) * pairs <= (size_t)cus)
+    return launch_x<4, 4, EPI, 4>(A, B, out, ref, err, m, n, k, descale, st, cus, batch);
   return launch_x<4, 4, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch);
 }
 

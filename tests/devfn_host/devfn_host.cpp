@@ -83,7 +83,7 @@ uint32_t devfn_ragged_round_split(size_t M, size_t N, size_t cus) {
 uint32_t devfn_small_plan(size_t M, size_t N, int codes, int force, uint32_t* waves) {
   const hif8gemm::SmallPlan p = hif8gemm::small_plan(M, N, codes != 0);
   *waves = p.waves;
-  return force || hif8gemm::small_problem(M, N) ? p.tm * 100 + p.tn * 10 : 0u;
+  return force || hif8gemm::small_problem(M, N, codes != 0) ? p.tm * 100 + p.tn * 10 : 0u;
 }
 // expanded-operand GEMM: tile (0 = 256 x 256, 1 = 256 x 192, 2 = 128 x 128, 3 = split) and the split column
 int devfn_tile_plan(size_t M, size_t N, size_t pairs, size_t cus, uint32_t* split) {

@@ -243,10 +243,12 @@ def test_gemm_tile_plan(dev):
         tiles = -(-M // bm) * -(-N // bn) * pairs
         if each:
             return -(-tiles // cus) * each
+        if tiles <= cus:
+            return 40
         rest = tiles % (2 * cus)
         return tiles // (2 * cus) * 76 + (0 if rest == 0 else 62 if rest <= cus else 76)
 
-    assert plan(4096, 4096)[0] == 0 and plan(2048, 11008)[0] == 1 and plan(2048, 4096)[0] == 2
+    assert plan(4096, 4096)[0] == 0 and plan(2048, 11008)[0] == 1 and plan(2048, 4096)[0] == 2 and plan(1500, 1500)[0] == 2
     assert plan(8192, 11008) == (3, 40 * 256) and plan(2048, 4096, 100)[0] == 0 and plan(1, 1)[0] == 2
     rng = np.random.default_rng(6)
     for _ in range(2000):
