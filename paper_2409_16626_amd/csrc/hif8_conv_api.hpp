@@ -60,4 +60,9 @@ inline uint64_t plan_item_tiles(uint64_t n, bool src_is_16bit) {
 // most per-workgroup partial maxima conv_quantize_tensor writes (size of its scratch in 32-bit words)
 constexpr uint32_t kMaxParts = 1024;
 
+// casts at `count` scales 2^e_lo .. expanded to bfloat16 (hif8_calib.hip)
+template <int SRCK>
+hif8_status cast_scales(const void* src, size_t rows, size_t K, int e_lo, int count, uint32_t mode, uint16_t* dst, size_t ld,
+                        size_t stride, hipStream_t st);
+
 }  // namespace hif8conv

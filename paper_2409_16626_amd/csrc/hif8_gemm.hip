@@ -320,16 +320,23 @@ static hif8_status gemm_ws(const uint8_t* A, const uint8_t* B, void* out, const 
 }
 
 // position of the smallest finite entry of err[rows * cols] -> best[0] = e_row_lo + row,
-// best[1] = e_col_lo + col (first minimum in row-major order; {e_row_lo, e_col_lo} if none is finite)
-__global__ void k_argmin_pair(const double* __restrict__ err, int rows, int cols, int e_row_lo, int e_col_lo,
-                              int32_t* __restrict__ best) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  int bi = 0;
+// best[1] = e_col_lo + col (first minimum in row-major order; {e_row_lo, e_col_lo} if none is finite).  One wavefront.
+__global__ void __launch_bounds__(64)
+k_argmin_pair(const double* __restrict__ err, int rows, int cols, int e_row_lo, int e_col_lo, int32_t* __restrict__ best) {
+  int bi = 0x7FFFFFFF;
   double bv = INFINITY;
-  for (int i = 0; i < rows * cols; ++i) {
+  for (int i = (int)threadIdx.x; i < rows * cols; i += 64) {
     const double v = err[i];
     if (v < bv) { bv = v; bi = i; }  // NaN and +Inf never compare below
   }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    const double v = __shfl_xor(bv, off, 64);
+    const int i = __shfl_xor(bi, off, 64);
+    if (v < bv || (v == bv && i < bi)) { bv = v; bi = i; }
+  }
+  if (threadIdx.x != 0) return;
+  if (bi == 0x7FFFFFFF) bi = 0;
   best[0] = e_row_lo + bi / cols;
   best[1] = e_col_lo + bi % cols;
 }
@@ -353,29 +360,20 @@ static hif8_status calibrate_layer(const void* a, const void* w, const float* o_
   if (!aligned_to(d_err, 8) || (d_best && !aligned_to(d_best, 4))) return HIF8_ERR_ARG;
   if (M == 0 || N == 0 || K == 0) return HIF8_ERR_ARG;
   if (M > 0x7FFFFFFFu || N > 0x7FFFFFFFu || K > kMaxLd) return HIF8_ERR_ARG;
-  // workspace: one code matrix at a time (the stream runs the cast, then the expansion, before the
-  // next cast overwrites it), then every cast operand expanded to bfloat16 for the matrix cores
+  // workspace: every cast operand expanded to bfloat16 for the matrix cores, behind room for one code matrix that
+  // hif8_calibrate_workspace_bytes has always counted
   const size_t ld = expanded_ld(K);
   const size_t code_bytes = ((M > N ? M : N) * K + 15) / 16 * 16;
   const size_t a_elems = M * ld, w_elems = N * ld;  // multiples of 64 elements: every matrix stays 128-byte aligned
   if (workspace_bytes < calibrate_bytes(M, N, K, ea_count, ew_count) || !aligned_to(workspace, 16)) return HIF8_ERR_ARG;
-  uint8_t* ws_codes = reinterpret_cast<uint8_t*>(workspace);
-  uint16_t* ws_a = reinterpret_cast<uint16_t*>(ws_codes + code_bytes);
+  uint16_t* ws_a = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(workspace) + code_bytes);
   uint16_t* ws_w = ws_a + a_elems * ea_count;
   hif8_status s = launch_fill_u32(reinterpret_cast<uint32_t*>(d_err), 0u, 2u * (uint32_t)(ea_count * ew_count), st);
   if (s != HIF8_OK) return s;
-  for (int i = 0; i < ea_count; ++i) {
-    s = hif8conv::conv_encode<SRCK>(a, ws_codes, M * K, std::ldexp(1.0f, ea_lo + i), nullptr, nullptr, mode, nullptr, st);
-    if (s != HIF8_OK) return s;
-    s = expand_rows(ws_codes, M, K, ws_a + a_elems * i, ld, st);
-    if (s != HIF8_OK) return s;
-  }
-  for (int j = 0; j < ew_count; ++j) {
-    s = hif8conv::conv_encode<SRCK>(w, ws_codes, N * K, std::ldexp(1.0f, ew_lo + j), nullptr, nullptr, mode, nullptr, st);
-    if (s != HIF8_OK) return s;
-    s = expand_rows(ws_codes, N, K, ws_w + w_elems * j, ld, st);
-    if (s != HIF8_OK) return s;
-  }
+  s = hif8conv::cast_scales<SRCK>(a, M, K, ea_lo, ea_count, mode, ws_a, ld, a_elems, st);
+  if (s != HIF8_OK) return s;
+  s = hif8conv::cast_scales<SRCK>(w, N, K, ew_lo, ew_count, mode, ws_w, ld, w_elems, st);
+  if (s != HIF8_OK) return s;
   // all pairs in one launch
   const Batch batch{(uint32_t)ea_count, (uint32_t)ew_count, ea_lo + ew_lo, a_elems, w_elems};
   s = gemm_expanded<EPI_ERR>(ws_a, ws_w, nullptr, o_ref, d_err, M, N, ld, 1.0f, st, batch);

@@ -107,3 +107,48 @@ def test_scale_search_over_every_tile(h, variant):
     assert torch.all((err - one).abs() <= 1e-12 * one)
     at = int(one.argmin())
     assert best.tolist() == [-3 + at // nb, -2 + at % nb]
+
+
+# every rounding method on every kind of source: rows of whole and of odd numbers of 8-element runs, K at, below and above
+# the 64-element pitch, a source off the 16-byte grid; inputs with NaN, both infinities, zeros and values of every binade
+@pytest.mark.parametrize("kind", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("mode", [orc.RM_TA, orc.RM_HR, orc.RM_TE, orc.RM_SSR, orc.RM_SR, orc.RM_TA | orc.FLAG_SAT])
+def test_scale_search_casts(h, kind, mode):
+    dtype = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[kind]
+    g = torch.Generator(device=dev()).manual_seed(mode + len(kind))
+    encode, calibrate = getattr(h, "hif8_encode_" + kind), getattr(h, "hif8_calibrate_layer_" + kind)
+    for M, N, K, off in ((40, 33, 64, 0), (37, 70, 61, 1), (33, 34, 200, 0), (65, 40, 3, 3)):
+        mats = []
+        for rows, std in ((M, 1.0), (N, 0.05)):
+            v = torch.randn(rows * K + off, device=dev(), generator=g) * std * torch.exp2(torch.randint(-12, 6, (rows * K + off,), device=dev(), generator=g))
+            v[off::97] = 0.0
+            mats.append(v.to(dtype)[off:])
+        if K == 61:  # a row of A and a column of B become NaN or Inf: so do the sums
+            mats[0][5], mats[1][7] = float("nan"), float("inf")
+        x, w = mats
+        ref = torch.zeros(M, N, device=dev())
+        na, nb, ea, ew = 3, 4, -2, 1
+        ws = torch.empty(h.hif8_calibrate_workspace_bytes(M, N, K, na, nb), dtype=torch.uint8, device=dev())
+        err, one = (torch.zeros(na, nb, dtype=torch.float64, device=dev()) for _ in range(2))
+        best = torch.zeros(2, dtype=torch.int32, device=dev())
+        calibrate(x, w, ref, M, N, K, ea, na, ew, nb, mode, ws, ws.numel(), err, best)
+        ld = h.hif8_expanded_ld(K)
+        cast = []
+        for t, rows, lo, count in ((x, M, ea, na), (w, N, ew, nb)):
+            codes, xs = torch.empty(rows * K, dtype=torch.uint8, device=dev()), torch.zeros(count, rows, ld, dtype=torch.bfloat16, device=dev())
+            for i in range(count):
+                encode(t, codes, rows * K, 2.0 ** (lo + i), mode)
+                h.hif8_expand_bf16(codes, rows, K, xs[i], ld)
+            cast.append(xs)
+        # the casts themselves, where the search leaves them: behind room for one code matrix, rows of the A casts first
+        at = (max(M, N) * K + 15) // 16 * 16
+        got = ws[at:at + 2 * (cast[0].numel() + cast[1].numel())].view(torch.int16)
+        assert torch.equal(got, torch.cat([c.reshape(-1).view(torch.int16) for c in cast]))
+        for i in range(na):
+            for j in range(nb):
+                h.hif8_gemm_expanded_sqerr(cast[0][i], cast[1][j], ref, M, N, K, ld, 2.0 ** (ea + i), 2.0 ** (ew + j), one[i, j:])
+        nan = torch.isnan(one)
+        assert torch.equal(torch.isnan(err), nan) and torch.all(((err - one).abs() <= 1e-6 * one)[~nan])
+        fin = torch.where(torch.isfinite(err), err, float("inf"))
+        pos = int(fin.argmin()) if torch.isfinite(err).any() else 0
+        assert best.tolist() == [ea + pos // nb, ew + pos % nb]
