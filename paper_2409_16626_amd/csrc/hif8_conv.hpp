@@ -625,6 +625,99 @@ k_amax_elem(const void* __restrict__ src, size_t n, uint32_t* __restrict__ out) 
 }
 
 // ------------------------------------------------------------------------------------
+// Per-tensor scaling of a small tensor in ONE launch: every workgroup reads the whole tensor for its amax (from the L2
+// after the first), derives the scale and casts a share of its own.  What bounds the small casts is the launches, not the
+// bytes: see kOneLaunchBytes for where reading the tensor once per workgroup starts to cost more than a second launch.
+// A workgroup writes its share while others may still read the tensor: with more than one workgroup the outputs must not
+// overlap the source.
+// ------------------------------------------------------------------------------------
+constexpr int kOneBlock = 512;
+constexpr int kOneU = 2;  // vectors of its share per lane
+constexpr size_t kOneVec = (size_t)kOneBlock * kOneU;
+template <int IMPL, int SRCK, bool DST, bool CODES>
+__global__ void __launch_bounds__(kOneBlock)
+k_quant_one(const void* src, void* dst, uint8_t* codes, uint32_t n, float target, int pow2, float* __restrict__ out_amax,
+            float* __restrict__ out_scale2, uint32_t mode, SrArg sr, const uint8_t* __restrict__ g_lut, const uint32_t* __restrict__ g_dec) {
+  __shared__ __attribute__((aligned(16))) uint8_t lut[lut_bytes<IMPL>()];
+  __shared__ HrLds<uses_exp_table<IMPL>()> hrt;
+  __shared__ uint32_t dec[DST ? 256 : 1];
+  __shared__ uint32_t wave_m[kOneBlock / 64];
+  const EncCtx ctx = make_ctx<IMPL>(lut, hrt.w, mode, sr.seed, stream_index<IMPL>(sr, 0));
+  constexpr int VE = vec_elems<SRCK>();
+  const uint4* src4 = reinterpret_cast<const uint4*>(src);
+  const uint32_t nvec = n >> vec_shift<SRCK>(), first = blockIdx.x * (uint32_t)kOneVec + threadIdx.x;
+  uint4 own[kOneU];
+#pragma unroll
+  for (int j = 0; j < kOneU; ++j) {
+    const uint32_t idx = first + j * kOneBlock;
+    own[j] = idx < nvec ? src4[idx] : make_uint4(0u, 0u, 0u, 0u);
+  }
+  uint32_t m = 0;
+  if (gridDim.x > 1u) {
+    // loads without branches, so that all are in flight together: past the end the last vector again
+    for (uint32_t i = threadIdx.x; i < nvec; i += 4u * kOneBlock) {
+      uint4 v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t idx = i + j * kOneBlock;
+        v[j] = src4[idx < nvec ? idx : nvec - 1u];
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) m = vec_amax<SRCK>(m, v[j]);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kOneU; ++j) m = vec_amax<SRCK>(m, own[j]);
+  }
+  m = fold_amax<SRCK>(m);
+  const uint32_t t = nvec * VE + threadIdx.x;  // ragged tail: read by every workgroup, cast by the first
+  uint32_t tail = 0;
+  if (t < n) {
+    tail = load_bits<SRCK>(src, t);
+    m = umax(m, tail & 0x7FFFFFFFu);
+  }
+  stage_enc_lut<IMPL, SRCK>(lut, g_lut, mode);
+  stage_exp_table<IMPL, SRCK>(hrt.w, mode);
+  if constexpr (DST) stage_dec_lut(dec, g_dec);
+  m = wave_max_u32(m);
+  if ((threadIdx.x & 63u) == 0u) wave_m[threadIdx.x >> 6] = m;
+  __syncthreads();
+  uint32_t r = wave_m[0];
+#pragma unroll
+  for (int w = 1; w < kOneBlock / 64; ++w) r = umax(r, wave_m[w]);
+  const float amax = __uint_as_float(r), scale = scale_from_amax_value(amax, target, pow2), inv = 1.0f / scale;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *out_amax = amax;
+    out_scale2[0] = scale;
+    out_scale2[1] = inv;
+  }
+#pragma unroll
+  for (int j = 0; j < kOneU; ++j) {
+    const uint32_t idx = first + j * kOneBlock;
+    if (idx >= nvec) continue;
+    if constexpr (SRCK == kSrcF32) {
+      const uint32_t c = encode4_f32<IMPL>(own[j], scale, ctx, stream_index<IMPL>(sr, (uint64_t)idx * VE));
+      if constexpr (DST) reinterpret_cast<uint4*>(dst)[idx] = descale4_f32(c, dec, inv);
+      if constexpr (CODES) reinterpret_cast<uint32_t*>(codes)[idx] = c;
+    } else {
+      const uint2 c = encode8_16<IMPL, SRCK>(own[j], scale, ctx, stream_index<IMPL>(sr, (uint64_t)idx * VE));
+      if constexpr (DST) reinterpret_cast<uint4*>(dst)[idx] = descale8_16<SRCK>(c, dec, inv);
+      if constexpr (CODES) reinterpret_cast<uint2*>(codes)[idx] = c;
+    }
+  }
+  if (blockIdx.x == 0 && t < n) {
+    const uint64_t e = stream_index<IMPL>(sr, t);
+    const uint32_t c = encode_one<IMPL, SRCK>(scaled_bits(tail, scale), keyed<IMPL>(ctx, e), e);
+    if constexpr (DST) {
+      const uint32_t b = descale_bits(c, dec, inv);
+      if constexpr (SRCK == kSrcF32) reinterpret_cast<uint32_t*>(dst)[t] = b;
+      else reinterpret_cast<uint16_t*>(dst)[t] = (uint16_t)narrow1<SRCK>(b);
+    }
+    if constexpr (CODES) codes[t] = (uint8_t)c;
+  }
+}
+
+// ------------------------------------------------------------------------------------
 // multi-tensor cast: many tensors per launch, so that a list of small tensors is not bound by
 // launch gaps.  All tensors share one global tile index space; items[i].first_tile is the
 // prefix sum of tile counts.  A tile is kMultiBlock * kMultiUnroll vector units of one tensor.
@@ -1138,11 +1231,49 @@ hif8_status conv_amax(const void* src, size_t n, float* d_amax, hipStream_t st) 
   return finish_launch();
 }
 
+// Largest source, in bytes, that takes one launch: where the GPU needs the same time for both (us per call in a graph, two
+// launches / one: bfloat16 to codes 32 KiB 5.4 / 2.7, 256 KiB 6.3 / 4.4, 512 KiB 6.3 / 6.1; round trip 512 KiB 7.1 / 6.5;
+// binary32 to codes 512 KiB 5.6 / 5.8).  Called one by one from the host the second launch costs 2.5 us more at any size
+// (10.9 / 8.4 us).
+constexpr size_t kOneLaunchBytes = (size_t)512 << 10;
+
+inline bool bytes_overlap(const void* a, size_t an, const void* b, size_t bn) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return b != nullptr && x < y + bn && y < x + an;
+}
+
+// k_quant_one where the tensor is small enough; false: nothing was launched.  The caller has checked the arguments and
+// the fast path's alignment; at least one of dst and codes is given.
+template <int SRCK>
+bool quant_one(const void* src, void* dst, uint8_t* codes, size_t n, float target, int pow2, uint32_t mode, float* d_amax,
+               float* d_scale2, const SrArg& sr, const DevTables& tb, hipStream_t st) {
+  const size_t bytes = n * (SRCK == kSrcF32 ? 4 : 2), nvec = n >> vec_shift<SRCK>();
+  const int impl = impl_for<SRCK>(mode);
+  if (bytes > kOneLaunchBytes || impl == IMPL_TA_ALU) return false;
+  const unsigned wgs = nvec <= kOneVec ? 1u : (unsigned)((nvec + kOneVec - 1) / kOneVec);
+  if (wgs > 1u && (bytes_overlap(src, bytes, dst, bytes) || bytes_overlap(src, bytes, codes, n))) return false;
+  dispatch_impl<SRCK>(impl, 2, [&](auto impl_c, auto) {
+    constexpr int IMPL = decltype(impl_c)::value;
+    auto go = [&](auto dst_c, auto codes_c) {
+      hipLaunchKernelGGL((k_quant_one<IMPL, SRCK, decltype(dst_c)::value, decltype(codes_c)::value>), dim3(wgs), dim3(kOneBlock), 0, st,
+                         src, dst, codes, (uint32_t)n, target, pow2, d_amax, d_scale2, mode, sr, enc_table_for<IMPL>(tb), tb.dec_lut);
+    };
+    using std::true_type;
+    using std::false_type;
+    if constexpr (IMPL != IMPL_TA_ALU) {
+      if (!dst) go(false_type{}, true_type{});
+      else if (codes) go(true_type{}, true_type{});
+      else go(true_type{}, false_type{});
+    }
+  });
+  return true;
+}
+
 // Per-tensor scaling in one call (Sec. 5: amax, scale factor, cast): pass 1 leaves one partial maximum per
 // workgroup in `parts` (ordinary loads, so a tensor that fits the last-level cache stays there), pass 2 is the
 // cast -- codes only when dst is null, else the fused round trip with optional codes -- whose workgroups reduce
-// the partial maxima and derive the scale themselves.  Two launches; no clearing launch, no atomics, no
-// separate scale launch.  Inputs that miss the fast path's alignment take the separate calls.
+// the partial maxima and derive the scale themselves.  Two launches (one for a small tensor: quant_one); no clearing
+// launch, no atomics, no separate scale launch.  Inputs that miss the fast path's alignment take the separate calls.
 template <int SRCK>
 hif8_status conv_quantize_tensor(const void* src, void* dst, uint8_t* codes, size_t n, float target, int pow2,
                                  uint32_t mode, float* d_amax, float* d_scale2, uint32_t* parts, const SrArg* sr_or_null,
@@ -1165,6 +1296,7 @@ hif8_status conv_quantize_tensor(const void* src, void* dst, uint8_t* codes, siz
                : conv_encode<SRCK>(src, codes, n, 1.0f, d_scale2, nullptr, mode, sr_or_null, st);
   }
   const SrArg sr = sr_or_null ? *sr_or_null : SrArg{sr_seed(), 0};
+  if (quant_one<SRCK>(src, dst, codes, n, target, pow2, mode, d_amax, d_scale2, sr, tb, st)) return finish_launch();
   const uint32_t nparts = launch_amax_fast<SRCK, true>(src, n, parts, true, cus, st);
   const ScaleArg sa{1.0f, 1.0f, nullptr, parts, nparts, target, pow2, d_amax, d_scale2};
   if (dst) launch_fake_quant_fast<SRCK>(src, dst, codes, n, sa, nullptr, mode, sr, cus, tb, st);

@@ -245,3 +245,49 @@ def test_sr_seeds_give_different_carry_counts_on_the_gpu(h):
         counts.append(int((c != c.min()).sum().item()))
     assert len(set(counts)) >= 14
     assert all(abs(k - n / 8) < 5 * 84.7 for k in counts)
+
+
+# one launch up to 512 KiB of source: one workgroup and several, a share that ends with a vector, one element and seven past
+# it, no whole vector at all, the largest size and the first that takes two launches
+@pytest.mark.parametrize("kind", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("mode", [orc.RM_TA, orc.RM_HR, orc.RM_TE, orc.RM_SSR, orc.RM_SR])
+def test_one_launch_equals_the_separate_calls(h, kind, mode):
+    dtype, esize = {"f32": (torch.float32, 4), "bf16": (torch.bfloat16, 2), "f16": (torch.float16, 2)}[kind]
+    ve = 16 // esize
+    most = (512 << 10) // esize
+    call, amax = getattr(h, "hif8_quantize_tensor_" + kind), getattr(h, "hif8_amax_" + kind)
+    g = torch.Generator(device="cuda").manual_seed(mode)
+    ws = torch.empty(h.hif8_quantize_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    for n in (1, ve - 1, ve, 1024 * ve, 1024 * ve + 1, 1024 * ve + ve - 1, 3 * 1024 * ve + 77 * ve + 3, most - 1, most, most + ve + 1):
+        x = (torch.randn(n, device="cuda", generator=g) * 3).to(dtype)
+        x[n - 1] = -50.0  # the amax, in the ragged tail where there is one
+        a0, s0 = torch.zeros(1, device="cuda"), torch.zeros(2, device="cuda")
+        amax(x, n, a0)
+        h.hif8_scale_from_amax(a0, s0, h.MAX_FINITE, 1)
+        want, wc = torch.empty_like(x), torch.empty(n, dtype=torch.uint8, device="cuda")
+        getattr(h, "hif8_fake_quant_%s_ds" % kind)(x, want, wc, n, s0, mode)
+        for dst, codes in ((True, True), (True, False), (False, True)):
+            d, c = torch.full((n + 8,), 3.0, dtype=dtype, device="cuda"), torch.full((n + 8,), 7, dtype=torch.uint8, device="cuda")
+            a1, s1 = torch.zeros(1, device="cuda"), torch.zeros(2, device="cuda")
+            call(x, d if dst else None, c if codes else None, n, a1, s1, ws, h.MAX_FINITE, 1, mode)
+            assert torch.equal(a0, a1) and torch.equal(s0, s1)
+            assert not dst or (torch.equal(d[:n], want) and torch.all(d[n:] == 3.0))
+            assert not codes or (torch.equal(c[:n], wc) and torch.all(c[n:] == 7))
+        y = x.clone()  # in place: one workgroup reads everything before it writes, more than one take two launches
+        call(y, y, None, n, a1, s1, ws, h.MAX_FINITE, 1, mode)
+        assert torch.equal(y, want)
+
+
+@pytest.mark.parametrize("value", [0.0, float("nan"), float("inf")])
+def test_one_launch_of_zeros_nan_and_inf(h, value):
+    n = 40000
+    x = torch.zeros(n, dtype=torch.bfloat16, device="cuda")
+    x[-1] = value
+    ws = torch.empty(h.hif8_quantize_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    a0, s0, a1, s1 = (torch.zeros(k, device="cuda") for k in (1, 2, 1, 2))
+    h.hif8_amax_bf16(x, n, a0)
+    h.hif8_scale_from_amax(a0, s0, h.MAX_FINITE, 1)
+    wc, c = (torch.empty(n, dtype=torch.uint8, device="cuda") for _ in range(2))
+    h.hif8_encode_bf16_ds(x, wc, n, s0, h.RM_TA)
+    h.hif8_quantize_tensor_bf16(x, None, c, n, a1, s1, ws, h.MAX_FINITE, 1, h.RM_TA)
+    assert torch.equal(a0.view(torch.int32), a1.view(torch.int32)) and torch.equal(s0, s1) and torch.equal(c, wc)
