@@ -583,7 +583,7 @@ hif8_status hif8_gemm_expanded_sqerr(const uint16_t* a, const uint16_t* b, const
 
 /*
  * hif8_gemm_* on code operands with a workspace: both code matrices are expanded to bfloat16 into the
- * workspace (hif8_expand_bf16) and multiplied by the expanded-operand kernel -- three launches on `stream`, and
+ * workspace (hif8_expand_bf16) and multiplied by the expanded-operand kernel -- two or three launches on `stream`, and
  * for matrix-core-bound shapes about two thirds of the time of hif8_gemm_* (whose kernel expands the codes on
  * their way into LDS and is bound by that work).  Small products with up to 128 rows in one operand are taken
  * straight from the codes instead, in one launch, and leave the workspace unused.  Arguments, result and error bound as for hif8_gemm_* (the

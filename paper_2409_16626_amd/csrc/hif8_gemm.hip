@@ -312,9 +312,7 @@ static hif8_status gemm_ws(const uint8_t* A, const uint8_t* B, void* out, const 
   const size_t ld = expanded_ld(K);
   uint16_t* xa = reinterpret_cast<uint16_t*>(ws);
   uint16_t* xb = xa + M * ld;  // M * ld * 2 bytes is a multiple of 128: still 16-byte aligned
-  hif8_status s = expand_rows(A, M, K, xa, ld, st);
-  if (s != HIF8_OK) return s;
-  s = expand_rows(B, N, K, xb, ld, st);
+  const hif8_status s = expand_rows(A, M, B, N, K, xa, ld, st);
   if (s != HIF8_OK) return s;
   return gemm_expanded<EPI>(xa, xb, out, ref, err, M, N, ld, descale, st);
 }

@@ -281,7 +281,9 @@ constexpr size_t kMaxLd = (size_t)1 << 22;
 // small-tile kernel (set through hif8_gemm_set_variant)
 int& expanded_variant();
 
-hif8_status expand_rows(const uint8_t* codes, size_t rows, size_t K, uint16_t* dst, size_t ld, hipStream_t st);
+// codes of a, then of b (rows_b may be 0), to bfloat16 rows of pitch ld that follow each other in dst
+hif8_status expand_rows(const uint8_t* a, size_t rows_a, const uint8_t* b, size_t rows_b, size_t K, uint16_t* dst, size_t ld,
+                        hipStream_t st);
 hif8_status expand_cols(const uint8_t* codes, size_t rows, size_t cols, uint16_t* dst, size_t ld, hipStream_t st);
 
 // out = (A x B^T) * descale on operands of pitch ld (zero beyond K); batch.nb != 0: `pairs` GEMMs in one launch

@@ -60,8 +60,8 @@ constexpr size_t kSmallCodesRows = 128;
 
 // Which problems go to the small-tile kernel (hif8_gemm_s.hip) although the tiled kernels could run them.  The tiled
 // kernels take a whole K walk however few tiles there are (K = 4096: 85 us on codes, 25.7 us expanded), the small-tile
-// kernel's time goes with M N.  On codes they meet between M N = 2.8 M (256 x 11008 x 4096: 92 against 93 us) and 4.2 M
-// (384 x 11008 135 / 120, 1024 x 4096 112 / 91), at K = 11008 likewise (512 x 4096 150 / 231, 1024 x 4096 278 / 232).
+// kernel's time goes with M N.  On codes (us, small tiles / 128 x 128): 192 x 11008 x 4096 75 / 85, 256 x 11008 x 4096 94 /
+// 85, 384 x 11008 135 / 120, 1024 x 4096 112 / 91; K = 11008 512 x 4096 150 / 231, 1024 x 4096 278 / 232.
 // On expanded operands (us, small tiles / 128 x 128): 256 x 4096 x 4096 19.6 / 25.7, 384 x 4096 x 4096 29.2 / 25.9, 64 x
 // 11008 x 4096 21.2 / 24.6, 100 x 11008 x 4096 29.1 / 25.4; K = 11008 256 x 4096 38 / 64, 512 x 4096 80 / 65; K = 2048 512 x
 // 2048 12.5 / 14.3; K = 1024 300 x 5000 12.6 / 9.5.  With up to 32 rows on either side three quarters of a tile would be
@@ -69,7 +69,7 @@ constexpr size_t kSmallCodesRows = 128;
 inline bool small_problem(size_t M, size_t N, bool codes) {
   const size_t s = M < N ? M : N, l = M < N ? N : M;
   if (s <= 32) return true;
-  return codes ? l <= (size_t)3 * 1048576 / s : l <= (size_t)5 * 262144 / ((s + 31) / 32 * 32);
+  return codes ? l <= (size_t)9 * 262144 / s : l <= (size_t)5 * 262144 / ((s + 31) / 32 * 32);
 }
 
 // Tile (16 tm x 16 tn) and wavefronts per workgroup of the small-tile kernel.  The wavefronts split K, so a wavefront

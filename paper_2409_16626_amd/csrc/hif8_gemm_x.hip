@@ -249,88 +249,117 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
   }
 }
 
-// codes [rows, K] -> bf16 [rows, ld]; one 16-byte output chunk (8 elements) per lane and step
-__global__ void __launch_bounds__(256)
-k_expand_rows(const uint8_t* __restrict__ codes, uint16_t* __restrict__ dst, size_t rows, uint32_t K, uint32_t ld,
-              int vec_ok) {
+// The W codes at src[k .. k + W - 1] of a row of K codes as dwords, zero codes (+0) past its end; reads inside the row only,
+// at any address (W = 8 or 16).
+template <int W>
+struct CodeRun {
+  uint32_t w[W / 4];
+};
+template <int W>
+__device__ __forceinline__ CodeRun<W> load_codes(const uint8_t* __restrict__ row, uint32_t k, uint32_t K) {
+  CodeRun<W> c{};
+  if (k >= K) return c;
+  const uint32_t rem = K - k;
+  if (rem >= (uint32_t)W) {
+    __builtin_memcpy(&c, row + k, W);
+  } else if (K >= (uint32_t)W) {  // the last W codes of the row, moved down
+    __builtin_memcpy(&c, row + (K - W), W);
+    const uint32_t bits = 8u * (W - rem);
+#pragma unroll
+    for (uint32_t by = 32u; by < 8u * W; by += 32u)  // whole dwords first
+      if (bits >= by) {
+#pragma unroll
+        for (int i = 0; i < W / 4; ++i) c.w[i] = i + 1 < W / 4 ? c.w[i + 1] : 0u;
+      }
+#pragma unroll
+    for (int i = 0; i < W / 4; ++i) c.w[i] = (uint32_t)((((uint64_t)(i + 1 < W / 4 ? c.w[i + 1] : 0u) << 32) | c.w[i]) >> (bits & 31u));
+  } else {
+#pragma unroll
+    for (uint32_t j = 0; j < (uint32_t)W; ++j)
+      if (j < rem) c.w[j >> 2] |= (uint32_t)row[k + j] << (8u * (j & 3u));
+  }
+  return c;
+}
+
+// codes -> bf16 [rows, ld], ld the pitch, of the matrix a (rows_a rows of K codes) and, below it, of b: one launch for both
+// operands of a product.  One 16-byte output chunk (8 elements) per lane and step, four steps in flight; bound by memory
+// (11008 x 4096: 135 MB in 21.6 us).  Rows at odd addresses cost no more loads than aligned ones (11007 x 4095: 27.3 us with byte loads, 22.0).
+constexpr uint32_t kExpandBlock = 256, kExpandSteps = 4;
+__global__ void __launch_bounds__(kExpandBlock)
+k_expand_rows(const uint8_t* __restrict__ a, const uint8_t* __restrict__ b, uint16_t* __restrict__ dst, size_t rows_a, size_t rows,
+              uint32_t K, uint32_t ld) {
   __shared__ uint16_t lut[256];
-  lut[threadIdx.x] = (uint16_t)(decode_bits(threadIdx.x) >> 16);  // blockDim.x == 256
+  lut[threadIdx.x] = (uint16_t)(decode_bits(threadIdx.x) >> 16);
   __syncthreads();
   const uint32_t cpr = ld / 8u;  // output chunks per row
   const size_t total = rows * cpr;
-  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < total; q += (size_t)gridDim.x * blockDim.x) {
-    const size_t row = q / cpr;
-    const uint32_t k = (uint32_t)(q - row * cpr) * 8u;
-    const uint8_t* src = codes + row * K + k;
-    uint32_t c[8];
-    if (vec_ok && k + 8u <= K) {
-      const uint2 v = *reinterpret_cast<const uint2*>(src);
+  for (size_t q0 = (size_t)blockIdx.x * (kExpandBlock * kExpandSteps) + threadIdx.x; q0 < total;
+       q0 += (size_t)gridDim.x * (kExpandBlock * kExpandSteps)) {
+    CodeRun<8> c[kExpandSteps];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        c[j] = (v.x >> (8 * j)) & 0xFFu;
-        c[4 + j] = (v.y >> (8 * j)) & 0xFFu;
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) c[j] = (k + j < K) ? (uint32_t)src[j] : 0u;  // code 0x00 is +0
+    for (uint32_t j = 0; j < kExpandSteps; ++j) {
+      const size_t q = q0 + j * kExpandBlock;
+      const size_t row = total <= 0xFFFFFFFFu ? (size_t)((uint32_t)q / cpr) : q / cpr;
+      const uint32_t k = (uint32_t)(q - row * cpr) * 8u;
+      c[j] = q < total ? load_codes<8>(row < rows_a ? a + row * K : b + (row - rows_a) * K, k, K) : CodeRun<8>{};
     }
-    uint4 o;
-    o.x = lut[c[0]] | ((uint32_t)lut[c[1]] << 16);
-    o.y = lut[c[2]] | ((uint32_t)lut[c[3]] << 16);
-    o.z = lut[c[4]] | ((uint32_t)lut[c[5]] << 16);
-    o.w = lut[c[6]] | ((uint32_t)lut[c[7]] << 16);
-    *reinterpret_cast<uint4*>(dst + row * ld + k) = o;
+#pragma unroll
+    for (uint32_t j = 0; j < kExpandSteps; ++j) {
+      const size_t q = q0 + j * kExpandBlock;
+      if (q >= total) break;
+      const uint32_t* w = c[j].w;
+      uint4 o;
+      o.x = lut[w[0] & 0xFFu] | ((uint32_t)lut[(w[0] >> 8) & 0xFFu] << 16);
+      o.y = lut[(w[0] >> 16) & 0xFFu] | ((uint32_t)lut[w[0] >> 24] << 16);
+      o.z = lut[w[1] & 0xFFu] | ((uint32_t)lut[(w[1] >> 8) & 0xFFu] << 16);
+      o.w = lut[(w[1] >> 16) & 0xFFu] | ((uint32_t)lut[w[1] >> 24] << 16);
+      *reinterpret_cast<uint4*>(dst + q * 8u) = o;  // rows follow each other without gaps
+    }
   }
 }
 
 // codes [rows, cols] -> bf16 [cols, ld], transposed: dst[c * ld + r] = value(codes[r * cols + c]), zeros for
-// rows <= r < ld.  64 x 64 tiles through LDS: 16 codes per lane on the way in, one 16-byte chunk of an
-// output row per lane on the way out (8 consecutive lanes write 128 contiguous bytes).
-constexpr int kTT = 64;           // tile edge
-constexpr int kTPitch = kTT + 2;  // LDS row pitch in elements (33 dwords: consecutive rows start one bank apart)
+// rows <= r < ld.  Tiles of 64 x 128 codes through LDS: 16 codes per lane on the way in, on the way out a lane reads 8 rows of
+// 4 columns as dwords and looks each code up on its way into the 16-byte chunk of an output row (8 consecutive lanes write
+// 128 contiguous bytes).  LDS operations bound it: values transposed as 16-bit elements took two and a half per element,
+// codes take one and a quarter (11008 x 4096: 28.6 us -> 21.4, 6.3 TB/s; 11007 x 4095, then byte by byte: 89.5 -> 28.2).
+constexpr int kTR = 64, kTC = 128;  // tile rows and columns
+constexpr int kTPitch = kTC / 4 + 1;  // LDS row pitch in dwords: 8 rows further is 8 banks further
 __global__ void __launch_bounds__(256)
 k_expand_cols(const uint8_t* __restrict__ codes, uint16_t* __restrict__ dst, uint32_t rows, uint32_t cols, uint32_t ld,
-              uint32_t tiles_c, uint32_t n_tiles, int vec_ok) {
+              uint32_t tiles_c, uint32_t n_tiles) {
   __shared__ uint16_t lut[256];
-  __shared__ __attribute__((aligned(16))) uint16_t tile[kTT * kTPitch];
+  __shared__ uint32_t tile[kTR * kTPitch];
   const uint32_t t = threadIdx.x;
   lut[t] = (uint16_t)(decode_bits(t) >> 16);  // blockDim.x == 256
   for (uint32_t id = blockIdx.x; id < n_tiles; id += gridDim.x) {
     const uint32_t tr = id / tiles_c, tc = id - tr * tiles_c;
-    const uint32_t r0 = tr * kTT, c0 = tc * kTT;
-    __syncthreads();  // table written (first pass) / previous tile fully read
-    {
-      const uint32_t r = r0 + (t >> 2), c = c0 + (t & 3u) * 16u;
-      uint32_t w[4] = {0u, 0u, 0u, 0u};  // code 0x00 is +0: everything outside the matrix expands to zero
-      if (r < rows && c < cols) {
-        const uint8_t* src = codes + (size_t)r * cols + c;
-        if (vec_ok && c + 16u <= cols) {
-          const uint4 v = *reinterpret_cast<const uint4*>(src);
-          w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
-        } else {
-          for (uint32_t j = 0; j < 16u && c + j < cols; ++j) w[j >> 2] |= (uint32_t)src[j] << (8u * (j & 3u));
-        }
-      }
-      uint32_t* trow = reinterpret_cast<uint32_t*>(tile + (t >> 2) * kTPitch + (t & 3u) * 16u);
+    const uint32_t r0 = tr * kTR, c0 = tc * kTC;
+    CodeRun<16> in[2];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        trow[2 * j] = lut[w[j] & 0xFFu] | ((uint32_t)lut[(w[j] >> 8) & 0xFFu] << 16);
-        trow[2 * j + 1] = lut[(w[j] >> 16) & 0xFFu] | ((uint32_t)lut[w[j] >> 24] << 16);
-      }
+    for (int p = 0; p < 2; ++p) {
+      const uint32_t r = r0 + p * 32u + (t >> 3);
+      in[p] = r < rows ? load_codes<16>(codes + (size_t)r * cols, c0 + (t & 7u) * 16u, cols) : CodeRun<16>{};  // code 0x00 is +0
     }
-    __syncthreads();
+    __syncthreads();  // table written (first pass) / previous tile fully read
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const uint32_t q = t + k * 256u, c = q >> 3, rc = (q & 7u) * 8u;  // output row c0 + c, elements r0 + rc .. + 7
-      if (c0 + c < cols) {
-        const uint16_t* col = tile + rc * kTPitch + c;
-        uint4 o;
-        o.x = col[0] | ((uint32_t)col[kTPitch] << 16);
-        o.y = col[2 * kTPitch] | ((uint32_t)col[3 * kTPitch] << 16);
-        o.z = col[4 * kTPitch] | ((uint32_t)col[5 * kTPitch] << 16);
-        o.w = col[6 * kTPitch] | ((uint32_t)col[7 * kTPitch] << 16);
-        *reinterpret_cast<uint4*>(dst + (size_t)(c0 + c) * ld + r0 + rc) = o;
-      }
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) tile[(p * 32u + (t >> 3)) * kTPitch + (t & 7u) * 4u + i] = in[p].w[i];
+    __syncthreads();
+    const uint32_t rc = (t & 7u) * 8u, g = t >> 3;  // output elements r0 + rc .. + 7 of rows c0 + 4 g .. + 3
+    uint32_t v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = tile[(rc + i) * kTPitch + g];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t c = c0 + g * 4u + k;
+      uint32_t e[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) e[i] = lut[(v[i] >> (8 * k)) & 0xFFu];
+      if (c < cols)
+        *reinterpret_cast<uint4*>(dst + (size_t)c * ld + r0 + rc) =
+            make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
     }
   }
 }
@@ -338,20 +367,18 @@ k_expand_cols(const uint8_t* __restrict__ codes, uint16_t* __restrict__ dst, uin
 // ====================================================================================
 // host side
 // ====================================================================================
-hif8_status expand_rows(const uint8_t* codes, size_t rows, size_t K, uint16_t* dst, size_t ld, hipStream_t st) {
-  if (rows == 0) return HIF8_OK;
-  if (!dst || (!codes && K != 0)) return HIF8_ERR_NULL;
+hif8_status expand_rows(const uint8_t* a, size_t rows_a, const uint8_t* b, size_t rows_b, size_t K, uint16_t* dst, size_t ld,
+                        hipStream_t st) {
+  if (rows_a + rows_b == 0) return HIF8_OK;
+  if (!dst || ((!a || (!b && rows_b != 0)) && K != 0)) return HIF8_ERR_NULL;
   if (ld == 0 || ld % kExpandK != 0 || ld < K || ld > 0x7FFFFFC0u || K > 0x7FFFFFFFu || !aligned_to(dst, 16))
     return HIF8_ERR_ARG;
-  if (rows > ((size_t)1 << 60) / ld) return HIF8_ERR_ARG;
-  int cus = 0;
-  hif8_status s = ensure_init(&cus, nullptr);
+  if (rows_a + rows_b > ((size_t)1 << 60) / ld) return HIF8_ERR_ARG;
+  const hif8_status s = ensure_init(nullptr, nullptr);
   if (s != HIF8_OK) return s;
-  const int vec_ok = (K % 8 == 0) && aligned_to(codes, 8);
-  const size_t total = rows * (ld / 8);
-  const size_t want = (total + 255) / 256;
-  const unsigned grid = (unsigned)(want < (size_t)cus * 16 ? want : (size_t)cus * 16);
-  hipLaunchKernelGGL(k_expand_rows, dim3(grid), dim3(256), 0, st, codes, dst, rows, (uint32_t)K, (uint32_t)ld, vec_ok);
+  const size_t rows = rows_a + rows_b, per_wg = kExpandBlock * kExpandSteps, want = (rows * (ld / 8) + per_wg - 1) / per_wg;
+  const unsigned grid = (unsigned)(want < ((size_t)1 << 20) ? want : (size_t)1 << 20);
+  hipLaunchKernelGGL(k_expand_rows, dim3(grid), dim3(kExpandBlock), 0, st, a, b, dst, rows_a, rows, (uint32_t)K, (uint32_t)ld);
   return finish_launch();
 }
 
@@ -364,12 +391,11 @@ hif8_status expand_cols(const uint8_t* codes, size_t rows, size_t cols, uint16_t
   int cus = 0;
   hif8_status s = ensure_init(&cus, nullptr);
   if (s != HIF8_OK) return s;
-  const int vec_ok = (cols % 16 == 0) && aligned_to(codes, 16);
-  const size_t tiles_c = (cols + kTT - 1) / kTT, n_tiles = (ld / kTT) * tiles_c;
-  if (n_tiles > 0x7FFFFFFFull) return HIF8_ERR_ARG;
+  if ((ld / kTR) * ((cols + 63) / 64) > 0x7FFFFFFFull) return HIF8_ERR_ARG;
+  const size_t tiles_c = (cols + kTC - 1) / kTC, n_tiles = (ld / kTR) * tiles_c;
   const unsigned grid = (unsigned)(n_tiles < (size_t)cus * 16 ? n_tiles : (size_t)cus * 16);
   hipLaunchKernelGGL(k_expand_cols, dim3(grid), dim3(256), 0, st, codes, dst, (uint32_t)rows, (uint32_t)cols, (uint32_t)ld,
-                     (uint32_t)tiles_c, (uint32_t)n_tiles, vec_ok);
+                     (uint32_t)tiles_c, (uint32_t)n_tiles);
   return finish_launch();
 }
 
@@ -495,7 +521,7 @@ size_t hif8_expanded_ld(size_t K) { return expanded_ld(K); }
 
 hif8_status hif8_expand_bf16(const uint8_t* codes, size_t rows, size_t K, uint16_t* dst, size_t ld,
                              hif8_stream_t stream) {
-  return expand_rows(codes, rows, K, dst, ld, (hipStream_t)stream);
+  return expand_rows(codes, rows, nullptr, 0, K, dst, ld, (hipStream_t)stream);
 }
 
 hif8_status hif8_expand_bf16_t(const uint8_t* codes, size_t rows, size_t cols, uint16_t* dst, size_t ld,

@@ -152,3 +152,40 @@ def test_scale_search_casts(h, kind, mode):
         fin = torch.where(torch.isfinite(err), err, float("inf"))
         pos = int(fin.argmin()) if torch.isfinite(err).any() else 0
         assert best.tolist() == [ea + pos // nb, ew + pos % nb]
+
+
+# rows of every remainder of a run of 8 codes and of 16, shorter and longer than a run; one past and one below a tile of
+# 64 x 128; the matrix at the start and at an odd address of its buffer, whose next byte is NaN
+@pytest.mark.parametrize("rows", [1, 5, 63, 64, 65, 130])
+def test_expansions_of_every_remainder(h, rows):
+    lut = torch.tensor([orc.decode_value(c) for c in range(256)], dtype=torch.float64).to(torch.bfloat16).view(torch.int16).to(dev())
+    lut[0x80] = torch.tensor(0x7FC0, dtype=torch.int16)
+    g = torch.Generator(device=dev()).manual_seed(rows)
+    for cols in (1, 2, 3, 7, 8, 9, 13, 15, 16, 17, 23, 24, 31, 33, 63, 64, 65, 120, 127, 128, 129, 136, 200):
+        for off in (0, 1):
+            buf = torch.full((rows * cols + off + 16,), 0x80, dtype=torch.uint8, device=dev())
+            codes = buf[off:off + rows * cols]
+            codes.copy_(torch.randint(0, 256, (rows * cols,), dtype=torch.uint8, device=dev(), generator=g))
+            want = lut[codes.long()].view(rows, cols)
+            for call, w in ((h.hif8_expand_bf16, want), (h.hif8_expand_bf16_t, want.t())):
+                r, c = w.shape
+                ld = h.hif8_expanded_ld(c)
+                dst = torch.full((r + 1, ld), 0x1234, dtype=torch.int16, device=dev())
+                call(codes, rows, cols, dst, ld)
+                assert torch.equal(dst[:r, :c], w) and torch.all(dst[:r, c:] == 0) and torch.all(dst[r] == 0x1234)
+
+
+def test_workspace_product_expands_both_operands(h):
+    """Both operands of hif8_gemm_ws_* are expanded in one launch: the bits of the two expansions and the product on them."""
+    rng = np.random.default_rng(4)
+    for M, N, K in ((1300, 1100, 67), (257, 8200, 5), (1500, 1400, 130)):
+        a, b = (torch.from_numpy(random_codes(rng, (r, K), "cast_normal")).to(dev()) for r in (M, N))
+        ld = h.hif8_expanded_ld(K)
+        xa, xb = (torch.empty(r, ld, dtype=torch.bfloat16, device=dev()) for r in (M, N))
+        h.hif8_expand_bf16(a, M, K, xa, ld)
+        h.hif8_expand_bf16(b, N, K, xb, ld)
+        ws = torch.full((h.hif8_gemm_workspace_bytes(M, N, K),), 0x7F, dtype=torch.uint8, device=dev())
+        one, two = (torch.empty(M, N, device=dev()) for _ in range(2))
+        h.hif8_gemm_ws_f32(a, b, one, M, N, K, ws, 2.0, 4.0)
+        h.hif8_gemm_expanded_f32(xa, xb, two, M, N, K, ld, 2.0, 4.0)
+        assert torch.equal(ws.view(torch.int16), torch.cat([xa, xb]).view(torch.int16).reshape(-1)) and torch.equal(one, two)
