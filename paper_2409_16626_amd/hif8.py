@@ -165,8 +165,16 @@ def _ptr(t):
     return t.data_ptr()
 
 
+_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
+    """Handle of `stream`, or of the current stream.  torch.cuda.current_stream() builds a Stream object first, 2.9 of the
+    7.2 us of a small call; the handle alone takes 0.2 us (the call: 4.5 us)."""
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream

@@ -160,3 +160,17 @@ def test_one_call_entry_points_replay_exactly(h):
             sk = orc.scale_from_amax(amk, 32768.0, True)
             assert graphed.am[2 + k].item() == float(amk)
             assert np.array_equal(graphed.c_mc[lo:lo + m].cpu().numpy(), orc.encode_bf16(xn[lo:lo + m], sk, orc.RM_TA)), (rep, k)
+
+
+def test_calls_without_a_stream_take_the_current_one(h):
+    """The handle the wrappers pass is the current stream's: the default, a side stream, nested, and after leaving them."""
+    from paper_2409_16626_amd import hif8
+    side, inner = torch.cuda.Stream(), torch.cuda.Stream()
+    assert hif8._stream(None) == torch.cuda.current_stream().cuda_stream == torch.cuda.default_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert hif8._stream(None) == side.cuda_stream
+        with torch.cuda.stream(inner):
+            assert hif8._stream(None) == inner.cuda_stream
+        assert hif8._stream(None) == side.cuda_stream
+    assert hif8._stream(None) == torch.cuda.default_stream().cuda_stream
+    assert hif8._stream(side) == side.cuda_stream and hif8._stream(side.cuda_stream) == side.cuda_stream
