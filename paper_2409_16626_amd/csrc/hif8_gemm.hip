@@ -74,6 +74,69 @@ __device__ __forceinline__ uint4 load_chunk(const uint8_t* __restrict__ P, uint3
   return ok ? v : make_uint4(0u, 0u, 0u, 0u);
 }
 
+// Epilogue of one wavefront, straight from the accumulators: TM x TN blocks of v_mfma_f32_32x32x16_bf16 whose top-left
+// element is (row0, col0).  Element v of a 32 x 32 block sits at row (v / 4) * 8 + (lane / 32) * 4 + v % 4,
+// column lane % 32.  EPI_ERR adds the squared differences to *err in fp64: the wavefronts of the workgroup
+// combine through `wg_scratch` (LDS, at least one double per wavefront, free of other use by now; every
+// wavefront of the workgroup must make this call) and issue one atomic per workgroup.  The K loop here leaves the memory
+// path idle, so whole lines through LDS (the epilogue of the expanded-operand kernel) gain little, 48.9 -> 46.2 us at 512 x
+// 6000 x 2048, and lose on rows that are not 16-byte aligned, 27.4 -> 30.1 us at 1501 x 1503 x 1024.
+template <int EPI, int TM, int TN>
+__device__ __forceinline__ void epilogue_direct(const f32x16 (&acc)[TM][TN], void* __restrict__ out,
+                                         const float* __restrict__ ref, double* __restrict__ err, uint32_t M,
+                                         uint32_t N, uint32_t row0, uint32_t col0, uint32_t lane, float descale,
+                                         double* wg_scratch, uint32_t wave, uint32_t n_waves) {
+  double e2 = 0.0;
+  // the whole wavefront tile inside the matrix (the usual case): no per-element bounds checks
+  const bool inside = row0 + TM * 32 <= M && col0 + TN * 32 <= N;
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const uint32_t col = col0 + j * 32 + (lane & 31u);
+      const uint32_t rbase = row0 + i * 32 + (lane >> 5) * 4;
+      if constexpr (EPI == EPI_ERR) {
+        // all 16 reference values of the block are requested before the first is used; positions
+        // outside the matrix read element 0 and contribute nothing
+        float r[16];
+        bool ok[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const uint32_t row = rbase + (v >> 2) * 8 + (v & 3);
+          ok[v] = inside || (row < M && col < N);
+          r[v] = ref[ok[v] ? (size_t)row * N + col : (size_t)0];
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const double d = (double)__fmul_rn(acc[i][j][v], descale) - (double)r[v];
+          e2 = ok[v] ? fma(d, d, e2) : e2;
+        }
+      } else if (inside) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          store_one<EPI>(out, (size_t)(rbase + (v >> 2) * 8 + (v & 3)) * N + col, __fmul_rn(acc[i][j][v], descale));
+      } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const uint32_t row = rbase + (v >> 2) * 8 + (v & 3);
+          if (row < M && col < N) store_one<EPI>(out, (size_t)row * N + col, __fmul_rn(acc[i][j][v], descale));
+        }
+      }
+    }
+  }
+  if constexpr (EPI == EPI_ERR) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) e2 += __shfl_xor(e2, off, 64);
+    if (lane == 0) wg_scratch[wave] = e2;
+    __syncthreads();
+    if (wave == 0 && lane == 0) {
+      double t = 0.0;
+      for (uint32_t w = 0; w < n_waves; ++w) t += wg_scratch[w];
+      unsafeAtomicAdd(err, t);  // hardware fp64 add at the L2, no compare-and-swap loop
+    }
+  }
+}
+
 template <int WM, int WN, int TM, int TN, int BK, int EPI>
 __global__ void __launch_bounds__(64 * WM * WN)
 k_gemm_nt(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __restrict__ out,
@@ -163,7 +226,7 @@ k_gemm_nt(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
     }
     store_tiles(set, buf ^ 1);
     __syncthreads();
@@ -184,9 +247,8 @@ k_gemm_nt(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __
   if (kt < nk) k_step(kt, 0, 1);
 
   // the last K step ended with a barrier: the tile buffers (behind the table) are free for the epilogue
-  static_assert(WM * WN * epilogue_lds(2) <= 4 * (BM + BN) * LDA, "LDS of the epilogue");
-  epilogue<EPI, TM, TN, 2>(acc, out, ref, err, M, N, m0 + wm * TM * 32, n0 + wn * TN * 32, lane, descale,
-                           reinterpret_cast<uint8_t*>(As), wave, WM * WN);
+  epilogue_direct<EPI, TM, TN>(acc, out, ref, err, M, N, m0 + wm * TM * 32, n0 + wn * TN * 32, lane, descale,
+                               reinterpret_cast<double*>(As), wave, WM * WN);
 }
 
 // ====================================================================================
@@ -267,7 +329,7 @@ static hif8_status gemm_dispatch(const uint8_t* A, const uint8_t* B, void* out, 
   if (s != HIF8_OK) return s;
   const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
   const bool fast = K != 0 && (K % 16) == 0 && aligned_to(A, 16) && aligned_to(B, 16);
-  if (!fast || g_gemm_variant == 12 || (g_gemm_variant == 0 && small_problem(M, N, true)))
+  if (!fast || g_gemm_variant == 12 || (g_gemm_variant == 0 && small_problem(M, N, true, K)))
     return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st);
   int variant = g_gemm_variant;
   uint32_t split = 0;

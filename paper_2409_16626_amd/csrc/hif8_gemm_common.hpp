@@ -56,9 +56,9 @@ __device__ __forceinline__ uint32_t pack16(float a, float b) {
   else return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, f16x2));
 }
 
-// Epilogue of one wavefront: TM x TN accumulator blocks of v_mfma_f32_32x32x16_bf16, multiplied as B x A^T so that a
-// lane holds runs of four neighbouring columns: element v of a block sits at row lane % 32, column
-// (v / 4) * 8 + (lane / 32) * 4 + v % 4.  (row0, col0): top-left element of the wavefront's tile.
+// Epilogue of one wavefront of the expanded-operand kernel: TM x TN blocks of 32 x 32, each of 2 x 2 accumulators of
+// v_mfma_f32_16x16x32_bf16, multiplied as B x A^T so that a lane holds runs of four neighbouring columns (row lane % 16,
+// columns (lane / 16) * 4 .. + 3).  (row0, col0): top-left element of the wavefront's tile.
 //
 // What bounds it is the number of memory instructions and the lines each of them touches: stored element by element from
 // the accumulators, a 256 x 256 tile takes 1024 store instructions, and a round of such tiles spent 11 us (bfloat16), 13
@@ -96,20 +96,7 @@ struct EpilogueChunks {
   }
 };
 
-// W blocks of 32 x 32 from block (I, J) on, descaled, into LDS: accumulators of v_mfma_f32_32x32x16_bf16 ...
-template <int I, int J, int W, int TM, int TN>
-__device__ __forceinline__ void blocks_to_lds(const f32x16 (&acc)[TM][TN], float* stage, int pitch, uint32_t lane, float descale) {
-  float* const at = stage + (lane & 31u) * pitch + (lane >> 5) * 4u;
-#pragma unroll
-  for (int j = 0; j < W; ++j)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const f32x16& a = acc[I][J + j];
-      *reinterpret_cast<f32x4*>(at + j * 32 + g * 8) = f32x4{__fmul_rn(a[4 * g], descale), __fmul_rn(a[4 * g + 1], descale),
-                                                             __fmul_rn(a[4 * g + 2], descale), __fmul_rn(a[4 * g + 3], descale)};
-    }
-}
-// ... and of v_mfma_f32_16x16x32_bf16 (row lane % 16, columns (lane / 16) * 4 .. + 3 of a 16 x 16 block)
+// W blocks of 32 x 32 from block (I, J) on, descaled, into LDS.
 template <int I, int J, int W, int TM2, int TN2>
 __device__ __forceinline__ void blocks_to_lds(const f32x4 (&acc)[TM2][TN2], float* stage, int pitch, uint32_t lane, float descale) {
   float* const at = stage + (lane & 15u) * pitch + (lane >> 4) * 4u;

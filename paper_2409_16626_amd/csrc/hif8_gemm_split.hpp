@@ -61,15 +61,16 @@ constexpr size_t kSmallCodesRows = 128;
 // Which problems go to the small-tile kernel (hif8_gemm_s.hip) although the tiled kernels could run them.  The tiled
 // kernels take a whole K walk however few tiles there are (K = 4096: 85 us on codes, 25.7 us expanded), the small-tile
 // kernel's time goes with M N.  On codes (us, small tiles / 128 x 128): 192 x 11008 x 4096 75 / 85, 256 x 11008 x 4096 94 /
-// 85, 384 x 11008 135 / 120, 1024 x 4096 112 / 91; K = 11008 512 x 4096 150 / 231, 1024 x 4096 278 / 232.
+// 85, 384 x 11008 135 / 120, 1024 x 4096 112 / 91; K = 1024 1500 x 1500 28.5 / 27.4, K = 512
+// 700 x 3000 19.4 / 18.6, K = 256 1000 x 2000 14.0 / 13.1 (below K = 1024 up to 1.6 M); K = 11008 512 x 4096 150 / 231, 1024 x 4096 278 / 232.
 // On expanded operands (us, small tiles / 128 x 128): 256 x 4096 x 4096 19.6 / 25.7, 384 x 4096 x 4096 29.2 / 25.9, 64 x
 // 11008 x 4096 21.2 / 24.6, 100 x 11008 x 4096 29.1 / 25.4; K = 11008 256 x 4096 38 / 64, 512 x 4096 80 / 65; K = 2048 512 x
 // 2048 12.5 / 14.3; K = 1024 300 x 5000 12.6 / 9.5.  With up to 32 rows on either side three quarters of a tile would be
 // padding, so such products stay with the small tiles whatever the other side is.
-inline bool small_problem(size_t M, size_t N, bool codes) {
+inline bool small_problem(size_t M, size_t N, bool codes, size_t K = 4096) {
   const size_t s = M < N ? M : N, l = M < N ? N : M;
   if (s <= 32) return true;
-  return codes ? l <= (size_t)9 * 262144 / s : l <= (size_t)5 * 262144 / ((s + 31) / 32 * 32);
+  return codes ? l <= (size_t)(K < 1024 ? 24 : 33) * 65536 / s : l <= (size_t)5 * 262144 / ((s + 31) / 32 * 32);
 }
 
 // Tile (16 tm x 16 tn) and wavefronts per workgroup of the small-tile kernel.  The wavefronts split K, so a wavefront
