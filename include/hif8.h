@@ -261,7 +261,8 @@ hif8_status hif8_fake_quant_f16_sr(const uint16_t* src, uint16_t* dst, uint8_t* 
  * pass leaves one partial maximum per workgroup in `workspace`, and every workgroup of the cast
  * reduces those and derives the scale itself (no clearing launch, no atomics, no scale launch).
  * The first pass reads with ordinary loads, so a tensor that fits the 256 MB last-level cache is
- * still there when the cast reads it again.
+ * still there when the cast reads it again.  A source of up to 512 KiB takes one launch, whose
+ * workgroups each read all of it, and leaves the workspace as it is.
  * At least one of dst, codes must be given; dst may equal src.  d_amax: one device float,
  * d_scale2: two device floats, both written.  workspace: device scratch of at least
  * hif8_quantize_workspace_bytes() bytes (4 KiB), 4-byte aligned, caller-owned; its contents need
