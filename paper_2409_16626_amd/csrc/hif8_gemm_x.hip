@@ -44,8 +44,8 @@ constexpr int kWaitVm0 = 0x0F70;          // vmcnt(0)
 constexpr int wait_vm(int n) { return (n & 15) | (n >> 4) << 14; }
 constexpr int kRsrcFlags = 0x00020000;    // word 3 of a raw (unstructured, untyped) buffer descriptor on gfx9-family parts
 
-// The K loop of a 256 x 256 tile is bound by the matrix cores at the clock that the power limit leaves them, provided that
-// a wavefront (alone on its SIMD) never makes them wait:
+// The K loop of a 256 x 256 tile is bound by what makes a wavefront (alone on its SIMD) keep the matrix cores waiting, above all
+// the barrier of each K step (70 % of the cycles busy), and by the clock that the power limit leaves them:
 //   * v_mfma_f32_16x16x32_bf16 costs less power than the 32 x 32 x 16 shape on operands with HiF8's few mantissa bits
 //     (in registers only 1.97 PFLOP/s against 1.80), and with 16 cycles each there is a place for a memory instruction
 //     every 16 cycles.
