@@ -28,11 +28,18 @@ inline bool ragged_round_split(size_t M, size_t N, size_t cus, uint32_t* split) 
 // Measured in us (256 x 256 / 256 x 192 / 128 x 128): 2048 x 11008 x 4096 151 / 128 / 138, 2048 x 4096 x 11008
 // 183 / 164 / 131, 11008 x 4096 x 2048 132 / 142 / 148, 4096^3 84 / 126 / 99.
 enum : int { TILE_256 = 0, TILE_192 = 1, TILE_128 = 2, TILE_SPLIT = 3 };
-inline uint64_t tile_cost(int tile, size_t M, size_t N, size_t pairs, size_t cus) {
+inline uint64_t tile_count(int tile, size_t M, size_t N, size_t pairs) {
   const uint64_t bm = tile == TILE_128 ? 128 : 256, bn = tile == TILE_256 ? 256 : tile == TILE_192 ? 192 : 128;
-  const uint64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * (uint64_t)pairs;
+  return ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * (uint64_t)pairs;
+}
+// LDS stages of a launch: four for 128 x 128 tiles where every workgroup has a compute unit to itself.  What is priced and
+// what is launched ask here (columns behind a split with two stages / four, us: 4096 x 5000 x 4096 124 / 116, 1792 x 9472 x
+// 4096 120 / 107).
+inline int tile_stages(int tile, uint64_t tiles, size_t cus) { return tile == TILE_128 && tiles <= cus ? 4 : 2; }
+inline uint64_t tile_cost(int tile, size_t M, size_t N, size_t pairs, size_t cus) {
+  const uint64_t tiles = tile_count(tile, M, N, pairs);
   if (tile != TILE_128) return (tiles + cus - 1) / cus * (tile == TILE_256 ? 130u : 100u);
-  if (tiles <= cus) return 40u;
+  if (tile_stages(tile, tiles, cus) == 4) return 40u;
   const uint64_t rest = tiles % (2 * cus);
   return tiles / (2 * cus) * 76u + (rest == 0 ? 0u : rest <= cus ? 62u : 76u);
 }
@@ -51,6 +58,24 @@ inline int tile_plan(size_t M, size_t N, size_t pairs, size_t cus, uint32_t* spl
       tile_cost(TILE_256, M, *split, 1, cus) + tile_cost(TILE_128, M, N - *split, 1, cus) + 10u < cost)
     best = TILE_SPLIT;
   return best;
+}
+
+// The launches of a plan, one after the other on columns [begin, end) each; returns how many (one or two).
+struct TileLaunch {
+  int tile, stages;
+  uint32_t begin, end;
+};
+inline int tile_launches(int plan, size_t M, size_t N, size_t pairs, size_t cus, uint32_t split, TileLaunch (&out)[2]) {
+  auto one = [&](int tile, size_t begin, size_t end) {
+    return TileLaunch{tile, tile_stages(tile, tile_count(tile, M, end - begin, pairs), cus), (uint32_t)begin, (uint32_t)end};
+  };
+  if (plan != TILE_SPLIT) {
+    out[0] = one(plan, 0, N);
+    return 1;
+  }
+  out[0] = one(TILE_256, 0, split);
+  out[1] = one(TILE_128, split, N);
+  return 2;
 }
 
 // Products with at most this many rows on one side run straight from the codes in hif8_gemm_ws_* when they go to the

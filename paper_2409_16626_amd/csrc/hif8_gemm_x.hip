@@ -406,11 +406,10 @@ int& expanded_variant() {
   return v;
 }
 
-template <int TA, int TB, int EPI, int ST = 2>
+template <int TA, int TB, int EPI, int ST>
 static hif8_status launch_x(const uint16_t* A, const uint16_t* B, void* out, const float* ref, double* err, uint32_t M,
                             uint32_t N, uint32_t ld, float descale, hipStream_t st, int cus, const Batch& batch,
-                            uint32_t col_begin = 0, uint32_t col_end = 0xFFFFFFFFu) {
-  if (col_end > N) col_end = N;
+                            uint32_t col_begin, uint32_t col_end) {
   constexpr bool WALK = EPI == EPI_ERR && TA == 8 && TB == 8;
   constexpr int BM = 32 * TA, BN = 32 * TB;
   constexpr size_t stage = (size_t)(BM + BN) * kRowBytes, epi = 4 * (size_t)epilogue_lds(TB < 8 ? 2 : 4);
@@ -425,7 +424,6 @@ static hif8_status launch_x(const uint16_t* A, const uint16_t* B, void* out, con
       return HIF8_ERR_HIP;
     attr_set[dev] = true;
   }
-  if (col_begin >= col_end) return HIF8_OK;
   const uint32_t tiles_m = (M + BM - 1) / BM, tiles_n = (col_end - col_begin + BN - 1) / BN;
   const uint64_t total = (uint64_t)tiles_m * tiles_n * (batch.na ? batch.na * batch.nb : 1u);
   if (total > 0x7FFFFFF0ull) return HIF8_ERR_ARG;
@@ -469,18 +467,18 @@ hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const
   if (pairs == 1 && batch.na == 0u && (variant == 12 || (variant == 0 && small_problem(M, N, false))))
     return gemm_small<EPI>(A, B, true, out, ref, err, M, N, ld, descale, st);
   uint32_t split = 0;
-  const int tile = variant == 9 ? TILE_128 : variant == 10 ? TILE_256 : variant == 11 ? TILE_192 : tile_plan(M, N, pairs, (size_t)cus, &split);
-  if (tile == TILE_SPLIT) {
-    s = launch_x<8, 8, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch, 0u, split);
-    if (s != HIF8_OK) return s;
-    return launch_x<4, 4, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch, split, n);
+  const int plan = variant == 9 ? TILE_128 : variant == 10 ? TILE_256 : variant == 11 ? TILE_192 : tile_plan(M, N, pairs, (size_t)cus, &split);
+  TileLaunch launches[2];
+  const int count = tile_launches(plan, M, N, pairs, (size_t)cus, split, launches);
+  for (int i = 0; i < count && s == HIF8_OK; ++i) {
+    const TileLaunch& l = launches[i];
+    auto run = [&](auto launch) { s = launch(A, B, out, ref, err, m, n, k, descale, st, cus, batch, l.begin, l.end); };
+    if (l.tile == TILE_256) run(launch_x<8, 8, EPI, 2>);
+    else if (l.tile == TILE_192) run(launch_x<8, 6, EPI, 2>);
+    else if (l.stages == 4) run(launch_x<4, 4, EPI, 4>);
+    else run(launch_x<4, 4, EPI, 2>);
   }
-  if (tile == TILE_256) return launch_x<8, 8, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch);
-  if (tile == TILE_192) return launch_x<8, 6, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch);
-  // 128 x 128: four stages where every workgroup has a compute unit to itself
-  if (((M + 127) / 128) * ((N + 127) / 128) * pairs <= (size_t)cus)
-    return launch_x<4, 4, EPI, 4>(A, B, out, ref, err, m, n, k, descale, st, cus, batch);
-  return launch_x<4, 4, EPI>(A, B, out, ref, err, m, n, k, descale, st, cus, batch);
+  return s;
 }
 
 template hif8_status gemm_expanded<EPI_F32>(const uint16_t*, const uint16_t*, void*, const float*, double*, size_t, size_t,

@@ -85,9 +85,19 @@ uint32_t devfn_small_plan(size_t M, size_t N, int codes, int force, uint32_t* wa
   *waves = p.waves;
   return force || hif8gemm::small_problem(M, N, codes != 0) ? p.tm * 100 + p.tn * 10 : 0u;
 }
-// expanded-operand GEMM: tile (0 = 256 x 256, 1 = 256 x 192, 2 = 128 x 128, 3 = split) and the split column
-int devfn_tile_plan(size_t M, size_t N, size_t pairs, size_t cus, uint32_t* split) {
-  *split = 0;
-  return hif8gemm::tile_plan(M, N, pairs, cus, split);
+// expanded-operand GEMM: the launches of its plan, 4 numbers each: tile (0 = 256 x 256, 1 = 256 x 192, 2 = 128 x 128), LDS
+// stages, first column, end; returns how many
+int devfn_tile_launches(size_t M, size_t N, size_t pairs, size_t cus, uint32_t* out) {
+  uint32_t split = 0;
+  const int plan = hif8gemm::tile_plan(M, N, pairs, cus, &split);
+  hif8gemm::TileLaunch l[2];
+  const int n = hif8gemm::tile_launches(plan, M, N, pairs, cus, split, l);
+  for (int i = 0; i < n; ++i) {
+    out[4 * i] = (uint32_t)l[i].tile;
+    out[4 * i + 1] = (uint32_t)l[i].stages;
+    out[4 * i + 2] = l[i].begin;
+    out[4 * i + 3] = l[i].end;
+  }
+  return n;
 }
 }

@@ -228,36 +228,59 @@ def test_small_gemm_plan(dev):
             assert got[0][1] == got[1][1]
 
 
-def test_gemm_tile_plan(dev):
-    """Tile of the expanded-operand GEMM: none of the single tiles has a shorter sum of rounds than the plan's, and a split
-    lies on a tile column inside the matrix."""
-    dev.devfn_tile_plan.restype = ctypes.c_int
-    dev.devfn_tile_plan.argtypes = [ctypes.c_size_t] * 4 + [ctypes.POINTER(ctypes.c_uint32)]
+# sum of rounds of a launch by the kernel it starts (tile, LDS stages): the measured times behind the rule, relative to each other
+def launch_price(tile, stages, tiles, cus):
+    if tile != 2:
+        assert stages == 2
+        return -(-tiles // cus) * (130, 100)[tile]
+    if stages == 4:
+        assert tiles <= cus  # a compute unit holds one workgroup of this form
+        return 40
+    rest = tiles % (2 * cus)
+    return tiles // (2 * cus) * 76 + (0 if rest == 0 else 62 if rest <= cus else 76)
 
-    def plan(M, N, pairs=1, cus=256):
-        s = ctypes.c_uint32(0)
-        return dev.devfn_tile_plan(M, N, pairs, cus, ctypes.byref(s)), s.value
 
-    def cost(t, M, N, pairs, cus):
-        bm, bn, each = ((256, 256, 130), (256, 192, 100), (128, 128, 0))[t]
-        tiles = -(-M // bm) * -(-N // bn) * pairs
-        if each:
-            return -(-tiles // cus) * each
-        if tiles <= cus:
-            return 40
-        rest = tiles % (2 * cus)
-        return tiles // (2 * cus) * 76 + (0 if rest == 0 else 62 if rest <= cus else 76)
+def tile_count(tile, M, N, pairs):
+    bm, bn = ((256, 256), (256, 192), (128, 128))[tile]
+    return -(-M // bm) * -(-N // bn) * pairs
 
-    assert plan(4096, 4096)[0] == 0 and plan(2048, 11008)[0] == 1 and plan(2048, 4096)[0] == 2 and plan(1500, 1500)[0] == 2
-    assert plan(8192, 11008) == (3, 40 * 256) and plan(2048, 4096, 100)[0] == 0 and plan(1, 1)[0] == 2
+
+@pytest.fixture(scope="module")
+def tile_launches(dev):
+    dev.devfn_tile_launches.restype = ctypes.c_int
+    dev.devfn_tile_launches.argtypes = [ctypes.c_size_t] * 4 + [ctypes.POINTER(ctypes.c_uint32)]
+
+    def launches(M, N, pairs=1, cus=256):
+        out = (ctypes.c_uint32 * 8)()
+        return [tuple(out[4 * i:4 * i + 4]) for i in range(dev.devfn_tile_launches(M, N, pairs, cus, out))]
+    return launches
+
+
+def test_gemm_tile_plan(tile_launches):
+    """Launches of the expanded-operand GEMM: they cover the columns; priced by the kernels they start, none of the single tiles
+    in its best form has a shorter sum of rounds; and a split is shorter than all of them by its second launch at least."""
+    assert [l[0] for l in tile_launches(4096, 4096)] == [0] and [l[0] for l in tile_launches(2048, 11008)] == [1]
+    assert [l[0] for l in tile_launches(2048, 4096)] == [2] and [l[0] for l in tile_launches(2048, 4096, 100)] == [0]
+    assert tile_launches(1, 1) == [(2, 4, 0, 1)]
+    assert tile_launches(8192, 11008) == [(0, 2, 0, 40 * 256), (2, 2, 40 * 256, 11008)]
+    assert tile_launches(4096, 5000) == [(0, 2, 0, 4096), (2, 4, 4096, 5000)]  # 256 tiles of 128 x 128 in the remainder
     rng = np.random.default_rng(6)
-    for _ in range(2000):
-        M, N, pairs = int(2.0 ** rng.uniform(0, 16)), int(2.0 ** rng.uniform(0, 16)), int(rng.choice([1, 1, 16, 100]))
-        cus = int(rng.choice([64, 256, 304]))
-        t, split = plan(M, N, pairs, cus)
-        least = min(cost(c, M, N, pairs, cus) for c in range(3))
-        if t == 3:
-            assert pairs == 1 and split % 256 == 0 and 0 < split < N
-            assert cost(0, M, split, 1, cus) + cost(2, M, N - split, 1, cus) < least
+    splits = 0
+    shapes = [(256 * int(rng.integers(1, 33)), 64 * int(rng.integers(4, 173)), 1, 256) for _ in range(2000)]
+    shapes += [(int(2.0 ** rng.uniform(0, 16)), int(2.0 ** rng.uniform(0, 16)), int(rng.choice([1, 1, 16, 100])),
+                int(rng.choice([64, 256, 304]))) for _ in range(2000)]
+    for M, N, pairs, cus in shapes:
+        got = tile_launches(M, N, pairs, cus)
+        assert got[0][2] == 0 and got[-1][3] == N and all(a[3] == b[2] for a, b in zip(got, got[1:]))
+        price = sum(launch_price(t, st, tile_count(t, M, end - begin, pairs), cus) for t, st, begin, end in got)
+        singles = []
+        for t in range(3):
+            n = tile_count(t, M, N, pairs)
+            singles.append(launch_price(t, 4 if t == 2 and n <= cus else 2, n, cus))
+        if len(got) == 2:
+            splits += 1
+            assert pairs == 1 and got[0][3] % 256 == 0 and 0 < got[0][3] < N
+            assert price + 10 < min(singles), (M, N, cus, got)
         else:
-            assert cost(t, M, N, pairs, cus) == least
+            assert price == min(singles), (M, N, pairs, cus, got)
+    assert splits > 100

@@ -14,9 +14,11 @@ pytestmark = pytest.mark.gpu
 
 
 # K steps 1, 2, 3, 4 and more; rows that are not 16-byte aligned (N odd), shorter than a run of four or of eight columns, one
-# past and one below a block; one tile, edge tiles only, whole tiles and edge tiles
+# past and one below a block; one tile, edge tiles only, whole tiles and edge tiles; more 128 x 128 tiles than compute units (two
+# LDS stages there, four in all the others)
 @pytest.mark.parametrize("variant", [9, 10, 11])
-@pytest.mark.parametrize("M,N,K", [(5, 1, 64), (300, 3, 65), (257, 7, 130), (130, 191, 200), (511, 385, 256), (256, 192, 300), (514, 770, 400)])
+@pytest.mark.parametrize("M,N,K", [(5, 1, 64), (300, 3, 65), (257, 7, 130), (130, 191, 200), (511, 385, 256), (256, 192, 300), (514, 770, 400),
+                                   (2100, 2300, 130)])
 def test_tiles_every_output(h, variant, M, N, K):
     rng = np.random.default_rng(variant + M + 3 * N + 7 * K)
     ca, cb = random_codes(rng, (M, K), "cast_normal"), random_codes(rng, (N, K), "cast_normal")
@@ -36,6 +38,27 @@ def test_tiles_every_output(h, variant, M, N, K):
     h.hif8_gemm_set_variant(0)
     want = float(((out.double() - ref.double()) ** 2).sum())
     assert err[1].item() == 0.0 and abs(err[0].item() - want) <= 1e-12 * want
+
+
+# the remaining columns of a split: at most one 128 x 128 tile per compute unit (four LDS stages), and more (two)
+@pytest.mark.parametrize("M,N,K", [(7290, 2238, 200), (3450, 10430, 67)])
+def test_column_split_equals_one_launch(h, M, N, K):
+    rng = np.random.default_rng(M)
+    (a, ld), (b, _) = (expand(h, random_codes(rng, (r, K), "cast_normal")) for r in (M, N))
+    got = {}
+    for variant in (0, 9):
+        h.hif8_gemm_set_variant(variant)
+        for name, d in (("f32", torch.float32), ("bf16", torch.bfloat16), ("f16", torch.float16)):
+            o = torch.full((M * N + 8,), 7.0, dtype=d, device=dev())
+            getattr(h, "hif8_gemm_expanded_" + name)(a, b, o, M, N, K, ld, 4.0, 2.0)
+            assert torch.all(o[M * N:] == 7.0)
+            assert variant == 0 or torch.equal(o, got[name])
+            got[name] = o
+    h.hif8_gemm_set_variant(0)
+    rows = rng.integers(0, M, 40)
+    want = a[rows].view(torch.bfloat16).double() @ b.view(torch.bfloat16).double().t() / 8.0
+    sums = a[rows].view(torch.bfloat16).double().abs() @ b.view(torch.bfloat16).double().abs().t() / 8.0
+    assert torch.all((got["f32"][:M * N].view(M, N)[rows].double() - want).abs() <= K * 2.0 ** -23 * sums)
 
 
 @pytest.mark.parametrize("variant", [9, 10, 11])
