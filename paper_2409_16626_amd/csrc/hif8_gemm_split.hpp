@@ -78,6 +78,23 @@ inline int tile_launches(int plan, size_t M, size_t N, size_t pairs, size_t cus,
   return 2;
 }
 
+// Most tiles of a launch: its threads, 256 for each workgroup, are counted in 32 bits, and its workgroups are dealt out in
+// whole rounds of the dies (kXcds).  The squared error in 256 x 256 tiles walks over tiles with one workgroup per compute unit,
+// so that there only the tile number is limited.
+constexpr uint64_t kMaxWorkgroups = 0xFFFFFFFFull / 256 / 8 * 8;
+inline uint64_t most_tiles(int tile, bool sqerr) { return tile == TILE_256 && sqerr ? 0x7FFFFFF0ull : kMaxWorkgroups; }
+
+// Pairs of a scale search (na x nb error products) that one launch takes: all of them, one row of nb, or a single one
+// (0: not even that).  tile: the tile asked for, or -1 for the plan's own choice, which goes by the pairs of the launch.
+inline uint32_t pairs_per_launch(int tile, size_t M, size_t N, uint32_t na, uint32_t nb, size_t cus) {
+  auto fits = [&](size_t pairs) {
+    uint32_t split = 0;
+    const int t = tile >= 0 ? tile : tile_plan(M, N, pairs, cus, &split);
+    return t == TILE_SPLIT || tile_count(t, M, N, pairs) <= most_tiles(t, true);  // a split: one part walks, the other has at most two rounds
+  };
+  return fits((size_t)na * nb) ? na * nb : fits(nb) ? nb : fits(1) ? 1u : 0u;
+}
+
 // Products with at most this many rows on one side run straight from the codes in hif8_gemm_ws_* when they go to the
 // small-tile kernel; above it expanding first is faster (128 x 11008 x 4096: 52 us against 55; 384 x 4096 x 4096:
 // 50 against 44; 512 x 4096 x 11008: 150 against 100).

@@ -426,7 +426,7 @@ static hif8_status launch_x(const uint16_t* A, const uint16_t* B, void* out, con
   }
   const uint32_t tiles_m = (M + BM - 1) / BM, tiles_n = (col_end - col_begin + BN - 1) / BN;
   const uint64_t total = (uint64_t)tiles_m * tiles_n * (batch.na ? batch.na * batch.nb : 1u);
-  if (total > 0x7FFFFFF0ull) return HIF8_ERR_ARG;
+  if (total > most_tiles(TB == 8 ? TILE_256 : TB == 6 ? TILE_192 : TILE_128, EPI == EPI_ERR)) return HIF8_ERR_ARG;
   const uint32_t tiles = tile_order_grid((uint32_t)total);  // a whole number of workgroups per die
   uint32_t grid = tiles;
   if (WALK) {
@@ -454,20 +454,24 @@ hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const
   if (s != HIF8_OK) return s;
   const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)ld;
   const size_t pairs = batch.na ? (size_t)batch.na * batch.nb : 1;
-  // tiles of a launch are counted in 32 bits: a search over a very large matrix goes row by row of its square
-  if (batch.na > 1u && (((uint64_t)M + 127) / 128) * (((uint64_t)N + 127) / 128) * pairs > 0x7FFFFFF0ull) {
-    for (uint32_t i = 0; i < batch.na; ++i) {
-      const Batch row{1u, batch.nb, batch.e_base + (int)i, batch.a_stride, batch.b_stride};
-      s = gemm_expanded<EPI>(A + i * batch.a_stride, B, out, ref, err + (size_t)i * batch.nb, M, N, ld, descale, st, row);
-      if (s != HIF8_OK) return s;
-    }
-    return HIF8_OK;
-  }
   int variant = expanded_variant();
   if (pairs == 1 && batch.na == 0u && (variant == 12 || (variant == 0 && small_problem(M, N, false))))
     return gemm_small<EPI>(A, B, true, out, ref, err, M, N, ld, descale, st);
+  const int asked = variant == 9 ? TILE_128 : variant == 10 ? TILE_256 : variant == 11 ? TILE_192 : -1;
+  if (batch.na != 0u) {
+    // a search over a very large matrix goes row by row of its square, or pair by pair
+    const uint32_t some = pairs_per_launch(asked, M, N, batch.na, batch.nb, (size_t)cus);
+    if (some == 0u) return HIF8_ERR_ARG;
+    for (uint32_t p = 0; some < pairs && p < pairs; p += some) {
+      const uint32_t i = p / batch.nb, j = p % batch.nb;
+      s = gemm_expanded<EPI>(A + i * batch.a_stride, B + j * batch.b_stride, out, ref, err + p, M, N, ld, descale, st,
+                             Batch{1u, some, batch.e_base + (int)(i + j), batch.a_stride, batch.b_stride});
+      if (s != HIF8_OK) return s;
+    }
+    if (some < pairs) return HIF8_OK;
+  }
   uint32_t split = 0;
-  const int plan = variant == 9 ? TILE_128 : variant == 10 ? TILE_256 : variant == 11 ? TILE_192 : tile_plan(M, N, pairs, (size_t)cus, &split);
+  const int plan = asked >= 0 ? asked : tile_plan(M, N, pairs, (size_t)cus, &split);
   TileLaunch launches[2];
   const int count = tile_launches(plan, M, N, pairs, (size_t)cus, split, launches);
   for (int i = 0; i < count && s == HIF8_OK; ++i) {

@@ -100,4 +100,7 @@ int devfn_tile_launches(size_t M, size_t N, size_t pairs, size_t cus, uint32_t* 
   }
   return n;
 }
+uint32_t devfn_pairs_per_launch(int tile, size_t M, size_t N, uint32_t na, uint32_t nb, size_t cus) {
+  return hif8gemm::pairs_per_launch(tile, M, N, na, nb, cus);
+}
 }

@@ -284,3 +284,32 @@ def test_gemm_tile_plan(tile_launches):
         else:
             assert price == min(singles), (M, N, pairs, cus, got)
     assert splits > 100
+
+
+def test_scale_search_launches_fit(dev, tile_launches):
+    """A scale search takes as many pairs in a launch as its workgroups of 256 threads, counted in 32 bits, allow (the 256 x 256
+    tiles of the squared error walk: one workgroup per compute unit); a row of the search, or one pair, always fits."""
+    f = dev.devfn_pairs_per_launch
+    f.restype, f.argtypes = ctypes.c_uint32, [ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_size_t]
+    assert f(-1, 2048, 4096, 10, 10, 256) == 100
+    assert tile_launches(116736, 1728, 4096)[0][0] == 1 and f(-1, 116736, 1728, 64, 64, 256) == 64  # 456 x 9 x 4096 > 2^24
+    assert f(2, 8256, 8256, 64, 64, 256) == 64 and f(0, 8256, 8256, 64, 64, 256) == 4096
+    assert f(2, 600000, 7000, 64, 64, 256) == 64 and f(2, 600000, 17000, 64, 64, 256) == 1
+    rng = np.random.default_rng(9)
+    seen = set()
+    for _ in range(5000):
+        M, N = int(2.0 ** rng.uniform(0, 27)), int(2.0 ** rng.uniform(0, 27))
+        na, nb, tile = int(rng.integers(1, 65)), int(rng.integers(1, 65)), int(rng.integers(-1, 3))
+        if M * N > 7e10:  # the reference would not fit the memory
+            continue
+        some = f(tile, M, N, na, nb, 256)
+        assert some in (na * nb, nb, 1)
+        seen.add("all" if some == na * nb else "row" if some == nb else "pair")
+
+        def fits(pairs):
+            launches = [(tile, 0, 0, N)] if tile >= 0 else tile_launches(M, N, pairs)
+            return all((t == 0 and tile_count(t, M, e - b, pairs) < 2 ** 31) or (tile_count(t, M, e - b, pairs) + 7) // 8 * 8 * 256 < 2 ** 32
+                       for t, _, b, e in launches)
+        assert fits(some)
+        assert some == na * nb or not fits(na * nb)
+    assert seen == {"all", "row", "pair"}

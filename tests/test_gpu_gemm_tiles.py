@@ -132,6 +132,31 @@ def test_scale_search_over_every_tile(h, variant):
     assert best.tolist() == [-3 + at // nb, -2 + at % nb]
 
 
+def test_scale_search_of_more_tiles_than_a_launch_has(h):
+    """65 x 65 tiles of 128 x 128 for 64 x 64 pairs are more workgroups of 256 threads than 32 bits count: the search goes row by
+    row.  Against the walking form in 256 x 256 tiles, which takes them in one launch."""
+    M, N, K, n = 8256, 8256, 40, 64
+    g = torch.Generator(device=dev()).manual_seed(11)
+    x, w = torch.randn(M, K, device=dev(), generator=g), torch.randn(N, K, device=dev(), generator=g) * 0.02
+    ref = (x.double() @ w.double().t()).float()
+    ws = torch.empty(h.hif8_calibrate_workspace_bytes(M, N, K, n, n), dtype=torch.uint8, device=dev())
+    got = {}
+    for variant in (9, 10):
+        err = torch.full((n, n), -1.0, dtype=torch.float64, device=dev())
+        best = torch.zeros(2, dtype=torch.int32, device=dev())
+        h.hif8_gemm_set_variant(variant)
+        h.hif8_calibrate_layer_f32(x, w, ref, M, N, K, -32, n, -32, n, orc.RM_TA, ws, ws.numel(), err, best)
+        torch.cuda.synchronize()
+        got[variant] = (err, best)
+    h.hif8_gemm_set_variant(0)
+    fin = torch.isfinite(got[10][0])  # large scales overflow to infinity, and 0 * infinity is NaN
+    assert fin.sum() > 1000 and torch.equal(torch.isnan(got[9][0]), torch.isnan(got[10][0]))
+    assert torch.all((got[9][0] - got[10][0]).abs()[fin] <= 1e-12 * got[10][0][fin])
+    for err, best in got.values():  # many scales cast to the same bits: the least entry of its own table
+        at = int(torch.where(torch.isfinite(err), err, float("inf")).argmin())
+        assert best.tolist() == [-32 + at // n, -32 + at % n]
+
+
 # every rounding method on every kind of source: rows of whole and of odd numbers of 8-element runs, K at, below and above
 # the 64-element pitch, a source off the 16-byte grid; inputs with NaN, both infinities, zeros and values of every binade
 @pytest.mark.parametrize("kind", ["f32", "bf16", "f16"])
