@@ -41,7 +41,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Operand kinds
 enum : int { OP_CODES = 0, OP_BF16 = 1 };
 
-constexpr uint32_t kUnitK = 128;  // K elements of the smallest share of a wavefront
+constexpr uint32_t kUnitK = (uint32_t)kShareK;  // K elements of the smallest share of a wavefront
 
 // 16 bytes from any address
 __device__ __forceinline__ u32x4 load16(const uint8_t* p) {
@@ -111,7 +111,7 @@ k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __r
   uint8_t* const area = smem + 512 + wave * (kBlocks * 16u * kRowStage);
   float* const red = reinterpret_cast<float*>(smem + 512);  // [wavefronts][16][kPitch]
   if constexpr (OP == OP_CODES) {
-    if (tid < 256u) reinterpret_cast<uint16_t*>(smem)[table_slots(tid)] = (uint16_t)(decode_bits(tid) >> 16);  // at least 4 wavefronts
+    for (uint32_t c = tid; c < 256u; c += threads) reinterpret_cast<uint16_t*>(smem)[table_slots(c)] = (uint16_t)(decode_bits(c) >> 16);
   }
   // this wavefront's share of K, in units of 128 elements for both operand kinds, as stages of kRowStage bytes per row
   const uint32_t row_bytes = K * kElem, units = (K + kUnitK - 1u) / kUnitK, stages = (row_bytes + kRowStage - 1u) / kRowStage;
@@ -294,7 +294,7 @@ template <int OP, int EPI>
 static hif8_status gemm_small_op(const void* A, const void* B, void* out, const float* ref, double* err, size_t M, size_t N,
                                  size_t K, float descale, hipStream_t st) {
   const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
-  const SmallPlan p = small_plan(M, N, OP == OP_CODES);
+  const SmallPlan p = small_plan(M, N, K, OP == OP_CODES);
   switch (p.tm * 10 + p.tn) {
     case 11:
       if constexpr (OP == OP_CODES) {

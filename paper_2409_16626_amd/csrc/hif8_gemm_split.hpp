@@ -121,17 +121,25 @@ inline bool small_problem(size_t M, size_t N, bool codes, size_t K = 4096) {
 // one operand has few rows (8 x 11008 x 4096 on codes: 1 x 1 14 us, 1 x 2 17, 2 x 4 20); more rows want the operand
 // reuse of larger ones, and fewer wavefronts once the tiles alone fill the chip (64 x 4096 x 4096: 2 x 2 with 16
 // wavefronts 14.2 us, with 8 16.2; 64 x 11008 x 4096: 4 wavefronts 33.6, 16 41.8).
+// With more than 256 tiles no more wavefronts than K has shares of kShareK elements: one without a share adds nothing to the
+// sum, and its staging area takes LDS that other workgroups could have (codes, us, all wavefronts / as many as shares:
+// 8 x 200000 x 64 42.1 / 14.7, 32 x 200000 x 256 80 / 29.5); with few tiles its lanes help with the table and the sum
+// (128 x 512 x 16 6.9 / 9.1).
 struct SmallPlan {
   uint32_t tm, tn, waves;
 };
-inline SmallPlan small_plan(size_t M, size_t N, bool codes) {
+constexpr size_t kShareK = 128;
+inline SmallPlan small_plan(size_t M, size_t N, size_t K, bool codes) {
   auto tiles = [&](size_t tm, size_t tn) { return ((M + 16 * tm - 1) / (16 * tm)) * ((N + 16 * tn - 1) / (16 * tn)); };
-  const size_t s = M < N ? M : N;
-  if (s <= 16) return {1, 1, 8};
-  if (s <= 32) return tiles(2, 4) >= 128 ? SmallPlan{2, 4, 8} : SmallPlan{1, 2, 8};
-  if (s <= 64) return {2, 2, tiles(2, 2) <= 256 ? 16u : 4u};
-  if (s <= kSmallCodesRows || (codes && small_problem(M, N, true))) return {2, 4, tiles(2, 4) <= 256 ? 8u : 4u};
-  return {4, 4, !codes && tiles(4, 4) <= 256 ? 8u : 4u};
+  const size_t s = M < N ? M : N, shares = K > kShareK ? (K + kShareK - 1) / kShareK : 1;
+  auto plan = [&](uint32_t tm, uint32_t tn, uint32_t waves) {
+    return SmallPlan{tm, tn, waves < shares || tiles(tm, tn) <= 256 ? waves : (uint32_t)shares};
+  };
+  if (s <= 16) return plan(1, 1, 8);
+  if (s <= 32) return tiles(2, 4) >= 128 ? plan(2, 4, 8) : plan(1, 2, 8);
+  if (s <= 64) return plan(2, 2, tiles(2, 2) <= 256 ? 16 : 4);
+  if (s <= kSmallCodesRows || (codes && small_problem(M, N, true))) return plan(2, 4, tiles(2, 4) <= 256 ? 8 : 4);
+  return plan(4, 4, !codes && tiles(4, 4) <= 256 ? 8 : 4);
 }
 
 // Workgroup -> tile of the expanded-operand kernel.  The hardware deals consecutive workgroups round-robin over the

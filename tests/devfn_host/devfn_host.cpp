@@ -80,8 +80,8 @@ uint32_t devfn_ragged_round_split(size_t M, size_t N, size_t cus) {
   return hif8gemm::ragged_round_split(M, N, cus, &split) ? split : 0u;
 }
 // small-tile GEMM kernel: 100 * tile rows + 10 * tile columns (in blocks of 16) and wavefronts, or 0 where the tiled kernels are used
-uint32_t devfn_small_plan(size_t M, size_t N, int codes, int force, uint32_t* waves) {
-  const hif8gemm::SmallPlan p = hif8gemm::small_plan(M, N, codes != 0);
+uint32_t devfn_small_plan(size_t M, size_t N, size_t K, int codes, int force, uint32_t* waves) {
+  const hif8gemm::SmallPlan p = hif8gemm::small_plan(M, N, K, codes != 0);
   *waves = p.waves;
   return force || hif8gemm::small_problem(M, N, codes != 0) ? p.tm * 100 + p.tn * 10 : 0u;
 }
