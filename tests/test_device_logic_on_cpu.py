@@ -208,8 +208,8 @@ def test_gemm_tile_order_is_a_bijection_and_compact_per_die(dev):
 
 def test_small_gemm_plan(dev):
     """Small-tile GEMM kernel: only the tiles that exist, up to 16 wavefronts (more than 8 only with the tile whose kernel allows
-    them) and no more than K has shares of 128, tile areas within the 160 KiB of LDS, and below 129 rows the same K split for
-    codes and for expanded operands, whose K is the pitch."""
+    them) and with more than 256 tiles no more than K has shares of 128, tile areas within the 160 KiB of LDS, and below 129 rows
+    the same K split for codes and for expanded operands, whose K is the pitch."""
     dev.devfn_small_plan.restype = ctypes.c_uint32
     dev.devfn_small_plan.argtypes = [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_uint32)]
 
@@ -218,15 +218,16 @@ def test_small_gemm_plan(dev):
         return dev.devfn_small_plan(M, N, K, codes, force, ctypes.byref(w)), w.value
 
     assert plan(8, 11008, 4096, 1, 0) == (110, 8) and plan(2048, 11008, 4096, 0, 0)[0] == 0
-    assert plan(32, 200000, 64, 1)[1] == 1 and plan(32, 200000, 129, 1)[1] == 2 and plan(8, 8, 0, 1) == (110, 1)
+    assert plan(32, 200000, 64, 1)[1] == 1 and plan(32, 200000, 129, 1)[1] == 2 and plan(8, 8, 0, 1) == (110, 8)
     rng = np.random.default_rng(4)
     for _ in range(3000):
         M, N, K = (int(2.0 ** rng.uniform(0, 20)) for _ in range(3))
         ld = -(-K // 64) * 64
         got = [plan(M, N, k, c) for c, k in ((0, ld), (1, K))]
         for t, w in got:
-            assert t in (110, 120, 220, 240, 440) and 1 <= w <= min(16 if t == 220 else 8, -(-K // 128))
-            assert w in (4, 8, 16) or w == -(-K // 128)
+            assert t in (110, 120, 220, 240, 440) and (w in (4, 8, 16) or w == -(-K // 128)) and (w <= 8 or t == 220)
+            tiles = -(-M // (16 * (t // 100))) * -(-N // (16 * (t // 10 % 10)))
+            assert tiles <= 256 or w <= -(-K // 128)
             assert 512 + w * (t // 100 + t // 10 % 10) * 16 * 128 <= 160 * 1024
         if min(M, N) <= 128:
             assert got[0] == got[1]
