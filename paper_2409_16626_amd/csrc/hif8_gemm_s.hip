@@ -266,10 +266,14 @@ k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __r
 // ====================================================================================
 template <int OP, int TM, int TN, int HALF, int EPI>
 static hif8_status launch_s(const void* A, const void* B, void* out, const float* ref, double* err, uint32_t M, uint32_t N,
-                            uint32_t K, float descale, uint32_t waves, hipStream_t st) {
+                            uint32_t K, float descale, uint32_t waves, int cus, hipStream_t st) {
   const uint64_t tiles_m = ((uint64_t)M + 16 * TM - 1) / (16 * TM), tiles_n = ((uint64_t)N + 16 * TN - 1) / (16 * TN);
   if (tiles_m * tiles_n > 0x7FFFFFF0ull) return HIF8_ERR_ARG;
-  const uint32_t total = tile_order_grid((uint32_t)(tiles_m * tiles_n)), most = 1u << 20;  // threads of a launch are counted in 32 bits
+  const uint32_t total = tile_order_grid((uint32_t)(tiles_m * tiles_n));
+  // threads of a launch are counted in 32 bits.  The squared error ends each workgroup with an atomic on one address, and those
+  // are served one after the other (3.7 ns each), so there four workgroups per compute unit walk over the tiles (codes, us, a
+  // workgroup per tile / 256, 512, 1024 workgroups: 8 x 200000 x 64 158 / 81, 46, 35; 64 x 32000 x 64 34 / 54, 32, 27).
+  const uint32_t most = EPI == EPI_ERR ? tile_order_grid((uint32_t)cus * 4u) : 1u << 20;
   const size_t stage = (size_t)waves * (TM + TN) * 16 * kRowStage, red = (size_t)waves * 16 * (TN * 16 + 4) * 4;
   const size_t smem = 512 + (stage > red ? stage : red);
   if (smem > 65536) {
@@ -294,17 +298,20 @@ template <int OP, int EPI>
 static hif8_status gemm_small_op(const void* A, const void* B, void* out, const float* ref, double* err, size_t M, size_t N,
                                  size_t K, float descale, hipStream_t st) {
   const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
+  int cus = 0;
+  const hif8_status s = ensure_init(&cus, nullptr);
+  if (s != HIF8_OK) return s;
   const SmallPlan p = small_plan(M, N, K, OP == OP_CODES);
   switch (p.tm * 10 + p.tn) {
     case 11:
       if constexpr (OP == OP_CODES) {
-        if (M <= 8) return launch_s<OP, 1, 1, 1, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
+        if (M <= 8) return launch_s<OP, 1, 1, 1, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
       }
-      return launch_s<OP, 1, 1, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
-    case 12: return launch_s<OP, 1, 2, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
-    case 22: return launch_s<OP, 2, 2, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
-    case 24: return launch_s<OP, 2, 4, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
-    default: return launch_s<OP, 4, 4, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, st);
+      return launch_s<OP, 1, 1, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
+    case 12: return launch_s<OP, 1, 2, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
+    case 22: return launch_s<OP, 2, 2, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
+    case 24: return launch_s<OP, 2, 4, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
+    default: return launch_s<OP, 4, 4, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
   }
 }
 

@@ -79,6 +79,22 @@ def test_small_gemm_16bit_outputs_and_squared_error(h):
         assert abs(err.item() - want) <= 1e-12 * want
 
 
+# more tiles than the four workgroups per compute unit that the squared error walks over them with, and as many
+@pytest.mark.parametrize("M,N,K", [(16, 33001, 40), (8, 16384, 130), (30, 70001, 17), (50, 40003, 129), (100, 20001, 300)])
+def test_small_gemm_squared_error_of_many_tiles(h, M, N, K):
+    rng = np.random.default_rng(M + N)
+    a, b = (on_gpu(random_codes(rng, (r, K), "cast_normal")) for r in (M, N))
+    out = torch.empty(M, N, dtype=torch.float32, device=dev())
+    h.hif8_gemm_set_variant(12)
+    h.hif8_gemm_f32(a, b, out, M, N, K, 2.0, 4.0)
+    ref = out + torch.randn(M, N, device=dev(), generator=torch.Generator(device=dev()).manual_seed(1))
+    err = torch.zeros(2, dtype=torch.float64, device=dev())
+    h.hif8_gemm_sqerr(a, b, ref, M, N, K, 2.0, 4.0, err)
+    h.hif8_gemm_set_variant(0)
+    want = float(((out.double() - ref.double()) ** 2).sum())
+    assert err[1].item() == 0.0 and abs(err[0].item() - want) <= 1e-12 * want
+
+
 def test_small_gemm_special_codes_follow_ieee(h):
     rng = np.random.default_rng(22)
     for M, N in ((7, 20), (40, 50)):
