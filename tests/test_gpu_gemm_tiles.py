@@ -40,6 +40,34 @@ def test_tiles_every_output(h, variant, M, N, K):
     assert err[1].item() == 0.0 and abs(err[0].item() - want) <= 1e-12 * want
 
 
+# every length of a row's last run, of 4 binary32 and of 8 16-bit values; rows and columns that end in each quarter of a tile,
+# so that whole blocks of it lie outside
+@pytest.mark.parametrize("variant", [9, 10, 11])
+def test_tiles_row_ends(h, variant):
+    rng = np.random.default_rng(variant)
+    K = 64
+    full, _ = expand(h, random_codes(rng, (300, K), "cast_normal"))
+    b_full, _ = expand(h, random_codes(rng, (300, K), "cast_normal"))
+    want = full.view(torch.bfloat16).double() @ b_full.view(torch.bfloat16).double().t() / 64.0
+    sums = full.view(torch.bfloat16).double().abs() @ b_full.view(torch.bfloat16).double().abs().t() / 64.0
+    h.hif8_gemm_set_variant(variant)
+    for M, N in [(40 + 37 * i, n) for i, n in enumerate((1, 2, 5, 6, 33, 58, 67))] + [(70, n) for n in range(128, 137)] + [(290, 259)]:
+        o32 = torch.full((M * N + 8,), 7.0, dtype=torch.float32, device=dev())
+        ob, oh = (torch.full((M * N + 8,), 7.0, dtype=d, device=dev()) for d in (torch.bfloat16, torch.float16))
+        for call, o in ((h.hif8_gemm_expanded_f32, o32), (h.hif8_gemm_expanded_bf16, ob), (h.hif8_gemm_expanded_f16, oh)):
+            call(full, b_full, o, M, N, K, K, 8.0, 8.0)
+            assert torch.all(o[M * N:] == 7.0), (M, N)
+        out = o32[:M * N].view(M, N)
+        assert torch.all((out.double() - want[:M, :N]).abs() <= K * 2.0 ** -23 * sums[:M, :N]), (M, N)
+        assert torch.equal(ob[:M * N].view(M, N), out.to(torch.bfloat16)) and torch.equal(oh[:M * N].view(M, N), out.to(torch.float16)), (M, N)
+        ref = (out * 1.01 + 0.5).contiguous()
+        err = torch.zeros(1, dtype=torch.float64, device=dev())
+        h.hif8_gemm_expanded_sqerr(full, b_full, ref, M, N, K, K, 8.0, 8.0, err)
+        e = float(((out.double() - ref.double()) ** 2).sum())
+        assert abs(err.item() - e) <= 1e-12 * e, (M, N)
+    h.hif8_gemm_set_variant(0)
+
+
 # the remaining columns of a split: at most one 128 x 128 tile per compute unit (four LDS stages), and more (two)
 @pytest.mark.parametrize("M,N,K", [(7290, 2238, 200), (3450, 10430, 67)])
 def test_column_split_equals_one_launch(h, M, N, K):
