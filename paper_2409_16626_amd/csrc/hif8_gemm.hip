@@ -329,7 +329,7 @@ static hif8_status gemm_dispatch(const uint8_t* A, const uint8_t* B, void* out, 
   if (s != HIF8_OK) return s;
   const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
   const bool fast = K != 0 && (K % 16) == 0 && aligned_to(A, 16) && aligned_to(B, 16);
-  if (!fast || g_gemm_variant == 12 || (g_gemm_variant == 0 && small_problem(M, N, true, K)))
+  if (!fast || g_gemm_variant == 12 || (g_gemm_variant == 0 && small_problem(M, N, K, true, EPI == EPI_ERR)))
     return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st);
   int variant = g_gemm_variant;
   uint32_t split = 0;
@@ -369,7 +369,7 @@ static hif8_status gemm_ws(const uint8_t* A, const uint8_t* B, void* out, const 
   if (ws_bytes < need || !aligned_to(ws, 16)) return HIF8_ERR_ARG;
   if (EPI == EPI_ERR && !aligned_to(err, 8)) return HIF8_ERR_ARG;
   // few rows: straight from the codes, which gives the bits that the expanded operands would give (see small_plan)
-  if (expanded_variant() == 0 && (M < N ? M : N) <= kSmallCodesRows && small_problem(M, N, false))
+  if (expanded_variant() == 0 && (M < N ? M : N) <= kSmallCodesRows && small_problem(M, N, expanded_ld(K), false, EPI == EPI_ERR))
     return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st);
   const size_t ld = expanded_ld(K);
   uint16_t* xa = reinterpret_cast<uint16_t*>(ws);

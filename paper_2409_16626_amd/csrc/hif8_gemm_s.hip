@@ -111,7 +111,10 @@ k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __r
   uint8_t* const area = smem + 512 + wave * (kBlocks * 16u * kRowStage);
   float* const red = reinterpret_cast<float*>(smem + 512);  // [wavefronts][16][kPitch]
   if constexpr (OP == OP_CODES) {
-    for (uint32_t c = tid; c < 256u; c += threads) reinterpret_cast<uint16_t*>(smem)[table_slots(c)] = (uint16_t)(decode_bits(c) >> 16);
+    auto entry = [&](uint32_t c) { reinterpret_cast<uint16_t*>(smem)[table_slots(c)] = (uint16_t)(decode_bits(c) >> 16); };
+    if (tid < 256u) entry(tid);
+    if (threads < 256u)
+      for (uint32_t c = tid + threads; c < 256u; c += threads) entry(c);
   }
   // this wavefront's share of K, in units of 128 elements for both operand kinds, as stages of kRowStage bytes per row
   const uint32_t row_bytes = K * kElem, units = (K + kUnitK - 1u) / kUnitK, stages = (row_bytes + kRowStage - 1u) / kRowStage;
@@ -271,9 +274,10 @@ static hif8_status launch_s(const void* A, const void* B, void* out, const float
   if (tiles_m * tiles_n > 0x7FFFFFF0ull) return HIF8_ERR_ARG;
   const uint32_t total = tile_order_grid((uint32_t)(tiles_m * tiles_n));
   // threads of a launch are counted in 32 bits.  The squared error ends each workgroup with an atomic on one address, and those
-  // are served one after the other (3.7 ns each), so there four workgroups per compute unit walk over the tiles (codes, us, a
-  // workgroup per tile / 256, 512, 1024 workgroups: 8 x 200000 x 64 158 / 81, 46, 35; 64 x 32000 x 64 34 / 54, 32, 27).
-  const uint32_t most = EPI == EPI_ERR ? tile_order_grid((uint32_t)cus * 4u) : 1u << 20;
+  // are served one after the other (10 ns each), so there four workgroups per compute unit walk over the tiles (codes, us, a
+  // workgroup per tile / 256, 512, 1024 workgroups: 8 x 200000 x 64 158 / 81, 46, 35; 64 x 32000 x 64 34 / 54, 32, 27).  With a long
+  // K the atomics come slowly enough, and dealing out the tiles evenly counts more (16 x 53248 x 4096 84 / 94 with 1024).
+  const uint32_t most = EPI == EPI_ERR && K < 4096u ? tile_order_grid((uint32_t)cus * 4u) : 1u << 20;
   const size_t stage = (size_t)waves * (TM + TN) * 16 * kRowStage, red = (size_t)waves * 16 * (TN * 16 + 4) * 4;
   const size_t smem = 512 + (stage > red ? stage : red);
   if (smem > 65536) {
@@ -301,7 +305,7 @@ static hif8_status gemm_small_op(const void* A, const void* B, void* out, const 
   int cus = 0;
   const hif8_status s = ensure_init(&cus, nullptr);
   if (s != HIF8_OK) return s;
-  const SmallPlan p = small_plan(M, N, K, OP == OP_CODES);
+  const SmallPlan p = small_plan(M, N, K, OP == OP_CODES, EPI == EPI_ERR);
   switch (p.tm * 10 + p.tn) {
     case 11:
       if constexpr (OP == OP_CODES) {

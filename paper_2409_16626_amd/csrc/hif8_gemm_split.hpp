@@ -100,19 +100,47 @@ inline uint32_t pairs_per_launch(int tile, size_t M, size_t N, uint32_t na, uint
 // 50 against 44; 512 x 4096 x 11008: 150 against 100).
 constexpr size_t kSmallCodesRows = 128;
 
-// Which problems go to the small-tile kernel (hif8_gemm_s.hip) although the tiled kernels could run them.  The tiled
-// kernels take a whole K walk however few tiles there are (K = 4096: 85 us on codes, 25.7 us expanded), the small-tile
-// kernel's time goes with M N.  On codes (us, small tiles / 128 x 128): 192 x 11008 x 4096 75 / 85, 256 x 11008 x 4096 94 /
-// 85, 384 x 11008 135 / 120, 1024 x 4096 112 / 91; K = 1024 1500 x 1500 28.5 / 27.4, K = 512
-// 700 x 3000 19.4 / 18.6, K = 256 1000 x 2000 14.0 / 13.1 (below K = 1024 up to 1.6 M); K = 11008 512 x 4096 150 / 231, 1024 x 4096 278 / 232.
-// On expanded operands (us, small tiles / 128 x 128): 256 x 4096 x 4096 19.6 / 25.7, 384 x 4096 x 4096 29.2 / 25.9, 64 x
-// 11008 x 4096 21.2 / 24.6, 100 x 11008 x 4096 29.1 / 25.4; K = 11008 256 x 4096 38 / 64, 512 x 4096 80 / 65; K = 2048 512 x
-// 2048 12.5 / 14.3; K = 1024 300 x 5000 12.6 / 9.5.  With up to 32 rows on either side three quarters of a tile would be
-// padding, so such products stay with the small tiles whatever the other side is.
-inline bool small_problem(size_t M, size_t N, bool codes, size_t K = 4096) {
+// Which problems go to the small-tile kernel (hif8_gemm_s.hip) although the tiled kernels could run them.  The tiled kernels
+// walk all of K however few tiles there are, so their time is a few us plus K (up to 256 tiles of 128 x 128: 7.5 us + 0.018
+// us * K on codes, 3.8 us + 0.005 us * K on expanded operands with their four LDS stages); the small-tile kernel's goes with
+// M N K.  s: the shorter side, l: the longer one.  In us, small tiles / tiled, on either side of each line:
+//   codes        64 x 16384 x 64 8.2 / 8.2, 32000 9.6 / 8.9; 128 x 5120 x 64 7.8 / 8.2, 10240 13.4 / 8.4; 64 x 26624 x 512 14.7 /
+//                17.2; 256 x 10240 x 1024 36 / 28; 512 x 3328 x 4096 64 / 90, 5120 104 / 89; 32 x 200000 x 64 20 / 32
+//   expanded     256 x 4096 x 512 9.2 / 7.0, x 1024 10.1 / 9.4, x 2048 13.6 / 14.4, 5120 19.4 / 14.8; 128 x 2560 x 512
+//                6.4 / 6.8; 128 x 8192 x 4096 23.4 / 26; 32 x 20480 x 1024 10.5 / 10.6
+// Up to 128 rows hif8_gemm_ws_* goes by the line of the expanded operands, whose bits it gives, and saves the expansion on this
+// side of it (expansion and tiled kernel / codes in small tiles: 64 x 20480 x 512 24 / 12, 128 x 8192 x 1024 24.5 / 12.3, 128 x 8192 x
+// 128 9.2 / 7.9), so the line lies farther out there: 128 x 8192 x 128 expanded 6.1 / 4.9, 64 x 2048 x 64 5.1 / 4.0, 64 x 20480 x
+// 512 8.7 / 7.1.
+// The squared error costs the small-tile kernel an atomic per workgroup, all on one address (10 us for the thousand workgroups
+// that walk), so there it wants a larger K:
+//   codes        8 x 8000 x 64 9.9 / 10.1; 8 x 32000 x 256 17.2 / 15.9, x 512 17.9 / 20.5; 32 x 10240 x 64 9.5 / 10.3, 20480 x 256
+//                14.8 / 14.8; 64 x 8000 x 128 12.7 / 11.4, x 256 12.9 / 13.7; 128 x 5120 x 64 11.9 / 9.9, x 256 11.8 / 13.8; 256 x
+//                5120 x 512 20.5 / 19.2, x 1024 24.9 / 29.0
+//   expanded     8 x 8000 x 512 9.9 / 7.8, x 1024 10.1 / 10.2; 32 x 10240 x 512 8.8 / 8.4, x 1024 9.3 / 10.8; 48 x 5120 x 256 8.4 /
+//                8.1, x 1024 9.6 / 11.7; 128 x 5120 x 1024 12.2 / 10.0, x 2048 15.4 / 15.0; 512 x 2048 x 2048 17.1 / 15.2, x 4096
+//                24.7 / 26.7
+inline bool small_problem(size_t M, size_t N, size_t K, bool codes, bool sqerr) {
   const size_t s = M < N ? M : N, l = M < N ? N : M;
-  if (s <= 32) return true;
-  return codes ? l <= (size_t)(K < 1024 ? 24 : 33) * 65536 / s : l <= (size_t)5 * 262144 / ((s + 31) / 32 * 32);
+  auto tiles = [&](size_t tm, size_t tn) { return ((M + 16 * tm - 1) / (16 * tm)) * ((N + 16 * tn - 1) / (16 * tn)); };
+  if (codes) {
+    if (s > 32 && l > (size_t)(K < 1024 ? 24 : 33) * 65536 / s) return false;
+    if (sqerr) {
+      if (s <= 16) return l <= 6144 || l > 65536 || K >= (l < 25600 ? l / 64 : 400);
+      if (s <= 32) return l <= 6144 || (l > 8192 && l <= 16384) || K >= (l <= 8192 ? 128 : 400);
+      if (s <= 64) return K >= (l <= 1024 ? 0 : l <= 2048 ? 64 : l <= 5632 ? 128 : l / 36);
+      return K >= (s * l <= (size_t)1 << 17 ? 0 : s * l <= (size_t)1 << 19 ? 64 : s * l <= 900000 ? 200 : s * l <= (size_t)1 << 20 ? 400 : 1024);
+    }
+    return s <= 32 || K > 64 || (s <= 64 ? l <= 16384 : tiles(2, 4) <= 512);
+  }
+  if (s <= 32) {
+    if (!sqerr || l <= 2048) return true;
+    if (K >= 2048 && l >= ((size_t)160 << 20) / K) return true;  // 320 MB of the longer operand: more than the last-level cache
+    return s <= 16 ? K * 8 >= l : K * 10 >= l && l <= 12288;
+  }
+  if (s <= 64) return sqerr ? l <= 1024 || (K >= 256 && K * 6 >= l && l <= 12288) : l <= 20480;
+  if (s <= kSmallCodesRows) return sqerr ? l <= 1024 || (K >= 384 && K * 7 >= l * 2 && tiles(2, 4) <= 512) : l <= 1310720 / ((s + 31) / 32 * 32);
+  return K >= (sqerr ? 2048 : 1024) && tiles(4, 4) <= (sqerr && K < 3072 ? 170 : 256);
 }
 
 // Tile (16 tm x 16 tn) and wavefronts per workgroup of the small-tile kernel.  The wavefronts split K, so a wavefront
@@ -120,25 +148,45 @@ inline bool small_problem(size_t M, size_t N, bool codes, size_t K = 4096) {
 // hif8_gemm_ws_* runs on the codes what hif8_gemm_expanded_* runs on expanded operands).  The smallest tiles win while
 // one operand has few rows (8 x 11008 x 4096 on codes: 1 x 1 14 us, 1 x 2 17, 2 x 4 20); more rows want the operand
 // reuse of larger ones, and fewer wavefronts once the tiles alone fill the chip (64 x 4096 x 4096: 2 x 2 with 16
-// wavefronts 14.2 us, with 8 16.2; 64 x 11008 x 4096: 4 wavefronts 33.6, 16 41.8).
-// With more than 256 tiles no more wavefronts than K has shares of kShareK elements: one without a share adds nothing to the
-// sum, and its staging area takes LDS that other workgroups could have (codes, us, all wavefronts / as many as shares:
-// 8 x 200000 x 64 42.1 / 14.7, 32 x 200000 x 256 80 / 29.5); with few tiles its lanes help with the table and the sum
-// (128 x 512 x 16 6.9 / 9.1).
+// wavefronts 14.2 us, with 8 16.2; 64 x 11008 x 4096: 4 wavefronts 33.6, 16 41.8; 32 rows, 2 x 4 with 8 wavefronts / 2 x 2 with 4,
+// codes and expanded: 32 x 40960 x 1024 25.3, 22.7 / 20.4, 16.3, 32 x 53248 x 2048 48, 45 / 38, 35, but 32 x 10240 x 11008 43, 41 /
+// 70, 45, 32 x 32768 x 11008 96, 139 / 104, 149; 128 rows, 2 x 4 / 2 x 2 with 4: 128 x 8192 x 256 7.7, 6.3 / 8.0, 5.8, 128 x 10240 x 512
+// 13.7, 8.7 / 12.6, 8.6, but x 4096 50, 30 / 55, 33).
+// A workgroup has no more wavefronts than K has shares of kShareK elements, in powers of two, but at least four: one without a
+// share adds nothing to the sum, and its staging area takes LDS that another workgroup could have, while its lanes help with the
+// table and the sum (codes, expanded, us: 32 x 10240 x 128 in 1 x 2 tiles with 8 wavefronts / 4 6.7, 5.3 / 5.1, 3.8; 128 x 8192 x
+// 64 with 4 / 1 7.8 / 9.7 on codes).  Where there are more tiles than the chip holds workgroups at a time, fewer than four, too
+// (codes, 8 / as many as shares: 8 x 200000 x 64 42.1 / 14.7; 64 x 32000 x 64 13.8 / 9.3).
 struct SmallPlan {
   uint32_t tm, tn, waves;
 };
 constexpr size_t kShareK = 128;
-inline SmallPlan small_plan(size_t M, size_t N, size_t K, bool codes) {
+// Workgroups that 256 compute units hold at a time: 160 KiB of LDS (table; per wavefront a staging area of 2 KiB for each
+// 16-row block), and on each of the four SIMDs as many wavefronts as the registers of a tile allow.
+inline size_t small_resident(uint32_t tm, uint32_t tn, uint32_t waves, bool codes) {
+  const uint32_t by_lds = 160u * 1024u / (512u + waves * (tm + tn) * 2048u), blocks = tm * tn;
+  const uint32_t by_regs = 4u * (blocks == 1u ? 6u : blocks == 2u ? 5u : blocks == 4u ? 4u : blocks == 8u && !codes ? 3u : 2u) / waves;
+  return 256u * (by_lds < by_regs ? by_lds : by_regs);
+}
+inline SmallPlan small_plan(size_t M, size_t N, size_t K, bool codes, bool sqerr) {
   auto tiles = [&](size_t tm, size_t tn) { return ((M + 16 * tm - 1) / (16 * tm)) * ((N + 16 * tn - 1) / (16 * tn)); };
-  const size_t s = M < N ? M : N, shares = K > kShareK ? (K + kShareK - 1) / kShareK : 1;
+  const size_t s = M < N ? M : N, l = M < N ? N : M, ld = (K + 63) / 64 * 64;  // codes plan as their expansion does
   auto plan = [&](uint32_t tm, uint32_t tn, uint32_t waves) {
-    return SmallPlan{tm, tn, waves < shares || tiles(tm, tn) <= 256 ? waves : (uint32_t)shares};
+    auto spare = [&] { return waves / 2u * kShareK >= ld; };
+    while (waves > 4u && spare()) waves /= 2u;
+    if (tiles(tm, tn) > small_resident(tm, tn, waves, codes))
+      while (waves > 1u && spare()) waves /= 2u;
+    return SmallPlan{tm, tn, waves};
   };
+  const bool short_k = ld <= 4 * kShareK && !sqerr;  // four wavefronts have all of K: the smaller tiles (fewer atomics with the larger ones)
   if (s <= 16) return plan(1, 1, 8);
-  if (s <= 32) return tiles(2, 4) >= 128 ? plan(2, 4, 8) : plan(1, 2, 8);
+  if (s <= 32) {
+    if (tiles(2, 4) < 128) return plan(1, 2, 8);
+    return (tiles(2, 4) <= 256 && !short_k) || l * ld >= (size_t)300 << 20 ? plan(2, 4, 8) : plan(2, 2, 4);
+  }
   if (s <= 64) return plan(2, 2, tiles(2, 2) <= 256 ? 16 : 4);
-  if (s <= kSmallCodesRows || (codes && small_problem(M, N, true))) return plan(2, 4, tiles(2, 4) <= 256 ? 8 : 4);
+  if (s <= kSmallCodesRows && short_k) return plan(2, 2, 4);
+  if (s <= kSmallCodesRows || (codes && M * N <= (size_t)33 * 65536)) return plan(2, 4, tiles(2, 4) <= 256 ? 8 : 4);
   return plan(4, 4, !codes && tiles(4, 4) <= 256 ? 8 : 4);
 }
 

@@ -79,12 +79,13 @@ uint32_t devfn_ragged_round_split(size_t M, size_t N, size_t cus) {
   uint32_t split = 0;
   return hif8gemm::ragged_round_split(M, N, cus, &split) ? split : 0u;
 }
-// small-tile GEMM kernel: 100 * tile rows + 10 * tile columns (in blocks of 16) and wavefronts, or 0 where the tiled kernels are used
-uint32_t devfn_small_plan(size_t M, size_t N, size_t K, int codes, int force, uint32_t* waves) {
-  const hif8gemm::SmallPlan p = hif8gemm::small_plan(M, N, K, codes != 0);
+// small-tile GEMM kernel: 100 * tile rows + 10 * tile columns (in blocks of 16) and wavefronts; whether a problem goes there
+uint32_t devfn_small_plan(size_t M, size_t N, size_t K, int codes, int sqerr, uint32_t* waves) {
+  const hif8gemm::SmallPlan p = hif8gemm::small_plan(M, N, K, codes != 0, sqerr != 0);
   *waves = p.waves;
-  return force || hif8gemm::small_problem(M, N, codes != 0) ? p.tm * 100 + p.tn * 10 : 0u;
+  return p.tm * 100 + p.tn * 10;
 }
+int devfn_small_problem(size_t M, size_t N, size_t K, int codes, int sqerr) { return hif8gemm::small_problem(M, N, K, codes != 0, sqerr != 0); }
 // expanded-operand GEMM: the launches of its plan, 4 numbers each: tile (0 = 256 x 256, 1 = 256 x 192, 2 = 128 x 128), LDS
 // stages, first column, end; returns how many
 int devfn_tile_launches(size_t M, size_t N, size_t pairs, size_t cus, uint32_t* out) {

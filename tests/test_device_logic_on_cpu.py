@@ -208,29 +208,68 @@ def test_gemm_tile_order_is_a_bijection_and_compact_per_die(dev):
 
 def test_small_gemm_plan(dev):
     """Small-tile GEMM kernel: only the tiles that exist, up to 16 wavefronts (more than 8 only with the tile whose kernel allows
-    them) and with more than 256 tiles no more than K has shares of 128, tile areas within the 160 KiB of LDS, and below 129 rows
-    the same K split for codes and for expanded operands, whose K is the pitch."""
+    them), above four not twice as many as K has shares of 128, nor at all with more tiles than fit the chip, tile areas within the 160 KiB of LDS, and below
+    129 rows the same K split for codes and for expanded operands, whose K is the pitch."""
     dev.devfn_small_plan.restype = ctypes.c_uint32
     dev.devfn_small_plan.argtypes = [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_uint32)]
 
-    def plan(M, N, K, codes, force=1):
+    def plan(M, N, K, codes, sqerr=0):
         w = ctypes.c_uint32(0)
-        return dev.devfn_small_plan(M, N, K, codes, force, ctypes.byref(w)), w.value
+        return dev.devfn_small_plan(M, N, K, codes, sqerr, ctypes.byref(w)), w.value
 
-    assert plan(8, 11008, 4096, 1, 0) == (110, 8) and plan(2048, 11008, 4096, 0, 0)[0] == 0
-    assert plan(32, 200000, 64, 1)[1] == 1 and plan(32, 200000, 129, 1)[1] == 2 and plan(8, 8, 0, 1) == (110, 8)
+    assert plan(8, 11008, 4096, 1) == (110, 8) and plan(8, 11008, 520, 1) == (110, 8) and plan(8, 11008, 512, 1) == (110, 4)
+    assert plan(32, 200000, 64, 1) == (220, 1) and plan(32, 200000, 129, 1)[1] == 2 and plan(8, 8, 0, 1) == (110, 4)
+    assert plan(32, 16384, 1024, 1) == (240, 8) and plan(128, 8192, 512, 0) == (220, 4) and plan(128, 8192, 513, 0) == plan(128, 8192, 512, 0, 1) == (240, 4)
+    assert plan(32, 32768, 11008, 1) == (240, 8) and plan(32, 20480, 11008, 1) == (220, 4)
     rng = np.random.default_rng(4)
     for _ in range(3000):
         M, N, K = (int(2.0 ** rng.uniform(0, 20)) for _ in range(3))
         ld = -(-K // 64) * 64
-        got = [plan(M, N, k, c) for c, k in ((0, ld), (1, K))]
-        for t, w in got:
-            assert t in (110, 120, 220, 240, 440) and (w in (4, 8, 16) or w == -(-K // 128)) and (w <= 8 or t == 220)
-            tiles = -(-M // (16 * (t // 100))) * -(-N // (16 * (t // 10 % 10)))
-            assert tiles <= 256 or w <= -(-K // 128)
-            assert 512 + w * (t // 100 + t // 10 % 10) * 16 * 128 <= 160 * 1024
-        if min(M, N) <= 128:
-            assert got[0] == got[1]
+        sqerr = int(rng.integers(2))
+        got = [plan(M, N, k, c, sqerr) for c, k in ((0, ld), (1, K))]
+        for codes, (t, w) in enumerate(got):
+            tm, tn = t // 100, t // 10 % 10
+            assert t in (110, 120, 220, 240, 440) and w in (1, 2, 4, 8, 16) and (w <= 8 or t == 220)
+            per_simd = {1: 6, 2: 5, 4: 4, 8: 2 if codes else 3, 16: 2}[tm * tn]  # wavefronts, by the kernels' registers
+            assert 512 + w * (tm + tn) * 2048 <= 160 * 1024
+            tiles = -(-M // (16 * tm)) * -(-N // (16 * tn))
+            assert w <= 4 or w // 2 < -(-ld // 128)
+            assert w == 1 or tiles <= 256 * min(4 * per_simd // w, 160 * 1024 // (512 + w * (tm + tn) * 2048)) or w // 2 < -(-ld // 128)
+            assert w >= min(4, -(-ld // 128))  # every share of K has a wavefront, up to the least full number of them
+        if min(M, N) <= 128:  # the same tile and the same K split: an equal number, or the shares one by one in both
+            assert got[0][0] == got[1][0] and (got[0][1] == got[1][1] or min(got[0][1], got[1][1]) >= -(-ld // 128))
+
+
+# (M, N, K) measured faster in small tiles, then those measured faster in the tiled kernels, in the kernels' own time
+SMALL_OR_TILED = {
+    ("codes", "store"): ([(8, 11008, 4096), (1, 200000, 16), (32, 8192, 64), (32, 200000, 64), (64, 8000, 64), (128, 8192, 64), (512, 2048, 64),
+                          (64, 24000, 512), (128, 11008, 256), (256, 6656, 1024), (512, 3328, 4096), (509, 1003, 2048), (1024, 1664, 11008)],
+                         [(64, 32000, 64), (128, 10240, 64), (512, 2560, 64), (1024, 1280, 64), (256, 10240, 1024), (512, 5120, 4096),
+                          (2048, 11008, 4096), (256, 10240, 256)]),
+    ("codes", "sqerr"): ([(8, 2000, 16), (8, 10240, 256), (8, 32000, 512), (8, 200000, 256), (32, 10240, 64), (32, 20480, 512), (64, 2000, 128),
+                          (64, 10240, 512), (128, 8192, 512), (256, 4096, 512), (1024, 1024, 512), (64, 20480, 1024)],
+                         [(8, 32000, 64), (16, 20480, 128), (32, 32000, 64), (64, 8000, 64), (64, 32000, 512), (128, 8000, 128),
+                          (512, 2000, 128), (1024, 1280, 256)]),
+    ("expanded", "store"): ([(8, 11008, 4096), (16, 200000, 64), (32, 8000, 64), (32, 20480, 1024), (32, 81920, 4096), (64, 8000, 512),
+                             (64, 10240, 4096), (128, 2560, 512), (128, 8192, 4096), (256, 4096, 2048), (512, 2048, 4096), (1024, 1024, 4096)],
+                            [(128, 11008, 4096), (64, 32000, 4096), (100, 20000, 512),
+                             (256, 512, 64), (256, 2000, 512), (512, 967, 128), (512, 2560, 4096), (1000, 1153, 256), (1024, 1280, 4096)]),
+    ("expanded", "sqerr"): ([(8, 512, 64), (8, 8000, 1024), (8, 10240, 2048), (16, 81920, 4096), (32, 4096, 512), (32, 10240, 4096),
+                             (64, 2048, 1024), (128, 2560, 2048), (192, 1706, 2048), (512, 2048, 4096)],
+                            [(8, 8000, 64), (16, 32000, 1024), (32, 20480, 1024), (64, 8000, 512), (64, 10240, 1024), (128, 8000, 1024),
+                             (256, 2000, 512), (512, 2560, 4096), (1000, 1153, 256)]),
+}
+
+
+@pytest.mark.parametrize("operands,out", list(SMALL_OR_TILED))
+def test_small_gemm_route(dev, operands, out):
+    f = dev.devfn_small_problem
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.c_int]
+    for want, shapes in zip((1, 0), SMALL_OR_TILED[operands, out]):
+        for M, N, K in shapes:
+            assert f(M, N, K, operands == "codes", out == "sqerr") == want, (M, N, K)
+            assert f(N, M, K, operands == "codes", out == "sqerr") == want, (N, M, K)
+    assert f(32, 1 << 30, 1 << 20, operands == "codes", out == "sqerr") == 1 and f(7, 9, 0, operands == "codes", out == "sqerr") == 1
 
 
 # sum of rounds of a launch by the kernel it starts (tile, LDS stages): the measured times behind the rule, relative to each other

@@ -62,6 +62,26 @@ def test_small_gemm_same_bits_from_codes_workspace_and_expanded(h, M, N, K):
         assert torch.equal(one.view(torch.int32), two.view(torch.int32))
 
 
+# more tiles than the chip holds workgroups: as many wavefronts as K has shares of 128 (1, 2 and 4), in every tile; and 2 x 2
+# tiles of four wavefronts for up to 128 rows with four shares or less, one element past and below that
+@pytest.mark.parametrize("M,N,K", [(16, 33001, 40), (30, 70001, 17), (50, 40003, 129), (128, 9000, 200), (100, 20001, 300), (32, 20000, 385),
+                                   (70, 300, 512), (70, 300, 513), (128, 10003, 449)])
+def test_small_gemm_wavefronts_by_shares(h, M, N, K):
+    rng = np.random.default_rng(M + N + K)
+    a, b, ld = on_gpu(random_codes(rng, (M, K), "cast_normal")), on_gpu(random_codes(rng, (N, K), "cast_normal")), h.hif8_expanded_ld(K)
+    xa, xb = (torch.empty(r, ld, dtype=torch.bfloat16, device=dev()) for r in (M, N))
+    h.hif8_expand_bf16(a, M, K, xa, ld)
+    h.hif8_expand_bf16(b, N, K, xb, ld)
+    one, two = (torch.full((M * N + 8,), 7.0, dtype=torch.float32, device=dev()) for _ in range(2))
+    h.hif8_gemm_set_variant(12)
+    h.hif8_gemm_f32(a, b, one, M, N, K, 8.0, 0.5)
+    h.hif8_gemm_expanded_f32(xa, xb, two, M, N, K, ld, 8.0, 0.5)
+    h.hif8_gemm_set_variant(0)
+    assert torch.equal(one.view(torch.int32), two.view(torch.int32)) and torch.all(one[M * N:] == 7.0)
+    want, sums = xa.double() @ xb.double().t() / 4.0, xa.double().abs() @ xb.double().abs().t() / 4.0
+    assert torch.all((one[:M * N].view(M, N).double() - want).abs() <= K * 2.0 ** -23 * sums)
+
+
 def test_small_gemm_16bit_outputs_and_squared_error(h):
     rng = np.random.default_rng(21)
     for M, N, K in ((8, 96, 333), (48, 130, 512), (200, 150, 257)):
