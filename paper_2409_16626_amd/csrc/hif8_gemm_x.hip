@@ -282,9 +282,11 @@ __device__ __forceinline__ CodeRun<W> load_codes(const uint8_t* __restrict__ row
 }
 
 // codes -> bf16 [rows, ld], ld the pitch, of the matrix a (rows_a rows of K codes) and, below it, of b: one launch for both
-// operands of a product.  One 16-byte output chunk (8 elements) per lane and step, four steps in flight; bound by memory
-// (11008 x 4096: 135 MB in 21.6 us).  Rows at odd addresses cost no more loads than aligned ones (11007 x 4095: 27.3 us with byte loads, 22.0).
-constexpr uint32_t kExpandBlock = 256, kExpandSteps = 4;
+// operands of a product.  One 16-byte output chunk (8 elements) per lane and step, all steps in flight; bound by memory
+// (11008 x 4096: 135 MB in 21.3 us).  Rows at odd addresses cost no more loads than aligned ones (11007 x 4095: 27.1 us with byte
+// loads, 19.2 to 22.2 by where the buffers lie).
+constexpr uint32_t kExpandBlock = 256;
+template <uint32_t STEPS>
 __global__ void __launch_bounds__(kExpandBlock)
 k_expand_rows(const uint8_t* __restrict__ a, const uint8_t* __restrict__ b, uint16_t* __restrict__ dst, size_t rows_a, size_t rows,
               uint32_t K, uint32_t ld) {
@@ -293,18 +295,18 @@ k_expand_rows(const uint8_t* __restrict__ a, const uint8_t* __restrict__ b, uint
   __syncthreads();
   const uint32_t cpr = ld / 8u;  // output chunks per row
   const size_t total = rows * cpr;
-  for (size_t q0 = (size_t)blockIdx.x * (kExpandBlock * kExpandSteps) + threadIdx.x; q0 < total;
-       q0 += (size_t)gridDim.x * (kExpandBlock * kExpandSteps)) {
-    CodeRun<8> c[kExpandSteps];
+  for (size_t q0 = (size_t)blockIdx.x * (kExpandBlock * STEPS) + threadIdx.x; q0 < total;
+       q0 += (size_t)gridDim.x * (kExpandBlock * STEPS)) {
+    CodeRun<8> c[STEPS];
 #pragma unroll
-    for (uint32_t j = 0; j < kExpandSteps; ++j) {
+    for (uint32_t j = 0; j < STEPS; ++j) {
       const size_t q = q0 + j * kExpandBlock;
       const size_t row = total <= 0xFFFFFFFFu ? (size_t)((uint32_t)q / cpr) : q / cpr;
       const uint32_t k = (uint32_t)(q - row * cpr) * 8u;
       c[j] = q < total ? load_codes<8>(row < rows_a ? a + row * K : b + (row - rows_a) * K, k, K) : CodeRun<8>{};
     }
 #pragma unroll
-    for (uint32_t j = 0; j < kExpandSteps; ++j) {
+    for (uint32_t j = 0; j < STEPS; ++j) {
       const size_t q = q0 + j * kExpandBlock;
       if (q >= total) break;
       const uint32_t* w = c[j].w;
@@ -319,41 +321,44 @@ k_expand_rows(const uint8_t* __restrict__ a, const uint8_t* __restrict__ b, uint
 }
 
 // codes [rows, cols] -> bf16 [cols, ld], transposed: dst[c * ld + r] = value(codes[r * cols + c]), zeros for
-// rows <= r < ld.  Tiles of 64 x 128 codes through LDS: 16 codes per lane on the way in, on the way out a lane reads 8 rows of
-// 4 columns as dwords and looks each code up on its way into the 16-byte chunk of an output row (8 consecutive lanes write
+// rows <= r < ld.  Tiles of 64 x 128 (or 64 x 64) codes through LDS: 16 codes per lane on the way in, on the way out a lane reads 8 rows
+// of 4 (or 2) columns as dwords and looks each code up on its way into the 16-byte chunk of an output row (8 consecutive lanes write
 // 128 contiguous bytes).  LDS operations bound it: values transposed as 16-bit elements took two and a half per element,
 // codes take one and a quarter (11008 x 4096: 28.6 us -> 21.4, 6.3 TB/s; 11007 x 4095, then byte by byte: 89.5 -> 28.2).
-constexpr int kTR = 64, kTC = 128;  // tile rows and columns
-constexpr int kTPitch = kTC / 4 + 1;  // LDS row pitch in dwords: 8 rows further is 8 banks further
+constexpr int kTR = 64;  // tile rows
+template <int TC>  // tile columns: 128 or 64
 __global__ void __launch_bounds__(256)
 k_expand_cols(const uint8_t* __restrict__ codes, uint16_t* __restrict__ dst, uint32_t rows, uint32_t cols, uint32_t ld,
               uint32_t tiles_c, uint32_t n_tiles) {
+  constexpr int kTPitch = TC / 4 + 1;  // LDS row pitch in dwords: 8 rows further is 8 (128 columns) or 8 * 17 % 64 = 8 banks further
+  constexpr uint32_t kRuns = TC / 16, kRowsIn = 256 / kRuns, kPasses = kTR / kRowsIn;  // 16-code runs of a row, rows a pass
+  constexpr uint32_t kCols = TC / 32;                                                  // columns of a lane on the way out
   __shared__ uint16_t lut[256];
   __shared__ uint32_t tile[kTR * kTPitch];
   const uint32_t t = threadIdx.x;
   lut[t] = (uint16_t)(decode_bits(t) >> 16);  // blockDim.x == 256
   for (uint32_t id = blockIdx.x; id < n_tiles; id += gridDim.x) {
     const uint32_t tr = id / tiles_c, tc = id - tr * tiles_c;
-    const uint32_t r0 = tr * kTR, c0 = tc * kTC;
-    CodeRun<16> in[2];
+    const uint32_t r0 = tr * kTR, c0 = tc * TC;
+    CodeRun<16> in[kPasses];
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const uint32_t r = r0 + p * 32u + (t >> 3);
-      in[p] = r < rows ? load_codes<16>(codes + (size_t)r * cols, c0 + (t & 7u) * 16u, cols) : CodeRun<16>{};  // code 0x00 is +0
+    for (uint32_t p = 0; p < kPasses; ++p) {
+      const uint32_t r = r0 + p * kRowsIn + t / kRuns;
+      in[p] = r < rows ? load_codes<16>(codes + (size_t)r * cols, c0 + (t % kRuns) * 16u, cols) : CodeRun<16>{};  // code 0x00 is +0
     }
     __syncthreads();  // table written (first pass) / previous tile fully read
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
+    for (uint32_t p = 0; p < kPasses; ++p)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) tile[(p * 32u + (t >> 3)) * kTPitch + (t & 7u) * 4u + i] = in[p].w[i];
+      for (int i = 0; i < 4; ++i) tile[(p * kRowsIn + t / kRuns) * kTPitch + (t % kRuns) * 4u + i] = in[p].w[i];
     __syncthreads();
-    const uint32_t rc = (t & 7u) * 8u, g = t >> 3;  // output elements r0 + rc .. + 7 of rows c0 + 4 g .. + 3
+    const uint32_t rc = (t & 7u) * 8u, g = t >> 3;  // output elements r0 + rc .. + 7 of rows c0 + kCols * g ..
     uint32_t v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = tile[(rc + i) * kTPitch + g];
+    for (int i = 0; i < 8; ++i) v[i] = tile[(rc + i) * kTPitch + g * kCols / 4u] >> (kCols == 4u ? 0u : (g & 1u) * 16u);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint32_t c = c0 + g * 4u + k;
+    for (uint32_t k = 0; k < kCols; ++k) {
+      const uint32_t c = c0 + g * kCols + k;
       uint32_t e[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) e[i] = lut[(v[i] >> (8 * k)) & 0xFFu];
@@ -374,11 +379,19 @@ hif8_status expand_rows(const uint8_t* a, size_t rows_a, const uint8_t* b, size_
   if (ld == 0 || ld % kExpandK != 0 || ld < K || ld > 0x7FFFFFC0u || K > 0x7FFFFFFFu || !aligned_to(dst, 16))
     return HIF8_ERR_ARG;
   if (rows_a + rows_b > ((size_t)1 << 60) / ld) return HIF8_ERR_ARG;
-  const hif8_status s = ensure_init(nullptr, nullptr);
+  int cus = 0;
+  const hif8_status s = ensure_init(&cus, nullptr);
   if (s != HIF8_OK) return s;
-  const size_t rows = rows_a + rows_b, per_wg = kExpandBlock * kExpandSteps, want = (rows * (ld / 8) + per_wg - 1) / per_wg;
-  const unsigned grid = (unsigned)(want < ((size_t)1 << 20) ? want : (size_t)1 << 20);
-  hipLaunchKernelGGL(k_expand_rows, dim3(grid), dim3(kExpandBlock), 0, st, a, b, dst, rows_a, rows, (uint32_t)K, (uint32_t)ld);
+  const size_t rows = rows_a + rows_b, chunks = rows * (ld / 8);
+  auto launch = [&](auto kernel, size_t steps) {
+    const size_t want = (chunks + kExpandBlock * steps - 1) / (kExpandBlock * steps), most = (size_t)1 << 20;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(want < most ? want : most)), dim3(kExpandBlock), 0, st, a, b, dst, rows_a, rows, (uint32_t)K,
+                       (uint32_t)ld);
+  };
+  // one step while that gives no more than four workgroups per compute unit (8 x 4096 2.3 us, with four steps 3.1, 512 x 4096 3.3,
+  // 3.6; 1024 x 4096 4.6, 4.4, 4096 x 4096 11.1, 9.0)
+  if (chunks <= (size_t)cus * 4 * kExpandBlock) launch(k_expand_rows<1>, 1);
+  else launch(k_expand_rows<4>, 4);
   return finish_launch();
 }
 
@@ -392,10 +405,16 @@ hif8_status expand_cols(const uint8_t* codes, size_t rows, size_t cols, uint16_t
   hif8_status s = ensure_init(&cus, nullptr);
   if (s != HIF8_OK) return s;
   if ((ld / kTR) * ((cols + 63) / 64) > 0x7FFFFFFFull) return HIF8_ERR_ARG;
-  const size_t tiles_c = (cols + kTC - 1) / kTC, n_tiles = (ld / kTR) * tiles_c;
-  const unsigned grid = (unsigned)(n_tiles < (size_t)cus * 16 ? n_tiles : (size_t)cus * 16);
-  hipLaunchKernelGGL(k_expand_cols, dim3(grid), dim3(256), 0, st, codes, dst, (uint32_t)rows, (uint32_t)cols, (uint32_t)ld,
-                     (uint32_t)tiles_c, (uint32_t)n_tiles);
+  auto launch = [&](auto kernel, size_t tc) {
+    const size_t tiles_c = (cols + tc - 1) / tc, n_tiles = (ld / kTR) * tiles_c;
+    const unsigned grid = (unsigned)(n_tiles < (size_t)cus * 16 ? n_tiles : (size_t)cus * 16);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, codes, dst, (uint32_t)rows, (uint32_t)cols, (uint32_t)ld, (uint32_t)tiles_c,
+                       (uint32_t)n_tiles);
+  };
+  // narrow tiles while wide ones are no more than two per compute unit, or half empty (64 x 64 2.2 us, in wide ones 2.6; 1024 x 4096
+  // 4.0, 4.1, 4096 x 4096 11.2, 8.6; 100000 x 16 3.6, 4.2)
+  if (cols <= 64 || (ld / kTR) * ((cols + 127) / 128) <= (size_t)cus * 2) launch(k_expand_cols<64>, 64);
+  else launch(k_expand_cols<128>, 128);
   return finish_launch();
 }
 

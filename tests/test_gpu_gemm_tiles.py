@@ -251,6 +251,23 @@ def test_expansions_of_every_remainder(h, rows):
                 assert torch.equal(dst[:r, :c], w) and torch.all(dst[:r, c:] == 0) and torch.all(dst[r] == 0x1234)
 
 
+# both forms of each expansion: one step and four per lane (2^21 codes of a padded matrix), tiles of 64 and of 128 columns
+# (512 tiles of 64 x 128; 64 columns and fewer), on either side of the lines
+@pytest.mark.parametrize("rows,cols", [(511, 4096), (512, 4096), (513, 4095), (1024, 4096), (1024, 4097), (1025, 4096), (40000, 64), (40000, 65),
+                                       (64, 65600)])
+def test_expansions_on_either_side_of_their_lines(h, rows, cols):
+    lut = torch.tensor([orc.decode_value(c) for c in range(256)], dtype=torch.float64).to(torch.bfloat16).view(torch.int16).to(dev())
+    lut[0x80] = torch.tensor(0x7FC0, dtype=torch.int16)
+    codes = torch.randint(0, 256, (rows, cols), dtype=torch.uint8, device=dev(), generator=torch.Generator(device=dev()).manual_seed(rows))
+    want = lut[codes.long()]
+    for call, w in ((h.hif8_expand_bf16, want), (h.hif8_expand_bf16_t, want.t())):
+        r, c = w.shape
+        ld = h.hif8_expanded_ld(c)
+        dst = torch.full((r + 1, ld), 0x1234, dtype=torch.int16, device=dev())
+        call(codes, rows, cols, dst, ld)
+        assert torch.equal(dst[:r, :c], w) and torch.all(dst[:r, c:] == 0) and torch.all(dst[r] == 0x1234)
+
+
 def test_workspace_product_expands_both_operands(h):
     """Both operands of hif8_gemm_ws_* are expanded in one launch: the bits of the two expansions and the product on them."""
     rng = np.random.default_rng(4)
