@@ -36,27 +36,45 @@ inline uint64_t tile_count(int tile, size_t M, size_t N, size_t pairs) {
 // what is launched ask here (columns behind a split with two stages / four, us: 4096 x 5000 x 4096 124 / 116, 1792 x 9472 x
 // 4096 120 / 107).
 inline int tile_stages(int tile, uint64_t tiles, size_t cus) { return tile == TILE_128 && tiles <= cus ? 4 : 2; }
-inline uint64_t tile_cost(int tile, size_t M, size_t N, size_t pairs, size_t cus) {
-  const uint64_t tiles = tile_count(tile, M, N, pairs);
-  if (tile != TILE_128) return (tiles + cus - 1) / cus * (tile == TILE_256 ? 130u : 100u);
-  if (tile_stages(tile, tiles, cus) == 4) return 40u;
-  const uint64_t rest = tiles % (2 * cus);
-  return tiles / (2 * cus) * 76u + (rest == 0 ? 0u : rest <= cus ? 62u : 76u);
+// With K below 1024 a round's epilogue counts as much as its MFMAs, and two 128 x 128 tiles on a compute unit hide it from each
+// other: there a round of single products costs a part that goes with the output and one that goes with K, in tenths of a us
+// (256 x 256 / 256 x 192 / 128 x 128: 8192 x 8192 x 128 46 / 52 / 38 bfloat16, 64 / 67 / 53 binary32, 71 / 80 / 66 squared error; x
+// 512 71 / 85 / 70 bfloat16; 4096 x 4096 x 512 21 / 29 / 21 bfloat16, 22.4 / 29 / 24 binary32; squared error
+// 4096 x 4096 x 128 19 / 26 / 21, with edge tiles 1500 x 9000 x 128 24 / 26 / 20).
+enum : int { OUT_16 = 0, OUT_32 = 1, OUT_ERR = 2 };
+struct TileProblem {
+  size_t M, N, K, pairs;
+  int out;
+};
+inline uint64_t tile_cost(int tile, const TileProblem& p, size_t cus) {
+  const uint64_t tiles = tile_count(tile, p.M, p.N, p.pairs), rest = tiles % (2 * cus);
+  uint64_t round[5] = {130, 100, 76, 62, 40};  // 256 x 256, 256 x 192, 128 x 128: two per compute unit, one, one with four stages
+  if (p.K < 1024 && p.pairs == 1) {
+    constexpr uint64_t kOut[3][5] = {{90, 70, 35, 32, 38}, {125, 95, 60, 45, 42}, {156, 125, 84, 55, 60}}, kPerStep[5] = {111, 87, 68, 59, 34};
+    for (int i = 0; i < 5; ++i) round[i] = kOut[p.out][i] + (p.K + 63) / 64 * kPerStep[i] / 10;
+    if (p.out == OUT_ERR && (p.M % 256 != 0 || p.N % 256 != 0)) round[0] += 40;  // edge tiles
+  }
+  if (tile != TILE_128) return (tiles + cus - 1) / cus * round[tile];
+  if (tile_stages(tile, tiles, cus) == 4) return round[4];
+  return tiles / (2 * cus) * round[2] + (rest == 0 ? 0u : rest <= cus ? round[3] : round[2]);
 }
-inline int tile_plan(size_t M, size_t N, size_t pairs, size_t cus, uint32_t* split) {
+inline int tile_plan(const TileProblem& p, size_t cus, uint32_t* split) {
   int best = TILE_256;
-  uint64_t cost = tile_cost(TILE_256, M, N, pairs, cus);
+  uint64_t cost = tile_cost(TILE_256, p, cus);
   for (int t = TILE_192; t <= TILE_128; ++t) {
-    const uint64_t c = tile_cost(t, M, N, pairs, cus);
+    const uint64_t c = tile_cost(t, p, cus);
     if (c < cost) {
       cost = c;
       best = t;
     }
   }
   // complete rounds of 256 x 256 tiles, then the remaining columns in 128 x 128 tiles
-  if (pairs == 1 && ragged_round_split(M, N, cus, split) &&
-      tile_cost(TILE_256, M, *split, 1, cus) + tile_cost(TILE_128, M, N - *split, 1, cus) + 10u < cost)
-    best = TILE_SPLIT;
+  if (p.pairs == 1 && ragged_round_split(p.M, p.N, cus, split)) {
+    TileProblem left = p, right = p;
+    left.N = *split;
+    right.N = p.N - *split;
+    if (tile_cost(TILE_256, left, cus) + tile_cost(TILE_128, right, cus) + (p.K < 1024 ? 25u : 10u) < cost) best = TILE_SPLIT;
+  }
   return best;
 }
 
@@ -65,16 +83,16 @@ struct TileLaunch {
   int tile, stages;
   uint32_t begin, end;
 };
-inline int tile_launches(int plan, size_t M, size_t N, size_t pairs, size_t cus, uint32_t split, TileLaunch (&out)[2]) {
+inline int tile_launches(int plan, const TileProblem& p, size_t cus, uint32_t split, TileLaunch (&out)[2]) {
   auto one = [&](int tile, size_t begin, size_t end) {
-    return TileLaunch{tile, tile_stages(tile, tile_count(tile, M, end - begin, pairs), cus), (uint32_t)begin, (uint32_t)end};
+    return TileLaunch{tile, tile_stages(tile, tile_count(tile, p.M, end - begin, p.pairs), cus), (uint32_t)begin, (uint32_t)end};
   };
   if (plan != TILE_SPLIT) {
-    out[0] = one(plan, 0, N);
+    out[0] = one(plan, 0, p.N);
     return 1;
   }
   out[0] = one(TILE_256, 0, split);
-  out[1] = one(TILE_128, split, N);
+  out[1] = one(TILE_128, split, p.N);
   return 2;
 }
 
@@ -86,10 +104,10 @@ inline uint64_t most_tiles(int tile, bool sqerr) { return tile == TILE_256 && sq
 
 // Pairs of a scale search (na x nb error products) that one launch takes: all of them, one row of nb, or a single one
 // (0: not even that).  tile: the tile asked for, or -1 for the plan's own choice, which goes by the pairs of the launch.
-inline uint32_t pairs_per_launch(int tile, size_t M, size_t N, uint32_t na, uint32_t nb, size_t cus) {
+inline uint32_t pairs_per_launch(int tile, size_t M, size_t N, size_t K, uint32_t na, uint32_t nb, size_t cus) {
   auto fits = [&](size_t pairs) {
     uint32_t split = 0;
-    const int t = tile >= 0 ? tile : tile_plan(M, N, pairs, cus, &split);
+    const int t = tile >= 0 ? tile : tile_plan(TileProblem{M, N, K, pairs, OUT_ERR}, cus, &split);
     return t == TILE_SPLIT || tile_count(t, M, N, pairs) <= most_tiles(t, true);  // a split: one part walks, the other has at most two rounds
   };
   return fits((size_t)na * nb) ? na * nb : fits(nb) ? nb : fits(1) ? 1u : 0u;

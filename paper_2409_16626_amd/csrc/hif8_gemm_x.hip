@@ -479,7 +479,7 @@ hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const
   const int asked = variant == 9 ? TILE_128 : variant == 10 ? TILE_256 : variant == 11 ? TILE_192 : -1;
   if (batch.na != 0u) {
     // a search over a very large matrix goes row by row of its square, or pair by pair
-    const uint32_t some = pairs_per_launch(asked, M, N, batch.na, batch.nb, (size_t)cus);
+    const uint32_t some = pairs_per_launch(asked, M, N, ld, batch.na, batch.nb, (size_t)cus);
     if (some == 0u) return HIF8_ERR_ARG;
     for (uint32_t p = 0; some < pairs && p < pairs; p += some) {
       const uint32_t i = p / batch.nb, j = p % batch.nb;
@@ -490,9 +490,10 @@ hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const
     if (some < pairs) return HIF8_OK;
   }
   uint32_t split = 0;
-  const int plan = asked >= 0 ? asked : tile_plan(M, N, pairs, (size_t)cus, &split);
+  const TileProblem problem{M, N, ld, pairs, EPI == EPI_ERR ? OUT_ERR : EPI == EPI_F32 ? OUT_32 : OUT_16};
+  const int plan = asked >= 0 ? asked : tile_plan(problem, (size_t)cus, &split);
   TileLaunch launches[2];
-  const int count = tile_launches(plan, M, N, pairs, (size_t)cus, split, launches);
+  const int count = tile_launches(plan, problem, (size_t)cus, split, launches);
   for (int i = 0; i < count && s == HIF8_OK; ++i) {
     const TileLaunch& l = launches[i];
     auto run = [&](auto launch) { s = launch(A, B, out, ref, err, m, n, k, descale, st, cus, batch, l.begin, l.end); };

@@ -88,11 +88,12 @@ uint32_t devfn_small_plan(size_t M, size_t N, size_t K, int codes, int sqerr, ui
 int devfn_small_problem(size_t M, size_t N, size_t K, int codes, int sqerr) { return hif8gemm::small_problem(M, N, K, codes != 0, sqerr != 0); }
 // expanded-operand GEMM: the launches of its plan, 4 numbers each: tile (0 = 256 x 256, 1 = 256 x 192, 2 = 128 x 128), LDS
 // stages, first column, end; returns how many
-int devfn_tile_launches(size_t M, size_t N, size_t pairs, size_t cus, uint32_t* out) {
+int devfn_tile_launches(size_t M, size_t N, size_t K, size_t pairs, size_t cus, int kind, uint32_t* out) {
   uint32_t split = 0;
-  const int plan = hif8gemm::tile_plan(M, N, pairs, cus, &split);
+  const hif8gemm::TileProblem p{M, N, K, pairs, kind};
+  const int plan = hif8gemm::tile_plan(p, cus, &split);
   hif8gemm::TileLaunch l[2];
-  const int n = hif8gemm::tile_launches(plan, M, N, pairs, cus, split, l);
+  const int n = hif8gemm::tile_launches(plan, p, cus, split, l);
   for (int i = 0; i < n; ++i) {
     out[4 * i] = (uint32_t)l[i].tile;
     out[4 * i + 1] = (uint32_t)l[i].stages;
@@ -101,7 +102,7 @@ int devfn_tile_launches(size_t M, size_t N, size_t pairs, size_t cus, uint32_t* 
   }
   return n;
 }
-uint32_t devfn_pairs_per_launch(int tile, size_t M, size_t N, uint32_t na, uint32_t nb, size_t cus) {
-  return hif8gemm::pairs_per_launch(tile, M, N, na, nb, cus);
+uint32_t devfn_pairs_per_launch(int tile, size_t M, size_t N, size_t K, uint32_t na, uint32_t nb, size_t cus) {
+  return hif8gemm::pairs_per_launch(tile, M, N, K, na, nb, cus);
 }
 }
