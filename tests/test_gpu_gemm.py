@@ -93,12 +93,13 @@ def test_gemm_exact_when_sums_fit_24_bits(h):
         assert torch.equal(o16.cpu(), want.to(torch.bfloat16)) and torch.equal(oh.cpu(), want.to(torch.float16))
 
 
-def test_gemm_16bit_outputs_and_scales(h):
+@pytest.mark.parametrize("variant", [0, 5, 6])     # by problem size (small tiles here), 256 x 256, 128 x 128
+def test_gemm_16bit_outputs_and_scales(h, variant):
     rng = np.random.default_rng(6)
     M, N, K = 192, 160, 256
     ca, cb = random_codes(rng, (M, K), "cast_normal"), random_codes(rng, (N, K), "cast_normal")
     a, b = torch.from_numpy(ca).to(dev()), torch.from_numpy(cb).to(dev())
-    h.hif8_gemm_set_variant(0)
+    h.hif8_gemm_set_variant(variant)
     for sa, sb in ((8.0, 8.0), (0.37, 1311.7), (2.0 ** -20, 2.0 ** 10)):
         o16 = torch.zeros(M, N, dtype=torch.bfloat16, device=dev())
         oh = torch.zeros(M, N, dtype=torch.float16, device=dev())
@@ -129,10 +130,14 @@ def test_gemm_special_codes_follow_ieee(h):
         assert np.array_equal(np.isnan(got), np.isnan(want))
         assert np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isneginf(got), np.isneginf(want))
         assert np.isnan(want[9]).all() and np.isnan(want[20, 11]) and np.isinf(want[3]).any()
+        ob = torch.zeros(M, N, dtype=torch.bfloat16, device=dev())
+        h.hif8_gemm_bf16(a, b, ob, M, N, K, 1.0, 1.0)
+        bits = bf16_bits(ob)
+        assert np.all(bits[np.isnan(want)] == 0x7FC0) and np.array_equal(bits == 0x7F80, np.isposinf(want))
 
 
 @pytest.mark.parametrize("M,N,K,off", [(40, 24, 17, 0), (5, 9, 100, 0), (64, 64, 64, 1), (3, 2, 1, 0)])
-def test_gemm_plain_kernel_for_odd_k_and_alignment(h, M, N, K, off):
+def test_gemm_odd_k_and_alignment(h, M, N, K, off):
     rng = np.random.default_rng(8)
     ca, cb = random_codes(rng, (M, K), "cast_normal"), random_codes(rng, (N, K), "cast_normal")
     abuf = torch.zeros(M * K + 16, dtype=torch.uint8, device=dev())

@@ -97,7 +97,7 @@ SHAPES = [(32, 32, 16), (128, 128, 64), (100, 70, 48), (257, 129, 80), (1, 1, 1)
           (300, 300, 256), (260, 140, 320), (270, 520, 448)]   # 4, 5 and 7 K steps: every length of the loop's tail
 
 
-@pytest.mark.parametrize("variant", [0, 9, 10, 11])     # by problem size; 128 x 128; 256 x 256 as 2 x 2 and as 2 x 4 wavefronts
+@pytest.mark.parametrize("variant", [0, 9, 10, 11])     # by problem size; 128 x 128; 256 x 256; 256 x 192
 @pytest.mark.parametrize("M,N,K", SHAPES)
 def test_gemm_expanded_f32_matches_oracle(h, variant, M, N, K):
     rng = np.random.default_rng(M * 7 + N * 3 + K)
@@ -114,7 +114,7 @@ def test_gemm_expanded_f32_matches_oracle(h, variant, M, N, K):
         assert np.mean(diff) <= 0.05 * K * 2.0 ** -23 * np.mean(bound) + 1e-45
 
 
-@pytest.mark.parametrize("M,N,K", [(200, 136, 512), (4100, 4200, 192)])     # 128 x 128 tiles, then 256 x 256 tiles
+@pytest.mark.parametrize("M,N,K", [(200, 136, 512), (4100, 4200, 192)])     # one tile and a part; several rounds and a column split
 def test_gemm_expanded_exact_when_sums_fit_24_bits(h, M, N, K):
     """Small integers as operands: every partial sum is an integer below 2^24, so FP32 accumulation
     is exact in any order and the result must equal the oracle bit for bit -- and the code-operand kernel."""
@@ -145,9 +145,11 @@ def test_gemm_expanded_exact_when_sums_fit_24_bits(h, M, N, K):
     assert torch.equal(o16.cpu(), want.to(torch.bfloat16)) and torch.equal(oh.cpu(), want.to(torch.float16))
 
 
-def test_gemm_expanded_16bit_outputs_and_scales(h):
+@pytest.mark.parametrize("variant", [0, 9, 10, 11, 12])
+def test_gemm_expanded_16bit_outputs_and_scales(h, variant):
     rng = np.random.default_rng(6)
     M, N, K = 192, 160, 256
+    h.hif8_gemm_set_variant(variant)
     ca, cb = random_codes(rng, (M, K), "cast_normal"), random_codes(rng, (N, K), "cast_normal")
     a, ld = expand(h, ca)
     b, _ = expand(h, cb)
@@ -161,6 +163,7 @@ def test_gemm_expanded_16bit_outputs_and_scales(h):
         want = go.gemm_hif8(ca, cb, sa, sb)
         if np.abs(want).max() < 6.0e4 and np.abs(want)[want != 0].min() > 1e-4:
             check(oh.float().cpu().numpy(), ca, cb, sa, sb, extra_rel=2.0 ** -10)
+    h.hif8_gemm_set_variant(0)
 
 
 def test_gemm_expanded_special_codes_follow_ieee(h):

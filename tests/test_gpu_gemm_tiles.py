@@ -89,6 +89,35 @@ def test_column_split_equals_one_launch(h, M, N, K):
     assert torch.all((got["f32"][:M * N].view(M, N)[rows].double() - want).abs() <= K * 2.0 ** -23 * sums)
 
 
+# codes in 256 x 256 and 128 x 128 tiles, expanded operands in 128 x 128, 256 x 256 and 256 x 192, both in small tiles; whole runs
+# of a row and shorter ones.  Sums of small integers are exact, so a result is one binary32 product and one rounding to 16 bits.
+@pytest.mark.parametrize("operands,variant", [("codes", 5), ("codes", 6), ("codes", 12), ("expanded", 9), ("expanded", 10), ("expanded", 11),
+                                              ("expanded", 12)])
+def test_results_below_the_normal_range(h, operands, variant):
+    rng = np.random.default_rng(variant)
+    M, N, K = 140, 267, 192
+    vals = np.array([0x00, 0x08, 0x10, 0x14, 0x20, 0x88, 0x90], np.uint8)  # 0, 1, 2, 3, 4, -1, -2
+    ca, cb = rng.choice(vals, size=(M, K)), rng.choice(vals, size=(N, K))
+    v = np.array([orc.decode_value(c) if np.isfinite(orc.decode_value(c)) else 0.0 for c in range(256)], np.float64)
+    sums = torch.from_numpy((v[ca] @ v[cb].T).astype(np.float32))
+    if operands == "codes":
+        a, b, ld = torch.from_numpy(ca).to(dev()), torch.from_numpy(cb).to(dev()), ()
+    else:
+        (a, ld), (b, _) = expand(h, ca), expand(h, cb)
+        ld = (ld,)
+    prefix = "hif8_gemm_" if operands == "codes" else "hif8_gemm_expanded_"
+    h.hif8_gemm_set_variant(variant)
+    for name, dtype, ea, eb in (("bf16", torch.bfloat16, 66, 68), ("bf16", torch.bfloat16, 66, 70), ("bf16", torch.bfloat16, 70, 71),
+                                ("f32", torch.float32, 70, 74), ("f16", torch.float16, 10, 12), ("f16", torch.float16, 14, 17)):
+        out = torch.full((M, N), 7.0, dtype=dtype, device=dev())
+        getattr(h, prefix + name)(a, b, out, M, N, K, *ld, 2.0 ** ea, 2.0 ** eb)
+        want = (sums * torch.tensor(2.0 ** -(ea + eb), dtype=torch.float32)).to(dtype)
+        assert torch.equal(out.cpu(), want), (name, ea, eb)
+        least = torch.finfo(dtype).tiny
+        assert ((want != 0) & (want.float().abs() < least)).float().mean() > 0.1
+    h.hif8_gemm_set_variant(0)
+
+
 @pytest.mark.parametrize("variant", [9, 10, 11])
 def test_tiles_nan_and_inf(h, variant):
     """A NaN of either operand reaches its row or column only, as 0x7FC0 in bfloat16, and nothing past the edge of a tile."""
