@@ -71,8 +71,9 @@ __device__ __forceinline__ u32x4 load16_tail(const uint8_t* row, uint32_t k, uin
 // their negatives (codes 0x40.., 0x60.., 0xC0.., 0xE0.. of values above 2^4) sit in different LDS banks.
 __device__ __forceinline__ uint32_t table_slots(uint32_t w) { return w ^ ((w >> 3) & 0x10101010u); }
 
-// Two neighbouring elements.  The table is the first thing in the kernel's (only) dynamic LDS, at LDS address 0; with
-// the address formed here an index costs one shift of a selected byte.
+// Two neighbouring elements.  The table is the first thing in the kernel's only LDS, which is dynamic, at LDS address 0 (a CPU
+// test holds the kernel to that); with the address formed here an index costs one shift of a selected byte, from the array's own
+// address an addition more (3 % more instructions in the kernel).
 __device__ __forceinline__ uint32_t lookup2(uint32_t lo, uint32_t hi) {
   typedef const __attribute__((address_space(3))) uint16_t* lds_u16;
   return (uint32_t)*(lds_u16)(lo << 1) | ((uint32_t)*(lds_u16)(hi << 1) << 16);

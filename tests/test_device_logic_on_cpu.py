@@ -8,6 +8,7 @@ random patterns, under every rounding method and option.
 """
 import ctypes
 import os
+import re
 import subprocess
 
 import numpy as np
@@ -368,3 +369,19 @@ def test_scale_search_launches_fit(dev, tile_launches):
         assert fits(some)
         assert some == na * nb or not fits(na * nb)
     assert seen == {"all", "row", "pair"}
+
+
+def test_small_gemm_kernel_has_no_static_lds(tmp_path):
+    """k_gemm_s looks codes up in a table at LDS address 0, the start of its dynamic LDS: static LDS would come before it."""
+    from paper_2409_16626_amd import build
+    obj = os.path.join(build.OBJDIR, "hif8_gemm_s.hip.o")
+    if not os.path.exists(obj):
+        build.build(force=False)
+    llvm = "/opt/rocm/llvm/bin/"
+    fat, code = str(tmp_path / "fat"), str(tmp_path / "code")
+    subprocess.run([llvm + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + fat, obj, str(tmp_path / "copy.o")], check=True)
+    subprocess.run([llvm + "clang-offload-bundler", "--type=o", "--unbundle", "--input=" + fat, "--output=" + code,
+                    "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], check=True)
+    notes = subprocess.run([llvm + "llvm-readelf", "--notes", code], check=True, stdout=subprocess.PIPE, text=True).stdout
+    sizes = re.findall(r"\.group_segment_fixed_size:\s*(\d+)", notes)
+    assert notes.count("k_gemm_s") > 0 and len(sizes) >= 40 and set(sizes) == {"0"}, sizes
