@@ -261,8 +261,9 @@ hif8_status hif8_fake_quant_f16_sr(const uint16_t* src, uint16_t* dst, uint8_t* 
  * pass leaves one partial maximum per workgroup in `workspace`, and every workgroup of the cast
  * reduces those and derives the scale itself (no clearing launch, no atomics, no scale launch).
  * The first pass reads with ordinary loads, so a tensor that fits the 256 MB last-level cache is
- * still there when the cast reads it again.  A source of up to 512 KiB takes one launch, whose
- * workgroups each read all of it, and leaves the workspace as it is.
+ * still there when the cast reads it again.  A source of up to 512 KiB that has the fast path's
+ * alignment and, beyond 16 KiB, does not overlap dst or codes takes one launch, whose workgroups each
+ * read all of it, and leaves the workspace as it is.
  * At least one of dst, codes must be given; dst may equal src.  d_amax: one device float,
  * d_scale2: two device floats, both written.  workspace: device scratch of at least
  * hif8_quantize_workspace_bytes() bytes (4 KiB), 4-byte aligned, caller-owned; its contents need
@@ -586,10 +587,11 @@ hif8_status hif8_gemm_expanded_sqerr(const uint16_t* a, const uint16_t* b, const
  * hif8_gemm_* on code operands with a workspace: both code matrices are expanded to bfloat16 into the
  * workspace (hif8_expand_bf16) and multiplied by the expanded-operand kernel -- two or three launches on `stream`, and
  * for matrix-core-bound shapes about two thirds of the time of hif8_gemm_* (whose kernel expands the codes on
- * their way into LDS and is bound by that work).  Small products with up to 128 rows in one operand are taken
- * straight from the codes instead, in one launch, and leave the workspace unused.  Arguments, result and error bound as for hif8_gemm_* (the
- * result equals that of hif8_gemm_expanded_* on the expanded operands bit for bit); any K and any alignment of
- * the code matrices.
+ * their way into LDS and is bound by that work; between about 128 and 1000 rows of a small product it is the faster
+ * one, since nothing has to be written first).  Small products with up to 128 rows in one operand are taken
+ * straight from the codes instead, in one launch, and leave the workspace unused.  Arguments, result and error bound
+ * as for hif8_gemm_* (the result equals that of hif8_gemm_expanded_* on the expanded operands bit for bit); any K and
+ * any alignment of the code matrices.
  * workspace: device memory, 16-byte aligned, at least hif8_gemm_workspace_bytes(M, N, K) bytes
  * (= 2 (M + N) hif8_expanded_ld(K), 0 when M, N or K is 0), caller-owned, free for other use once the
  * work enqueued here has run; a smaller workspace_bytes is HIF8_ERR_ARG.  K beyond 2^22 (the expanded-operand
@@ -619,10 +621,12 @@ hif8_status hif8_gemm_ws_sqerr(const uint8_t* a_codes, const uint8_t* b_codes, c
  * and, if d_best_or_null is given, write the pair with the smallest finite error to it as two
  * int32 {Ea, Ew}.  The paper casts with TA here; any rounding_mode is accepted.  The model-level
  * loop (collecting o_ref, feeding O_q through the non-linearities to the next layer) is the
- * caller's.  Enqueues ea_count + ew_count casts (each followed by its expansion to bfloat16) and
- * ea_count * ew_count error GEMMs (one batched launch) on `stream`.
- * workspace: device scratch for one code matrix and the expanded operands, at least
- * hif8_calibrate_workspace_bytes(M, N, K, ea_count, ew_count) bytes, 16-byte aligned, caller-owned.
+ * caller's.  Enqueues on `stream` a clearing of d_err, the casts of each operand at all its scales, straight to
+ * bfloat16 (one launch per operand), the ea_count * ew_count error GEMMs (one batched launch; several where
+ * the search has more tiles than a launch counts) and the choice of the pair.
+ * workspace: device scratch for the operands cast at every scale, behind max(M, N) * K bytes (rounded up to 16) that
+ * are reserved and not used, at least hif8_calibrate_workspace_bytes(M, N, K, ea_count, ew_count) bytes,
+ * 16-byte aligned, caller-owned.
  * Counts are limited to 64 each, exponents to [-60, 60], K to 2^22.
  */
 size_t hif8_calibrate_workspace_bytes(size_t M, size_t N, size_t K, int ea_count, int ew_count);

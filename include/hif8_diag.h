@@ -59,11 +59,13 @@ int hif8_get_tuning(int key); /* -1 for an unknown key */
  *                                              choice when there is such a tile for every compute unit);
  *                                              6 = 128 x 128 x 32, 4 wavefronts, two workgroups per CU
  *   expanded-operand kernel (hif8_gemm_expanded_*), 4 wavefronts as 2 x 2 each: 9 = 128 x 128 x 64, two workgroups
- *                                              per CU; 10 = 256 x 256 x 64; 11 = 256 x 192 x 64 (the choice is the
- *                                              one with the shortest sum of rounds)
+ *                                              per CU, or one with four LDS stages where there are no more tiles
+ *                                              than compute units; 10 = 256 x 256 x 64; 11 = 256 x 192 x 64 (the
+ *                                              choice is the one with the shortest sum of rounds)
  *   both:                                      12 = the small-tile kernel that few output tiles and unaligned code
  *                                              operands take (its tile still follows the problem size)
- * 0 resets both choices.  Other values: HIF8_ERR_ARG.
+ * A value holds for its kernel until another one for that kernel or 0, which resets both: after 12, 9 leaves the
+ * code-operand kernel on 12.  Other values: HIF8_ERR_ARG.
  */
 hif8_status hif8_gemm_set_variant(int variant);
 

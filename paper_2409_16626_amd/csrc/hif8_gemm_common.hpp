@@ -1,6 +1,7 @@
-// Pieces shared by the two simulated-HiF8 GEMM kernels (u8 code operands expanded in the kernel,
-// and operands already expanded to bfloat16): accumulator types, the batched-launch descriptor
-// of Algorithm 1's scale search, and the epilogue (descale, then store or score against a reference).
+// Declarations of the simulated-HiF8 GEMM kernels (u8 code operands expanded in the kernel, operands already expanded to
+// bfloat16, small tiles of either) and what they share: accumulator types, output kinds, the batched-launch descriptor of
+// Algorithm 1's scale search, the store of one element.  Then the epilogue of the expanded-operand kernel (descale, then
+// store or score against a reference in whole lines); the other two store from their own sums.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -306,7 +307,7 @@ hif8_status expand_rows(const uint8_t* a, size_t rows_a, const uint8_t* b, size_
                         hipStream_t st);
 hif8_status expand_cols(const uint8_t* codes, size_t rows, size_t cols, uint16_t* dst, size_t ld, hipStream_t st);
 
-// out = (A x B^T) * descale on operands of pitch ld (zero beyond K); batch.nb != 0: `pairs` GEMMs in one launch
+// out = (A x B^T) * descale on operands of pitch ld (zero beyond K); batch.na != 0: the na x nb products of a scale search
 template <int EPI>
 hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const float* ref, double* err, size_t M,
                           size_t N, size_t ld, float descale, hipStream_t st, const Batch& batch = Batch{});

@@ -113,9 +113,10 @@ inline uint32_t pairs_per_launch(int tile, size_t M, size_t N, size_t K, uint32_
   return fits((size_t)na * nb) ? na * nb : fits(nb) ? nb : fits(1) ? 1u : 0u;
 }
 
-// Products with at most this many rows on one side run straight from the codes in hif8_gemm_ws_* when they go to the
-// small-tile kernel; above it expanding first is faster (128 x 11008 x 4096: 52 us against 55; 384 x 4096 x 4096:
-// 50 against 44; 512 x 4096 x 11008: 150 against 100).
+// Products with at most this many rows on one side run straight from the codes in hif8_gemm_ws_* when the expanded operands
+// would go to the small-tile kernel: up to here both operand kinds have one plan (small_plan) and so the same bits.  Above it
+// the codes are expanded first, which is faster for large products (codes / expanded first, us: 384 x 4096 x 4096 50 / 44, 512
+// x 4096 x 11008 150 / 100) and slower for small ones (256 x 4096 x 4096 32 / 36, 700 x 700 x 700 10 / 15.5).
 constexpr size_t kSmallCodesRows = 128;
 
 // Which problems go to the small-tile kernel (hif8_gemm_s.hip) although the tiled kernels could run them.  The tiled kernels
