@@ -115,8 +115,8 @@ inline uint32_t pairs_per_launch(int tile, size_t M, size_t N, size_t K, uint32_
 
 // Products with at most this many rows on one side run straight from the codes in hif8_gemm_ws_* when the expanded operands
 // would go to the small-tile kernel: up to here both operand kinds have one plan (small_plan) and so the same bits.  Above it
-// the codes are expanded first, which is faster for large products (codes / expanded first, us: 384 x 4096 x 4096 50 / 44, 512
-// x 4096 x 11008 150 / 100) and slower for small ones (256 x 4096 x 4096 32 / 36, 700 x 700 x 700 10 / 15.5).
+// the codes are expanded first, which is faster for large products (codes / expanded first, us: 512 x 2560 x 4096 50 / 38, 1024 x
+// 2560 x 2048 47 / 26) and slower for small ones (256 x 1280 x 4096 18 / 31, 512 x 2048 x 2048 19 / 23, 700 x 700 x 700 10 / 15.5).
 constexpr size_t kSmallCodesRows = 128;
 
 // Which problems go to the small-tile kernel (hif8_gemm_s.hip) although the tiled kernels could run them.  The tiled kernels
