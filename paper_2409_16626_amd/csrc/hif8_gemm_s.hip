@@ -12,8 +12,10 @@
 // straight from global memory, 16 rows in 16 neighbouring lanes, ran at half the speed on rows that are not 16-byte
 // aligned), passes them through its own 2 KiB of LDS per 16-row block, with the loads of the next 128 bytes in flight
 // meanwhile, and expands codes on their way from there into the fragments of v_mfma_f32_16x16x32_bf16 through a
-// 256-entry table in LDS.  That table look-up, one LDS read and three vector instructions per element, is what bounds
-// the code form: without it 8 x 11008 x 4096 takes 11 us, without the loads 14 us, as it is 14 us (45 MB: 7.5 us at
+// 256-entry table in LDS.  That table look-up, one LDS read and three vector instructions per element, is the larger part of
+// the code form: without it 8 x 11008 x 4096 takes 11 us, without the loads 14 us, as it is 14 us; the LDS is active 56 % of
+// the cycles, a fifth of them bank conflicts, the vector ALUs 55 %.  With one workgroup per compute unit (509 x 1003 x 2049) both
+// are busy a quarter of the time, and the chain of loads, stages and the sum counts.  (8 x 11008 x 4096: 45 MB, 7.5 us at
 // the memory's rate); the tiled kernel took 85 us.  Measured against the tiled kernels (us per call, codes / expanded
 // operands): 8 x 4096 x 4096 7.9 / 9.3 (80 / 55), 64 x 4096 x 4096 14.2 / 14.9 (84 / 55), 256 x 4096 x 4096 33 / 23
 // (85 / 55), 512 x 4096 x 11008 150 / 80 (231 / 143); odd K, 509 x 1003 x 2049: 18.6 (3810 with one output per lane).
