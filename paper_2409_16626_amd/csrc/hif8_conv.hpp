@@ -725,8 +725,9 @@ k_quant_one(const void* src, void* dst, uint8_t* codes, uint32_t n, float target
 // Tiles per workgroup of the multi-tensor cast.  Two keep the most workgroups in flight, which is what the plain
 // TA cast wants; with the amax accumulation (one atomic per workgroup and tensor) or a larger table to stage per
 // workgroup (every implementation but TA), four measured 3-16 % faster on the 225-tensor LLM weight list.
-template <int IMPL, bool ACC>
-__host__ __device__ constexpr uint32_t multi_tpw_encode() { return (ACC || IMPL != IMPL_TA_LUT) ? 4u : 2u; }
+enum : int { ACC_NO = 0, ACC_YES = 1, ACC_SAMPLED = 2 };  // what a multi-tensor cast does about the amax of what it reads
+template <int IMPL, int ACC>
+__host__ __device__ constexpr uint32_t multi_tpw_encode() { return (ACC != ACC_NO || IMPL != IMPL_TA_LUT) ? 4u : 2u; }
 constexpr uint32_t kMultiTpwAmax = 8;
 
 // largest i with items[i].first_tile <= tile (zero-size items are skipped by construction)
@@ -796,33 +797,54 @@ __device__ __forceinline__ void multi_amax_tiles(const hif8_cast_item* __restric
   if (cur != 0xFFFFFFFFu) block_max_to_global(umax(fold_amax<SRCK>(m), mt), amax_out + cur);
 }
 
+// The scale that a sample's amax gives holds for the whole tensor.  amax: the maximum over a part that contains the sample, or
+// over all of it: false for a part is false for the whole (a scale only falls as the amax grows, see scale_from_amax_value).
+__device__ __forceinline__ bool sample_holds(uint32_t sample, uint32_t amax, float target, float* scale) {
+  bool regular, regular_all;
+  *scale = scale_from_amax_value(__uint_as_float(sample), target, 1, &regular);
+  const float s = scale_from_amax_value(__uint_as_float(amax), target, 1, &regular_all);
+  return regular && (amax <= sample || (regular_all && s == *scale));
+}
+
 // Cast of the tiles [first, first + multi_tpw_encode()) below tile_end, each tensor with the scale d_scale2[2 * item]
-// (written earlier on the stream).  ACC: also accumulate the amax of every tensor's source into amax_acc[item]
-// (delayed scaling: the scales in use come from earlier iterations, the accumulators feed the next update).
+// (written earlier on the stream).
+// ACC_YES: also accumulate the amax of every tensor's source into amax_acc[item] (delayed scaling: the scales in use come
+// from earlier iterations, the accumulators feed the next update).
+// ACC_SAMPLED: d_scale2[2 * item] holds the amax pattern of the tensor's sample, the scale follows from it and `target`;
+// amax_acc[item] receives what is above the sample's amax.  A tensor whose sample is known not to hold (for the first
+// tensor of the workgroup: by amax_first, what amax_acc held a moment ago) is only read.
 // The encode tables must be staged (and a barrier passed) before.
-template <int IMPL, int SRCK, bool ACC>
+template <int IMPL, int SRCK, int ACC>
 __device__ __forceinline__ void multi_encode_tiles(const hif8_cast_item* __restrict__ items, uint32_t count,
                                                    uint64_t first, uint64_t tile_end, const float* __restrict__ d_scale2,
-                                                   uint32_t* __restrict__ amax_acc, const EncCtx& ctx) {
+                                                   uint32_t* __restrict__ amax_acc, const EncCtx& ctx, float target = 0.0f, uint32_t amax_first = 0u) {
   constexpr int VE = vec_elems<SRCK>();
   uint32_t m = 0, mt = 0, cur = 0xFFFFFFFFu;  // ACC: as in multi_amax_tiles
+  uint32_t sample = 0u;
+  float scale = 1.0f;
+  bool holds = true;
   for (uint32_t i = 0; i < multi_tpw_encode<IMPL, ACC>(); ++i) {
     const uint64_t tile = first + i;
     if (tile >= tile_end) break;
     const uint32_t it = multi_find_item(items, count, tile);
-    if (ACC && it != cur) {
+    if (ACC != ACC_NO && it != cur) {
       if (cur != 0xFFFFFFFFu) {
-        block_max_to_global(umax(fold_amax<SRCK>(m), mt), amax_acc + cur);
+        block_max_to_global(umax(fold_amax<SRCK>(m), mt), amax_acc + cur, sample);
         __syncthreads();
+        amax_first = 0u;
       }
       cur = it;
       m = 0;
       mt = 0;
+      if constexpr (ACC == ACC_SAMPLED) {
+        sample = __float_as_uint(d_scale2[2 * it]);
+        holds = sample_holds(sample, amax_first, target, &scale);
+      }
     }
     const uint64_t n = items[it].n;
     const uint64_t nvec = n >> vec_shift<SRCK>();
     const uint64_t local = tile - items[it].first_tile;
-    const float scale = d_scale2[2 * it];
+    if constexpr (ACC != ACC_SAMPLED) scale = d_scale2[2 * it];
     const uint4* __restrict__ src4 = reinterpret_cast<const uint4*>(items[it].src);
     uint8_t* __restrict__ dst = items[it].dst;
     const uint64_t v0 = local * kMultiTileVec + threadIdx.x;
@@ -832,13 +854,13 @@ __device__ __forceinline__ void multi_encode_tiles(const hif8_cast_item* __restr
       for (int j = 0; j < kMultiUnroll; ++j) {
         const uint64_t idx = v0 + (uint64_t)j * kMultiBlock;
         if (idx < nvec) v[j] = ld_stream(src4 + idx);
-        else if (ACC) v[j] = make_uint4(0u, 0u, 0u, 0u);
+        else if (ACC != ACC_NO) v[j] = make_uint4(0u, 0u, 0u, 0u);
       }
 #pragma unroll
       for (int j = 0; j < kMultiUnroll; ++j) {
         const uint64_t idx = v0 + (uint64_t)j * kMultiBlock;
-        if (ACC) m = vec_amax<SRCK>(m, v[j]);
-        if (idx < nvec) {
+        if (ACC != ACC_NO) m = vec_amax<SRCK>(m, v[j]);
+        if (idx < nvec && holds) {
           if constexpr (SRCK == kSrcF32)
             st_stream(reinterpret_cast<uint32_t*>(dst) + idx, encode4_f32<IMPL>(v[j], scale, ctx, idx * VE));
           else
@@ -850,12 +872,12 @@ __device__ __forceinline__ void multi_encode_tiles(const hif8_cast_item* __restr
       const uint64_t t = nvec * VE + threadIdx.x;
       if (t < n) {
         const uint32_t xb = load_bits<SRCK>(items[it].src, t);
-        if (ACC) mt = umax(mt, xb & 0x7FFFFFFFu);
-        dst[t] = (uint8_t)encode_one<IMPL, SRCK>(scaled_bits(xb, scale), keyed<IMPL>(ctx, t), t);
+        if (ACC != ACC_NO) mt = umax(mt, xb & 0x7FFFFFFFu);
+        if (holds) dst[t] = (uint8_t)encode_one<IMPL, SRCK>(scaled_bits(xb, scale), keyed<IMPL>(ctx, t), t);
       }
     }
   }
-  if (ACC && cur != 0xFFFFFFFFu) block_max_to_global(umax(fold_amax<SRCK>(m), mt), amax_acc + cur);
+  if (ACC != ACC_NO && cur != 0xFFFFFFFFu) block_max_to_global(umax(fold_amax<SRCK>(m), mt), amax_acc + cur, sample);
 }
 
 template <int SRCK>
@@ -865,19 +887,171 @@ k_multi_amax(const hif8_cast_item* __restrict__ items, uint32_t count, uint64_t 
   multi_amax_tiles<SRCK, true, kMultiTpwAmax>(items, count, (uint64_t)blockIdx.x * kMultiTpwAmax, total_tiles, amax_out);
 }
 
-template <int IMPL, int SRCK, bool ACC>
+template <int IMPL, int SRCK, int ACC>
 __global__ void __launch_bounds__(kMultiBlock)
 k_multi_encode(const hif8_cast_item* __restrict__ items, uint32_t count, uint64_t total_tiles,
                const float* __restrict__ d_scale2, uint32_t* __restrict__ amax_acc, uint32_t mode, uint64_t seed,
-               const uint8_t* __restrict__ g_lut) {
+               const uint8_t* __restrict__ g_lut, float target) {
   __shared__ __attribute__((aligned(16))) uint8_t lut[lut_bytes<IMPL>()];
   __shared__ HrLds<uses_exp_table<IMPL>()> hrt;
+  __shared__ uint32_t amax_first;
+  const uint64_t first = (uint64_t)blockIdx.x * multi_tpw_encode<IMPL, ACC>();
   const EncCtx ctx = make_ctx<IMPL>(lut, hrt.w, mode, seed);
+  if constexpr (ACC == ACC_SAMPLED) {
+    // one lane asks: requests for one address are served one after the other
+    if (threadIdx.x == 0) amax_first = __hip_atomic_load(amax_acc + multi_find_item(items, count, first), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   stage_enc_lut<IMPL, SRCK>(lut, g_lut, mode);
   stage_exp_table<IMPL, SRCK>(hrt.w, mode);
   __syncthreads();
-  multi_encode_tiles<IMPL, SRCK, ACC>(items, count, (uint64_t)blockIdx.x * multi_tpw_encode<IMPL, ACC>(), total_tiles, d_scale2,
-                                      amax_acc, ctx);
+  multi_encode_tiles<IMPL, SRCK, ACC>(items, count, first, total_tiles, d_scale2, amax_acc, ctx, target, ACC == ACC_SAMPLED ? amax_first : 0u);
+}
+
+// Multi-tensor cast with power-of-two scales in one pass and a sixteenth.  A power of two changes with the amax only where
+// that crosses a power of two, so the amax of a sample gives the scale of most tensors: the cast goes ahead with it while
+// it gathers the amax of all it reads (k_multi_encode<.., ACC_SAMPLED>), and a tensor whose scale turns out to be another is cast a
+// second time (k_multi_recast).  The order of the launches is all the synchronisation there is.  Between them
+//   d_scale2[2 i]   holds the pattern of the sample's amax, from the sample on until k_multi_finish writes the pairs
+//   amax[i]         the amax of what the cast read, where that is above the sample's: without this floor all the workgroups that start
+//                   on a tensor together would queue up at one address (10 ns each, 100 us for 0.94 G values)
+// A cast that knows its sample not to hold leaves its share to the second one, so that a wrong sample costs less when it
+// is found out early.  Bound by memory: 0.94 G bfloat16 values in 29 tensors 722 us in two passes, 487 so (sample 20, cast 450, the rest
+// launches); 12 tensors of 16 Mi, us, two passes 170, every sample right 126, all wrong by a boundary just above it 192, by one
+// value that it misses 229, all zeros 177 (153).
+constexpr uint32_t kSampleEvery = 16;  // of so many pieces one is read
+constexpr uint32_t kSampleTiles = 4;   // tiles of a piece
+constexpr uint32_t kSamplePeriod = kSampleEvery * kSampleTiles;  // a tensor of fewer tiles is read whole
+// Workgroup b < piece_wgs reads the sampled pieces [b * pieces, (b + 1) * pieces) of the list, one after the other, so that few
+// tensors and few atomics fall to each; the workgroups behind them take the `split`-th part of a tensor each, if it is small.
+template <int SRCK>
+__global__ void __launch_bounds__(kMultiBlock)
+k_multi_sample(const hif8_cast_item* __restrict__ items, uint32_t count, uint64_t total_tiles, uint32_t piece_wgs, uint32_t pieces,
+               uint32_t split, uint32_t* __restrict__ sample) {
+  constexpr int kLoads = kSampleTiles * kMultiUnroll;
+  uint32_t m = 0;
+  auto read = [&](uint32_t it, uint64_t local) {  // kSampleTiles tiles
+    const uint64_t nvec = items[it].n >> vec_shift<SRCK>(), v0 = local * kMultiTileVec + threadIdx.x;
+    if (nvec == 0) return;
+    const uint4* __restrict__ src4 = reinterpret_cast<const uint4*>(items[it].src);
+    uint4 v[kLoads];
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const uint64_t idx = v0 + (uint64_t)j * kMultiBlock;
+      v[j] = ld_stream(src4 + (idx < nvec ? idx : nvec - 1));  // past the tensor's end: its last vector again
+    }
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) m = vec_amax<SRCK>(m, v[j]);
+  };
+  if (blockIdx.x >= piece_wgs) {
+    const uint32_t share = (blockIdx.x - piece_wgs) % split;
+    for (uint32_t it = (blockIdx.x - piece_wgs) / split; it < count; it += (gridDim.x - piece_wgs) / split) {
+      const uint64_t n = items[it].n;
+      const uint32_t tiles = (uint32_t)(multi_item_tiles<SRCK>(n) < kSamplePeriod ? multi_item_tiles<SRCK>(n) : kSamplePeriod);
+      if (tiles == kSamplePeriod || tiles <= share * kSampleTiles) continue;
+      m = 0;
+      for (uint32_t local = share * kSampleTiles; local < tiles; local += split * kSampleTiles) read(it, local);
+      const uint64_t t = (n >> vec_shift<SRCK>()) * vec_elems<SRCK>() + threadIdx.x;
+      const uint32_t tail = t < n ? load_bits<SRCK>(items[it].src, t) & 0x7FFFFFFFu : 0u;
+      block_max_to_global(umax(fold_amax<SRCK>(m), tail), sample + 2 * it);
+      __syncthreads();
+    }
+    return;
+  }
+  uint32_t cur = 0xFFFFFFFFu;
+  for (uint32_t i = 0; i < pieces; ++i) {
+    // of every kSampleEvery pieces not always the same one: rows of a power of two of pieces are met at every column
+    const uint64_t p = (uint64_t)blockIdx.x * pieces + i, tile = (p * kSampleEvery + (p * 7u) % kSampleEvery) * kSampleTiles;
+    if (tile >= total_tiles) break;
+    const uint32_t it = cur != 0xFFFFFFFFu && tile - items[cur].first_tile < multi_item_tiles<SRCK>(items[cur].n) ? cur : multi_find_item(items, count, tile);
+    if (multi_item_tiles<SRCK>(items[it].n) < kSamplePeriod) continue;
+    if (it != cur) {
+      if (cur != 0xFFFFFFFFu) {
+        block_max_to_global(fold_amax<SRCK>(m), sample + 2 * cur);
+        __syncthreads();
+      }
+      cur = it;
+      m = 0;
+    }
+    read(it, tile - items[it].first_tile);
+  }
+  if (cur != 0xFFFFFFFFu) block_max_to_global(fold_amax<SRCK>(m), sample + 2 * cur);
+}
+
+template <int IMPL, int SRCK>
+__global__ void __launch_bounds__(kMultiBlock)
+k_multi_recast(const hif8_cast_item* __restrict__ items, uint32_t count, const uint32_t* __restrict__ amax, const uint32_t* __restrict__ sample,
+               float target, uint32_t mode, uint64_t seed, const uint8_t* __restrict__ g_lut) {
+  __shared__ __attribute__((aligned(16))) uint8_t lut[lut_bytes<IMPL>()];
+  __shared__ HrLds<uses_exp_table<IMPL>()> hrt;
+  __shared__ uint32_t todo[kMultiBlock / 32];  // a bit for each of kMultiBlock tensors
+  constexpr int VE = vec_elems<SRCK>();
+  const EncCtx ctx = make_ctx<IMPL>(lut, hrt.w, mode, seed);
+  bool staged = false;
+  for (uint32_t base = 0; base < count; base += kMultiBlock) {
+    const uint32_t mine = base + threadIdx.x;
+    bool again = false;
+    if (mine < count && items[mine].n != 0) {
+      float unused;
+      again = !sample_holds(sample[2 * mine], umax(amax[mine], sample[2 * mine]), target, &unused);
+    }
+    if (!__syncthreads_or(again)) continue;
+    const uint64_t bits = __ballot(again);
+    if ((threadIdx.x & 31u) == 0u) todo[threadIdx.x >> 5] = (uint32_t)(bits >> (threadIdx.x & 32u));
+    if (!staged) {
+      stage_enc_lut<IMPL, SRCK>(lut, g_lut, mode);
+      stage_exp_table<IMPL, SRCK>(hrt.w, mode);
+      staged = true;
+    }
+    __syncthreads();
+    for (uint32_t k = 0; k < kMultiBlock / 32; ++k) {
+      for (uint32_t left = todo[k]; left != 0u; left &= left - 1u) {
+        const uint32_t at = base + k * 32u + (uint32_t)__ffs((int)left) - 1u;
+        const hif8_cast_item item = items[at];
+        const float scale = scale_from_amax_value(__uint_as_float(umax(amax[at], sample[2 * at])), target, 1);
+        const uint64_t nvec = item.n >> vec_shift<SRCK>(), tiles = multi_item_tiles<SRCK>(item.n);
+        const uint4* __restrict__ src4 = reinterpret_cast<const uint4*>(item.src);
+        // the tiles of the whole list go round the workgroups, so that small tensors are spread over them as well
+        const uint32_t skew = (uint32_t)(item.first_tile % gridDim.x);
+        for (uint64_t tile = blockIdx.x >= skew ? blockIdx.x - skew : blockIdx.x + gridDim.x - skew; tile < tiles; tile += gridDim.x) {
+          const uint64_t v0 = tile * kMultiTileVec + threadIdx.x;
+          uint4 v[kMultiUnroll];
+#pragma unroll
+          for (int j = 0; j < kMultiUnroll; ++j) {
+            const uint64_t idx = v0 + (uint64_t)j * kMultiBlock;
+            if (idx < nvec) v[j] = ld_stream(src4 + idx);
+          }
+#pragma unroll
+          for (int j = 0; j < kMultiUnroll; ++j) {
+            const uint64_t idx = v0 + (uint64_t)j * kMultiBlock;
+            if (idx < nvec) {
+              if constexpr (SRCK == kSrcF32)
+                st_stream(reinterpret_cast<uint32_t*>(item.dst) + idx, encode4_f32<IMPL>(v[j], scale, ctx, idx * VE));
+              else
+                st_stream(reinterpret_cast<uint2*>(item.dst) + idx, encode8_16<IMPL, SRCK>(v[j], scale, ctx, idx * VE));
+            }
+          }
+          const uint64_t t = nvec * VE + threadIdx.x;
+          if (tile + 1 == tiles && t < item.n)
+            item.dst[t] = (uint8_t)encode_one<IMPL, SRCK>(scaled_bits(load_bits<SRCK>(item.src, t), scale), keyed<IMPL>(ctx, t), t);
+        }
+      }
+    }
+    __syncthreads();  // todo is written again
+  }
+}
+
+static __global__ void k_multi_clear(uint32_t* amax, uint32_t* pairs, uint32_t count) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < count) amax[i] = 0u;
+  if (i < 2u * count) pairs[i] = 0u;
+}
+static __global__ void k_multi_finish(uint32_t* amax, float* pairs, uint32_t count, float target) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= count) return;
+  amax[i] = umax(amax[i], __float_as_uint(pairs[2 * i]));
+  const float s = scale_from_amax_value(__uint_as_float(amax[i]), target, 1);
+  pairs[2 * i] = s;
+  pairs[2 * i + 1] = 1.0f / s;
 }
 
 // One stage of the group-wise multi-tensor cast: am_wgs workgroups gather the amax of the tensors am[] of one
@@ -1319,17 +1493,46 @@ inline void dispatch_multi_impl(uint32_t mode, F&& go) {
   }
 }
 
-template <int SRCK, bool ACC>
+template <int SRCK, int ACC>
 void launch_multi_encode(const hif8_cast_item* d_items, uint32_t cnt, uint64_t total_tiles, const float* d_scale2,
-                         uint32_t* amax_acc, uint32_t mode, uint64_t seed, const DevTables& tb, hipStream_t st) {
+                         uint32_t* amax_acc, uint32_t mode, uint64_t seed, const DevTables& tb, hipStream_t st, float target = 0.0f) {
   const dim3 blk(kMultiBlock);
   dispatch_multi_impl<SRCK>(mode, [&](auto impl_c) {
     constexpr int IMPL = decltype(impl_c)::value;
     constexpr uint32_t tpw = multi_tpw_encode<IMPL, ACC>();
     const dim3 g2((unsigned)((total_tiles + tpw - 1) / tpw));
     hipLaunchKernelGGL((k_multi_encode<IMPL, SRCK, ACC>), g2, blk, 0, st, d_items, cnt, total_tiles, d_scale2, amax_acc, mode,
+                       seed, enc_table_for<IMPL>(tb), target);
+  });
+}
+
+// Lists that are cast by sample (k_multi_sample) where the scales are powers of two: five launches, whatever the count, against a
+// launch for each group (at least two) or four with two passes over everything.  From 48 MiB of source with the host's copy of the
+// items at hand, 24 MiB without, or 64 tensors on (us, groups / four launches / sample, bfloat16: 16 of 1 Mi values 34 / 35 / 33,
+// 32 of them 50 / 53 / 43, 2 of 16 Mi 41 / 45 / 36, 8 of 16 Mi 122 / 138 / 92; 64 of 64 Ki 27 / 28 / 28, 128 of them 47 / 31 / 30; 4 of 1 Mi
+// 18 / 25 / 26; 0.94 G values in 29 tensors 722 / 800 / 489).
+constexpr uint64_t kSampledTilesHost = 3072, kSampledTiles = 1536;
+constexpr size_t kSampledCount = 64;
+
+// Multi-tensor cast with power-of-two scales from a sample: see k_multi_sample.
+template <int SRCK>
+hif8_status multi_cast_sampled(const hif8_cast_item* d_items, uint32_t count, uint64_t total_tiles, uint32_t* am, float* d_scale2, float target,
+                               uint32_t mode, uint64_t seed, int cus, const DevTables& tb, hipStream_t st) {
+  uint32_t* const sample = reinterpret_cast<uint32_t*>(d_scale2);
+  hipLaunchKernelGGL(k_multi_clear, dim3((2 * count + 255) / 256), dim3(256), 0, st, am, sample, count);
+  const uint64_t all = (total_tiles - 1) / kSamplePeriod + 1, pieces = (all + cus - 1) / cus;
+  const uint32_t piece_wgs = (uint32_t)((all + pieces - 1) / pieces), split = total_tiles > 8u * (uint64_t)count ? 4u : 1u,
+                 item_wgs = (count < 2048u ? count : 2048u) * split;
+  hipLaunchKernelGGL(k_multi_sample<SRCK>, dim3(piece_wgs + item_wgs), dim3(kMultiBlock), 0, st, d_items, count, total_tiles, piece_wgs,
+                     (uint32_t)pieces, split, sample);
+  launch_multi_encode<SRCK, ACC_SAMPLED>(d_items, count, total_tiles, d_scale2, am, mode, seed, tb, st, target);
+  dispatch_multi_impl<SRCK>(mode, [&](auto impl_c) {
+    constexpr int IMPL = decltype(impl_c)::value;
+    hipLaunchKernelGGL((k_multi_recast<IMPL, SRCK>), dim3((unsigned)cus * 4u), dim3(kMultiBlock), 0, st, d_items, count, am, sample, target, mode,
                        seed, enc_table_for<IMPL>(tb));
   });
+  hipLaunchKernelGGL(k_multi_finish, dim3((count + 255) / 256), dim3(256), 0, st, am, d_scale2, count, target);
+  return finish_launch();
 }
 
 // Multi-tensor cast with the scales already on the device (delayed scaling): one launch.
@@ -1345,12 +1548,13 @@ hif8_status conv_multi_encode_ds(const hif8_cast_item* d_items, size_t count, ui
   if (s != HIF8_OK) return s;
   if (total_tiles == 0) return HIF8_OK;
   uint32_t* acc = reinterpret_cast<uint32_t*>(d_amax_acc);
-  if (acc) launch_multi_encode<SRCK, true>(d_items, (uint32_t)count, total_tiles, d_scale2, acc, mode, sr_seed(), tb, st);
-  else launch_multi_encode<SRCK, false>(d_items, (uint32_t)count, total_tiles, d_scale2, nullptr, mode, sr_seed(), tb, st);
+  if (acc) launch_multi_encode<SRCK, ACC_YES>(d_items, (uint32_t)count, total_tiles, d_scale2, acc, mode, sr_seed(), tb, st);
+  else launch_multi_encode<SRCK, ACC_NO>(d_items, (uint32_t)count, total_tiles, d_scale2, nullptr, mode, sr_seed(), tb, st);
   return finish_launch();
 }
 
-// Multi-tensor cast with fresh per-tensor scales.  With the planned items also at hand on the host the list is cut
+// Multi-tensor cast with fresh per-tensor scales: by sample (multi_cast_sampled) where that applies, else in two passes.
+// Two passes, with the planned items also at hand on the host: the list is cut
 // into groups of whole tensors of at most `group_bytes` of source each (a larger tensor is a group of its own), and
 // the stages [amax of group g+1 | cast of group g] are enqueued back to back, one launch each: the cast of a group
 // then finds its source in the 256 MB last-level cache instead of reading it from HBM a second time.  Without the
@@ -1379,6 +1583,8 @@ hif8_status conv_multi_cast(const hif8_cast_item* host_items_or_null, const hif8
   const uint64_t seed = sr_seed();
   const uint32_t cnt = (uint32_t)count;
   uint32_t* am = reinterpret_cast<uint32_t*>(d_amax);
+  if (pow2 && (total_tiles >= (host_items_or_null ? kSampledTilesHost : kSampledTiles) || (count >= kSampledCount && total_tiles != 0)))
+    return multi_cast_sampled<SRCK>(d_items, cnt, total_tiles, am, d_scale2, target, mode, seed, cus, tb, st);
   s = launch_fill_u32(am, 0u, cnt, st);
   if (s != HIF8_OK) return s;
   if (!host_items_or_null) {
@@ -1388,7 +1594,7 @@ hif8_status conv_multi_cast(const hif8_cast_item* host_items_or_null, const hif8
     }
     s = launch_scale_from_amax(d_amax, d_scale2, cnt, target, pow2, st);
     if (s != HIF8_OK) return s;
-    if (total_tiles != 0) launch_multi_encode<SRCK, false>(d_items, cnt, total_tiles, d_scale2, nullptr, mode, seed, tb, st);
+    if (total_tiles != 0) launch_multi_encode<SRCK, ACC_NO>(d_items, cnt, total_tiles, d_scale2, nullptr, mode, seed, tb, st);
     return finish_launch();
   }
   // tensors without elements own no tile, hence no workgroup that would write their pair: with every amax

@@ -457,13 +457,17 @@ __device__ __forceinline__ uint32_t trunc_table_pattern(uint32_t i) {
 // Per-tensor scale from an amax (Sec. 5): fl32(target / amax), with pow2 the largest power of two not
 // above it; amax zero, Inf or NaN, or a quotient that is not finite and positive, gives 1.
 // The division must be the correctly rounded one (the library is compiled that way).
-__device__ __forceinline__ float scale_from_amax_value(float amax, float target, int pow2) {
+// *regular: amax and the quotient are finite and positive, so that the scale is the rule's and not the 1 of the
+// degenerate cases; over regular values it never grows with amax, and above a regular value come regular ones, then none.
+__device__ __forceinline__ float scale_from_amax_value(float amax, float target, int pow2, bool* regular = nullptr) {
   union { uint32_t u; float f; } a, q, s;
   a.f = amax;
   s.f = 1.0f;
+  bool ok = false;
   if (a.u != 0u && a.u < 0x7F800000u) {  // positive, finite, non-zero
     q.f = target / amax;
     if (q.u != 0u && q.u < 0x7F800000u) {
+      ok = true;
       s.f = q.f;
       if (pow2) {
         if ((q.u >> 23) != 0u) s.u = q.u & 0x7F800000u;
@@ -471,6 +475,7 @@ __device__ __forceinline__ float scale_from_amax_value(float amax, float target,
       }
     }
   }
+  if (regular) *regular = ok;
   return s.f;
 }
 

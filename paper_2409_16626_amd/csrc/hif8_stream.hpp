@@ -121,11 +121,12 @@ __device__ __forceinline__ uint32_t block_max_thread0(uint32_t m) {
 // amax of its input took 57.6 us against 32.7 us without; 33.4 us with the check).  The accumulator only
 // grows, so a stale read can only cause an atomic that was not needed, never skip one that was.
 // CHECK = false (few workgroups per address, e.g. one row chunk each): the atomic whenever the maximum is not zero.
+// A maximum not above `floor` (what the caller knows to be counted elsewhere) is left out without a look at *out.
 // Every lane of the workgroup must call it (it contains a barrier).
 template <bool CHECK = true>
-__device__ __forceinline__ void block_max_to_global(uint32_t m, uint32_t* out) {
+__device__ __forceinline__ void block_max_to_global(uint32_t m, uint32_t* out, uint32_t floor = 0u) {
   const uint32_t r = block_max_thread0(m);
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == 0 && (floor == 0u || r > floor)) {
     if (CHECK ? r > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : r != 0u) atomicMax(out, r);
   }
 }

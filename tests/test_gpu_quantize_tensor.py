@@ -291,3 +291,59 @@ def test_one_launch_of_zeros_nan_and_inf(h, value):
     h.hif8_encode_bf16_ds(x, wc, n, s0, h.RM_TA)
     h.hif8_quantize_tensor_bf16(x, None, c, n, a1, s1, ws, h.MAX_FINITE, 1, h.RM_TA)
     assert torch.equal(a0.view(torch.int32), a1.view(torch.int32)) and torch.equal(s0, s1) and torch.equal(c, wc)
+
+
+@pytest.mark.parametrize("kind", ["bf16", "f32", "f16"])
+@pytest.mark.parametrize("mode", [TA, HR | SAT, SR])
+def test_multi_cast_by_sample_equals_the_oracle_whatever_the_sample_misses(h, kind, mode):
+    """Power-of-two scales over 64 tensors and more: the scale of a tensor comes from a sample first.  Tensors around the size
+    from which only a part is read, with the largest value in the ragged tail, outside the sample, on a power of two, Inf, NaN
+    or so small that the scale is 1, all zeros, empty; garbage in the outputs; the host's copy of the items given or not."""
+    _, amx, enc, _ = KINDS[kind]
+    rng = np.random.default_rng(91)
+    tile = 4096 if kind == "f32" else 8192
+    big = [63 * tile, 64 * tile - 1, 64 * tile, 64 * tile + 5, 130 * tile + 3]
+    hows = ["plain", "tail", "inside", "power", "inf", "nan", "tiny", "zeros"]
+    jobs = [(n, how) for n in big for how in hows] + [(n, how) for n in (0, 1, 7, 9, tile + 1) for how in ("plain", "zeros", "nan", "tail", "power")]
+    offs, total = [], 0
+    for n, _ in jobs:
+        offs.append(total)
+        total += (n + 15) // 16 * 16
+    xs = np.zeros(total, np.float32)
+    for (n, how), o in zip(jobs, offs):
+        v = (rng.standard_normal(n) * 0.02).astype(np.float32)
+        if n:
+            if how == "tail":
+                v[-1] = -3.0
+            if how == "inside":
+                v[int(rng.integers(n // 3, n // 2))] = 5.0
+            if how == "power":
+                v[n // 2] = 0.125
+            if how in ("inf", "nan"):
+                v[n // 2] = -np.inf if how == "inf" else np.nan
+            if how == "tiny":
+                v = np.where(v > 0, np.float32(1e-39 if kind != "f16" else 6e-8), np.float32(0)).astype(np.float32)
+            if how == "zeros":
+                v[:] = 0
+        xs[o:o + n] = v
+    x = torch.from_numpy(xs).to(dev()).to(KINDS[kind][0])
+    codes = torch.zeros(total, dtype=torch.uint8, device=dev())
+    items = [(x[o:o + n], codes[o:o + n], n) if n else (0, 0, 0) for (n, _), o in zip(jobs, offs)]
+    plan = h.hif8_multi_plan(items, src_is_16bit=kind != "f32")
+    assert plan.count >= 64
+    xn = host_view(x)
+    for host in (plan.host_items, None):
+        am = torch.full((plan.count,), 9e9, dtype=torch.float32, device=dev())
+        sc = torch.full((plan.count, 2), -1.0, dtype=torch.float32, device=dev())
+        codes.fill_(0x55)
+        getattr(h, "hif8_multi_cast_" + kind)(plan.d_items, plan.count, plan.total_tiles, am, sc, 32768.0, 1, mode, host_items=host)
+        torch.cuda.synchronize()
+        cg, amg, scg = codes.cpu().numpy(), am.cpu().numpy(), sc.cpu().numpy()
+        for i, ((n, how), o) in enumerate(zip(jobs, offs)):
+            part = xn[o:o + n]
+            w_am = np.float32(amx(part))
+            w_s = orc.scale_from_amax(w_am, 32768.0, True)
+            assert amg[i] == w_am or (np.isnan(w_am) and np.isnan(amg[i])), (i, n, how, amg[i], w_am)
+            assert scg[i, 0] == w_s and scg[i, 1] == np.float32(1.0) / w_s, (i, n, how)
+            assert_same_bytes(cg[o:o + n], enc(part, w_s, mode), "item %d (n=%d, %s, %s)" % (i, n, how, kind))
+            assert (cg[o + n:o + (n + 15) // 16 * 16] == 0x55).all()
