@@ -9,8 +9,8 @@
 //   GEMM:    O[M, N] = (A[M, ld] x B[N, ld]^T) * descale
 //
 // Kernel design (gfx950): a workgroup of 2 x 2 wavefronts owns a (32 TA) x (32 TB) tile of O, each wavefront TA x TB blocks
-// of v_mfma_f32_16x16x32_bf16.  K advances in steps of 64 through two LDS stages.  Tiles go from global memory straight
-// into LDS (buffer_load_dwordx4 ... lds: 64 lanes x 16 bytes land contiguously), so the operands never pass
+// of v_mfma_f32_16x16x32_bf16.  K advances in steps of 64 through LDS: 128 x 128 tiles in two or four stages, larger tiles in a
+// ring of five operand slots.  Tiles go from global memory straight into LDS (buffer_load_dwordx4 ... lds: 64 lanes x 16 bytes land contiguously), so the operands never pass
 // through registers.  A tile row is 128 bytes = 8 chunks of 16 bytes; chunk position p of tile row r
 // holds k-chunk p ^ ((r >> 1) & 7).  LDS has 64 banks of 4 bytes and serves a 16-byte read 16 lanes
 // at a time: the 16 lanes of a fragment read touch 16 consecutive rows of one k-chunk, which the
@@ -44,38 +44,45 @@ constexpr int kWaitVm0 = 0x0F70;          // vmcnt(0)
 constexpr int wait_vm(int n) { return (n & 15) | (n >> 4) << 14; }
 constexpr int kRsrcFlags = 0x00020000;    // word 3 of a raw (unstructured, untyped) buffer descriptor on gfx9-family parts
 
-// The K loop of a 256 x 256 tile is bound by what makes a wavefront (alone on its SIMD) keep the matrix cores waiting, above all
-// the barrier of each K step (70 % of the cycles busy), and by the clock that the power limit leaves them:
+// The K loop of a 256 x 256 tile is bound by what keeps a wavefront, alone on its SIMD, from issuing MFMAs (78 % of the cycles
+// busy, counters), and by the clock that the power limit leaves them:
 //   * v_mfma_f32_16x16x32_bf16 costs less power than the 32 x 32 x 16 shape on operands with HiF8's few mantissa bits
 //     (in registers only 1.97 PFLOP/s against 1.80), and with 16 cycles each there is a place for a memory instruction
 //     every 16 cycles.
-//   * One fragment read behind each of the first TA + TB MFMAs of a half step; a tile load behind every kLoadEvery-th
-//     MFMA of the half behind the barrier.  A compute unit's address path needs 16 cycles for each of them, times four
-//     wavefronts, which is what one load per four MFMAs leaves it: one per two stalls the issue of the MFMAs, and a load
-//     that waits for the next half step arrives too late for its barrier (8192^3: 667 us; one load per two MFMAs 684, half
-//     of the loads in the next half step 767).
 //   * MFMAs in inline assembly with the accumulator as one operand: built from the intrinsic, the loop moved 16 of the
-//     256 accumulator registers to and fro in every step and waited for MFMAs to do so (710 us).
-// Measured (us; with 32 x 32 x 16 MFMAs, all loads behind the last 16 of a K step / now): 8192^3 727 / 667, 4096^3 97 / 84,
-// 2048 x 4096 x 11008 in 128 x 128 tiles 140 / 131; the scale search of a 2048 x 4096 x 4096 layer 5820 / 4860.
+//     256 accumulator registers to and fro in every step and waited for MFMAs to do so (8192^3: 710 us, then 667).
+//   * A wavefront that issues a tile load while the compute unit's address path or the L2 is behind stands still, and its MFMAs with it.
+//     So the loads are spread over the whole K step: a ring of five slots, one operand's rows of a K step each (RING), has room for
+//     the A rows of the step after next before the barrier that frees the slots of the current one, and its B rows follow behind
+//     the barrier.  With two whole stages all loads had to go out in the half step behind the barrier, at the full rate of
+//     the L2, and the last ones had 1024 cycles left to arrive (waits: 5.6e7 -> 2.9e7; loop alone, all loads from the L2: 607 us).
+//   * Fragment reads at every third MFMA, tile loads at every sixth: four wavefronts that read at every MFMA fill the LDS for 256
+//     cycles (all reads behind the first MFMAs of a half step 645 us, so 642).  Four loads share an LDS base, by immediate offsets.
+// Measured (us, two stages / ring, walking): 8192^3 671 / 642, 4096^3 86.6 / 85.1, 2048 x 11008 x 4096 128.5 / 122.9, 8192 x 11008 x 4096
+// 520 / 472, 11008 x 4096 x 2048 132.7 / 133.1; the scale search of a 2048 x 4096 x 4096 layer 4550 / 4467.  Streaming stores instead of
+// plain ones: 8192^3 621, but 8192 x 8192 x 1024 103 -> 109.
 //
-// WALK: a workgroup takes tiles blockIdx.x, + gridDim.x, ... (as many workgroups as compute units) and requests the first
+// WALK (ring): a workgroup takes tiles blockIdx.x, + gridDim.x, ... (as many workgroups as compute units) and requests the first
 // K step of the next tile before the epilogue of the current one, so that neither the launch of a workgroup nor its first
-// round trip to memory stands between two tiles.  For the squared error only: the stores of the other epilogues would
-// still be counted by the waits of the next tile's loads.
+// round trip to memory stands between two tiles.  Loads and stores are counted together and in order: the next tile waits until only
+// the stores of the epilogue, issued behind its loads, are in flight.
 //
-// ST: LDS stages.  With two, a K step lasts at least as long as its loads take to arrive, which two workgroups on a compute
-// unit hide from each other and the MFMAs of a large tile outlast; a 128 x 128 tile with the compute unit to itself
-// waited for them half of the time (768 x 4096 x 4096: 39 us) and takes four (27 us).
-template <int TA, int TB, int EPI, bool WALK, int ST>
+// ST: LDS stages of a 128 x 128 tile.  With two, a K step lasts at least as long as its loads take to arrive, which two workgroups on a
+// compute unit hide from each other; a tile with the compute unit to itself waited for them half of the time (768 x 4096 x 4096: 39
+// us) and takes four (27 us).  ST == 0: the ring.
+constexpr uint32_t kSlotBytes = 32768, kRingBytes = 5 * kSlotBytes;  // 256 rows of 128 bytes; all of a compute unit's 160 KiB
+template <int TA, int TB, int EPI, int ST>
 __global__ void __launch_bounds__(256, TA * TB <= 16 && ST == 2 ? 2 : 1)
 k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* __restrict__ out,
          const float* __restrict__ ref, double* __restrict__ err, uint32_t M, uint32_t N, uint32_t ld,
          float descale, uint32_t tiles_n, uint32_t tiles, uint32_t col_begin, Batch batch) {
   constexpr int kWaves = 4, BM = 32 * TA, BN = 32 * TB;
   constexpr int NL = TA + TB;  // tile loads per wavefront and K step (8 rows each)
-  constexpr int kStageBytes = (BM + BN) * kRowBytes;
-  extern __shared__ __attribute__((aligned(128))) uint8_t smem[];  // [ST][BM + BN][128 bytes]
+  constexpr bool RING = ST == 0;
+  // where the B rows of a K step lie behind its A rows, and all that one K step takes
+  constexpr uint32_t kBOffset = RING ? kSlotBytes : BM * kRowBytes, kStageBytes = RING ? 2 * kSlotBytes : (BM + BN) * kRowBytes;
+  static_assert(BM * kRowBytes <= (int)kSlotBytes || !RING, "an operand's rows fit a slot");
+  extern __shared__ __attribute__((aligned(128))) uint8_t smem[];  // [ST][BM + BN][128 bytes], or five slots
 
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: LDS destinations of the loads stay in SGPRs
@@ -123,52 +130,77 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
   for (int i = 0; i < TA; ++i) off_a[i] = lane_offset((wave * TA + i) * kRowsPerLoad + lr);
 #pragma unroll
   for (int i = 0; i < TB; ++i) off_b[i] = lane_offset((wave * TB + i) * kRowsPerLoad + lr);
-  // load i of the K step at byte offset k; stage: byte offset of an LDS stage
-  auto load = [&](uint32_t stage, int i, uint32_t k) {
-    if (i < TA)
+  // the slot n slots further on in the ring
+  auto slot_after = [](uint32_t slot, uint32_t n) {
+    slot += n * kSlotBytes;
+    return slot >= kRingBytes ? slot - kRingBytes : slot;
+  };
+  // load i of the K step at byte offset k: A rows at byte offset `at_a` of the LDS, B rows at `at_b`.  An immediate offset counts for
+  // both addresses, so runs of four loads share an LDS base (M0); a lane's offset in memory is at least 1024 bytes for
+  // each load before its own (8 rows of 64 elements or more), so the difference never is negative.
+  auto load = [&](uint32_t at_a, uint32_t at_b, int i, uint32_t k) {
+    const bool is_a = i < TA;
+    const int o = is_a ? i : i - TA;
+    auto with_offset = [&](auto imm_c) {
+      constexpr int imm = decltype(imm_c)::value;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          res_a, (__attribute__((address_space(3))) void*)(smem + stage + (wave * TA + i) * kRowsPerLoad * kRowBytes), 16, (int)off_a[i],
-          (int)k, 0, 0);
-    else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          res_b, (__attribute__((address_space(3))) void*)(smem + stage + BM * kRowBytes + (wave * TB + i - TA) * kRowsPerLoad * kRowBytes),
-          16, (int)off_b[i - TA], (int)k, 0, 0);
+          is_a ? res_a : res_b,
+          (__attribute__((address_space(3))) void*)(smem + (is_a ? at_a : at_b) + (wave * (is_a ? TA : TB) + (o & ~3)) * kRowsPerLoad * kRowBytes), 16,
+          (int)((is_a ? off_a[is_a ? o : 0] : off_b[is_a ? 0 : o]) - imm), (int)k, imm, 0);
+    };
+    switch (o & 3) {
+      case 0: with_offset(std::integral_constant<int, 0>{}); break;
+      case 1: with_offset(std::integral_constant<int, 1024>{}); break;
+      case 2: with_offset(std::integral_constant<int, 2048>{}); break;
+      default: with_offset(std::integral_constant<int, 3072>{}); break;
+    }
   };
   auto load_all = [&](uint32_t stage, uint32_t k) {
 #pragma unroll
-    for (int i = 0; i < NL; ++i) load(stage, i, k);
+    for (int i = 0; i < NL; ++i) load(stage, stage + kBOffset, i, k);
   };
 
   // MFMA operand of lane l: row l % 16 of the block, k elements 8 * (l / 16) .. + 7 of the half step
   const uint32_t frow = lane & 15u, swz = (frow >> 1) & 7u;  // block offsets are multiples of 16 rows: the permutation depends on frow only
-  uint32_t fbase[2];  // LDS address of the lane's first A fragment of each half step; the others are constant offsets from it
+  uint32_t fa_base[2], fb_base[2];  // of each half step: LDS address of the lane's first A and B fragment in its operand's rows
 #pragma unroll
-  for (int s = 0; s < 2; ++s) fbase[s] = (wm * (16u * TA) + frow) * kRowBytes + ((((uint32_t)(s * 4) + (lane >> 4)) ^ swz) * 16u);
-  const uint32_t b_delta = BM * kRowBytes + (wn * (16u * TB)) * kRowBytes - (wm * (16u * TA)) * kRowBytes;  // scalar
+  for (int s = 0; s < 2; ++s) {
+    const uint32_t chunk = (((uint32_t)(s * 4) + (lane >> 4)) ^ swz) * 16u;
+    fa_base[s] = (wm * (16u * TA) + frow) * kRowBytes + chunk;
+    fb_base[s] = (wn * (16u * TB) + frow) * kRowBytes + chunk;
+  }
   f32x4 acc[TA][TB];
   bf16x8 fa[2][TA], fb[2][TB];
   auto read = [&](int buf, uint32_t stage, int s, int r) {
-    const uint8_t* base = smem + stage + fbase[s];
-    if (r < TA) fa[buf][r] = *reinterpret_cast<const bf16x8*>(base + r * 16 * kRowBytes);
-    else fb[buf][r - TA] = *reinterpret_cast<const bf16x8*>(base + b_delta + (r - TA) * 16 * kRowBytes);
+    if (r < TA) fa[buf][r] = *reinterpret_cast<const bf16x8*>(smem + stage + fa_base[s] + r * 16 * kRowBytes);
+    else fb[buf][r - TA] = *reinterpret_cast<const bf16x8*>(smem + (RING ? slot_after(stage, 1) : stage + kBOffset) + fb_base[s] + (r - TA) * 16 * kRowBytes);
   };
 
-  // One K step on stage `cur`; LOADS: the K step ST further on, at byte offset k, follows into the same stage.  The scheduling
-  // barriers keep every instruction where it is written.  The last step of a tile reads fragments that nothing uses.
+  // One K step on stage `cur`; LOADS: another K step, at byte offset k, is requested: the one after next into the slots of the
+  // previous step's B rows (before the barrier) and this one's A rows (behind it), or the one ST further on into the same
+  // stage.  The scheduling barriers keep every instruction where it is written.  The last step of a tile reads fragments that nothing uses.
   const uint32_t nk = ld / kBK;  // >= 1
-  static_assert((ST == 2 || (ST * kStageBytes & (ST * kStageBytes - 1)) == 0) && (ST - 1) * NL < 64, "stages wrap by a mask, loads in flight are counted in 6 bits");
-  auto next_stage = [](uint32_t cur) { return ST == 2 ? cur ^ kStageBytes : (cur + kStageBytes) & (ST * kStageBytes - 1u); };
+  static_assert(RING || ST == 2 || (ST * kStageBytes & (ST * kStageBytes - 1)) == 0, "stages wrap by a mask");
+  static_assert(RING || (ST - 1) * NL < 64, "loads in flight are counted in 6 bits");
+  auto next_stage = [&](uint32_t cur) {
+    if constexpr (RING) return slot_after(cur, 2);
+    else return ST == 2 ? cur ^ kStageBytes : (cur + kStageBytes) & (ST * kStageBytes - 1u);
+  };
   auto k_step = [&](auto loads_c, uint32_t cur, uint32_t k) {
     constexpr bool LOADS = decltype(loads_c)::value;
-    constexpr int NM = TA * TB, kLoadEvery = NM / NL;
+    constexpr int NM = TA * TB;
+    constexpr int kReadEvery = RING ? NM / NL < 3 ? 2 : 3 : 1;                               // with the last 16 MFMAs left free
+    constexpr int kLoadEvery = RING ? NM / TA < 6 ? NM / TA : 6 : NM / NL, kLoadAt = RING ? 1 : 0;
+    static_assert(kReadEvery * (NL - 1) < NM && kLoadEvery * ((RING ? TA : NL) - 1) + kLoadAt < NM, "every read and load has its MFMA");
+    const uint32_t ahead = RING ? slot_after(cur, 4) : cur;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       __builtin_amdgcn_sched_barrier(0);
       if (s == 1) {
         // the next K step has landed and the last fragments of this one are in registers; behind the barrier that holds
-        // for the whole workgroup, so stage `cur` may be overwritten
-        __builtin_amdgcn_s_waitcnt(kWaitVm0Lgkm0 + (LOADS ? wait_vm((ST - 2) * NL) : 0));
-        __syncthreads();
+        // for the whole workgroup, so the slots of stage `cur` may be overwritten
+        __builtin_amdgcn_s_waitcnt(kWaitVm0Lgkm0 + (LOADS ? wait_vm(RING ? TA : (ST - 2) * NL) : 0));
+        __builtin_amdgcn_s_barrier();
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -176,27 +208,37 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
         const int i = idx / TB, j = idx % TB;
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fb[s][j]), "v"(fa[s][i]));
         __builtin_amdgcn_sched_barrier(0);  // the MFMA first: the memory instructions issue while it runs
-        if (idx < NL) {  // first what the first MFMAs of the next half step use
-          const int r = idx == 0 ? 0 : idx <= TB ? TA + idx - 1 : idx - TB;
+        if (idx % kReadEvery == 0 && idx / kReadEvery < NL) {  // first what the first MFMAs of the next half step use
+          const int n = idx / kReadEvery, r = n == 0 ? 0 : n <= TB ? TA + n - 1 : n - TB;
           if (s == 0) read(1, cur, 1, r);
           else read(0, next_stage(cur), 0, r);
         }
-        if (LOADS && s == 1 && idx % kLoadEvery == 0 && idx / kLoadEvery < NL) load(cur, idx / kLoadEvery, k);
+        if (LOADS && idx % kLoadEvery == kLoadAt) {
+          const int n = idx / kLoadEvery;
+          if (RING && s == 0 && n < TA) load(ahead, 0, n, k);
+          if (RING && s == 1 && n < TB) load(0, cur, TA + n, k);
+          if (!RING && s == 1 && n < NL) load(cur, cur + kBOffset, n, k);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
 
   uint32_t at = blockIdx.x;
-  if (!take_tile(at)) return;  // the whole workgroup leaves; WALK: every later number of its die's share lies further on
+  if (!take_tile(at)) return;  // the whole workgroup leaves; RING: every later number of its die's share lies further on
   load_all(0, 0);
+  // vector memory instructions that are issued behind the first loads of a walk's next tile before they are waited for: the stores of
+  // a tile inside the matrix (an edge tile has fewer, and a score waits for all it issues)
+  constexpr int kStores = EPI == EPI_ERR ? 0 : 16 * TA * 16 * TB / (64 * (EPI == EPI_F32 ? 4 : 8));
+  bool stores_behind = false;
   for (;;) {
 #pragma unroll
     for (int i = 0; i < TA; ++i)
 #pragma unroll
       for (int j = 0; j < TB; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    if constexpr (ST == 2) {
-      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    if constexpr (RING || ST == 2) {
+      if (stores_behind) __builtin_amdgcn_s_waitcnt(kWaitVm0 + wait_vm(kStores < 63 ? kStores : 63));
+      else __builtin_amdgcn_s_waitcnt(kWaitVm0);
       __syncthreads();
       if (nk > 1) load_all(kStageBytes, kBK * 2);
     } else {
@@ -209,14 +251,15 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
     }
 #pragma unroll
     for (int r = 0; r < NL; ++r) read(0, 0, 0, r);
-    uint32_t cur = 0, k = ST * kBK * 2;
-    for (uint32_t kt = ST; kt < nk; ++kt) {
+    constexpr uint32_t kAhead = RING ? 2 : ST;  // K steps that are requested before the first is multiplied
+    uint32_t cur = 0, k = kAhead * kBK * 2;
+    for (uint32_t kt = kAhead; kt < nk; ++kt) {
       k_step(std::true_type{}, cur, k);
       cur = next_stage(cur);
       k += kBK * 2;
     }
 #pragma unroll
-    for (uint32_t t = ST - 1; t >= 1u; --t) {
+    for (uint32_t t = kAhead - 1; t >= 1u; --t) {
       if (nk > t) {
         k_step(std::false_type{}, cur, 0);
         cur = next_stage(cur);
@@ -231,21 +274,24 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
 #pragma unroll
       for (int j = 0; j < TB; j += 2) asm volatile("" : "+a"(acc[i][j]), "+a"(acc[i][j + 1]));
 
-    // the fragments of the last half step were in registers before the last barrier, so the tile LDS is free; WALK: stage 0
-    // receives the next tile's first K step meanwhile
+    // the fragments of the last half step were in registers before the last barrier, so the tile LDS is free; RING: the first two
+    // slots receive the next tile's first K step meanwhile
     constexpr int TM = TA / 2, TN = TB / 2, CB = TN < 4 ? 2 : 4;
     static_assert(TA % 2 == 0 && TB % 2 == 0, "whole 32 x 32 blocks");
     const uint32_t row0 = m0 + wm * TM * 32, col0 = n0 + wn * TN * 32;
     double* const e = tile_err;
     const float ds = tile_descale;
     bool more = false;
-    if constexpr (WALK) {
+    if constexpr (RING) {
       at += gridDim.x;
       more = at < tiles && take_tile(at);
       if (more) load_all(0, 0);
     }
-    epilogue<EPI, TM, TN, CB>(acc, out, ref, e, M, N, row0, col0, lane, ds, smem + (WALK ? kStageBytes : 0), wave, kWaves);
+    uint32_t out_lane = lane;
+    if constexpr (RING) asm volatile("" : "+v"(out_lane));  // its addresses are formed here, not kept in registers through the K loop
+    epilogue<EPI, TM, TN, CB>(acc, out, ref, e, M, N, row0, col0, out_lane, ds, smem + (RING ? kStageBytes : 0), wave, kWaves);
     if (!more) return;
+    stores_behind = row0 + TM * 32 <= M && col0 + TN * 32 <= N;
   }
 }
 
@@ -429,16 +475,16 @@ template <int TA, int TB, int EPI, int ST>
 static hif8_status launch_x(const uint16_t* A, const uint16_t* B, void* out, const float* ref, double* err, uint32_t M,
                             uint32_t N, uint32_t ld, float descale, hipStream_t st, int cus, const Batch& batch,
                             uint32_t col_begin, uint32_t col_end) {
-  constexpr bool WALK = EPI == EPI_ERR && TA == 8 && TB == 8;
   constexpr int BM = 32 * TA, BN = 32 * TB;
   constexpr size_t stage = (size_t)(BM + BN) * kRowBytes, epi = 4 * (size_t)epilogue_lds(TB < 8 ? 2 : 4);
-  constexpr size_t smem = stage + ((ST - 1) * stage > epi ? (ST - 1) * stage : epi);  // WALK: the epilogue runs behind stage 0
+  constexpr size_t smem = ST == 0 ? kRingBytes : ST * stage > epi ? ST * stage : epi;
+  static_assert(ST != 0 || 2 * kSlotBytes + epi <= kRingBytes, "the epilogue runs behind the first two slots");
   static bool attr_set[kMaxDevices] = {};
   int dev = 0;
   if (!hip_ok(hipGetDevice(&dev))) return HIF8_ERR_HIP;
   if (dev < 0 || dev >= kMaxDevices) return HIF8_ERR_ARG;
   if (!attr_set[dev]) {
-    if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_x<TA, TB, EPI, WALK, ST>),
+    if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_x<TA, TB, EPI, ST>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem)))
       return HIF8_ERR_HIP;
     attr_set[dev] = true;
@@ -448,11 +494,11 @@ static hif8_status launch_x(const uint16_t* A, const uint16_t* B, void* out, con
   if (total > most_tiles(TB == 8 ? TILE_256 : TB == 6 ? TILE_192 : TILE_128, EPI == EPI_ERR)) return HIF8_ERR_ARG;
   const uint32_t tiles = tile_order_grid((uint32_t)total);  // a whole number of workgroups per die
   uint32_t grid = tiles;
-  if (WALK) {
+  if (ST == 0) {
     const uint32_t resident = tile_order_grid((uint32_t)cus);
     if (grid > resident) grid = resident;
   }
-  hipLaunchKernelGGL((k_gemm_x<TA, TB, EPI, WALK, ST>), dim3(grid), dim3(256), smem, st, A, B, out, ref, err, M, N, ld, descale,
+  hipLaunchKernelGGL((k_gemm_x<TA, TB, EPI, ST>), dim3(grid), dim3(256), smem, st, A, B, out, ref, err, M, N, ld, descale,
                      tiles_n, tiles, col_begin, batch);
   return finish_launch();
 }
@@ -497,8 +543,8 @@ hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const
   for (int i = 0; i < count && s == HIF8_OK; ++i) {
     const TileLaunch& l = launches[i];
     auto run = [&](auto launch) { s = launch(A, B, out, ref, err, m, n, k, descale, st, cus, batch, l.begin, l.end); };
-    if (l.tile == TILE_256) run(launch_x<8, 8, EPI, 2>);
-    else if (l.tile == TILE_192) run(launch_x<8, 6, EPI, 2>);
+    if (l.tile == TILE_256) run(launch_x<8, 8, EPI, 0>);
+    else if (l.tile == TILE_192) run(launch_x<8, 6, EPI, 0>);
     else if (l.stages == 4) run(launch_x<4, 4, EPI, 4>);
     else run(launch_x<4, 4, EPI, 2>);
   }

@@ -89,6 +89,25 @@ def test_column_split_equals_one_launch(h, M, N, K):
     assert torch.all((got["f32"][:M * N].view(M, N)[rows].double() - want).abs() <= K * 2.0 ** -23 * sums)
 
 
+# more tiles of 256 columns or 192 than compute units: workgroups that walk over several, inside the matrix and at its edges, rows
+# that are not 16-byte aligned, K steps 1 to 5 (the first loads of a tile go out before the stores of the one before it)
+@pytest.mark.parametrize("variant", [10, 11])
+@pytest.mark.parametrize("M,N,K", [(4100, 5001, 64), (4100, 5001, 128), (4352, 4608, 192), (4100, 5001, 250), (8200, 4096, 320)])
+def test_walk_over_tiles_equals_small_tiles(h, variant, M, N, K):
+    rng = np.random.default_rng(variant + K)
+    (a, ld), (b, _) = (expand(h, random_codes(rng, (r, K), "cast_normal")) for r in (M, N))
+    for name, d in (("f32", torch.float32), ("bf16", torch.bfloat16), ("f16", torch.float16)):
+        got = []
+        for v in (9, variant):
+            o = torch.full((M * N + 8,), 7.0, dtype=d, device=dev())
+            h.hif8_gemm_set_variant(v)
+            getattr(h, "hif8_gemm_expanded_" + name)(a, b, o, M, N, K, ld, 4.0, 2.0)
+            h.hif8_gemm_set_variant(0)
+            assert torch.all(o[M * N:] == 7.0)
+            got.append(o)
+        assert torch.equal(got[0], got[1]), name
+
+
 # codes in 256 x 256 and 128 x 128 tiles, expanded operands in 128 x 128, 256 x 256 and 256 x 192, both in small tiles; whole runs
 # of a row and shorter ones.  Sums of small integers are exact, so a result is one binary32 product and one rounding to 16 bits.
 @pytest.mark.parametrize("operands,variant", [("codes", 5), ("codes", 6), ("codes", 12), ("expanded", 9), ("expanded", 10), ("expanded", 11),
