@@ -96,6 +96,16 @@ inline int tile_launches(int plan, const TileProblem& p, size_t cus, uint32_t sp
   return 2;
 }
 
+// 128 x 128 tiles, two to a compute unit, run as 256 x 128 tiles, one to a compute unit with three LDS stages, where K is long: three
+// quarters of the tile loads, but an epilogue that nothing hides (us, 128 x 128 / 256 x 128: 2048 x 4096 x 1024 18.2 / 18.9, 1500 x 5000 x
+// 2048 27.1 / 28.2, 1000 x 7000 x 3000 36.0 / 36.1, 2048 x 4096 x 4096 51.1 / 50.5, x 11008 135.7 / 123.8; as the remaining columns of 8192 x
+// 11008 x 4096 500 / 486), and where that takes no more rounds (M of 128 more than a multiple of 256).
+inline bool paired_tiles(const TileProblem& p, const TileLaunch& l, size_t cus) {
+  if (l.tile != TILE_128 || l.stages != 2 || p.K < 4096) return false;
+  const uint64_t cols = (l.end - l.begin + 127) / 128 * p.pairs, ones = (p.M + 127) / 128 * cols, twos = (p.M + 255) / 256 * cols;
+  return (twos + cus - 1) / cus <= (ones + 2 * cus - 1) / (2 * cus);
+}
+
 // Most tiles of a launch: its threads, 256 for each workgroup, are counted in 32 bits, and its workgroups are dealt out in
 // whole rounds of the dies (kXcds).  The squared error in 256 x 256 tiles walks over tiles with one workgroup per compute unit,
 // so that there only the tile number is limited.

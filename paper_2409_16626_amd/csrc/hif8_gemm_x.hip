@@ -9,8 +9,8 @@
 //   GEMM:    O[M, N] = (A[M, ld] x B[N, ld]^T) * descale
 //
 // Kernel design (gfx950): a workgroup of 2 x 2 wavefronts owns a (32 TA) x (32 TB) tile of O, each wavefront TA x TB blocks
-// of v_mfma_f32_16x16x32_bf16.  K advances in steps of 64 through LDS: 128 x 128 tiles in two or four stages, larger tiles in a
-// ring of five operand slots.  Tiles go from global memory straight into LDS (buffer_load_dwordx4 ... lds: 64 lanes x 16 bytes land contiguously), so the operands never pass
+// of v_mfma_f32_16x16x32_bf16.  K advances in steps of 64 through LDS: 128 x 128 tiles in two or four stages, 256 x 128 in three, larger
+// tiles in a ring of five operand slots.  Tiles go from global memory straight into LDS (buffer_load_dwordx4 ... lds: 64 lanes x 16 bytes land contiguously), so the operands never pass
 // through registers.  A tile row is 128 bytes = 8 chunks of 16 bytes; chunk position p of tile row r
 // holds k-chunk p ^ ((r >> 1) & 7).  LDS has 64 banks of 4 bytes and serves a 16-byte read 16 lanes
 // at a time: the 16 lanes of a fragment read touch 16 consecutive rows of one k-chunk, which the
@@ -67,9 +67,10 @@ constexpr int kRsrcFlags = 0x00020000;    // word 3 of a raw (unstructured, unty
 // round trip to memory stands between two tiles.  Loads and stores are counted together and in order: the next tile waits until only
 // the stores of the epilogue, issued behind its loads, are in flight.
 //
-// ST: LDS stages of a 128 x 128 tile.  With two, a K step lasts at least as long as its loads take to arrive, which two workgroups on a
+// ST: LDS stages of a smaller tile.  256 x 128 tiles have three, 144 KiB, and spread their loads as the ring does.  128 x 128: with two, a K step lasts at least as long as its loads take to arrive, which two workgroups on a
 // compute unit hide from each other; a tile with the compute unit to itself waited for them half of the time (768 x 4096 x 4096: 39
-// us) and takes four (27 us).  ST == 0: the ring.
+// us) and takes four (27 us); the ring, in half the size, was no faster there (2048 x 4096 x 11008, two workgroups: 0.78 us a K step in
+// either form, 0.68 in 256 x 128 tiles).  ST == 0: the ring.
 constexpr uint32_t kSlotBytes = 32768, kRingBytes = 5 * kSlotBytes;  // 256 rows of 128 bytes; all of a compute unit's 160 KiB
 template <int TA, int TB, int EPI, int ST>
 __global__ void __launch_bounds__(256, TA * TB <= 16 && ST == 2 ? 2 : 1)
@@ -178,28 +179,31 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
 
   // One K step on stage `cur`; LOADS: another K step, at byte offset k, is requested: the one after next into the slots of the
   // previous step's B rows (before the barrier) and this one's A rows (behind it), or the one ST further on into the same
-  // stage.  The scheduling barriers keep every instruction where it is written.  The last step of a tile reads fragments that nothing uses.
+  // stage.  With three stages k is the step after next, too, whose B rows go out before the barrier, and behind it (LOADS_ALL) the A
+  // rows of the one after that.  The scheduling barriers keep every instruction where it is written.  The last step of a tile reads fragments that nothing uses.
   const uint32_t nk = ld / kBK;  // >= 1
-  static_assert(RING || ST == 2 || (ST * kStageBytes & (ST * kStageBytes - 1)) == 0, "stages wrap by a mask");
+  static_assert(RING || ST == 2 || ST == 3 || (ST * kStageBytes & (ST * kStageBytes - 1)) == 0, "stages wrap by a mask");
   static_assert(RING || (ST - 1) * NL < 64, "loads in flight are counted in 6 bits");
   auto next_stage = [&](uint32_t cur) {
     if constexpr (RING) return slot_after(cur, 2);
+    else if constexpr (ST == 3) return cur == 2 * kStageBytes ? 0u : cur + kStageBytes;
     else return ST == 2 ? cur ^ kStageBytes : (cur + kStageBytes) & (ST * kStageBytes - 1u);
   };
+  enum : int { LOADS_NO = 0, LOADS_BEFORE = 1, LOADS_ALL = 2 };
   auto k_step = [&](auto loads_c, uint32_t cur, uint32_t k) {
-    constexpr bool LOADS = decltype(loads_c)::value;
-    constexpr int NM = TA * TB;
-    constexpr int kReadEvery = RING ? NM / NL < 3 ? 2 : 3 : 1;                               // with the last 16 MFMAs left free
-    constexpr int kLoadEvery = RING ? NM / TA < 6 ? NM / TA : 6 : NM / NL, kLoadAt = RING ? 1 : 0;
-    static_assert(kReadEvery * (NL - 1) < NM && kLoadEvery * ((RING ? TA : NL) - 1) + kLoadAt < NM, "every read and load has its MFMA");
-    const uint32_t ahead = RING ? slot_after(cur, 4) : cur;
+    constexpr int LOADS = decltype(loads_c)::value, NM = TA * TB;
+    constexpr bool SPREAD = RING || ST == 3;                                    // loads in both half steps
+    constexpr int kReadEvery = SPREAD ? NM / NL < 3 ? 2 : 3 : 1;                // with the last MFMAs left free
+    constexpr int kLoadEvery = SPREAD ? NM / TA < 6 ? NM / TA : 6 : NM / NL, kLoadAt = SPREAD ? 1 : 0;
+    static_assert(kReadEvery * (NL - 1) < NM && kLoadEvery * ((SPREAD ? TA : NL) - 1) + kLoadAt < NM, "every read and load has its MFMA");
+    const uint32_t ahead = RING ? slot_after(cur, 4) : ST == 3 ? next_stage(next_stage(cur)) + kBOffset : cur;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       __builtin_amdgcn_sched_barrier(0);
       if (s == 1) {
         // the next K step has landed and the last fragments of this one are in registers; behind the barrier that holds
         // for the whole workgroup, so the slots of stage `cur` may be overwritten
-        __builtin_amdgcn_s_waitcnt(kWaitVm0Lgkm0 + (LOADS ? wait_vm(RING ? TA : (ST - 2) * NL) : 0));
+        __builtin_amdgcn_s_waitcnt(kWaitVm0Lgkm0 + (LOADS != LOADS_NO ? wait_vm(RING ? TA : (ST - 2) * NL) : 0));
         __builtin_amdgcn_s_barrier();
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -213,11 +217,13 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
           if (s == 0) read(1, cur, 1, r);
           else read(0, next_stage(cur), 0, r);
         }
-        if (LOADS && idx % kLoadEvery == kLoadAt) {
+        if (LOADS != LOADS_NO && idx % kLoadEvery == kLoadAt) {
           const int n = idx / kLoadEvery;
           if (RING && s == 0 && n < TA) load(ahead, 0, n, k);
           if (RING && s == 1 && n < TB) load(0, cur, TA + n, k);
-          if (!RING && s == 1 && n < NL) load(cur, cur + kBOffset, n, k);
+          if (ST == 3 && s == 0 && n < TB) load(0, ahead, TA + n, k);
+          if (ST == 3 && s == 1 && n < TA && LOADS == LOADS_ALL) load(cur, 0, n, k + kBK * 2);
+          if (!SPREAD && s == 1 && n < NL) load(cur, cur + kBOffset, n, k);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -241,6 +247,16 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
       else __builtin_amdgcn_s_waitcnt(kWaitVm0);
       __syncthreads();
       if (nk > 1) load_all(kStageBytes, kBK * 2);
+    } else if constexpr (ST == 3) {
+      if (nk > 1) load_all(kStageBytes, kBK * 2);
+      if (nk > 2) {
+#pragma unroll
+        for (int i = 0; i < TA; ++i) load(2 * kStageBytes, 0, i, 2 * kBK * 2);
+        __builtin_amdgcn_s_waitcnt(kWaitVm0 + wait_vm(NL + TA));
+      } else {
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+      }
+      __syncthreads();
     } else {
 #pragma unroll
       for (uint32_t t = 1; t < (uint32_t)ST; ++t)
@@ -252,20 +268,21 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
 #pragma unroll
     for (int r = 0; r < NL; ++r) read(0, 0, 0, r);
     constexpr uint32_t kAhead = RING ? 2 : ST;  // K steps that are requested before the first is multiplied
-    uint32_t cur = 0, k = kAhead * kBK * 2;
+    uint32_t cur = 0, k = (ST == 3 ? 2 : kAhead) * kBK * 2;
     for (uint32_t kt = kAhead; kt < nk; ++kt) {
-      k_step(std::true_type{}, cur, k);
+      k_step(std::integral_constant<int, LOADS_ALL>{}, cur, k);
       cur = next_stage(cur);
       k += kBK * 2;
     }
 #pragma unroll
     for (uint32_t t = kAhead - 1; t >= 1u; --t) {
       if (nk > t) {
-        k_step(std::false_type{}, cur, 0);
+        if (ST == 3 && t == 2u) k_step(std::integral_constant<int, LOADS_BEFORE>{}, cur, k);
+        else k_step(std::integral_constant<int, LOADS_NO>{}, cur, 0);
         cur = next_stage(cur);
       }
     }
-    k_step(std::false_type{}, cur, 0);
+    k_step(std::integral_constant<int, LOADS_NO>{}, cur, 0);
     // the compiler does not know the assembly for MFMAs: wait states before their results are read, and a use of every
     // accumulator behind them
     asm volatile("s_nop 15\n\ts_nop 15");
@@ -491,7 +508,7 @@ static hif8_status launch_x(const uint16_t* A, const uint16_t* B, void* out, con
   }
   const uint32_t tiles_m = (M + BM - 1) / BM, tiles_n = (col_end - col_begin + BN - 1) / BN;
   const uint64_t total = (uint64_t)tiles_m * tiles_n * (batch.na ? batch.na * batch.nb : 1u);
-  if (total > most_tiles(TB == 8 ? TILE_256 : TB == 6 ? TILE_192 : TILE_128, EPI == EPI_ERR)) return HIF8_ERR_ARG;
+  if (total > most_tiles(TB == 8 ? TILE_256 : TB == 6 ? TILE_192 : TILE_128, EPI == EPI_ERR)) return HIF8_ERR_ARG;  // 256 x 128: half as many as 128 x 128
   const uint32_t tiles = tile_order_grid((uint32_t)total);  // a whole number of workgroups per die
   uint32_t grid = tiles;
   if (ST == 0) {
@@ -546,6 +563,7 @@ hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const
     if (l.tile == TILE_256) run(launch_x<8, 8, EPI, 0>);
     else if (l.tile == TILE_192) run(launch_x<8, 6, EPI, 0>);
     else if (l.stages == 4) run(launch_x<4, 4, EPI, 4>);
+    else if (paired_tiles(problem, l, (size_t)cus)) run(launch_x<8, 4, EPI, 3>);
     else run(launch_x<4, 4, EPI, 2>);
   }
   return s;

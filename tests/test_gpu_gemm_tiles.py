@@ -108,6 +108,30 @@ def test_walk_over_tiles_equals_small_tiles(h, variant, M, N, K):
         assert torch.equal(got[0], got[1]), name
 
 
+# 128 x 128 tiles in pairs (256 x 128) from K = 4096 on, more than a round and part of one, edge tiles and whole ones: the same bits as in
+# 256 x 256 tiles, and a score of them
+@pytest.mark.parametrize("M,N,K", [(2048, 2304, 4096), (2100, 2301, 4100), (4400, 4203, 4096)])
+def test_paired_tiles_equal_large_tiles(h, M, N, K):
+    rng = np.random.default_rng(M)
+    (a, ld), (b, _) = (expand(h, random_codes(rng, (r, K), "cast_normal")) for r in (M, N))
+    got = {}
+    for v in (9, 10):
+        h.hif8_gemm_set_variant(v)
+        for name, d in (("f32", torch.float32), ("bf16", torch.bfloat16), ("f16", torch.float16)):
+            o = torch.full((M * N + 8,), 7.0, dtype=d, device=dev())
+            getattr(h, "hif8_gemm_expanded_" + name)(a, b, o, M, N, K, ld, 4.0, 2.0)
+            assert torch.all(o[M * N:] == 7.0)
+            assert v == 9 or torch.equal(got[name], o), name
+            got[name] = o
+        out = got["f32"][:M * N]
+        ref = (out * 1.01 + 0.5).contiguous()
+        err = torch.zeros(1, dtype=torch.float64, device=dev())
+        h.hif8_gemm_expanded_sqerr(a, b, ref, M, N, K, ld, 4.0, 2.0, err)
+        h.hif8_gemm_set_variant(0)
+        want = float(((out.double() - ref.double()) ** 2).sum())
+        assert abs(err.item() - want) <= 1e-12 * want
+
+
 # codes in 256 x 256 and 128 x 128 tiles, expanded operands in 128 x 128, 256 x 256 and 256 x 192, both in small tiles; whole runs
 # of a row and shorter ones.  Sums of small integers are exact, so a result is one binary32 product and one rounding to 16 bits.
 @pytest.mark.parametrize("operands,variant", [("codes", 5), ("codes", 6), ("codes", 12), ("expanded", 9), ("expanded", 10), ("expanded", 11),
