@@ -221,20 +221,23 @@ inline SmallPlan small_plan(size_t M, size_t N, size_t K, bool codes, bool sqerr
 
 // Workgroup -> tile of the expanded-operand kernel.  The hardware deals consecutive workgroups round-robin over the
 // kXcds accelerator dies (XCDs), each with its own L2.  Workgroup b therefore takes tile number
-// (b % kXcds) * per_xcd + b / kXcds of a tile order that walks groups of kGroupM tile rows column by column: the
-// workgroups resident on one die at a time then cover a compact kGroupM x (a few) block of tiles and share their
-// operand panels in that die's L2, whatever tiles_n is.  The launch has tile_order_grid() workgroups; returns false
+// (b % kXcds) * per_xcd + b / kXcds of a tile order that walks groups of `group` tile rows column by column: the
+// workgroups resident on one die at a time then cover a compact group x (a few) block of tiles and share their
+// operand panels in that die's L2, whatever tiles_n is.  Of the large tiles a die holds 32: 4 x 8 of them take 2560 operand rows
+// (256 x 192) or 2048 (256 x 128), 8 x 4 2816 and 2560, and a row of the first operand is asked for by fewer dies at a time (2048 x 4096 x
+// 11008 from cold memory 159 us with groups of 8, 155 with 4).  The launch has tile_order_grid() workgroups; returns false
 // for the few at the end of the last die's share that have no tile.
 constexpr uint32_t kXcds = 8;    // accelerator dies, each with an L2 of its own
-constexpr uint32_t kGroupM = 8;  // tile rows per group of the tile order
+constexpr uint32_t kGroupM = 8, kGroupLarge = 4;  // tile rows per group of the tile order; of large tiles
 __host__ __device__ inline uint32_t tile_order_grid(uint32_t n_tiles) { return (n_tiles + kXcds - 1u) / kXcds * kXcds; }
-__host__ __device__ inline bool tile_order(uint32_t b, uint32_t tiles_m, uint32_t tiles_n, uint32_t* tile_m, uint32_t* tile_n) {
+__host__ __device__ inline bool tile_order(uint32_t b, uint32_t tiles_m, uint32_t tiles_n, uint32_t* tile_m, uint32_t* tile_n,
+                                           uint32_t group = kGroupM) {
   const uint32_t n_tiles = tiles_m * tiles_n, per_xcd = (n_tiles + kXcds - 1u) / kXcds;
   const uint32_t t = (b % kXcds) * per_xcd + b / kXcds;
   if (t >= n_tiles) return false;
-  const uint32_t grp = t / (kGroupM * tiles_n), first_m = grp * kGroupM;
-  const uint32_t grp_rows = tiles_m - first_m < kGroupM ? tiles_m - first_m : kGroupM;
-  const uint32_t in_grp = t - grp * (kGroupM * tiles_n);
+  const uint32_t grp = t / (group * tiles_n), first_m = grp * group;
+  const uint32_t grp_rows = tiles_m - first_m < group ? tiles_m - first_m : group;
+  const uint32_t in_grp = t - grp * (group * tiles_n);
   *tile_n = in_grp / grp_rows;
   *tile_m = first_m + (in_grp - *tile_n * grp_rows);
   return true;

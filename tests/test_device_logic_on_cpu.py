@@ -273,6 +273,19 @@ def test_small_gemm_route(dev, operands, out):
     assert f(32, 1 << 30, 1 << 20, operands == "codes", out == "sqerr") == 1 and f(7, 9, 0, operands == "codes", out == "sqerr") == 1
 
 
+@pytest.mark.parametrize("tm,tn", [(1, 1), (3, 5), (4, 8), (5, 1), (8, 32), (13, 7), (43, 16), (8, 58), (64, 3)])
+def test_gemm_tile_order_of_large_tiles(dev, tm, tn):
+    """Every tile once, and the 32 workgroups that run together on a die within 4 tile rows of a group (two groups where one ends)."""
+    dev.devfn_tile_order_large.restype, dev.devfn_tile_order_large.argtypes = ctypes.c_uint32, [ctypes.c_uint32] * 3
+    grid = (tm * tn + 7) // 8 * 8
+    got = [dev.devfn_tile_order_large(b, tm, tn) for b in range(grid)]
+    assert sorted(t for t in got if t != 0xFFFFFFFF) == list(range(tm * tn))
+    for die in range(8):
+        mine = [t for t in got[die::8] if t != 0xFFFFFFFF]
+        for at in range(0, len(mine) - 31, 32):
+            assert len({t // tn // 4 for t in mine[at:at + 32]}) <= (1 if tn * 4 % 32 == 0 and len(mine) % 32 == 0 else 1 + 32 // tn + 1)
+
+
 # sum of rounds of a launch by the kernel it starts (tile, LDS stages): the measured times behind the rule, relative to each other
 # from K = 1024 on, below it in tenths of a us by output (0: 16-bit, 1: binary32, 2: squared error) and K
 def launch_price(tile, stages, tiles, cus, K, kind, pairs, edges):
