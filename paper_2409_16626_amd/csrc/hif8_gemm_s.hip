@@ -18,7 +18,7 @@
 // are busy a quarter of the time, and the chain of loads, stages and the sum counts.  (8 x 11008 x 4096: 45 MB, 7.5 us at
 // the memory's rate); the tiled kernel took 85 us.  Measured against the tiled kernels (us per call, codes / expanded
 // operands): 8 x 4096 x 4096 7.9 / 9.3 (80 / 55), 64 x 4096 x 4096 14.2 / 14.9 (84 / 55), 256 x 4096 x 4096 33 / 23
-// (85 / 55), 512 x 4096 x 11008 150 / 80 (231 / 143); odd K, 509 x 1003 x 2049: 18.6 (3810 with one output per lane).
+// (85 / 55), 512 x 4096 x 11008 150 / 80 (231 / 143); odd K, 509 x 1003 x 2049: 15.5 (3810 with one output per lane).
 //
 // The element order of a K share is the same for both operand kinds, so that one product gives the same bits whether
 // its operands come as codes or expanded.
@@ -43,7 +43,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Operand kinds
 enum : int { OP_CODES = 0, OP_BF16 = 1 };
 
-constexpr uint32_t kUnitK = (uint32_t)kShareK;  // K elements of the smallest share of a wavefront
+// K is shared out in units of 64 elements, one pass of fragments.  In units of 128, a stage of codes, 509 x 1003 x 2049 with eight
+// wavefronts gave one of them three stages and the others two (64 x 2048 x 129 7.3 us, now 6.3; with all loads of a row's end in flight 4.7;
+// 509 x 1003 x 2049 17.9, 15.5; 1200 x 1200 x 3000 44, 36; 8 x 11008 x 4096 as before).
+constexpr uint32_t kUnitK = 64;
 
 // 16 bytes from any address
 __device__ __forceinline__ u32x4 load16(const uint8_t* p) {
@@ -52,20 +55,26 @@ __device__ __forceinline__ u32x4 load16(const uint8_t* p) {
   return v;
 }
 
-// The 16 codes at k .. k + 15 of a row of K codes, zero codes past its end; reads inside the row only.
-__device__ __forceinline__ u32x4 load16_tail(const uint8_t* row, uint32_t k, uint32_t K) {
-  u32x4 v = {0u, 0u, 0u, 0u};
-  if (k >= K) return v;
-  const uint32_t rem = K - k;
-  if (rem >= 16u) return load16(row + k);
-  if (K >= 16u) {  // the last 16 codes of the row, moved down
-    unsigned __int128 x;
-    __builtin_memcpy(&x, row + (K - 16u), 16);
-    x >>= 8u * (16u - rem);
-    __builtin_memcpy(&v, &x, 16);
-    return v;
+// The last bytes of a row: v holds the 16 bytes that end with the row, `past` of them before the ones asked for; those move down and zero
+// codes follow.
+__device__ __forceinline__ u32x4 drop_bytes(u32x4 v, uint32_t past) {
+  const uint32_t words = past >> 2;
+  u32x4 w;
+#pragma unroll
+  for (uint32_t i = 0; i < 4u; ++i) {
+    w[i] = 0u;
+#pragma unroll
+    for (uint32_t j = i; j < 4u; ++j) w[i] = j - i == words ? v[j] : w[i];
   }
-  for (uint32_t j = 0; j < rem; ++j) v[j >> 2] |= (uint32_t)row[k + j] << (8u * (j & 3u));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_alignbyte(i < 3 ? w[i + 1] : 0u, w[i], past);
+  return v;
+}
+
+// 16 codes of a row with fewer than 16, from k on.
+__device__ __forceinline__ u32x4 load_short_row(const uint8_t* row, uint32_t k, uint32_t K) {
+  u32x4 v = {0u, 0u, 0u, 0u};
+  for (uint32_t j = k; j < K; ++j) v[(j - k) >> 2] |= (uint32_t)row[j] << (8u * ((j - k) & 3u));
   return v;
 }
 
@@ -99,14 +108,16 @@ __device__ __forceinline__ void expand16(const u32x4& c, bf16x8 (&f)[2]) {
 constexpr uint32_t kRowStage = 128;
 
 // K: codes per row (OP_CODES) or row pitch, a multiple of 64 (OP_BF16).  HALF: at most 8 rows of A (codes): the lanes
-// of the upper eight rows expand the second half of a fragment pair for the lower eight, half the look-ups for A.
+// of the upper eight rows expand the second half of a fragment pair for the lower eight, half the look-ups for A.  It is held to six
+// wavefronts on a SIMD, which its work fills at the sizes it is for: aiming at seven, the compiler waits for look-ups one pair
+// after the other to save registers (4 x 4096 x 4096 7.1 us, 7.7 so; 5 x 7001 x 1999 7.6, 7.85).
 template <int OP, int TM, int TN, int HALF, int EPI>
-__global__ void __launch_bounds__(TM * TN <= 4 ? 1024 : 512)
+__global__ void __launch_bounds__(TM * TN <= 4 ? 1024 : 512) __attribute__((amdgpu_waves_per_eu(TM * TN <= 4 ? 4 : 2, HALF != 0 ? 6 : 8)))
 k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __restrict__ out,
          const float* __restrict__ ref, double* __restrict__ err, uint32_t M, uint32_t N, uint32_t K, float descale,
          uint32_t tiles_m, uint32_t tiles_n) {
   constexpr int kPitch = TN * 16 + 4;  // floats per row of the reduction buffer: the four lane groups start 16 banks apart
-  constexpr uint32_t kElem = OP == OP_CODES ? 1u : 2u, kBlocks = TM + TN, kPerUnit = OP == OP_CODES ? 1u : 2u;
+  constexpr uint32_t kElem = OP == OP_CODES ? 1u : 2u, kBlocks = TM + TN, kStageUnits = OP == OP_CODES ? 2u : 1u;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // [512] table, then one area per wavefront, reused by the reduction
   const uint32_t tid = threadIdx.x, lane = tid & 63u, threads = blockDim.x;
   const uint32_t waves = threads >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -119,11 +130,9 @@ k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __r
     if (threads < 256u)
       for (uint32_t c = tid + threads; c < 256u; c += threads) entry(c);
   }
-  // this wavefront's share of K, in units of 128 elements for both operand kinds, as stages of kRowStage bytes per row
-  const uint32_t row_bytes = K * kElem, units = (K + kUnitK - 1u) / kUnitK, stages = (row_bytes + kRowStage - 1u) / kRowStage;
-  uint32_t s0 = (uint32_t)((uint64_t)units * wave / waves) * kPerUnit, s1 = (uint32_t)((uint64_t)units * (wave + 1u) / waves) * kPerUnit;
-  if (s1 > stages) s1 = stages;
-  const uint32_t full = row_bytes / kRowStage;
+  // this wavefront's share of K: units [u0, u1), staged kStageUnits at a time, kRowStage bytes per row
+  const uint32_t row_bytes = K * kElem, units = (K + kUnitK - 1u) / kUnitK;
+  const uint32_t u0 = (uint32_t)((uint64_t)units * wave / waves), u1 = (uint32_t)((uint64_t)units * (wave + 1u) / waves);
   // staging: 8 lanes x 16 bytes per row, 8 rows per load; chunk c of row r sits at position c ^ ((r >> 1) & 7)
   const uint32_t lrow = lane >> 3, lchunk = lane & 7u;
   double e2 = 0.0;
@@ -149,21 +158,37 @@ k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __r
       for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
     u32x4 raw[kBlocks][2];
-    auto load_stage = [&](uint32_t s) {
-      const uint32_t at = s * kRowStage + lchunk * 16u;
-      if (s < full) {
+    bool tail = false;   // of the stage in `raw`: it reaches past the rows' end;
+    uint32_t past = 0u;  // bytes before the ones asked for
+    auto load_stage = [&](uint32_t u) {
+      const uint32_t first = u * (kUnitK * kElem), left = (u1 - u) * (kUnitK * kElem);
+      // of a stage of one unit of codes the lanes of the second half repeat the first: no other wavefront's codes
+      const uint32_t at = first + (left < kRowStage ? lchunk & 3u : lchunk) * 16u;
+      tail = first + (left < kRowStage ? left : kRowStage) > row_bytes;
+      if (!tail || row_bytes >= 16u) {
+        // past a row's end its last 16 bytes, put right on the way into LDS: all loads are in flight together (with a load and its shift
+        // behind a branch each, the last stage waited for one row after the other)
+        uint32_t from = at;
+        if (OP == OP_CODES && tail) from = at + 16u <= row_bytes ? at : row_bytes - 16u;
+        past = at - from;
 #pragma unroll
         for (int i = 0; i < (int)kBlocks; ++i)
 #pragma unroll
-          for (int h = 0; h < 2; ++h) raw[i][h] = load16(rows[i][h] + at);
+          for (int h = 0; h < 2; ++h) raw[i][h] = load16(rows[i][h] + from);
       } else {
 #pragma unroll
         for (int i = 0; i < (int)kBlocks; ++i)
 #pragma unroll
-          for (int h = 0; h < 2; ++h) raw[i][h] = load16_tail(rows[i][h], at, row_bytes);
+          for (int h = 0; h < 2; ++h) raw[i][h] = load_short_row(rows[i][h], at, row_bytes);
       }
     };
     auto stage_to_lds = [&]() {
+      if (OP == OP_CODES && tail && row_bytes >= 16u) {
+#pragma unroll
+        for (int i = 0; i < (int)kBlocks; ++i)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) raw[i][h] = drop_bytes(raw[i][h], past);
+      }
       // through the wavefront's own LDS: a wavefront's LDS operations run in order, so only the compiler needs fences
 #pragma unroll
       for (int i = 0; i < (int)kBlocks; ++i)
@@ -175,13 +200,14 @@ k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __r
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
     };
-    auto compute_stage = [&]() {
+    auto compute_stage = [&](uint32_t u) {
       auto frag = [&](int block, uint32_t chunk) {
         return *reinterpret_cast<const u32x4*>(area + (block * 16u + r16) * kRowStage + ((chunk ^ ((r16 >> 1) & 7u)) * 16u));
       };
-      // element order within a unit: 16 q + 0..7, 16 q + 8..15, then the same 64 further on
+      // element order within a unit: 16 q + 0..7, then 16 q + 8..15
 #pragma unroll
-      for (int p = 0; p < (OP == OP_CODES ? 2 : 1); ++p) {
+      for (uint32_t p = 0; p < kStageUnits; ++p) {
+        if (u + p >= u1) break;  // a stage of one unit
         bf16x8 fa[TM][2], fb[2];
         auto get = [&](int block, bf16x8 (&f)[2]) {
           if constexpr (OP == OP_CODES) {
@@ -218,12 +244,12 @@ k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __r
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
     };
-    if (s0 < s1) load_stage(s0);
+    if (u0 < u1) load_stage(u0);
     __syncthreads();  // table written; reduction buffer of the previous tile read
-    for (uint32_t s = s0; s < s1; ++s) {
+    for (uint32_t u = u0; u < u1; u += kStageUnits) {
       stage_to_lds();
-      if (s + 1 < s1) load_stage(s + 1);
-      compute_stage();
+      if (u + kStageUnits < u1) load_stage(u + kStageUnits);
+      compute_stage(u);
     }
     __syncthreads();  // staging areas free: the reduction uses the same LDS
 

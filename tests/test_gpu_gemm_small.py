@@ -41,6 +41,26 @@ def test_small_gemm_codes_match_oracle(h, M, N, K, off):
         assert torch.all(out[M] == 7.0)
 
 
+# shares of K in units of 64: one element to a unit and a bit, an odd number of units (a stage of one), rows whose last 16 bytes
+# begin in every position before the one asked for; codes and expanded operands give the same bits
+@pytest.mark.parametrize("M,N", [(5, 37), (14, 20), (20, 50), (40, 70), (100, 131)])
+def test_small_gemm_units_of_k(h, M, N):
+    rng = np.random.default_rng(M)
+    for K in (1, 7, 15, 16, 17, 31, 63, 64, 65, 77, 127, 128, 129, 190, 193, 200, 577, 641, 1027, 1088, 2049):
+        ca, cb = random_codes(rng, (M, K), "uniform_codes"), random_codes(rng, (N, K), "cast_normal")
+        a, b, ld = on_gpu(ca, K % 3), on_gpu(cb, K % 2), h.hif8_expanded_ld(K)
+        xa, xb = (torch.empty(r, ld, dtype=torch.bfloat16, device=dev()) for r in (M, N))
+        h.hif8_expand_bf16(a, M, K, xa, ld)
+        h.hif8_expand_bf16(b, N, K, xb, ld)
+        one, two = (torch.full((M + 1, N), 7.0, dtype=torch.float32, device=dev()) for _ in range(2))
+        h.hif8_gemm_set_variant(12)
+        h.hif8_gemm_f32(a, b, one, M, N, K, 8.0, 0.5)
+        h.hif8_gemm_expanded_f32(xa, xb, two, M, N, K, ld, 8.0, 0.5)
+        h.hif8_gemm_set_variant(0)
+        check(one[:M].cpu().numpy(), ca, cb, 8.0, 0.5)
+        assert torch.equal(one.view(torch.int32), two.view(torch.int32)) and torch.all(one[M] == 7.0), K
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 100, 100), (8, 4100, 300), (20, 70, 1001), (32, 9000, 65), (64, 2100, 272), (50, 9000, 257),
                                    (128, 700, 900), (129, 700, 900), (256, 4096, 130), (700, 40, 1111)])
 def test_small_gemm_same_bits_from_codes_workspace_and_expanded(h, M, N, K):
