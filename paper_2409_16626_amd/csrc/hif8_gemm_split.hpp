@@ -24,8 +24,8 @@ inline bool ragged_round_split(size_t M, size_t N, size_t cus, uint32_t* split) 
 // takes as long as its rounds of resident workgroups, so the tile with the shortest sum of rounds is taken.  A round
 // costs, relative to each other, 13 (256 x 256), 10 (256 x 192), 7.6 (128 x 128, two per compute unit) or 6.2 (128 x 128,
 // one), 4.0 (128 x 128 on at most one per compute unit, with four LDS stages): measured 84, 63.8, 47.7, 40.7 and 25.7 us
-// at K = 4096.  The column split adds a launch (a twelfth of a large round).
-// Measured in us (256 x 256 / 256 x 192 / 128 x 128): 2048 x 11008 x 4096 151 / 128 / 138, 2048 x 4096 x 11008
+// at K = 4096, in two LDS stages (in the ring 83 and 60.5, in 256 x 128 pairs 43 to 50).  The column split adds a launch (a twelfth of a large round).
+// Measured in us (256 x 256 / 256 x 192 / 128 x 128, two stages): 2048 x 11008 x 4096 151 / 128 / 138, 2048 x 4096 x 11008
 // 183 / 164 / 131, 11008 x 4096 x 2048 132 / 142 / 148, 4096^3 84 / 126 / 99.
 enum : int { TILE_256 = 0, TILE_192 = 1, TILE_128 = 2, TILE_SPLIT = 3 };
 inline uint64_t tile_count(int tile, size_t M, size_t N, size_t pairs) {

@@ -313,22 +313,24 @@ k_gemm_x(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, void* _
 }
 
 // The W codes at src[k .. k + W - 1] of a row of K codes as dwords, zero codes (+0) past its end; reads inside the row only,
-// at any address (W = 8 or 16).  Streaming loads: what a product reads next is the expansion, and codes that take its place in the
-// last-level cache make its operands come from memory, cold and behind the write-back of what else is there (the six expansions and three
-// products of a 2048-token 4096 -> 11008 layer: 532 us with ordinary loads, 475 so; its 2048 x 4096 x 11008 product 170 us, 123 so).
+// at any address (W = 8 or 16).  STREAM: with streaming loads, see expand_streams.
 template <int W>
 struct CodeRun {
   uint32_t w[W / 4];
 };
-template <int W>
+template <int W, bool STREAM>
 __device__ __forceinline__ CodeRun<W> load_codes(const uint8_t* __restrict__ row, uint32_t k, uint32_t K) {
   typedef uint32_t Run __attribute__((ext_vector_type(W / 4), aligned(1)));
   CodeRun<W> c{};
   if (k >= K) return c;
   const uint32_t rem = K - k;
   if (rem >= (uint32_t)W) {
-    const Run v = __builtin_nontemporal_load(reinterpret_cast<const Run*>(row + k));
-    __builtin_memcpy(&c, &v, W);
+    if constexpr (STREAM) {
+      const Run v = __builtin_nontemporal_load(reinterpret_cast<const Run*>(row + k));
+      __builtin_memcpy(&c, &v, W);
+    } else {
+      __builtin_memcpy(&c, row + k, W);
+    }
   } else if (K >= (uint32_t)W) {  // the last W codes of the row, moved down
     __builtin_memcpy(&c, row + (K - W), W);
     const uint32_t bits = 8u * (W - rem);
@@ -353,7 +355,7 @@ __device__ __forceinline__ CodeRun<W> load_codes(const uint8_t* __restrict__ row
 // (11008 x 4096: 135 MB in 21.3 us).  Rows at odd addresses cost no more loads than aligned ones (11007 x 4095: 27.1 us with byte
 // loads, 19.2 to 22.2 by where the buffers lie).
 constexpr uint32_t kExpandBlock = 256;
-template <uint32_t STEPS>
+template <uint32_t STEPS, bool STREAM>
 __global__ void __launch_bounds__(kExpandBlock)
 k_expand_rows(const uint8_t* __restrict__ a, const uint8_t* __restrict__ b, uint16_t* __restrict__ dst, size_t rows_a, size_t rows,
               uint32_t K, uint32_t ld) {
@@ -370,7 +372,7 @@ k_expand_rows(const uint8_t* __restrict__ a, const uint8_t* __restrict__ b, uint
       const size_t q = q0 + j * kExpandBlock;
       const size_t row = total <= 0xFFFFFFFFu ? (size_t)((uint32_t)q / cpr) : q / cpr;
       const uint32_t k = (uint32_t)(q - row * cpr) * 8u;
-      c[j] = q < total ? load_codes<8>(row < rows_a ? a + row * K : b + (row - rows_a) * K, k, K) : CodeRun<8>{};
+      c[j] = q < total ? load_codes<8, STREAM>(row < rows_a ? a + row * K : b + (row - rows_a) * K, k, K) : CodeRun<8>{};
     }
 #pragma unroll
     for (uint32_t j = 0; j < STEPS; ++j) {
@@ -393,7 +395,7 @@ k_expand_rows(const uint8_t* __restrict__ a, const uint8_t* __restrict__ b, uint
 // 128 contiguous bytes).  LDS operations bound it: values transposed as 16-bit elements took two and a half per element,
 // codes take one and a quarter (11008 x 4096: 28.6 us -> 21.4, 6.3 TB/s; 11007 x 4095, then byte by byte: 89.5 -> 28.2).
 constexpr int kTR = 64;  // tile rows
-template <int TC>  // tile columns: 128 or 64
+template <int TC, bool STREAM>  // tile columns: 128 or 64
 __global__ void __launch_bounds__(256)
 k_expand_cols(const uint8_t* __restrict__ codes, uint16_t* __restrict__ dst, uint32_t rows, uint32_t cols, uint32_t ld,
               uint32_t tiles_c, uint32_t n_tiles) {
@@ -411,7 +413,7 @@ k_expand_cols(const uint8_t* __restrict__ codes, uint16_t* __restrict__ dst, uin
 #pragma unroll
     for (uint32_t p = 0; p < kPasses; ++p) {
       const uint32_t r = r0 + p * kRowsIn + t / kRuns;
-      in[p] = r < rows ? load_codes<16>(codes + (size_t)r * cols, c0 + (t % kRuns) * 16u, cols) : CodeRun<16>{};  // code 0x00 is +0
+      in[p] = r < rows ? load_codes<16, STREAM>(codes + (size_t)r * cols, c0 + (t % kRuns) * 16u, cols) : CodeRun<16>{};  // code 0x00 is +0
     }
     __syncthreads();  // table written (first pass) / previous tile fully read
 #pragma unroll
@@ -439,6 +441,14 @@ k_expand_cols(const uint8_t* __restrict__ codes, uint16_t* __restrict__ dst, uin
 // ====================================================================================
 // host side
 // ====================================================================================
+// Codes that with their expansion (3 bytes an element) take a quarter of the 256 MiB last-level cache or more are read with
+// streaming loads: what products read behind is the expansion, and codes that take its place, or that of the other operand's,
+// make them come from memory, behind the write-back of what else is there (six expansions and three products of a 2048-token 4096 ->
+// 11008 layer 532 us with ordinary loads, 475 to 505 so; 535 with only the weight's 45 M elements streamed).  Smaller ones are found in the
+// cache when they are read again.  In a workspace the product follows at once and nothing else comes between: there from half
+// of the cache on (repeated call, ordinary / streaming, us: 420 x 8523 x 3952 62.2 / 65.3, 951 x 7813 x 2832 53.1 / 55.5).
+static bool expand_streams(size_t elements, bool kept) { return elements >= ((size_t)(kept ? 64 : 128) << 20) / 3; }
+
 hif8_status expand_rows(const uint8_t* a, size_t rows_a, const uint8_t* b, size_t rows_b, size_t K, uint16_t* dst, size_t ld,
                         hipStream_t st) {
   if (rows_a + rows_b == 0) return HIF8_OK;
@@ -457,8 +467,9 @@ hif8_status expand_rows(const uint8_t* a, size_t rows_a, const uint8_t* b, size_
   };
   // one step while that gives no more than four workgroups per compute unit (8 x 4096 2.3 us, with four steps 3.1, 512 x 4096 3.3,
   // 3.6; 1024 x 4096 4.6, 4.4, 4096 x 4096 11.1, 9.0)
-  if (chunks <= (size_t)cus * 4 * kExpandBlock) launch(k_expand_rows<1>, 1);
-  else launch(k_expand_rows<4>, 4);
+  if (chunks <= (size_t)cus * 4 * kExpandBlock) launch(k_expand_rows<1, false>, 1);
+  else if (!expand_streams(rows * K, b == nullptr)) launch(k_expand_rows<4, false>, 4);
+  else launch(k_expand_rows<4, true>, 4);
   return finish_launch();
 }
 
@@ -480,8 +491,9 @@ hif8_status expand_cols(const uint8_t* codes, size_t rows, size_t cols, uint16_t
   };
   // narrow tiles while wide ones are no more than two per compute unit, or half empty (64 x 64 2.2 us, in wide ones 2.6; 1024 x 4096
   // 4.0, 4.1, 4096 x 4096 11.2, 8.6; 100000 x 16 3.6, 4.2)
-  if (cols <= 64 || (ld / kTR) * ((cols + 127) / 128) <= (size_t)cus * 2) launch(k_expand_cols<64>, 64);
-  else launch(k_expand_cols<128>, 128);
+  if (cols <= 64 || (ld / kTR) * ((cols + 127) / 128) <= (size_t)cus * 2) launch(k_expand_cols<64, false>, 64);
+  else if (!expand_streams(rows * cols, true)) launch(k_expand_cols<128, false>, 128);
+  else launch(k_expand_cols<128, true>, 128);
   return finish_launch();
 }
 

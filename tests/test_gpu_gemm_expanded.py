@@ -377,3 +377,18 @@ def test_ragged_round_shape_all_outputs_and_sqerr(h):
         torch.cuda.synchronize()
         want = float(((out.double() - ref.double()) ** 2).sum())
         assert abs(err.item() - want) <= 1e-10 * want
+
+
+# both sides of the size from which codes are read with streaming loads, rows at odd addresses
+@pytest.mark.parametrize("rows,cols", [(4101, 5451), (4101, 5459)])
+def test_expansions_of_large_matrices(h, rows, cols):
+    c = torch.randint(0, 256, (rows, cols), dtype=torch.uint8, device=dev(), generator=torch.Generator(device=dev()).manual_seed(3))
+    tab = torch.empty(256, dtype=torch.bfloat16, device=dev())
+    h.hif8_decode_bf16(torch.arange(256, dtype=torch.uint8, device=dev()), tab, 256, 1.0)
+    ld, ldt = h.hif8_expanded_ld(cols), h.hif8_expanded_ld(rows)
+    x, xt = torch.full((rows, ld), 7.0, dtype=torch.bfloat16, device=dev()), torch.full((cols, ldt), 7.0, dtype=torch.bfloat16, device=dev())
+    h.hif8_expand_bf16(c, rows, cols, x, ld)
+    h.hif8_expand_bf16_t(c, rows, cols, xt, ldt)
+    want = tab.view(torch.int16)[c.long()]
+    assert torch.equal(x[:, :cols].view(torch.int16), want) and not x[:, cols:].view(torch.int16).any()
+    assert torch.equal(xt[:, :rows].view(torch.int16), want.t()) and not xt[:, rows:].view(torch.int16).any()
