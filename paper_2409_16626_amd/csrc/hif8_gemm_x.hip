@@ -44,7 +44,7 @@ constexpr int kWaitVm0 = 0x0F70;          // vmcnt(0)
 constexpr int wait_vm(int n) { return (n & 15) | (n >> 4) << 14; }
 constexpr int kRsrcFlags = 0x00020000;    // word 3 of a raw (unstructured, untyped) buffer descriptor on gfx9-family parts
 
-// The K loop of a 256 x 256 tile is bound by what keeps a wavefront, alone on its SIMD, from issuing MFMAs (78 % of the cycles
+// The K loop of a 256 x 256 tile is bound by what keeps a wavefront, alone on its SIMD, from issuing MFMAs (80 % of the cycles
 // busy, counters), and by the clock that the power limit leaves them:
 //   * v_mfma_f32_16x16x32_bf16 costs less power than the 32 x 32 x 16 shape on operands with HiF8's few mantissa bits
 //     (in registers only 1.97 PFLOP/s against 1.80), and with 16 cycles each there is a place for a memory instruction
@@ -55,7 +55,7 @@ constexpr int kRsrcFlags = 0x00020000;    // word 3 of a raw (unstructured, unty
 //     So the loads are spread over the whole K step: a ring of five slots, one operand's rows of a K step each (RING), has room for
 //     the A rows of the step after next before the barrier that frees the slots of the current one, and its B rows follow behind
 //     the barrier.  With two whole stages all loads had to go out in the half step behind the barrier, at the full rate of
-//     the L2, and the last ones had 1024 cycles left to arrive (waits: 5.6e7 -> 2.9e7; loop alone, all loads from the L2: 607 us).
+//     the L2, and the last ones had 1024 cycles left to arrive (waits: 5.4e7 -> 2.5e7; loop alone, all loads from the L2: 607 us).
 //   * Fragment reads at every third MFMA, tile loads at every sixth: four wavefronts that read at every MFMA fill the LDS for 256
 //     cycles (all reads behind the first MFMAs of a half step 645 us, so 642).  Four loads share an LDS base, by immediate offsets.
 // Measured (us, two stages / ring, walking): 8192^3 671 / 642, 4096^3 86.6 / 85.1, 2048 x 11008 x 4096 128.5 / 122.9, 8192 x 11008 x 4096
