@@ -223,12 +223,14 @@ inline SmallPlan small_plan(size_t M, size_t N, size_t K, bool codes, bool sqerr
 // kXcds accelerator dies (XCDs), each with its own L2.  Workgroup b therefore takes tile number
 // (b % kXcds) * per_xcd + b / kXcds of a tile order that walks groups of `group` tile rows column by column: the
 // workgroups resident on one die at a time then cover a compact group x (a few) block of tiles and share their
-// operand panels in that die's L2, whatever tiles_n is.  Of the large tiles a die holds 32: 4 x 8 of them take 2560 operand rows
-// (256 x 192) or 2048 (256 x 128), 8 x 4 2816 and 2560, and a row of the first operand is asked for by fewer dies at a time (2048 x 4096 x
-// 11008 from cold memory 159 us with groups of 8, 155 with 4).  The launch has tile_order_grid() workgroups; returns false
+// operand panels in that die's L2, whatever tiles_n is.  Of 256 x 128 tiles a die holds 32: 4 x 8 of them take 2048 operand rows, 8 x 4
+// 2560, and a row of the first operand is asked for by fewer dies at a time (2048 x 4096 x 11008 from cold memory 159 us with groups of 8, 155
+// with 4).  The wider tiles stay with 8: groups of 4 gave 1 % at 8192^3, but a product with a short K right behind its expansions took
+// longer (with expansions, groups of 8 / 4: 1537 x 6197 x 688 31.5 / 34.5, 2011 x 4511 x 1168 38.7 / 42.5).
+// The launch has tile_order_grid() workgroups; returns false
 // for the few at the end of the last die's share that have no tile.
 constexpr uint32_t kXcds = 8;    // accelerator dies, each with an L2 of its own
-constexpr uint32_t kGroupM = 8, kGroupLarge = 4;  // tile rows per group of the tile order; of large tiles
+constexpr uint32_t kGroupM = 8, kGroupPaired = 4;  // tile rows per group of the tile order; of 256 x 128 tiles
 __host__ __device__ inline uint32_t tile_order_grid(uint32_t n_tiles) { return (n_tiles + kXcds - 1u) / kXcds * kXcds; }
 __host__ __device__ inline bool tile_order(uint32_t b, uint32_t tiles_m, uint32_t tiles_n, uint32_t* tile_m, uint32_t* tile_n,
                                            uint32_t group = kGroupM) {

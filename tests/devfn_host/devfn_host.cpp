@@ -73,9 +73,9 @@ uint32_t devfn_tile_order(uint32_t b, uint32_t tiles_m, uint32_t tiles_n) {
   uint32_t tm = 0, tn = 0;
   return hif8gemm::tile_order(b, tiles_m, tiles_n, &tm, &tn) ? tm * tiles_n + tn : 0xFFFFFFFFu;
 }
-uint32_t devfn_tile_order_large(uint32_t b, uint32_t tiles_m, uint32_t tiles_n) {  // the same for the large tiles
+uint32_t devfn_tile_order_paired(uint32_t b, uint32_t tiles_m, uint32_t tiles_n) {  // the same for 256 x 128 tiles
   uint32_t tm = 0, tn = 0;
-  return hif8gemm::tile_order(b, tiles_m, tiles_n, &tm, &tn, hif8gemm::kGroupLarge) ? tm * tiles_n + tn : 0xFFFFFFFFu;
+  return hif8gemm::tile_order(b, tiles_m, tiles_n, &tm, &tn, hif8gemm::kGroupPaired) ? tm * tiles_n + tn : 0xFFFFFFFFu;
 }
 uint32_t devfn_tile_order_grid(uint32_t n_tiles) { return hif8gemm::tile_order_grid(n_tiles); }
 // host-side launch planning of the GEMM kernels: returns the split column, or 0 for a single launch

@@ -274,11 +274,11 @@ def test_small_gemm_route(dev, operands, out):
 
 
 @pytest.mark.parametrize("tm,tn", [(1, 1), (3, 5), (4, 8), (5, 1), (8, 32), (13, 7), (43, 16), (8, 58), (64, 3)])
-def test_gemm_tile_order_of_large_tiles(dev, tm, tn):
+def test_gemm_tile_order_of_paired_tiles(dev, tm, tn):
     """Every tile once, and the 32 workgroups that run together on a die within 4 tile rows of a group (two groups where one ends)."""
-    dev.devfn_tile_order_large.restype, dev.devfn_tile_order_large.argtypes = ctypes.c_uint32, [ctypes.c_uint32] * 3
+    dev.devfn_tile_order_paired.restype, dev.devfn_tile_order_paired.argtypes = ctypes.c_uint32, [ctypes.c_uint32] * 3
     grid = (tm * tn + 7) // 8 * 8
-    got = [dev.devfn_tile_order_large(b, tm, tn) for b in range(grid)]
+    got = [dev.devfn_tile_order_paired(b, tm, tn) for b in range(grid)]
     assert sorted(t for t in got if t != 0xFFFFFFFF) == list(range(tm * tn))
     for die in range(8):
         mine = [t for t in got[die::8] if t != 0xFFFFFFFF]
