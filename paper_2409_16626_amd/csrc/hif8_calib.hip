@@ -216,8 +216,11 @@ k_cast_scales(const void* __restrict__ src, uint16_t* __restrict__ dst, size_t r
 
 // ------------------------------------------------------------------------------------
 // per-channel kernels.  Row-major [rows, cols]; axis 0: one scale per row, axis 1: one per column.
-// Fast paths need 16-byte aligned bases and cols a multiple of the vector width, so that no
-// 16-byte vector straddles two rows; otherwise the element kernels below do the same work.
+// A row of at least one vector is covered by vectors that start at its first element, wherever that lies in memory; the
+// last one ends with the row, so that it shares elements with the one before where cols is not a multiple of the vector width
+// (a maximum does not mind, and a cast writes the same bytes twice).  Rows of fewer elements go to the element kernels.
+// Maximum, scale and codes in us, element by element with an atomic for each (until now) / now: 316 x 5267 bfloat16 3400 / 4.8, 11008 x
+// 4099 7190 / 30 (11008 x 4096 23.5), binary32 7310 / 40 (38.7).
 //
 // axis 0: a workgroup owns one chunk of one row (block index -> row, chunk).
 // axis 1: a workgroup owns a strip of 64 * VE columns and a run of rows, its wavefronts taking
@@ -230,18 +233,35 @@ constexpr int kAxWaves = kAxBlock / 64;
 constexpr int kAxRowsInFlight = 4;  // axis 1: rows loaded per lane before any is used
 constexpr int kAmaxColsWaves = 8;   // axis 1 amax: wavefronts per workgroup
 
+// first element, in its row of `cols`, of vector c of VE elements
+template <int VE>
+__device__ __forceinline__ uint32_t vec_begin(uint32_t c, uint32_t cols) {
+  const uint32_t e = c * VE;
+  return e <= cols - VE ? e : cols - VE;
+}
+template <int KIND>
+__device__ __forceinline__ const uint8_t* elem_ptr(const void* p, size_t e) {
+  return reinterpret_cast<const uint8_t*>(p) + e * (KIND == kSrcF32 ? 4 : 2);
+}
+// one vector of values at element e -> codes
+template <int IMPL, int SRCK>
+__device__ __forceinline__ void encode_vec_any(const uint4& v, float scale, const EncCtx& ctx, uint8_t* __restrict__ dst, size_t e) {
+  if constexpr (SRCK == kSrcF32) st_stream_any(dst + e, encode4_f32<IMPL>(v, scale, ctx, e));
+  else st_stream_any(dst + e, encode8_16<IMPL, SRCK>(v, scale, ctx, e));
+}
+
 template <int SRCK>
 __global__ void __launch_bounds__(kAxBlock)
-k_amax_rows(const void* __restrict__ src, uint32_t cols_vec, uint32_t chunks, uint32_t* __restrict__ out) {
+k_amax_rows(const void* __restrict__ src, uint32_t cols, uint32_t cols_vec, uint32_t chunks, uint32_t* __restrict__ out) {
   // chunks == 1: the workgroup owns the whole row and stores its maximum (the array needs no clearing);
   // otherwise the chunks of a row meet in an atomic max on the cleared array
   const uint32_t row = blockIdx.x / chunks, chunk = blockIdx.x - row * chunks;
-  const uint4* __restrict__ p = reinterpret_cast<const uint4*>(src) + (size_t)row * cols_vec;
   uint32_t m = 0;
 #pragma unroll
   for (int j = 0; j < kAxUnroll; ++j) {
     const uint32_t c = (chunk * kAxUnroll + j) * kAxBlock + threadIdx.x;
-    if (c < cols_vec) m = vec_amax<SRCK>(m, ld_stream(p + c));
+    if (c < cols_vec)
+      m = vec_amax<SRCK>(m, ld_stream_any<uint4>(elem_ptr<SRCK>(src, (size_t)row * cols + vec_begin<vec_elems<SRCK>()>(c, cols))));
   }
   if (chunks == 1u) {
     const uint32_t r = block_max_thread0(fold_amax<SRCK>(m));
@@ -271,7 +291,7 @@ __device__ __forceinline__ uint4 colmax(const uint4& m, const uint4& v) {
 
 template <int SRCK, int WAVES>
 __global__ void __launch_bounds__(WAVES * 64)
-k_amax_cols(const void* __restrict__ src, uint32_t rows, uint32_t cols_vec, uint32_t strips,
+k_amax_cols(const void* __restrict__ src, uint32_t rows, uint32_t cols, uint32_t cols_vec, uint32_t strips,
             uint32_t rows_per_wg, uint32_t* __restrict__ out) {
   constexpr int VE = vec_elems<SRCK>();
   __shared__ uint4 part[WAVES][64];
@@ -281,7 +301,7 @@ k_amax_cols(const void* __restrict__ src, uint32_t rows, uint32_t cols_vec, uint
   const bool active = cv < cols_vec;
   const uint32_t r0 = rchunk * rows_per_wg;
   const uint32_t r1 = min(rows, r0 + rows_per_wg);
-  const uint4* __restrict__ p = reinterpret_cast<const uint4*>(src) + cv;
+  const uint32_t c0 = vec_begin<VE>(cv, cols);
   uint4 m = make_uint4(0u, 0u, 0u, 0u);  // FP32: four magnitudes; 16-bit: eight packed 15-bit magnitudes
   if (active) {
     for (uint32_t r = r0 + wv; r < r1; r += WAVES * kAxRowsInFlight) {
@@ -289,7 +309,7 @@ k_amax_cols(const void* __restrict__ src, uint32_t rows, uint32_t cols_vec, uint
 #pragma unroll
       for (int j = 0; j < kAxRowsInFlight; ++j) {
         const uint32_t rr = r + j * WAVES;
-        v[j] = rr < r1 ? ld_stream(p + (size_t)rr * cols_vec) : make_uint4(0u, 0u, 0u, 0u);
+        v[j] = rr < r1 ? ld_stream_any<uint4>(elem_ptr<SRCK>(src, (size_t)rr * cols + c0)) : make_uint4(0u, 0u, 0u, 0u);
       }
 #pragma unroll
       for (int j = 0; j < kAxRowsInFlight; ++j) m = colmax<SRCK>(m, v[j]);
@@ -300,7 +320,7 @@ k_amax_cols(const void* __restrict__ src, uint32_t rows, uint32_t cols_vec, uint
   if (wv != 0 || !active) return;
 #pragma unroll
   for (int w = 1; w < WAVES; ++w) m = colmax<SRCK>(m, part[w][lane]);  // masks are no-ops on magnitudes
-  uint32_t* o = out + (size_t)cv * VE;
+  uint32_t* o = out + c0;
   auto put = [&](int j, uint32_t bits) { if (bits) atomicMax(o + j, bits); };
   if constexpr (SRCK == kSrcF32) {
     put(0, m.x); put(1, m.y); put(2, m.z); put(3, m.w);
@@ -310,20 +330,31 @@ k_amax_cols(const void* __restrict__ src, uint32_t rows, uint32_t cols_vec, uint
   }
 }
 
+// Rows shorter than a vector.  axis 0: a lane per row, which stores its maximum; axis 1: a lane stays in one column (the lanes
+// that walk are a multiple of cols), one atomic for each that found something.
 template <int SRCK>
 __global__ void __launch_bounds__(256)
-k_amax_axis_elem(const void* __restrict__ src, size_t rows, size_t cols, int axis, uint32_t* __restrict__ out) {
-  const size_t n = rows * cols;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const size_t r = i / cols;
-    const uint32_t a = load_bits<SRCK>(src, i) & 0x7FFFFFFFu;
-    if (a) atomicMax(out + (axis == 0 ? r : i - r * cols), a);
+k_amax_axis_elem(const void* __restrict__ src, size_t rows, uint32_t cols, int axis, uint32_t* __restrict__ out) {
+  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x, lanes = (size_t)gridDim.x * blockDim.x;
+  auto at = [&](size_t i) { return load_bits<SRCK>(src, i) & 0x7FFFFFFFu; };
+  if (axis == 0) {
+    for (size_t r = t; r < rows; r += lanes) {
+      uint32_t m = 0;
+      for (uint32_t c = 0; c < cols; ++c) m = umax(m, at(r * cols + c));
+      out[r] = m;
+    }
+    return;
   }
+  const size_t step = lanes / cols * cols, n = rows * cols;
+  if (t >= step) return;
+  uint32_t m = 0;
+  for (size_t i = t; i < n; i += step) m = umax(m, at(i));
+  if (m) atomicMax(out + t % cols, m);
 }
 
 template <int IMPL, int SRCK>
 __global__ void __launch_bounds__(kAxBlock)
-k_encode_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t cols_vec, uint32_t chunks,
+k_encode_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t cols, uint32_t cols_vec, uint32_t chunks,
               const float* __restrict__ d_scale2, uint32_t mode, uint64_t seed,
               const uint8_t* __restrict__ g_lut) {
   __shared__ __attribute__((aligned(16))) uint8_t lut[lut_bytes<IMPL>()];
@@ -331,13 +362,12 @@ k_encode_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t 
   const EncCtx ctx = make_ctx<IMPL>(lut, hrt.w, mode, seed);
   constexpr int VE = vec_elems<SRCK>();
   const uint32_t row = blockIdx.x / chunks, chunk = blockIdx.x - row * chunks;
-  const size_t rbase = (size_t)row * cols_vec;
-  const uint4* __restrict__ p = reinterpret_cast<const uint4*>(src) + rbase;
+  const size_t rbase = (size_t)row * cols;
   uint4 v[kAxUnroll];
 #pragma unroll
   for (int j = 0; j < kAxUnroll; ++j) {
     const uint32_t c = (chunk * kAxUnroll + j) * kAxBlock + threadIdx.x;
-    if (c < cols_vec) v[j] = ld_stream(p + c);
+    if (c < cols_vec) v[j] = ld_stream_any<uint4>(elem_ptr<SRCK>(src, rbase + vec_begin<VE>(c, cols)));
   }
   const float scale = d_scale2[2 * (size_t)row];
   stage_enc_lut<IMPL, SRCK>(lut, g_lut, mode);
@@ -346,51 +376,52 @@ k_encode_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t 
 #pragma unroll
   for (int j = 0; j < kAxUnroll; ++j) {
     const uint32_t c = (chunk * kAxUnroll + j) * kAxBlock + threadIdx.x;
-    if (c < cols_vec) {
-      const size_t idx = rbase + c;
-      if constexpr (SRCK == kSrcF32)
-        st_stream(reinterpret_cast<uint32_t*>(dst) + idx, encode4_f32<IMPL>(v[j], scale, ctx, idx * VE));
-      else
-        st_stream(reinterpret_cast<uint2*>(dst) + idx, encode8_16<IMPL, SRCK>(v[j], scale, ctx, idx * VE));
-    }
+    if (c < cols_vec) encode_vec_any<IMPL, SRCK>(v[j], scale, ctx, dst, rbase + vec_begin<VE>(c, cols));
   }
 }
 
 // Per-row scaling in one pass: amax of the row, its scale, and the cast, with the row held in registers
-// between the two (one read of the source instead of two).  A workgroup walks rows blockIdx.x, + gridDim.x, ...;
-// a lane holds VPT 16-byte vectors of the row (vector j * kQrBlock + lane index), the next row is requested
-// before the current one is reduced, and one barrier per row publishes the wavefront maxima (two sets of
+// between the two (one read of the source instead of two).  LANES lanes share a row and walk rows: a whole workgroup
+// (rows blockIdx.x, + gridDim.x, ...), or one wavefront (kQrWaves rows of a workgroup at a time) where a row is short.
+// A lane holds VPT vectors of the row (vector j * LANES + lane index), the next row is requested
+// before the current one is reduced, and for a workgroup one barrier per row publishes the wavefront maxima (two sets of
 // slots, used alternately).  Same arithmetic as hif8_amax_axis + hif8_scale_from_amax_n + hif8_encode_axis
 // with axis 0: d_amax[row] and d_scale2[2 row], [2 row + 1] receive the same values.
+// A short row leaves most lanes of a workgroup idle and pays a barrier for it; a wavefront's row may have four vectors a lane (us, workgroup /
+// wavefront, bfloat16: 11008 x 256 12.4 / 5.7, x 1024 13.5 / 8.3, x 2048 15.8 / 14.1, 4096 x 2048 7.8 / 6.0).
 constexpr int kQrBlock = 512;
 constexpr int kQrWaves = kQrBlock / 64;
+constexpr int kQrWaveVecs = 4;  // vectors of a lane up to which a wavefront takes a row by itself
 
-template <int IMPL, int SRCK, int VPT>
+template <int IMPL, int SRCK, int VPT, int LANES>
 __global__ void __launch_bounds__(kQrBlock)
-k_quant_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t rows, uint32_t cols_vec, float target,
+k_quant_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t rows, uint32_t cols, uint32_t cols_vec, float target,
              int pow2, uint32_t* __restrict__ d_amax, float* __restrict__ d_scale2, uint32_t mode, uint64_t seed,
              const uint8_t* __restrict__ g_lut) {
+  static_assert(LANES == kQrBlock || LANES == 64, "a workgroup or a wavefront per row");
+  constexpr bool WAVE = LANES == 64;
   __shared__ __attribute__((aligned(16))) uint8_t lut[lut_bytes<IMPL>()];
   __shared__ HrLds<uses_exp_table<IMPL>()> hrt;
   __shared__ uint32_t part[2][kQrWaves];
   const EncCtx ctx = make_ctx<IMPL>(lut, hrt.w, mode, seed);
   constexpr int VE = vec_elems<SRCK>();
-  const uint4* __restrict__ src4 = reinterpret_cast<const uint4*>(src);
-  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
+  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6, at = WAVE ? lane : threadIdx.x;
   uint4 nxt[VPT];
   auto request = [&](uint32_t r) {
-    const uint4* __restrict__ p = src4 + (size_t)r * cols_vec;
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
-      const uint32_t c = j * kQrBlock + threadIdx.x;
-      nxt[j] = c < cols_vec ? ld_stream(p + c) : make_uint4(0u, 0u, 0u, 0u);
+      const uint32_t c = j * LANES + at;
+      nxt[j] = c < cols_vec ? ld_stream_any<uint4>(elem_ptr<SRCK>(src, (size_t)r * cols + vec_begin<VE>(c, cols))) : make_uint4(0u, 0u, 0u, 0u);
     }
   };
-  uint32_t r = blockIdx.x;  // uniform over the workgroup, as is every branch on it
+  const uint32_t step = WAVE ? gridDim.x * kQrWaves : gridDim.x;
+  // uniform over the lanes that share a row, as is every branch on it
+  uint32_t r = WAVE ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * kQrWaves + wv)) : blockIdx.x;
   if (r < rows) request(r);
   stage_enc_lut<IMPL, SRCK>(lut, g_lut, mode);
   stage_exp_table<IMPL, SRCK>(hrt.w, mode);
-  for (uint32_t it = 0; r < rows; r += gridDim.x, ++it) {
+  if constexpr (WAVE) __syncthreads();
+  for (uint32_t it = 0; r < rows; r += step, ++it) {
     uint4 cur[VPT];
     uint32_t m = 0;
 #pragma unroll
@@ -398,37 +429,35 @@ k_quant_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t r
       cur[j] = nxt[j];
       m = vec_amax<SRCK>(m, cur[j]);  // vectors past the row are zeros
     }
-    m = wave_max_u32(fold_amax<SRCK>(m));
-    if (lane == 0u) part[it & 1u][wv] = m;
-    if (r + gridDim.x < rows) request(r + gridDim.x);
-    __syncthreads();  // also orders the table staging before the first row's lookups
-    uint32_t a = part[it & 1u][0];
+    uint32_t a = wave_max_u32(fold_amax<SRCK>(m));
+    if constexpr (!WAVE) {
+      if (lane == 0u) part[it & 1u][wv] = a;
+    }
+    if (r + step < rows) request(r + step);
+    if constexpr (!WAVE) {
+      __syncthreads();  // also orders the table staging before the first row's lookups
+      a = part[it & 1u][0];
 #pragma unroll
-    for (int w = 1; w < kQrWaves; ++w) a = umax(a, part[it & 1u][w]);
+      for (int w = 1; w < kQrWaves; ++w) a = umax(a, part[it & 1u][w]);
+    }
     const float scale = scale_from_amax_value(__uint_as_float(a), target, pow2);
-    if (threadIdx.x == 0u) {
+    if (at == 0u) {
       d_amax[r] = a;
       d_scale2[2 * (size_t)r] = scale;
       d_scale2[2 * (size_t)r + 1] = 1.0f / scale;
     }
-    const size_t rbase = (size_t)r * cols_vec;
+    const size_t rbase = (size_t)r * cols;
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
-      const uint32_t c = j * kQrBlock + threadIdx.x;
-      if (c < cols_vec) {
-        const size_t idx = rbase + c;
-        if constexpr (SRCK == kSrcF32)
-          st_stream(reinterpret_cast<uint32_t*>(dst) + idx, encode4_f32<IMPL>(cur[j], scale, ctx, idx * VE));
-        else
-          st_stream(reinterpret_cast<uint2*>(dst) + idx, encode8_16<IMPL, SRCK>(cur[j], scale, ctx, idx * VE));
-      }
+      const uint32_t c = j * LANES + at;
+      if (c < cols_vec) encode_vec_any<IMPL, SRCK>(cur[j], scale, ctx, dst, rbase + vec_begin<VE>(c, cols));
     }
   }
 }
 
 template <int IMPL, int SRCK>
 __global__ void __launch_bounds__(kAxBlock)
-k_encode_cols(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t rows, uint32_t cols_vec,
+k_encode_cols(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t rows, uint32_t cols, uint32_t cols_vec,
               uint32_t strips, uint32_t rows_per_wg, const float* __restrict__ d_scale2, uint32_t mode,
               uint64_t seed, const uint8_t* __restrict__ g_lut) {
   __shared__ __attribute__((aligned(16))) uint8_t lut[lut_bytes<IMPL>()];
@@ -442,32 +471,35 @@ k_encode_cols(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t 
   const uint32_t rchunk = blockIdx.x / strips, strip = blockIdx.x - rchunk * strips;
   const uint32_t cv = strip * 64u + lane;
   if (cv >= cols_vec) return;
+  const uint32_t c0 = vec_begin<VE>(cv, cols);
   float sc[VE];
 #pragma unroll
-  for (int j = 0; j < VE; ++j) sc[j] = d_scale2[2 * ((size_t)cv * VE + j)];
+  for (int j = 0; j < VE; ++j) sc[j] = d_scale2[2 * ((size_t)c0 + j)];
   const uint32_t r0 = rchunk * rows_per_wg;
   const uint32_t r1 = min(rows, r0 + rows_per_wg);
-  const uint4* __restrict__ p = reinterpret_cast<const uint4*>(src) + cv;
   auto encode_row = [&](uint32_t r, const uint4& v) {
-    const size_t idx = (size_t)r * cols_vec + cv;
-    const uint64_t e0 = (uint64_t)idx * VE;
-    const EncCtx kc = keyed<IMPL>(ctx, e0);
+    const uint64_t e0 = (uint64_t)r * cols + c0;
+    const bool split = straddles_block<IMPL, VE>(e0);
+    const EncCtx k0 = keyed<IMPL>(ctx, e0);
+    auto code = [&](uint32_t bits, int j) {
+      return encode_one<IMPL, SRCK>(scaled_bits(bits, sc[j]), split ? keyed<IMPL>(ctx, e0 + j) : k0, e0 + j);
+    };
     if constexpr (SRCK == kSrcF32) {
-      const uint32_t c0 = encode_one<IMPL, SRCK>(scaled_bits(v.x, sc[0]), kc, e0);
-      const uint32_t c1 = encode_one<IMPL, SRCK>(scaled_bits(v.y, sc[1]), kc, e0 + 1);
-      const uint32_t c2 = encode_one<IMPL, SRCK>(scaled_bits(v.z, sc[2]), kc, e0 + 2);
-      const uint32_t c3 = encode_one<IMPL, SRCK>(scaled_bits(v.w, sc[3]), kc, e0 + 3);
-      st_stream(reinterpret_cast<uint32_t*>(dst) + idx, c0 | (c1 << 8) | (c2 << 16) | (c3 << 24));
+      const uint32_t b0 = code(v.x, 0);
+      const uint32_t b1 = code(v.y, 1);
+      const uint32_t b2 = code(v.z, 2);
+      const uint32_t b3 = code(v.w, 3);
+      st_stream_any(dst + e0, b0 | (b1 << 8) | (b2 << 16) | (b3 << 24));
     } else {
       const uint32_t w[4] = {v.x, v.y, v.z, v.w};
       uint32_t o[2] = {0u, 0u};
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const uint32_t c0 = encode_one<IMPL, SRCK>(scaled_bits(widen_lo<SRCK>(w[j]), sc[2 * j]), kc, e0 + 2 * j);
-        const uint32_t c1 = encode_one<IMPL, SRCK>(scaled_bits(widen_hi<SRCK>(w[j]), sc[2 * j + 1]), kc, e0 + 2 * j + 1);
-        o[j >> 1] |= (c0 | (c1 << 8)) << (16 * (j & 1));
+        const uint32_t b0 = code(widen_lo<SRCK>(w[j]), 2 * j);
+        const uint32_t b1 = code(widen_hi<SRCK>(w[j]), 2 * j + 1);
+        o[j >> 1] |= (b0 | (b1 << 8)) << (16 * (j & 1));
       }
-      st_stream(reinterpret_cast<uint2*>(dst) + idx, make_uint2(o[0], o[1]));
+      st_stream_any(dst + e0, make_uint2(o[0], o[1]));
     }
   };
   for (uint32_t r = r0 + wv; r < r1; r += kAxWaves * kAxRowsInFlight) {
@@ -475,7 +507,7 @@ k_encode_cols(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t 
 #pragma unroll
     for (int j = 0; j < kAxRowsInFlight; ++j) {
       const uint32_t rr = r + j * kAxWaves;
-      if (rr < r1) v[j] = ld_stream(p + (size_t)rr * cols_vec);
+      if (rr < r1) v[j] = ld_stream_any<uint4>(elem_ptr<SRCK>(src, (size_t)rr * cols + c0));
     }
 #pragma unroll
     for (int j = 0; j < kAxRowsInFlight; ++j) {
@@ -500,31 +532,29 @@ k_encode_axis_elem(const void* __restrict__ src, uint8_t* __restrict__ dst, size
 // decode: one lane's worth of codes (VE of them) -> one 16-byte vector of DSTK values
 template <int DSTK>
 __global__ void __launch_bounds__(kAxBlock)
-k_decode_rows(const uint8_t* __restrict__ src, void* __restrict__ dst, uint32_t cols_vec, uint32_t chunks,
+k_decode_rows(const uint8_t* __restrict__ src, void* __restrict__ dst, uint32_t cols, uint32_t cols_vec, uint32_t chunks,
               const float* __restrict__ d_scale2, const uint32_t* __restrict__ g_dec) {
   __shared__ uint32_t dec[256];
   stage_dec_lut(dec, g_dec);
   __syncthreads();
   const uint32_t row = blockIdx.x / chunks, chunk = blockIdx.x - row * chunks;
-  const size_t rbase = (size_t)row * cols_vec;
+  const size_t rbase = (size_t)row * cols;
   const float inv = d_scale2[2 * (size_t)row + 1];
-  uint4* __restrict__ d4 = reinterpret_cast<uint4*>(dst);
 #pragma unroll
   for (int j = 0; j < kAxUnroll; ++j) {
     const uint32_t c = (chunk * kAxUnroll + j) * kAxBlock + threadIdx.x;
     if (c < cols_vec) {
-      const size_t idx = rbase + c;
-      if constexpr (DSTK == kSrcF32)
-        st_stream(d4 + idx, descale4_f32(ld_stream(reinterpret_cast<const uint32_t*>(src) + idx), dec, inv));
-      else
-        st_stream(d4 + idx, descale8_16<DSTK>(ld_stream(reinterpret_cast<const uint2*>(src) + idx), dec, inv));
+      const size_t e = rbase + vec_begin<vec_elems<DSTK>()>(c, cols);
+      uint8_t* const d = const_cast<uint8_t*>(elem_ptr<DSTK>(dst, e));
+      if constexpr (DSTK == kSrcF32) st_stream_any(d, descale4_f32(ld_stream_any<uint32_t>(src + e), dec, inv));
+      else st_stream_any(d, descale8_16<DSTK>(ld_stream_any<uint2>(src + e), dec, inv));
     }
   }
 }
 
 template <int DSTK>
 __global__ void __launch_bounds__(kAxBlock)
-k_decode_cols(const uint8_t* __restrict__ src, void* __restrict__ dst, uint32_t rows, uint32_t cols_vec,
+k_decode_cols(const uint8_t* __restrict__ src, void* __restrict__ dst, uint32_t rows, uint32_t cols, uint32_t cols_vec,
               uint32_t strips, uint32_t rows_per_wg, const float* __restrict__ d_scale2,
               const uint32_t* __restrict__ g_dec) {
   __shared__ uint32_t dec[256];
@@ -535,28 +565,27 @@ k_decode_cols(const uint8_t* __restrict__ src, void* __restrict__ dst, uint32_t 
   const uint32_t rchunk = blockIdx.x / strips, strip = blockIdx.x - rchunk * strips;
   const uint32_t cv = strip * 64u + lane;
   if (cv >= cols_vec) return;
+  const uint32_t c0 = vec_begin<VE>(cv, cols);
   float inv[VE];
 #pragma unroll
-  for (int j = 0; j < VE; ++j) inv[j] = d_scale2[2 * ((size_t)cv * VE + j) + 1];
+  for (int j = 0; j < VE; ++j) inv[j] = d_scale2[2 * ((size_t)c0 + j) + 1];
   const uint32_t r0 = rchunk * rows_per_wg;
   const uint32_t r1 = min(rows, r0 + rows_per_wg);
-  uint4* __restrict__ d4 = reinterpret_cast<uint4*>(dst);
   for (uint32_t r = r0 + wv; r < r1; r += kAxWaves * kAxRowsInFlight) {
     uint2 w[kAxRowsInFlight];
 #pragma unroll
     for (int j = 0; j < kAxRowsInFlight; ++j) {
       const uint32_t rr = r + j * kAxWaves;
       if (rr < r1) {
-        const size_t idx = (size_t)rr * cols_vec + cv;
-        if constexpr (DSTK == kSrcF32) w[j] = make_uint2(ld_stream(reinterpret_cast<const uint32_t*>(src) + idx), 0u);
-        else w[j] = ld_stream(reinterpret_cast<const uint2*>(src) + idx);
+        const uint8_t* const at = src + (size_t)rr * cols + c0;
+        if constexpr (DSTK == kSrcF32) w[j] = make_uint2(ld_stream_any<uint32_t>(at), 0u);
+        else w[j] = ld_stream_any<uint2>(at);
       }
     }
 #pragma unroll
     for (int j = 0; j < kAxRowsInFlight; ++j) {
       const uint32_t rr = r + j * kAxWaves;
       if (rr < r1) {
-        const size_t idx = (size_t)rr * cols_vec + cv;
         uint4 o;
         if constexpr (DSTK == kSrcF32) {
           o.x = descale_bits(w[j].x, dec, inv[0]);
@@ -569,7 +598,7 @@ k_decode_cols(const uint8_t* __restrict__ src, void* __restrict__ dst, uint32_t 
           o.z = narrow2<DSTK>(descale_bits(w[j].y, dec, inv[4]), descale_bits(w[j].y >> 8, dec, inv[5]));
           o.w = narrow2<DSTK>(descale_bits(w[j].y >> 16, dec, inv[6]), descale_bits(w[j].y >> 24, dec, inv[7]));
         }
-        st_stream(d4 + idx, o);
+        st_stream_any(const_cast<uint8_t*>(elem_ptr<DSTK>(dst, (size_t)rr * cols + c0)), o);
       }
     }
   }
@@ -684,11 +713,11 @@ struct AxisPlan {
 
 // shapes of the per-channel launches; sizes are limited to what 32-bit row / vector counts hold
 template <int KIND>
-bool plan_axis(size_t rows, size_t cols, int cus, bool aligned, AxisPlan* p) {
+bool plan_axis(size_t rows, size_t cols, int cus, AxisPlan* p) {
   constexpr size_t VE = vec_elems<KIND>();
   if (rows > 0x7FFFFFFFu || cols > 0x7FFFFFFFu) return false;
-  p->fast = aligned && (cols % VE) == 0;
-  p->cols_vec = (uint32_t)(cols / VE);
+  p->fast = cols >= VE;
+  p->cols_vec = (uint32_t)((cols + VE - 1) / VE);
   const uint32_t per_chunk = kAxBlock * kAxUnroll;
   p->chunks = (p->cols_vec + per_chunk - 1) / per_chunk;
   p->strips = (p->cols_vec + 63) / 64;
@@ -716,17 +745,19 @@ hif8_status amax_axis(const void* src, size_t rows, size_t cols, int axis, float
   hif8_status s = ensure_init(&cus, nullptr);
   if (s != HIF8_OK) return s;
   AxisPlan p;
-  if (!plan_axis<SRCK>(rows, cols, cus, aligned_to(src, 16), &p)) return HIF8_ERR_ARG;
+  if (!plan_axis<SRCK>(rows, cols, cus, &p)) return HIF8_ERR_ARG;
   uint32_t* out = reinterpret_cast<uint32_t*>(d_amax);
-  const bool stores = p.fast && axis == 0 && p.chunks == 1 && rows * cols != 0;  // k_amax_rows writes every row itself
+  const bool stores = axis == 0 && p.chunks == 1 && rows * cols != 0;  // k_amax_rows and k_amax_axis_elem write every row themselves
   if (!stores) {
     s = launch_fill_u32(out, 0u, (uint32_t)nch, st);
     if (s != HIF8_OK || rows * cols == 0) return s;
   }
   if (!p.fast) {
-    hipLaunchKernelGGL(k_amax_axis_elem<SRCK>, dim3(grid_elem(rows * cols, cus)), dim3(256), 0, st, src, rows, cols, axis, out);
+    hipLaunchKernelGGL(k_amax_axis_elem<SRCK>, dim3(grid_elem(rows * cols, cus)), dim3(256), 0, st, src, rows,
+                       (uint32_t)cols, axis, out);
   } else if (axis == 0) {
-    hipLaunchKernelGGL(k_amax_rows<SRCK>, dim3((unsigned)(rows * p.chunks)), dim3(kAxBlock), 0, st, src, p.cols_vec, p.chunks, out);
+    hipLaunchKernelGGL(k_amax_rows<SRCK>, dim3((unsigned)(rows * p.chunks)), dim3(kAxBlock), 0, st, src, (uint32_t)cols,
+                       p.cols_vec, p.chunks, out);
   } else {
     // longer runs of rows than the casts use -- about one workgroup per CU -- because every
     // workgroup ends with one atomic per column (measured on [11008, 4096] BF16: 50 us with 64-row
@@ -741,7 +772,7 @@ hif8_status amax_axis(const void* src, size_t rows, size_t cols, int axis, float
     if (rpw < 64u) rpw = 64u;
     const uint32_t row_chunks = (uint32_t)((rows + rpw - 1) / rpw);
     hipLaunchKernelGGL((k_amax_cols<SRCK, kAmaxColsWaves>), dim3(row_chunks * p.strips), dim3(kAmaxColsWaves * 64), 0,
-                       st, src, (uint32_t)rows, p.cols_vec, p.strips, rpw, out);
+                       st, src, (uint32_t)rows, (uint32_t)cols, p.cols_vec, p.strips, rpw, out);
   }
   return finish_launch();
 }
@@ -758,8 +789,7 @@ hif8_status encode_axis(const void* src, uint8_t* dst, size_t rows, size_t cols,
   hif8_status s = ensure_init(&cus, &tb);
   if (s != HIF8_OK) return s;
   AxisPlan p;
-  const bool al = aligned_to(src, 16) && aligned_to(dst, SRCK == kSrcF32 ? 4 : 8);
-  if (!plan_axis<SRCK>(rows, cols, cus, al, &p)) return HIF8_ERR_ARG;
+  if (!plan_axis<SRCK>(rows, cols, cus, &p)) return HIF8_ERR_ARG;
   const uint64_t seed = sr_seed();
   if (!p.fast) {
     hipLaunchKernelGGL(k_encode_axis_elem<SRCK>, dim3(grid_elem(rows * cols, cus)), dim3(256), 0, st, src, dst, rows,
@@ -770,15 +800,15 @@ hif8_status encode_axis(const void* src, uint8_t* dst, size_t rows, size_t cols,
     constexpr int IMPL = decltype(impl_c)::value;
     if (axis == 0)
       hipLaunchKernelGGL((k_encode_rows<IMPL, SRCK>), dim3((unsigned)(rows * p.chunks)), dim3(kAxBlock), 0, st, src,
-                         dst, p.cols_vec, p.chunks, d_scale2, mode, seed, tb.enc_lut);
+                         dst, (uint32_t)cols, p.cols_vec, p.chunks, d_scale2, mode, seed, tb.enc_lut);
     else
       hipLaunchKernelGGL((k_encode_cols<IMPL, SRCK>), dim3(p.row_chunks * p.strips), dim3(kAxBlock), 0, st, src, dst,
-                         (uint32_t)rows, p.cols_vec, p.strips, p.rows_per_wg, d_scale2, mode, seed, tb.enc_lut);
+                         (uint32_t)rows, (uint32_t)cols, p.cols_vec, p.strips, p.rows_per_wg, d_scale2, mode, seed, tb.enc_lut);
   });
   return finish_launch();
 }
 
-// Fused per-row path when a row fits the registers of one workgroup and the fast-path alignment holds;
+// Fused per-row path when a row has at least one vector and fits the registers of one workgroup;
 // otherwise the three separate launches (same results).
 template <int SRCK>
 hif8_status quantize_rows(const void* src, uint8_t* dst, size_t rows, size_t cols, float target, int pow2, uint32_t mode,
@@ -793,9 +823,8 @@ hif8_status quantize_rows(const void* src, uint8_t* dst, size_t rows, size_t col
   hif8_status s = ensure_init(&cus, &tb);
   if (s != HIF8_OK) return s;
   constexpr size_t VE = vec_elems<SRCK>();
-  const bool al = aligned_to(src, 16) && aligned_to(dst, SRCK == kSrcF32 ? 4 : 8);
-  const size_t cols_vec = cols / VE;
-  if (!al || cols == 0 || (cols % VE) != 0 || cols_vec > (size_t)kQrBlock * 8) {
+  const size_t cols_vec = (cols + VE - 1) / VE;
+  if (cols < VE || cols_vec > (size_t)kQrBlock * 8) {
     s = amax_axis<SRCK>(src, rows, cols, 0, d_amax, st);
     if (s != HIF8_OK) return s;
     s = hif8host::launch_scale_from_amax(d_amax, d_scale2, (uint32_t)rows, target, pow2, st);
@@ -804,22 +833,28 @@ hif8_status quantize_rows(const void* src, uint8_t* dst, size_t rows, size_t col
   }
   const uint64_t seed = sr_seed();
   // enough workgroups to fill the chip (four of 512 lanes per CU), each walking several rows (measured flat from 3 to 8 per CU)
+  const bool by_wave = cols_vec <= (size_t)64 * kQrWaveVecs;
+  const size_t lanes = by_wave ? 64 : kQrBlock, want = by_wave ? (rows + kQrWaves - 1) / kQrWaves : rows;
   size_t wgs = (size_t)cus * 4;
-  if (wgs > rows) wgs = rows;
-  const int vpt = cols_vec <= (size_t)kQrBlock ? 1 : cols_vec <= (size_t)kQrBlock * 2 ? 2 : cols_vec <= (size_t)kQrBlock * 4 ? 4 : 8;
+  if (wgs > want) wgs = want;
+  const int vpt = cols_vec <= lanes ? 1 : cols_vec <= lanes * 2 ? 2 : cols_vec <= lanes * 4 ? 4 : 8;
   uint32_t* am = reinterpret_cast<uint32_t*>(d_amax);
   dispatch_impl_only(impl_no_alu(mode), [&](auto impl_c) {
     constexpr int IMPL = decltype(impl_c)::value;
-    auto go = [&](auto vpt_c) {
-      constexpr int VPT = decltype(vpt_c)::value;
-      hipLaunchKernelGGL((k_quant_rows<IMPL, SRCK, VPT>), dim3((unsigned)wgs), dim3(kQrBlock), 0, st, src, dst, (uint32_t)rows,
-                         (uint32_t)cols_vec, target, pow2, am, d_scale2, mode, seed, tb.enc_lut);
+    auto go = [&](auto vpt_c, auto lanes_c) {
+      constexpr int VPT = decltype(vpt_c)::value, LANES = decltype(lanes_c)::value;
+      hipLaunchKernelGGL((k_quant_rows<IMPL, SRCK, VPT, LANES>), dim3((unsigned)wgs), dim3(kQrBlock), 0, st, src, dst, (uint32_t)rows,
+                         (uint32_t)cols, (uint32_t)cols_vec, target, pow2, am, d_scale2, mode, seed, tb.enc_lut);
     };
-    using std::integral_constant;
-    if (vpt == 1) go(integral_constant<int, 1>{});
-    else if (vpt == 2) go(integral_constant<int, 2>{});
-    else if (vpt == 4) go(integral_constant<int, 4>{});
-    else go(integral_constant<int, 8>{});
+    auto vecs = [&](auto lanes_c) {
+      using std::integral_constant;
+      if (vpt == 1) go(integral_constant<int, 1>{}, lanes_c);
+      else if (vpt == 2) go(integral_constant<int, 2>{}, lanes_c);
+      else if (vpt == 4 || decltype(lanes_c)::value == 64) go(integral_constant<int, 4>{}, lanes_c);
+      else if constexpr (decltype(lanes_c)::value != 64) go(integral_constant<int, 8>{}, lanes_c);
+    };
+    if (by_wave) vecs(std::integral_constant<int, 64>{});
+    else vecs(std::integral_constant<int, kQrBlock>{});
   });
   return finish_launch();
 }
@@ -835,17 +870,16 @@ hif8_status decode_axis(const uint8_t* src, void* dst, size_t rows, size_t cols,
   hif8_status s = ensure_init(&cus, &tb);
   if (s != HIF8_OK) return s;
   AxisPlan p;
-  const bool al = aligned_to(dst, 16) && aligned_to(src, DSTK == kSrcF32 ? 4 : 8);
-  if (!plan_axis<DSTK>(rows, cols, cus, al, &p)) return HIF8_ERR_ARG;
+  if (!plan_axis<DSTK>(rows, cols, cus, &p)) return HIF8_ERR_ARG;
   if (!p.fast) {
     hipLaunchKernelGGL(k_decode_axis_elem<DSTK>, dim3(grid_elem(rows * cols, cus)), dim3(256), 0, st, src, dst, rows,
                        cols, axis, d_scale2);
   } else if (axis == 0) {
     hipLaunchKernelGGL(k_decode_rows<DSTK>, dim3((unsigned)(rows * p.chunks)), dim3(kAxBlock), 0, st, src, dst,
-                       p.cols_vec, p.chunks, d_scale2, tb.dec_lut);
+                       (uint32_t)cols, p.cols_vec, p.chunks, d_scale2, tb.dec_lut);
   } else {
     hipLaunchKernelGGL(k_decode_cols<DSTK>, dim3(p.row_chunks * p.strips), dim3(kAxBlock), 0, st, src, dst,
-                       (uint32_t)rows, p.cols_vec, p.strips, p.rows_per_wg, d_scale2, tb.dec_lut);
+                       (uint32_t)rows, (uint32_t)cols, p.cols_vec, p.strips, p.rows_per_wg, d_scale2, tb.dec_lut);
   }
   return finish_launch();
 }

@@ -42,6 +42,19 @@ __device__ __forceinline__ void st_stream(uint2* p, const uint2& v) {
 }
 __device__ __forceinline__ void st_stream(uint32_t* p, uint32_t v) { __builtin_nontemporal_store(v, p); }
 
+// The same at any address (the hardware takes them): W = uint4, uint2 or uint32_t.
+template <typename W>
+__device__ __forceinline__ W ld_stream_any(const void* p) {
+  typedef uint32_t V __attribute__((ext_vector_type(sizeof(W) / 4), aligned(1)));
+  const V t = __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
+  return __builtin_bit_cast(W, t);
+}
+template <typename W>
+__device__ __forceinline__ void st_stream_any(void* p, const W& v) {
+  typedef uint32_t V __attribute__((ext_vector_type(sizeof(W) / 4), aligned(1)));
+  __builtin_nontemporal_store(__builtin_bit_cast(V, v), reinterpret_cast<V*>(p));
+}
+
 // Vector unit = one 16-byte source load per lane (decode: one lane's worth of codes).  A tile
 // is blockDim.x * U vector units.  The first tile's loads are issued before `prologue` (table
 // staging + barrier) runs, so the staging latency overlaps with the first HBM round trip.

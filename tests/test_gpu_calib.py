@@ -249,3 +249,49 @@ def test_per_channel_unaligned_base_and_special_values(h):
         assert_same_bytes(f32_bits(am), w.view(np.uint32), "special amax")
         w_sc = np.array([orc.scale_from_amax(a, 32768.0, False) for a in w], np.float32)
         assert np.array_equal(sc.cpu().numpy()[:, 0], w_sc)   # degenerate channels (0, Inf, NaN) get scale 1
+
+
+# one below, at and above a vector (4 or 8 values); a wavefront's vectors of a row (64 to 256) and one more; a workgroup's (512 to 4096) and one more,
+# which takes the three launches; several chunks of a row; many short rows; strips of columns
+@pytest.mark.parametrize("rows,cols", [(700, 1), (65, 3), (3000, 7), (33, 9), (40, 513), (9, 1021), (2500, 259), (17, 2047), (6, 2051), (5, 4099), (3, 16381),
+                                       (2, 32771), (300, 1547)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_per_channel_any_columns_and_address(h, rows, cols, off):
+    """Rows that start anywhere (odd numbers of columns, a base one element or one byte off): bit for bit the oracle's, nothing
+    written outside."""
+    g = torch.Generator(device=dev()).manual_seed(rows * 31 + cols)
+    n = rows * cols
+    xf = torch.randn(rows, cols, generator=g, device=dev()) * torch.exp2(torch.rand((rows, 1), generator=g, device=dev()) * 14 - 7)
+    for kind in ("f32", "bf16", "f16"):
+        flat = xf.to({"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[kind]).reshape(-1)
+        src = torch.full((n + 2,), 3e4, dtype=flat.dtype, device=dev())  # larger than the values: a read outside shows
+        src[off:off + n] = flat
+        x = src[off:off + n]
+        xn = as_kind(flat.float().view(rows, cols), kind)[1]
+        for axis in (0, 1):
+            nch = rows if axis == 0 else cols
+            am, sc = torch.full((nch,), 5.0, device=dev()), torch.empty(nch, 2, device=dev())
+            getattr(h, "hif8_amax_axis_" + kind)(x.data_ptr(), rows, cols, axis, am)
+            h.hif8_scale_from_amax_n(am, sc, nch, 32768.0, 1)
+            w_am = orc.amax_axis(xn, KINDS[kind], axis)
+            assert_same_bytes(f32_bits(am), w_am.view(np.uint32), "amax %s %d" % (kind, axis))
+            w_sc = np.array([orc.scale_from_amax(a, 32768.0, True) for a in w_am], np.float32)
+            for mode in (TA, HR, SR):
+                codes = torch.full((n + 2,), 0xAA, dtype=torch.uint8, device=dev())
+                getattr(h, "hif8_encode_axis_" + kind)(x.data_ptr(), codes.data_ptr() + off, rows, cols, axis, sc, mode)
+                want = orc.encode_axis(xn, w_sc, KINDS[kind], axis, mode).reshape(-1)
+                got = codes.cpu().numpy()
+                assert_same_bytes(got[off:off + n], want, "encode %s %d %#x" % (kind, axis, mode))
+                assert np.all(got[:off] == 0xAA) and np.all(got[off + n:] == 0xAA)
+                if axis == 0:
+                    am2, sc2 = torch.full((rows,), 5.0, device=dev()), torch.empty(rows, 2, device=dev())
+                    codes.fill_(0xAA)
+                    getattr(h, "hif8_quantize_rows_" + kind)(x.data_ptr(), codes.data_ptr() + off, rows, cols, am2, sc2, 32768.0, 1, mode)
+                    assert np.array_equal(codes.cpu().numpy(), got)
+                    assert torch.equal(am2.view(torch.int32), am.view(torch.int32)) and torch.equal(sc2.view(torch.int32), sc.view(torch.int32))
+            out = torch.full((n + 2,), 7.0, dtype=flat.dtype, device=dev())
+            getattr(h, "hif8_decode_axis_" + kind)(codes.data_ptr() + off, out[off:].data_ptr(), rows, cols, axis, sc)
+            wd = orc.decode_axis(want.reshape(rows, cols), w_sc, KINDS[kind], axis)
+            gd = f32_bits(out) if kind == "f32" else bits16(out)
+            assert_same_bytes(gd[off:off + n], (wd.view(np.uint32) if kind == "f32" else wd).reshape(-1), "decode %s %d" % (kind, axis))
+            assert torch.all(out[:off] == 7.0) and torch.all(out[off + n:] == 7.0)
