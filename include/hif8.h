@@ -599,9 +599,8 @@ hif8_status hif8_gemm_expanded_sqerr(const uint16_t* a, const uint16_t* b, const
  * hif8_gemm_* on code operands with a workspace: both code matrices are expanded to bfloat16 into the
  * workspace (hif8_expand_bf16) and multiplied by the expanded-operand kernel -- two or three launches on `stream`, and
  * for matrix-core-bound shapes about two thirds of the time of hif8_gemm_* (whose kernel expands the codes on
- * their way into LDS and is bound by that work; between about 128 and 1000 rows of a small product it is the faster
- * one, since nothing has to be written first).  Small products with up to 128 rows in one operand are taken
- * straight from the codes instead, in one launch, and leave the workspace unused.  Arguments, result and error bound
+ * their way into LDS and is bound by that work).  Small products are taken
+ * straight from the codes where that is faster, in one launch, and leave the workspace unused.  Arguments, result and error bound
  * as for hif8_gemm_* (the result equals that of hif8_gemm_expanded_* on the expanded operands bit for bit); any K and
  * any alignment of the code matrices.
  * workspace: device memory, 16-byte aligned, at least hif8_gemm_workspace_bytes(M, N, K) bytes

@@ -329,7 +329,7 @@ static hif8_status gemm_dispatch(const uint8_t* A, const uint8_t* B, void* out, 
   if (s != HIF8_OK) return s;
   const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
   const bool fast = K != 0 && (K % 16) == 0 && aligned_to(A, 16) && aligned_to(B, 16);
-  if (!fast || g_gemm_variant == 12 || (g_gemm_variant == 0 && small_problem(M, N, K, true, EPI == EPI_ERR)))
+  if (!fast || g_gemm_variant == 12 || (g_gemm_variant == 0 && small_route(M, N, K, true, EPI == EPI_ERR)))
     return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st);
   int variant = g_gemm_variant;
   uint32_t split = 0;
@@ -372,6 +372,10 @@ static hif8_status gemm_ws(const uint8_t* A, const uint8_t* B, void* out, const 
   if (expanded_variant() == 0 && (M < N ? M : N) <= kSmallCodesRows && small_problem(M, N, expanded_ld(K), false, EPI == EPI_ERR))
     return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st);
   const size_t ld = expanded_ld(K);
+  if (EPI != EPI_ERR && expanded_variant() == 0 && (M < N ? M : N) > kSmallCodesRows && small_route(M, N, ld, false, false)) {
+    const uint32_t waves = small_codes_waves(M, N, K);
+    if (waves != 0u) return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st, waves);
+  }
   uint16_t* xa = reinterpret_cast<uint16_t*>(ws);
   uint16_t* xb = xa + M * ld;  // M * ld * 2 bytes is a multiple of 128: still 16-byte aligned
   const hif8_status s = expand_rows(A, M, B, N, K, xa, ld, st);

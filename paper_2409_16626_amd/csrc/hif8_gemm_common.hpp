@@ -319,9 +319,10 @@ hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const
                           size_t N, size_t ld, float descale, hipStream_t st, const Batch& batch = Batch{});
 
 // ---- few output tiles, any K and alignment of code operands (hif8_gemm_s.hip) ----
-// out = (A x B^T) * descale; expanded: operands are bfloat16 of pitch K (a multiple of 64), else codes of pitch K
+// out = (A x B^T) * descale; expanded: operands are bfloat16 of pitch K (a multiple of 64), else codes of pitch K; waves: wavefronts that share K,
+// 0: the plan's
 template <int EPI>
 hif8_status gemm_small(const void* A, const void* B, bool expanded, void* out, const float* ref, double* err, size_t M,
-                       size_t N, size_t K, float descale, hipStream_t st);
+                       size_t N, size_t K, float descale, hipStream_t st, uint32_t waves = 0);
 
 }  // namespace hif8gemm

@@ -334,35 +334,45 @@ static hif8_status launch_s(const void* A, const void* B, void* out, const float
 
 template <int OP, int EPI>
 static hif8_status gemm_small_op(const void* A, const void* B, void* out, const float* ref, double* err, size_t M, size_t N,
-                                 size_t K, float descale, hipStream_t st) {
+                                 size_t K, float descale, hipStream_t st, uint32_t waves) {
   const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
   int cus = 0;
   const hif8_status s = ensure_init(&cus, nullptr);
   if (s != HIF8_OK) return s;
-  const SmallPlan p = small_plan(M, N, K, OP == OP_CODES, EPI == EPI_ERR);
+  const SmallPlan p = small_choice(M, N, K, OP == OP_CODES, EPI == EPI_ERR, waves);
+  auto run = [&](auto launch) { return launch(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st); };
   switch (p.tm * 10 + p.tn) {
     case 11:
       if constexpr (OP == OP_CODES) {
-        if (M <= 8) return launch_s<OP, 1, 1, 1, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
+        if (M <= 8) return run(launch_s<OP, 1, 1, 1, EPI>);
       }
-      return launch_s<OP, 1, 1, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
-    case 12: return launch_s<OP, 1, 2, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
-    case 22: return launch_s<OP, 2, 2, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
-    case 24: return launch_s<OP, 2, 4, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
-    default: return launch_s<OP, 4, 4, 0, EPI>(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st);
+      return run(launch_s<OP, 1, 1, 0, EPI>);
+    case 12: return run(launch_s<OP, 1, 2, 0, EPI>);
+    case 22: return run(launch_s<OP, 2, 2, 0, EPI>);
+    case 24: return run(launch_s<OP, 2, 4, 0, EPI>);
+    case 44: return run(launch_s<OP, 4, 4, 0, EPI>);
   }
+  if constexpr (EPI != EPI_ERR) {
+    switch (p.tm * 10 + p.tn) {
+      case 13: return run(launch_s<OP, 1, 3, 0, EPI>);
+      case 23: return run(launch_s<OP, 2, 3, 0, EPI>);
+      case 34: return run(launch_s<OP, 3, 4, 0, EPI>);
+      case 43: return run(launch_s<OP, 4, 3, 0, EPI>);
+    }
+  }
+  return HIF8_ERR_ARG;  // no such tile in the plans
 }
 
 template <int EPI>
 hif8_status gemm_small(const void* A, const void* B, bool expanded, void* out, const float* ref, double* err, size_t M, size_t N,
-                       size_t K, float descale, hipStream_t st) {
-  return expanded ? gemm_small_op<OP_BF16, EPI>(A, B, out, ref, err, M, N, K, descale, st)
-                  : gemm_small_op<OP_CODES, EPI>(A, B, out, ref, err, M, N, K, descale, st);
+                       size_t K, float descale, hipStream_t st, uint32_t waves) {
+  return expanded ? gemm_small_op<OP_BF16, EPI>(A, B, out, ref, err, M, N, K, descale, st, waves)
+                  : gemm_small_op<OP_CODES, EPI>(A, B, out, ref, err, M, N, K, descale, st, waves);
 }
 
-template hif8_status gemm_small<EPI_F32>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t);
-template hif8_status gemm_small<EPI_BF16>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t);
-template hif8_status gemm_small<EPI_F16>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t);
-template hif8_status gemm_small<EPI_ERR>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t);
+template hif8_status gemm_small<EPI_F32>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t, uint32_t);
+template hif8_status gemm_small<EPI_BF16>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t, uint32_t);
+template hif8_status gemm_small<EPI_F16>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t, uint32_t);
+template hif8_status gemm_small<EPI_ERR>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t, uint32_t);
 
 }  // namespace hif8gemm

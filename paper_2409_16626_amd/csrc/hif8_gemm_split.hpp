@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <cmath>
+
 namespace hif8gemm {
 
 // A ragged last round of 256 x 256 tiles leaves most compute units idle for a whole tile time.  When that
@@ -208,6 +210,18 @@ inline size_t small_resident(uint32_t tm, uint32_t tn, uint32_t waves, bool code
   const uint32_t by_regs = 4u * (blocks == 1u ? 6u : blocks == 2u ? 5u : blocks == 4u ? 4u : blocks == 8u && !codes ? 3u : 2u) / waves;
   return 256u * (by_lds < by_regs ? by_lds : by_regs);
 }
+// The same on one compute unit, for the kernels that store: by the registers that they take (a wavefront's, codes / expanded: 1 x 1 67 (half-row form 75) / 60, 1 x 2 87 / 76, 1 x 3 107 /
+// 96, 2 x 2 120 / 112, 2 x 3 140 / 130, 2 x 4 160 / 152, 3 x 4, 4 x 3 and 4 x 4 192 to 236).
+inline uint32_t small_resident_stored(const SmallPlan& p, bool codes) {
+  const uint32_t by_lds = 160u * 1024u / (512u + p.waves * (p.tm + p.tn) * 2048u), blocks = p.tm * p.tn;
+  const uint32_t per_simd = blocks == 1u ? (codes ? 6u : 8u) : blocks == 2u ? (codes ? 5u : 6u) : blocks == 3u ? (codes ? 4u : 5u) : blocks == 4u ? 4u : blocks <= 8u ? 3u : 2u;
+  const uint32_t by_regs = 4u * per_simd / p.waves, most = by_lds < by_regs ? by_lds : by_regs;
+  return most == 0u ? 1u : most;
+}
+// What a kernel can be launched with: 1024 lanes up to four blocks, 512 above, and LDS for the wavefronts' areas.
+inline bool small_fits(const SmallPlan& p) {
+  return p.waves <= (p.tm * p.tn <= 4u ? 16u : 8u) && 512u + p.waves * (p.tm + p.tn) * 2048u <= 160u * 1024u;
+}
 // The wavefronts' shares of K in pairs of units of 64, 128 codes: whole cache lines for every wavefront, unless single units give the longest
 // share fewer of them (us, single units / pairs, the weight from memory, eight wavefronts: 2 x 4096 x 11008, 172 units, 14.7 / 14.4, 8 x 4096 x 2624, 41,
 // 6.2 / 6.0, but 8 x 4096 x 5200, 82, 9.1 / 9.3, 509 x 1003 x 2049, 33, 15.7 / 18).
@@ -235,6 +249,126 @@ inline SmallPlan small_plan(size_t M, size_t N, size_t K, bool codes, bool sqerr
   if (s <= kSmallCodesRows && short_k) return plan(2, 2, 4);
   if (s <= kSmallCodesRows || (codes && M * N <= (size_t)33 * 65536)) return plan(2, 4, tiles(2, 4) <= 256 ? 8 : 4);
   return plan(4, 4, !codes && tiles(4, 4) <= 256 ? 8 : 4);
+}
+
+// Time of the small-tile kernel with stored results, us, as far as the tile and the wavefronts decide it.  A compute unit has `turns` tiles at most.
+// Either its LDS (stages, look-ups, fragments) is busy with all their rows; or, with few wavefronts on it, each of them works off its share of
+// K one stage after the other, and as many tiles as fit at a time go side by side; then the partial tiles are added.  The constants
+// are a least-squares fit, in the logarithm, to 296 shapes of 4 to 1000 rows on codes and 178 on expanded operands, weights from memory, each in up to 40
+// tiles and numbers of wavefronts: 13 and 12 % off on average.
+struct SmallRates {
+  double base, lds, wave, unit, turn, add, memory;
+};
+constexpr SmallRates kSmallRates[2] = {{1.88, 0.024, 0.078, 0.048, 1.49, 0.042, 1.36}, {2.2, 0.036, 0.2125, 0.0, 1.36, 0.054, 0.97}};  // expanded, codes
+struct SmallCost {
+  size_t M, N;
+  bool codes;
+  uint32_t units, tiles_m[5], tiles_n[5];  // of 16 to 64 rows and columns
+  double memory;                           // fourth power of the memory's part
+
+  SmallCost(size_t m, size_t n, size_t k, bool c) : M(m), N(n), codes(c), units((uint32_t)((k + 63) / 64)) {
+    auto count = [](uint32_t (&t)[5], size_t rows) {
+      t[1] = (uint32_t)((rows + 15) / 16);
+      t[2] = (t[1] + 1) / 2;
+      t[3] = (t[1] + 2) / 3;
+      t[4] = (t[1] + 3) / 4;
+    };
+    count(tiles_m, m);
+    count(tiles_n, n);
+    memory = fourth((double)(m + n) * units * (codes ? 64.0 : 128.0) / 6e6 * kSmallRates[c ? 1 : 0].memory);
+  }
+  static double fourth(double x) { return x * x * x * x; }
+  // what plans are compared by: the largest of the parts, more where two are close
+  double score(const SmallPlan& p) const {
+    const SmallRates& r = kSmallRates[codes ? 1 : 0];
+    const uint64_t tiles = (uint64_t)tiles_m[p.tm] * tiles_n[p.tn], of_unit = (tiles + 255u) / 256u;
+    const uint32_t turns = of_unit > 0xFFFFFF00u ? 0xFFFFFF00u : (uint32_t)of_unit, resident = small_resident_stored(p, codes);
+    const double rows = (codes && M <= 8 && p.tm * p.tn == 1u ? 0.5 : (double)p.tm) + p.tn;  // in blocks of 16; the half-row form
+    const double lds = (double)turns * units * rows * r.lds;
+    const double wave = (double)((turns + resident - 1) / resident) * ((units + p.waves - 1) / p.waves * (rows * r.wave + r.unit) + r.turn + r.add * p.waves * (p.tm * p.tn));
+    return fourth(lds) + fourth(wave) + memory;
+  }
+  double us(const SmallPlan& p) const { return kSmallRates[codes ? 1 : 0].base + std::sqrt(std::sqrt(score(p))); }
+};
+
+// Tile and wavefronts: the cheapest by SmallCost of the tiles that are built.  What that changes against small_plan(), whose lines were measured at
+// few sizes: a number of tiles just below that of the compute units, or with each of them two, instead of a little more; small tiles with many
+// wavefronts where there are few tiles and a long K; three blocks of columns or rows.  Measured (us, small_plan / now, weights from memory): codes 42 x 816 x 3693
+// 14.2 / 7.7, 46 x 5162 x 7536 38 / 28, 48 x 10642 x 8528 63 / 45, 106 x 6133 x 7600 61 / 41, 173 x 3951 x 6832 53 / 36; expanded 80 x 1644 x 2528 10.0 /
+// 6.9, 128 x 674 x 7456 18.8 / 10, 200 x 594 x 4176 18.6 / 7.1, 400 x 835 x 3456 16.9 / 10.  Over the shapes above it is 1.8 % (codes) and 3 %
+// (expanded) behind the best tile for each; small_plan 22 and 26 %.
+// The wavefronts decide the bits.  Up to kSmallCodesRows rows they are those of the code operands, for both kinds; the squared error takes the wavefronts of the stored product, with
+// the tiles of its kernels and 0.01 us for each workgroup's atomic.  With fewer than four wavefronts (more tiles than the chip holds, a short K)
+// small_plan() stands.  waves != 0: that number is asked for.
+// Another plan than small_plan()'s has to promise 7 % (the fit's own error; without that 12 of 296 shapes on codes lost 4 to 10 %, with it 2).  No 16
+// wavefronts up to 16 rows: 5 to 7 % better or worse from shape to shape.
+constexpr double kSmallGain = 0.93;
+// 16 wavefronts have to promise 12 % over 8 (here fourth powers): where they do less, codes gain nothing and expanded operands, which take over the
+// split, lose 8 to 10 % (24 x 3398 x 5600 12.9 / 13.0 and 9.0 / 10.0).
+constexpr double kSixteen = 1.6;
+// What the host takes for a launch: with less on the GPU nothing is gained, and the look at all tiles would come on top.
+// Up to 16 rows it pays from larger products on (16 x 4447 x 7104 16.9 us, now 14.7, 16 x 10257 x 10453 41.8, 33.5; 16 x 1131 x 4272 8.0, 8.0).
+constexpr double kLaunchBound = 5.2, kFewRowsBound = 9.0;
+constexpr uint32_t kSmallTiles[][2] = {{1, 1}, {1, 2}, {1, 3}, {2, 2}, {2, 3}, {2, 4}, {3, 4}, {4, 3}, {4, 4}};
+inline double atomics(const SmallCost& c, const SmallPlan& p, size_t K) {  // of a squared error, see launch_s
+  const double wgs = (double)c.tiles_m[p.tm] * c.tiles_n[p.tn];
+  return K < 4096 && wgs > 1024.0 ? 1024.0 : wgs;
+}
+inline SmallPlan small_choice(size_t M, size_t N, size_t K, bool codes, bool sqerr = false, uint32_t waves = 0) {
+  const size_t s = M < N ? M : N, ld = (K + 63) / 64 * 64;
+  const SmallPlan base = small_plan(M, N, K, codes, sqerr);
+  if (waves == 0u) {
+    const bool both = s <= kSmallCodesRows;  // kinds that have to agree
+    if ((both || codes) && small_plan(M, N, K, true, false).waves < 4u) return base;
+    if ((both || !codes) && small_plan(M, N, K, false, false).waves < 4u) return base;
+    if (both && (!codes || sqerr)) waves = small_choice(M, N, K, true).waves;
+    else if (sqerr) waves = small_choice(M, N, K, codes).waves;
+  }
+  const SmallCost cost(M, N, ld, codes);
+  const bool may_stay = waves == 0u || waves == base.waves;
+  const double base_us = cost.us(base);
+  if (may_stay && base_us < (s <= 16 ? kFewRowsBound : kLaunchBound)) return base;
+  SmallPlan best = base;
+  double least = 1e300;
+  for (const auto& t : kSmallTiles) {
+    if (16u * (t[0] - 1u) >= M || 16u * (t[1] - 1u) >= N) continue;  // a block outside the matrix
+    for (uint32_t w = s <= 16 ? 8 : 16; w >= 4u; w /= 2u) {
+      const SmallPlan p{t[0], t[1], w};
+      if (waves != 0u ? w != waves : w > 4u && w / 2u * kShareK >= ld) continue;  // no wavefronts without a share
+      if (!small_fits(p) || (sqerr && (p.tm == 3u || p.tn == 3u))) continue;
+      const double c = (cost.score(p) + (sqerr ? SmallCost::fourth(0.01 * atomics(cost, p, K)) : 0.0)) * (w == 16u ? kSixteen : 1.0);
+      if (c < least) {
+        best = p;
+        least = c;
+      }
+    }
+  }
+  return may_stay && cost.us(best) > kSmallGain * base_us ? base : best;
+}
+
+// Products that go to the small-tile kernel: small_problem()'s, whose lines were drawn with small_plan(), and of the other stored products those for
+// which SmallCost is 15 % below what the tiled kernels take at least while every 128 x 128 tile has a compute unit (codes: half of one) to itself (us,
+// weights from memory, tiled / small tiles: codes, 5 + 0.021 to 0.026 K at best, 300 x 9133 x 6368 165 / 112, 700 x 4177 x 5136 131 / 95, but
+// 1000 x 7514 x 5136 171 / 211, 1375 x 2571 x 2240 51 / 58; expanded, 4 + 0.0055 K, up to 256 rows, where few tiles wait for the memory, 0.0065: 160 x 1086 x 448
+// 7.1 / 4.6, 200 x 2730 x 640 8.0 / 6.2, 135 x 1959 x 964 9.5 / 7.0, but 256 x 10456 x 4661 51 / 60, 512 x 3521 x 4496 28.6 / 31.8, 931 x 1244 x 828 9.8 / 11.1;
+// squared error, whose atomics come on top, 185 x 7315 x 6047 37 / 45, 782 x 806 x 274 8.2 / 10.3).
+inline bool small_route(size_t M, size_t N, size_t K, bool codes, bool sqerr) {
+  if (small_problem(M, N, K, codes, sqerr)) return true;
+  const size_t s = M < N ? M : N, tiles = ((M + 127) / 128) * ((N + 127) / 128);
+  if (s <= (codes ? 32 : kSmallCodesRows) || tiles > (codes ? 512u : 256u) || K < 320 || sqerr) return false;  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
+  const double k = (double)K, tiled = codes ? 5 + (tiles <= 256 ? 0.021 : 0.026) * k : 4 + (s <= 256 ? 0.0065 : 0.0055) * k;
+  return SmallCost(M, N, K, codes).us(small_choice(M, N, K, codes)) < 0.85 * tiled;
+}
+
+// A product through the workspace, of operands whose expansions would go to the small-tile kernel with more than kSmallCodesRows rows: straight from the codes with
+// the expansions' wavefronts, which gives their bits, where that is faster than writing them (2.5 us and 3 bytes an element; us, expanded first / from
+// the codes: 130 x 1477 x 2730 20.2 / 11.4, 168 x 981 x 1216 14.6 / 8, 454 x 1143 x 5168 28 / 25).  Returns those wavefronts, 0: expand.
+inline uint32_t small_codes_waves(size_t M, size_t N, size_t K) {
+  const size_t ld = (K + 63) / 64 * 64;
+  const SmallPlan x = small_choice(M, N, ld, false);
+  if (x.waves < 4u) return 0;
+  const double expand = 2.5 + (double)(M + N) * (double)ld * 3.0 / 5.5e6;
+  return SmallCost(M, N, K, true).us(small_choice(M, N, K, true, false, x.waves)) < SmallCost(M, N, ld, false).us(x) + expand ? x.waves : 0u;
 }
 
 // Workgroup -> tile of the expanded-operand kernel.  The hardware deals consecutive workgroups round-robin over the

@@ -99,6 +99,15 @@ uint32_t devfn_small_plan(size_t M, size_t N, size_t K, int codes, int sqerr, ui
   *waves = p.waves;
   return p.tm * 100 + p.tn * 10;
 }
+// the kernel's choice (waves_asked != 0: that many wavefronts); whether a product goes there; wavefronts with which a product through
+// the workspace is taken from the codes
+uint32_t devfn_small_choice(size_t M, size_t N, size_t K, int codes, int sqerr, uint32_t waves_asked, uint32_t* waves) {
+  const hif8gemm::SmallPlan p = hif8gemm::small_choice(M, N, K, codes != 0, sqerr != 0, waves_asked);
+  *waves = p.waves;
+  return p.tm * 100 + p.tn * 10;
+}
+int devfn_small_route(size_t M, size_t N, size_t K, int codes, int sqerr) { return hif8gemm::small_route(M, N, K, codes != 0, sqerr != 0); }
+uint32_t devfn_small_codes_waves(size_t M, size_t N, size_t K) { return hif8gemm::small_codes_waves(M, N, K); }
 int devfn_small_by_pairs(size_t K, uint32_t waves) { return hif8gemm::small_by_pairs(K, waves); }
 int devfn_small_problem(size_t M, size_t N, size_t K, int codes, int sqerr) { return hif8gemm::small_problem(M, N, K, codes != 0, sqerr != 0); }
 // expanded-operand GEMM: the launches of its plan, 4 numbers each: tile (0 = 256 x 256, 1 = 256 x 192, 2 = 128 x 128), LDS

@@ -242,6 +242,56 @@ def test_small_gemm_plan(dev):
             assert got[0][0] == got[1][0] and (got[0][1] == got[1][1] or min(got[0][1], got[1][1]) >= -(-ld // 128))
 
 
+def test_small_gemm_choice(dev):
+    """Only tiles that are built, lanes and LDS within a launch's limits, wavefronts with a share of K; up to 128 rows one K split for codes and expanded
+    operands, and above it the codes can be asked for the expanded operands' split; the squared error's split that of the stored product; small_problem()'s products stay, and what the workspace takes
+    from the codes is what the expanded operands would take to the same kernel."""
+    f, route, waves_of = dev.devfn_small_choice, dev.devfn_small_route, dev.devfn_small_codes_waves
+    f.restype, f.argtypes = ctypes.c_uint32, [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.c_int, ctypes.c_uint32, ctypes.POINTER(ctypes.c_uint32)]
+    route.restype, route.argtypes = ctypes.c_int, [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.c_int]
+    waves_of.restype, waves_of.argtypes = ctypes.c_uint32, [ctypes.c_size_t] * 3
+    small = dev.devfn_small_problem
+    small.restype, small.argtypes = ctypes.c_int, [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.c_int]
+
+    def plan(M, N, K, codes, asked=0, sqerr=0):
+        w = ctypes.c_uint32(0)
+        return f(M, N, K, codes, sqerr, asked, ctypes.byref(w)), w.value
+
+    assert plan(48, 10642, 8528, 1) == (340, 8) and plan(42, 816, 3693, 1)[0] == 110 and plan(64, 11008, 4096, 1) == (430, 8) and plan(32, 11008, 4096, 1) == (230, 8)
+    tiles = (110, 120, 130, 220, 230, 240, 340, 430, 440)
+    rng = np.random.default_rng(6)
+    seen = set()
+    for i in range(4000):
+        M, N, K = (int(2.0 ** rng.uniform(0, 20 if i % 4 == 0 else 13)) for _ in range(3))
+        ld = -(-K // 64) * 64
+        got = [plan(M, N, k, c) for c, k in ((0, ld), (1, K))]
+        checked = list(got)
+        if min(M, N) > 128 and got[0][1] >= 4:
+            checked.append(plan(M, N, K, 1, got[0][1]))
+            assert checked[-1][1] == got[0][1]
+        for t, w in checked:
+            tm, tn = t // 100, t // 10 % 10
+            assert t in tiles and w in (1, 2, 4, 8, 16) and w <= (16 if tm * tn <= 4 else 8)
+            assert 512 + w * (tm + tn) * 2048 <= 160 * 1024 and (w <= 4 or w // 2 < -(-ld // 128))
+        seen.update(t for t, w in got)
+        for (_, w), codes, k in zip(got, (0, 1), (ld, K)):  # the squared error of the stored product's bits
+            t, we = plan(M, N, k, codes, 0, 1)
+            assert t in (110, 120, 220, 240, 440) and (we == w or min(w, we) >= -(-ld // 128)) and we <= (16 if t in (110, 120, 220) else 8)
+        if min(M, N) <= 128:
+            assert got[0][1] == got[1][1] or min(got[0][1], got[1][1]) >= -(-ld // 128)
+        for codes, k in ((0, ld), (1, K)):
+            assert all(not small(M, N, k, codes, e) or route(M, N, k, codes, e) for e in (0, 1))
+            assert route(M, N, k, codes, 1) == small(M, N, k, codes, 1)
+        if min(M, N) > 128 and waves_of(M, N, K):
+            assert waves_of(M, N, K) == got[0][1] >= 4
+    assert seen == set(tiles)
+    # both sides of the routes' lines: small tiles, tiled
+    for codes, yes, no in ((1, [(700, 4177, 5136), (300, 9133, 6368)], [(1000, 7514, 5136), (512, 10419, 3392)]),
+                           (0, [(160, 1086, 448), (200, 2730, 640), (135, 1959, 1024)], [(256, 10456, 4672), (512, 3521, 4544), (256, 10236, 448)])):
+        assert all(route(*x, codes, 0) for x in yes) and not any(route(*x, codes, 0) for x in no)
+    assert waves_of(130, 1477, 2730) and not waves_of(1000, 1000, 100000)
+
+
 # (M, N, K) measured faster in small tiles, then those measured faster in the tiled kernels, in the kernels' own time
 SMALL_OR_TILED = {
     ("codes", "store"): ([(8, 11008, 4096), (1, 200000, 16), (32, 8192, 64), (32, 200000, 64), (64, 8000, 64), (128, 8192, 64), (512, 2048, 64),

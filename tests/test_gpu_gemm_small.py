@@ -159,3 +159,28 @@ def test_small_gemm_more_tiles_than_workgroups(h):
     h.hif8_gemm_f32(on_gpu(ca), on_gpu(cb), out, M, N, K, 1.0, 1.0)
     v = np.array([orc.decode_value(c) if np.isfinite(orc.decode_value(c)) else 0.0 for c in range(256)], np.float32)
     assert np.array_equal(out.cpu().numpy(), v[ca] @ v[cb].T)
+
+
+# tiles of three blocks of rows or columns (two of 1 x 3, two of 2 x 3, 3 x 4, 4 x 3), then others; edges of their blocks, rows at odd addresses, a K with a remainder; codes, the
+# workspace above 128 rows (from the codes) and the expanded operands give the same bits
+@pytest.mark.parametrize("M,N,K", [(200, 643, 1999), (16, 10641, 4097), (130, 2001, 1500), (36, 5700, 1999), (130, 10001, 577), (100, 5701, 1999), (130, 1477, 577),
+                                   (173, 2000, 577), (1266, 148, 1345), (255, 257, 2049)])
+def test_small_gemm_tiles_of_three_blocks(h, M, N, K):
+    rng = np.random.default_rng(M + N + K)
+    a, b, ld = on_gpu(random_codes(rng, (M, K), "cast_normal"), 1), on_gpu(random_codes(rng, (N, K), "cast_normal"), 1), h.hif8_expanded_ld(K)
+    xa, xb = (torch.empty(r, ld, dtype=torch.bfloat16, device=dev()) for r in (M, N))
+    h.hif8_expand_bf16(a, M, K, xa, ld)
+    h.hif8_expand_bf16(b, N, K, xb, ld)
+    ws = torch.empty(h.hif8_gemm_workspace_bytes(M, N, K), dtype=torch.uint8, device=dev())
+    want, sums = xa.double() @ xb.double().t() / 4.0, xa.double().abs() @ xb.double().abs().t() / 4.0
+    got = {}
+    for name, call in (("codes", lambda o: h.hif8_gemm_f32(a, b, o, M, N, K, 8.0, 0.5)), ("ws", lambda o: h.hif8_gemm_ws_f32(a, b, o, M, N, K, ws, 8.0, 0.5)),
+                       ("expanded", lambda o: h.hif8_gemm_expanded_f32(xa, xb, o, M, N, K, ld, 8.0, 0.5))):
+        out = torch.full((M * N + 8,), 7.0, dtype=torch.float32, device=dev())
+        call(out)
+        assert torch.all(out[M * N:] == 7.0)
+        got[name] = out[:M * N].view(M, N)
+        assert torch.all((got[name].double() - want).abs() <= K * 2.0 ** -23 * sums), name
+    assert torch.equal(got["ws"].view(torch.int32), got["expanded"].view(torch.int32))
+    if min(M, N) <= 128:
+        assert torch.equal(got["codes"].view(torch.int32), got["ws"].view(torch.int32))
