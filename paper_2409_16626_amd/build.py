@@ -1,7 +1,8 @@
 """Builds libhif8.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree.
 
 Every .hip / .cpp file under csrc/ is one translation unit; they are compiled in parallel
-into _build/ and linked into one shared library.
+into _build/ and linked into one shared library.  binding/native_call.cpp, the marshalling of Python arguments,
+becomes an extension module of its own (g++, Python's and torch's headers), _native_call.so.
 """
 import glob
 import os
@@ -13,6 +14,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJDIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libhif8.so")
+NATIVE_SRC = os.path.join(PKG, "binding", "native_call.cpp")
+NATIVE = os.path.join(PKG, "_native_call.so")
 
 
 def sources():
@@ -33,6 +36,33 @@ HIPCC_FLAGS = [
 ]
 
 
+def build_native(force: bool = True, verbose: bool = False) -> str:
+    """The extension module that hif8.py calls the library through."""
+    inputs = [NATIVE_SRC, os.path.join(ROOT, "include", "hif8.h")]
+    if not force and os.path.exists(NATIVE) and all(os.path.getmtime(f) <= os.path.getmtime(NATIVE) for f in inputs):
+        return NATIVE
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    dirs = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"]] + cpp_extension.include_paths()
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+    for d in dirs:
+        cmd += ["-isystem", d]
+    cmd += [NATIVE_SRC, "-o", tmp]
+    for d in cpp_extension.library_paths():
+        cmd += ["-L", d]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-lc10", "-ldl"]  # found by their names in a process that has imported torch
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on %s:\n%s" % (NATIVE_SRC, r.stdout))
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
 def is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
@@ -42,6 +72,7 @@ def is_stale() -> bool:
 
 def build(force: bool = True, verbose: bool = False, jobs: int = 8) -> str:
     if not force and not is_stale():
+        build_native(False, verbose)
         return LIB
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJDIR, exist_ok=True)
@@ -63,7 +94,9 @@ def build(force: bool = True, verbose: bool = False, jobs: int = 8) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=jobs) as pool:
+        native = pool.submit(build_native, force, verbose)
         objs = list(pool.map(compile_one, sources()))
+        native.result()
     tmp = LIB + ".tmp.%d" % os.getpid()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
     if verbose:

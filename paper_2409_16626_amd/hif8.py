@@ -1,12 +1,14 @@
-"""Thin ctypes binding over libhif8.so: same names as the C ABI in include/hif8.h.
+"""Thin binding over libhif8.so: same names as the C ABI in include/hif8.h.
 
-Argument marshalling only -- every step of the conversion runs in the HIP kernels.
+Argument marshalling only -- every step of the conversion runs in the HIP kernels.  The usual arguments of a launch are taken in native
+code (binding/native_call.cpp); what that does not take goes through ctypes, in the line below it.
 Data arguments are torch tensors living on the GPU (or raw integer device pointers);
 bfloat16 / float16 tensors may be passed as such or as int16/uint16 views.  The HIP
 stream defaults to torch's current stream.  There is no CPU fallback: if the library
 is missing or a call fails, an exception is raised.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch
@@ -186,6 +188,24 @@ def _check(status):
         raise Hif8Error(status, lib.hif8_last_hip_error())
 
 
+def _load_native():
+    """The native marshalling, bound to the library that is loaded here: each of its functions returns None after a successful call and
+    NotImplemented for arguments it leaves to ctypes.  4 tokens x 4096, scaled and encoded: 6.1 us a call through ctypes, 4.45 so."""
+    if not os.path.exists(_build.NATIVE):
+        _build.build_native()
+    spec = importlib.util.spec_from_file_location("_native_call", _build.NATIVE)
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    if _device is None or _raw_stream is None:
+        native.set_up(lib._handle, _check, torch.cuda.current_device, lambda device: torch.cuda.current_stream(device).cuda_stream)
+    else:
+        native.set_up(lib._handle, _check, _device, _raw_stream)
+    return native
+
+
+_native = _load_native()
+
+
 def hif8_version():
     return lib.hif8_version()
 
@@ -211,103 +231,125 @@ def hif8_sr_threshold(seed, index):
 
 
 def hif8_amax_f16(src, n, d_amax, stream=None):
-    _check(lib.hif8_amax_f16(_ptr(src), n, _ptr(d_amax), _stream(stream)))
+    if _native.hif8_amax_f16(src, n, d_amax, stream) is not None:
+        _check(lib.hif8_amax_f16(_ptr(src), n, _ptr(d_amax), _stream(stream)))
 
 
 def hif8_encode_f16(src, dst, n, scale=1.0, rounding_mode=RM_TA, stream=None):
-    _check(lib.hif8_encode_f16(_ptr(src), _ptr(dst), n, scale, rounding_mode, _stream(stream)))
+    if _native.hif8_encode_f16(src, dst, n, scale, rounding_mode, stream) is not None:
+        _check(lib.hif8_encode_f16(_ptr(src), _ptr(dst), n, scale, rounding_mode, _stream(stream)))
 
 
 def hif8_decode_f16(src, dst, n, scale=1.0, stream=None):
-    _check(lib.hif8_decode_f16(_ptr(src), _ptr(dst), n, scale, _stream(stream)))
+    if _native.hif8_decode_f16(src, dst, n, scale, stream) is not None:
+        _check(lib.hif8_decode_f16(_ptr(src), _ptr(dst), n, scale, _stream(stream)))
 
 
 def hif8_fake_quant_f16(src, dst, codes_or_none, n, scale=1.0, rounding_mode=RM_TA, stream=None):
-    _check(lib.hif8_fake_quant_f16(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, scale, rounding_mode,
-                                   _stream(stream)))
+    if _native.hif8_fake_quant_f16(src, dst, codes_or_none, n, scale, rounding_mode, stream) is not None:
+        _check(lib.hif8_fake_quant_f16(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, scale, rounding_mode,
+                                       _stream(stream)))
 
 
 def hif8_encode_f16_ds(src, dst, n, d_scale2, rounding_mode=RM_TA, stream=None, d_amax_accum=None):
-    _check(lib.hif8_encode_f16_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _ptr(d_amax_accum), rounding_mode,
-                                  _stream(stream)))
+    if _native.hif8_encode_f16_ds(src, dst, n, d_scale2, d_amax_accum, rounding_mode, stream) is not None:
+        _check(lib.hif8_encode_f16_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _ptr(d_amax_accum), rounding_mode,
+                                      _stream(stream)))
 
 
 def hif8_decode_f16_ds(src, dst, n, d_scale2, stream=None):
-    _check(lib.hif8_decode_f16_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _stream(stream)))
+    if _native.hif8_decode_f16_ds(src, dst, n, d_scale2, stream) is not None:
+        _check(lib.hif8_decode_f16_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _stream(stream)))
 
 
 def hif8_fake_quant_f16_ds(src, dst, codes_or_none, n, d_scale2, rounding_mode=RM_TA, stream=None,
                            d_amax_accum=None):
-    _check(lib.hif8_fake_quant_f16_ds(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, _ptr(d_scale2),
-                                      _ptr(d_amax_accum), rounding_mode, _stream(stream)))
+    if _native.hif8_fake_quant_f16_ds(src, dst, codes_or_none, n, d_scale2, d_amax_accum, rounding_mode, stream) is not None:
+        _check(lib.hif8_fake_quant_f16_ds(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, _ptr(d_scale2),
+                                          _ptr(d_amax_accum), rounding_mode, _stream(stream)))
 
 
 def hif8_amax_f32(src, n, d_amax, stream=None):
-    _check(lib.hif8_amax_f32(_ptr(src), n, _ptr(d_amax), _stream(stream)))
+    if _native.hif8_amax_f32(src, n, d_amax, stream) is not None:
+        _check(lib.hif8_amax_f32(_ptr(src), n, _ptr(d_amax), _stream(stream)))
 
 
 def hif8_amax_bf16(src, n, d_amax, stream=None):
-    _check(lib.hif8_amax_bf16(_ptr(src), n, _ptr(d_amax), _stream(stream)))
+    if _native.hif8_amax_bf16(src, n, d_amax, stream) is not None:
+        _check(lib.hif8_amax_bf16(_ptr(src), n, _ptr(d_amax), _stream(stream)))
 
 
 def hif8_scale_from_amax(d_amax, d_scale2, target=MAX_FINITE, pow2=0, stream=None):
-    _check(lib.hif8_scale_from_amax(_ptr(d_amax), _ptr(d_scale2), target, int(pow2), _stream(stream)))
+    if _native.hif8_scale_from_amax(d_amax, d_scale2, target, pow2, stream) is not None:
+        _check(lib.hif8_scale_from_amax(_ptr(d_amax), _ptr(d_scale2), target, int(pow2), _stream(stream)))
 
 
 def hif8_encode_f32(src, dst, n, scale=1.0, rounding_mode=RM_TA, stream=None):
-    _check(lib.hif8_encode_f32(_ptr(src), _ptr(dst), n, scale, rounding_mode, _stream(stream)))
+    if _native.hif8_encode_f32(src, dst, n, scale, rounding_mode, stream) is not None:
+        _check(lib.hif8_encode_f32(_ptr(src), _ptr(dst), n, scale, rounding_mode, _stream(stream)))
 
 
 def hif8_encode_bf16(src, dst, n, scale=1.0, rounding_mode=RM_TA, stream=None):
-    _check(lib.hif8_encode_bf16(_ptr(src), _ptr(dst), n, scale, rounding_mode, _stream(stream)))
+    if _native.hif8_encode_bf16(src, dst, n, scale, rounding_mode, stream) is not None:
+        _check(lib.hif8_encode_bf16(_ptr(src), _ptr(dst), n, scale, rounding_mode, _stream(stream)))
 
 
 def hif8_decode_f32(src, dst, n, scale=1.0, stream=None):
-    _check(lib.hif8_decode_f32(_ptr(src), _ptr(dst), n, scale, _stream(stream)))
+    if _native.hif8_decode_f32(src, dst, n, scale, stream) is not None:
+        _check(lib.hif8_decode_f32(_ptr(src), _ptr(dst), n, scale, _stream(stream)))
 
 
 def hif8_decode_bf16(src, dst, n, scale=1.0, stream=None):
-    _check(lib.hif8_decode_bf16(_ptr(src), _ptr(dst), n, scale, _stream(stream)))
+    if _native.hif8_decode_bf16(src, dst, n, scale, stream) is not None:
+        _check(lib.hif8_decode_bf16(_ptr(src), _ptr(dst), n, scale, _stream(stream)))
 
 
 def hif8_fake_quant_f32(src, dst, codes_or_none, n, scale=1.0, rounding_mode=RM_TA, stream=None):
-    _check(lib.hif8_fake_quant_f32(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, scale, rounding_mode,
-                                   _stream(stream)))
+    if _native.hif8_fake_quant_f32(src, dst, codes_or_none, n, scale, rounding_mode, stream) is not None:
+        _check(lib.hif8_fake_quant_f32(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, scale, rounding_mode,
+                                       _stream(stream)))
 
 
 def hif8_fake_quant_bf16(src, dst, codes_or_none, n, scale=1.0, rounding_mode=RM_TA, stream=None):
-    _check(lib.hif8_fake_quant_bf16(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, scale, rounding_mode,
-                                    _stream(stream)))
+    if _native.hif8_fake_quant_bf16(src, dst, codes_or_none, n, scale, rounding_mode, stream) is not None:
+        _check(lib.hif8_fake_quant_bf16(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, scale, rounding_mode,
+                                        _stream(stream)))
 
 
 def hif8_encode_f32_ds(src, dst, n, d_scale2, rounding_mode=RM_TA, stream=None, d_amax_accum=None):
-    _check(lib.hif8_encode_f32_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _ptr(d_amax_accum), rounding_mode,
-                                  _stream(stream)))
+    if _native.hif8_encode_f32_ds(src, dst, n, d_scale2, d_amax_accum, rounding_mode, stream) is not None:
+        _check(lib.hif8_encode_f32_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _ptr(d_amax_accum), rounding_mode,
+                                      _stream(stream)))
 
 
 def hif8_encode_bf16_ds(src, dst, n, d_scale2, rounding_mode=RM_TA, stream=None, d_amax_accum=None):
-    _check(lib.hif8_encode_bf16_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _ptr(d_amax_accum), rounding_mode,
-                                   _stream(stream)))
+    if _native.hif8_encode_bf16_ds(src, dst, n, d_scale2, d_amax_accum, rounding_mode, stream) is not None:
+        _check(lib.hif8_encode_bf16_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _ptr(d_amax_accum), rounding_mode,
+                                       _stream(stream)))
 
 
 def hif8_decode_f32_ds(src, dst, n, d_scale2, stream=None):
-    _check(lib.hif8_decode_f32_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _stream(stream)))
+    if _native.hif8_decode_f32_ds(src, dst, n, d_scale2, stream) is not None:
+        _check(lib.hif8_decode_f32_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _stream(stream)))
 
 
 def hif8_decode_bf16_ds(src, dst, n, d_scale2, stream=None):
-    _check(lib.hif8_decode_bf16_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _stream(stream)))
+    if _native.hif8_decode_bf16_ds(src, dst, n, d_scale2, stream) is not None:
+        _check(lib.hif8_decode_bf16_ds(_ptr(src), _ptr(dst), n, _ptr(d_scale2), _stream(stream)))
 
 
 def hif8_fake_quant_f32_ds(src, dst, codes_or_none, n, d_scale2, rounding_mode=RM_TA, stream=None,
                            d_amax_accum=None):
-    _check(lib.hif8_fake_quant_f32_ds(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, _ptr(d_scale2),
-                                      _ptr(d_amax_accum), rounding_mode, _stream(stream)))
+    if _native.hif8_fake_quant_f32_ds(src, dst, codes_or_none, n, d_scale2, d_amax_accum, rounding_mode, stream) is not None:
+        _check(lib.hif8_fake_quant_f32_ds(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, _ptr(d_scale2),
+                                          _ptr(d_amax_accum), rounding_mode, _stream(stream)))
 
 
 def hif8_fake_quant_bf16_ds(src, dst, codes_or_none, n, d_scale2, rounding_mode=RM_TA, stream=None,
                             d_amax_accum=None):
-    _check(lib.hif8_fake_quant_bf16_ds(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, _ptr(d_scale2),
-                                       _ptr(d_amax_accum), rounding_mode, _stream(stream)))
+    if _native.hif8_fake_quant_bf16_ds(src, dst, codes_or_none, n, d_scale2, d_amax_accum, rounding_mode, stream) is not None:
+        _check(lib.hif8_fake_quant_bf16_ds(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, _ptr(d_scale2),
+                                           _ptr(d_amax_accum), rounding_mode, _stream(stream)))
 
 
 class CastItem(ctypes.Structure):
@@ -379,15 +421,21 @@ def hif8_quantize_tensor_static(src, dst_or_none, codes_or_none, n, src_kind, d_
 def _def_tensor_calls(sfx):
     enc_sr, fq_sr = getattr(lib, "hif8_encode_%s_sr" % sfx), getattr(lib, "hif8_fake_quant_%s_sr" % sfx)
     qt = getattr(lib, "hif8_quantize_tensor_" + sfx)
+    n_enc_sr, n_fq_sr = getattr(_native, "hif8_encode_%s_sr" % sfx), getattr(_native, "hif8_fake_quant_%s_sr" % sfx)
+    n_qt = getattr(_native, "hif8_quantize_tensor_" + sfx)
 
     def encode_sr(src, dst, n, scale, rounding_mode, seed, index_base=0, stream=None):
-        _check(enc_sr(_ptr(src), _ptr(dst), n, scale, rounding_mode, seed, index_base, _stream(stream)))
+        if n_enc_sr(src, dst, n, scale, rounding_mode, seed, index_base, stream) is not None:
+            _check(enc_sr(_ptr(src), _ptr(dst), n, scale, rounding_mode, seed, index_base, _stream(stream)))
 
     def fake_quant_sr(src, dst, codes_or_none, n, scale, rounding_mode, seed, index_base=0, stream=None):
-        _check(fq_sr(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, scale, rounding_mode, seed, index_base, _stream(stream)))
+        if n_fq_sr(src, dst, codes_or_none, n, scale, rounding_mode, seed, index_base, stream) is not None:
+            _check(fq_sr(_ptr(src), _ptr(dst), _ptr(codes_or_none), n, scale, rounding_mode, seed, index_base, _stream(stream)))
 
     def quantize_tensor(src, dst_or_none, codes_or_none, n, d_amax, d_scale2, workspace, target=MAX_FINITE, pow2=0,
                         rounding_mode=RM_TA, stream=None, workspace_bytes=None):
+        if n_qt(src, dst_or_none, codes_or_none, n, target, pow2, rounding_mode, d_amax, d_scale2, workspace, workspace_bytes, stream) is None:
+            return
         if workspace_bytes is None:
             workspace_bytes = 0 if workspace is None or isinstance(workspace, int) else workspace.numel() * workspace.element_size()
         _check(qt(_ptr(src), _ptr(dst_or_none), _ptr(codes_or_none), n, target, int(pow2), rounding_mode, _ptr(d_amax),
@@ -402,10 +450,11 @@ hif8_encode_f16_sr, hif8_fake_quant_f16_sr, hif8_quantize_tensor_f16 = _def_tens
 
 
 def _def_multi_encode_ds(sfx):
-    fn = getattr(lib, "hif8_multi_encode_%s_ds" % sfx)
+    fn, native = getattr(lib, "hif8_multi_encode_%s_ds" % sfx), getattr(_native, "hif8_multi_encode_%s_ds" % sfx)
 
     def multi_encode_ds(d_items, count, total_tiles, d_scale2, rounding_mode=RM_TA, stream=None, d_amax_accum=None):
-        _check(fn(_ptr(d_items), count, total_tiles, _ptr(d_scale2), _ptr(d_amax_accum), rounding_mode, _stream(stream)))
+        if native(d_items, count, total_tiles, d_scale2, d_amax_accum, rounding_mode, stream) is not None:
+            _check(fn(_ptr(d_items), count, total_tiles, _ptr(d_scale2), _ptr(d_amax_accum), rounding_mode, _stream(stream)))
 
     return multi_encode_ds
 
@@ -416,24 +465,31 @@ hif8_multi_encode_f16_ds = _def_multi_encode_ds("f16")
 
 
 def hif8_scale_from_amax_n(d_amax, d_scale2, count, target=MAX_FINITE, pow2=0, stream=None):
-    _check(lib.hif8_scale_from_amax_n(_ptr(d_amax), _ptr(d_scale2), count, target, int(pow2), _stream(stream)))
+    if _native.hif8_scale_from_amax_n(d_amax, d_scale2, count, target, pow2, stream) is not None:
+        _check(lib.hif8_scale_from_amax_n(_ptr(d_amax), _ptr(d_scale2), count, target, int(pow2), _stream(stream)))
 
 
 def _def_calib(sfx):
     sweep, amax = getattr(lib, "hif8_scale_sweep_" + sfx), getattr(lib, "hif8_amax_axis_" + sfx)
     enc, dec = getattr(lib, "hif8_encode_axis_" + sfx), getattr(lib, "hif8_decode_axis_" + sfx)
+    n_sweep, n_amax = getattr(_native, "hif8_scale_sweep_" + sfx), getattr(_native, "hif8_amax_axis_" + sfx)
+    n_enc, n_dec = getattr(_native, "hif8_encode_axis_" + sfx), getattr(_native, "hif8_decode_axis_" + sfx)
 
     def scale_sweep(src, n, e_lo, count, rounding_mode, d_err, stream=None):
-        _check(sweep(_ptr(src), n, e_lo, count, rounding_mode, _ptr(d_err), _stream(stream)))
+        if n_sweep(src, n, e_lo, count, rounding_mode, d_err, stream) is not None:
+            _check(sweep(_ptr(src), n, e_lo, count, rounding_mode, _ptr(d_err), _stream(stream)))
 
     def amax_axis(src, rows, cols, axis, d_amax, stream=None):
-        _check(amax(_ptr(src), rows, cols, axis, _ptr(d_amax), _stream(stream)))
+        if n_amax(src, rows, cols, axis, d_amax, stream) is not None:
+            _check(amax(_ptr(src), rows, cols, axis, _ptr(d_amax), _stream(stream)))
 
     def encode_axis(src, dst, rows, cols, axis, d_scale2, rounding_mode=RM_TA, stream=None):
-        _check(enc(_ptr(src), _ptr(dst), rows, cols, axis, _ptr(d_scale2), rounding_mode, _stream(stream)))
+        if n_enc(src, dst, rows, cols, axis, d_scale2, rounding_mode, stream) is not None:
+            _check(enc(_ptr(src), _ptr(dst), rows, cols, axis, _ptr(d_scale2), rounding_mode, _stream(stream)))
 
     def decode_axis(src, dst, rows, cols, axis, d_scale2, stream=None):
-        _check(dec(_ptr(src), _ptr(dst), rows, cols, axis, _ptr(d_scale2), _stream(stream)))
+        if n_dec(src, dst, rows, cols, axis, d_scale2, stream) is not None:
+            _check(dec(_ptr(src), _ptr(dst), rows, cols, axis, _ptr(d_scale2), _stream(stream)))
 
     return scale_sweep, amax_axis, encode_axis, decode_axis
 
@@ -444,11 +500,12 @@ hif8_scale_sweep_f16, hif8_amax_axis_f16, hif8_encode_axis_f16, hif8_decode_axis
 
 
 def _def_quantize_rows(sfx):
-    fn = getattr(lib, "hif8_quantize_rows_" + sfx)
+    fn, native = getattr(lib, "hif8_quantize_rows_" + sfx), getattr(_native, "hif8_quantize_rows_" + sfx)
 
     def quantize_rows(src, dst, rows, cols, d_amax, d_scale2, target=MAX_FINITE, pow2=0, rounding_mode=RM_TA, stream=None):
-        _check(fn(_ptr(src), _ptr(dst), rows, cols, target, int(pow2), rounding_mode, _ptr(d_amax), _ptr(d_scale2),
-                  _stream(stream)))
+        if native(src, dst, rows, cols, target, pow2, rounding_mode, d_amax, d_scale2, stream) is not None:
+            _check(fn(_ptr(src), _ptr(dst), rows, cols, target, int(pow2), rounding_mode, _ptr(d_amax), _ptr(d_scale2),
+                      _stream(stream)))
 
     return quantize_rows
 
@@ -496,15 +553,18 @@ def hif8_als_update(state, found_overflow):
 
 
 def hif8_gemm_f32(a_codes, b_codes, out, M, N, K, scale_a=1.0, scale_b=1.0, stream=None):
-    _check(lib.hif8_gemm_f32(_ptr(a_codes), _ptr(b_codes), _ptr(out), M, N, K, scale_a, scale_b, _stream(stream)))
+    if _native.hif8_gemm_f32(a_codes, b_codes, out, M, N, K, scale_a, scale_b, stream) is not None:
+        _check(lib.hif8_gemm_f32(_ptr(a_codes), _ptr(b_codes), _ptr(out), M, N, K, scale_a, scale_b, _stream(stream)))
 
 
 def hif8_gemm_bf16(a_codes, b_codes, out, M, N, K, scale_a=1.0, scale_b=1.0, stream=None):
-    _check(lib.hif8_gemm_bf16(_ptr(a_codes), _ptr(b_codes), _ptr(out), M, N, K, scale_a, scale_b, _stream(stream)))
+    if _native.hif8_gemm_bf16(a_codes, b_codes, out, M, N, K, scale_a, scale_b, stream) is not None:
+        _check(lib.hif8_gemm_bf16(_ptr(a_codes), _ptr(b_codes), _ptr(out), M, N, K, scale_a, scale_b, _stream(stream)))
 
 
 def hif8_gemm_f16(a_codes, b_codes, out, M, N, K, scale_a=1.0, scale_b=1.0, stream=None):
-    _check(lib.hif8_gemm_f16(_ptr(a_codes), _ptr(b_codes), _ptr(out), M, N, K, scale_a, scale_b, _stream(stream)))
+    if _native.hif8_gemm_f16(a_codes, b_codes, out, M, N, K, scale_a, scale_b, stream) is not None:
+        _check(lib.hif8_gemm_f16(_ptr(a_codes), _ptr(b_codes), _ptr(out), M, N, K, scale_a, scale_b, _stream(stream)))
 
 
 def hif8_gemm_workspace_bytes(M, N, K):
@@ -518,11 +578,12 @@ def _ws_bytes(workspace, workspace_bytes):
 
 
 def _def_gemm_ws(sfx):
-    fn = getattr(lib, "hif8_gemm_ws_" + sfx)
+    fn, native = getattr(lib, "hif8_gemm_ws_" + sfx), getattr(_native, "hif8_gemm_ws_" + sfx)
 
     def gemm_ws(a_codes, b_codes, out, M, N, K, workspace, scale_a=1.0, scale_b=1.0, stream=None, workspace_bytes=None):
-        _check(fn(_ptr(a_codes), _ptr(b_codes), _ptr(out), M, N, K, scale_a, scale_b, _ptr(workspace),
-                  _ws_bytes(workspace, workspace_bytes), _stream(stream)))
+        if native(a_codes, b_codes, out, M, N, K, scale_a, scale_b, workspace, workspace_bytes, stream) is not None:
+            _check(fn(_ptr(a_codes), _ptr(b_codes), _ptr(out), M, N, K, scale_a, scale_b, _ptr(workspace),
+                      _ws_bytes(workspace, workspace_bytes), _stream(stream)))
 
     return gemm_ws
 
@@ -531,13 +592,15 @@ hif8_gemm_ws_f32, hif8_gemm_ws_bf16, hif8_gemm_ws_f16 = _def_gemm_ws("f32"), _de
 
 
 def hif8_gemm_ws_sqerr(a_codes, b_codes, ref, M, N, K, scale_a, scale_b, d_err, workspace, stream=None, workspace_bytes=None):
-    _check(lib.hif8_gemm_ws_sqerr(_ptr(a_codes), _ptr(b_codes), _ptr(ref), M, N, K, scale_a, scale_b, _ptr(d_err),
-                                  _ptr(workspace), _ws_bytes(workspace, workspace_bytes), _stream(stream)))
+    if _native.hif8_gemm_ws_sqerr(a_codes, b_codes, ref, M, N, K, scale_a, scale_b, d_err, workspace, workspace_bytes, stream) is not None:
+        _check(lib.hif8_gemm_ws_sqerr(_ptr(a_codes), _ptr(b_codes), _ptr(ref), M, N, K, scale_a, scale_b, _ptr(d_err),
+                                      _ptr(workspace), _ws_bytes(workspace, workspace_bytes), _stream(stream)))
 
 
 def hif8_gemm_sqerr(a_codes, b_codes, ref, M, N, K, scale_a, scale_b, d_err, stream=None):
-    _check(lib.hif8_gemm_sqerr(_ptr(a_codes), _ptr(b_codes), _ptr(ref), M, N, K, scale_a, scale_b, _ptr(d_err),
-                               _stream(stream)))
+    if _native.hif8_gemm_sqerr(a_codes, b_codes, ref, M, N, K, scale_a, scale_b, d_err, stream) is not None:
+        _check(lib.hif8_gemm_sqerr(_ptr(a_codes), _ptr(b_codes), _ptr(ref), M, N, K, scale_a, scale_b, _ptr(d_err),
+                                   _stream(stream)))
 
 
 def hif8_gemm_set_variant(variant):
@@ -549,28 +612,34 @@ def hif8_expanded_ld(K):
 
 
 def hif8_expand_bf16(codes, rows, K, dst, ld, stream=None):
-    _check(lib.hif8_expand_bf16(_ptr(codes), rows, K, _ptr(dst), ld, _stream(stream)))
+    if _native.hif8_expand_bf16(codes, rows, K, dst, ld, stream) is not None:
+        _check(lib.hif8_expand_bf16(_ptr(codes), rows, K, _ptr(dst), ld, _stream(stream)))
 
 
 def hif8_expand_bf16_t(codes, rows, cols, dst, ld, stream=None):
-    _check(lib.hif8_expand_bf16_t(_ptr(codes), rows, cols, _ptr(dst), ld, _stream(stream)))
+    if _native.hif8_expand_bf16_t(codes, rows, cols, dst, ld, stream) is not None:
+        _check(lib.hif8_expand_bf16_t(_ptr(codes), rows, cols, _ptr(dst), ld, _stream(stream)))
 
 
 def hif8_gemm_expanded_f32(a, b, out, M, N, K, ld, scale_a=1.0, scale_b=1.0, stream=None):
-    _check(lib.hif8_gemm_expanded_f32(_ptr(a), _ptr(b), _ptr(out), M, N, K, ld, scale_a, scale_b, _stream(stream)))
+    if _native.hif8_gemm_expanded_f32(a, b, out, M, N, K, ld, scale_a, scale_b, stream) is not None:
+        _check(lib.hif8_gemm_expanded_f32(_ptr(a), _ptr(b), _ptr(out), M, N, K, ld, scale_a, scale_b, _stream(stream)))
 
 
 def hif8_gemm_expanded_bf16(a, b, out, M, N, K, ld, scale_a=1.0, scale_b=1.0, stream=None):
-    _check(lib.hif8_gemm_expanded_bf16(_ptr(a), _ptr(b), _ptr(out), M, N, K, ld, scale_a, scale_b, _stream(stream)))
+    if _native.hif8_gemm_expanded_bf16(a, b, out, M, N, K, ld, scale_a, scale_b, stream) is not None:
+        _check(lib.hif8_gemm_expanded_bf16(_ptr(a), _ptr(b), _ptr(out), M, N, K, ld, scale_a, scale_b, _stream(stream)))
 
 
 def hif8_gemm_expanded_f16(a, b, out, M, N, K, ld, scale_a=1.0, scale_b=1.0, stream=None):
-    _check(lib.hif8_gemm_expanded_f16(_ptr(a), _ptr(b), _ptr(out), M, N, K, ld, scale_a, scale_b, _stream(stream)))
+    if _native.hif8_gemm_expanded_f16(a, b, out, M, N, K, ld, scale_a, scale_b, stream) is not None:
+        _check(lib.hif8_gemm_expanded_f16(_ptr(a), _ptr(b), _ptr(out), M, N, K, ld, scale_a, scale_b, _stream(stream)))
 
 
 def hif8_gemm_expanded_sqerr(a, b, ref, M, N, K, ld, scale_a, scale_b, d_err, stream=None):
-    _check(lib.hif8_gemm_expanded_sqerr(_ptr(a), _ptr(b), _ptr(ref), M, N, K, ld, scale_a, scale_b, _ptr(d_err),
-                                        _stream(stream)))
+    if _native.hif8_gemm_expanded_sqerr(a, b, ref, M, N, K, ld, scale_a, scale_b, d_err, stream) is not None:
+        _check(lib.hif8_gemm_expanded_sqerr(_ptr(a), _ptr(b), _ptr(ref), M, N, K, ld, scale_a, scale_b, _ptr(d_err),
+                                            _stream(stream)))
 
 
 def hif8_calibrate_workspace_bytes(M, N, K, ea_count=10, ew_count=10):
