@@ -118,6 +118,16 @@ inline int tile_form(const TileProblem& p, const TileLaunch& l, size_t cus) {
   return (twos + cus - 1) / cus <= (ones + 2 * cus - 1) / (2 * cus) ? FORM_PAIRED : FORM_TWO;
 }
 
+// The tile that a launch of FORM_FOUR runs: 64 x 64 or 128 x 64 where each of them still has a compute unit to itself.  us, weights from memory,
+// 128 x 128 / 128 x 64 / 64 x 64 and two of these on some compute units: 512 x 2006 x 1024 10.7 / 8.2 / 6.4, x 8000 44.9 / 34.4 / 25.1; 1000 x 2000 x 256
+// binary32 6.5 / 5.3, x 4096 26.3 / 21.2; 900 x 1100 (270 tiles of 64 x 64) x 1024 10.7 / 8.2 / 8.0, x 4096 26.2 / 19.4 / 21.9; 128 x 64 two to a
+// compute unit 472 x 5928 x 2102 17.1 / 20.4.
+enum : int { FINE_128 = 0, FINE_HALF = 1, FINE_64 = 2 };
+inline int fine_tile(const TileProblem& p, const TileLaunch& l, size_t cus) {
+  const uint64_t cols = (l.end - l.begin + 63) / 64 * p.pairs;
+  return (p.M + 63) / 64 * cols <= cus ? FINE_64 : (p.M + 127) / 128 * cols <= cus ? FINE_HALF : FINE_128;
+}
+
 // Most tiles of a launch: its threads, 256 for each workgroup, are counted in 32 bits, and its workgroups are dealt out in
 // whole rounds of the dies (kXcds).  The large tiles walk with one workgroup per compute unit, so that there only the tile number would be
 // limited; that is made use of for the squared error in 256 x 256 tiles, which has several products to a launch, and what other launches
@@ -346,18 +356,29 @@ inline SmallPlan small_choice(size_t M, size_t N, size_t K, bool codes, bool sqe
   return may_stay && cost.us(best) > kSmallGain * base_us ? base : best;
 }
 
-// Products that go to the small-tile kernel: small_problem()'s, whose lines were drawn with small_plan(), and of the other stored products those for
-// which SmallCost is 15 % below what the tiled kernels take at least while every 128 x 128 tile has a compute unit (codes: half of one) to itself (us,
-// weights from memory, tiled / small tiles: codes, 5 + 0.021 to 0.026 K at best, 300 x 9133 x 6368 165 / 112, 700 x 4177 x 5136 131 / 95, but
-// 1000 x 7514 x 5136 171 / 211, 1375 x 2571 x 2240 51 / 58; expanded, 4 + 0.0055 K, up to 256 rows, where few tiles wait for the memory, 0.0065: 160 x 1086 x 448
-// 7.1 / 4.6, 200 x 2730 x 640 8.0 / 6.2, 135 x 1959 x 964 9.5 / 7.0, but 256 x 10456 x 4661 51 / 60, 512 x 3521 x 4496 28.6 / 31.8, 931 x 1244 x 828 9.8 / 11.1;
-// squared error, whose atomics come on top, 185 x 7315 x 6047 37 / 45, 782 x 806 x 274 8.2 / 10.3).
+// Products that go to the small-tile kernel: small_problem()'s, whose lines were drawn with small_plan() and 128 x 128 tiles, but for the stored ones on the far side of
+// those lines whose price is below the tiled kernels'.
+// Codes: 15 % below what the tiled kernel takes at least while every 128 x 128 tile has half a compute unit to itself (us, weights from memory, tiled / small
+// tiles: 5 + 0.021 to 0.026 K at best, 300 x 9133 x 6368 165 / 112, 700 x 4177 x 5136 131 / 95, but 1000 x 7514 x 5136 171 / 211, 1375 x 2571 x 2240 51 / 58).
+// Expanded operands of more than kSmallCodesRows rows: by price on either side, that of the finest tiles that have a compute unit each (fine_tile: 64 x 64 3.0 + 0.00275 K us,
+// 128 x 64 3.9 + 0.0038 K, 128 x 128 4 + 0.0055 K; tiled / small tiles: 512 x 2006 x 4096 14.7 / 19.9, 256 x 3163 x 2048 8.9 / 13.0, but 512 x 1000 x 8000 24 / 21, 200 x
+// 594 x 4176 14 / 7.1).  Where the two are within 15 % the product through the workspace, which has to give the same bits, decides: from the codes, or expanded first.
+inline double expand_us(size_t M, size_t N, size_t ld) { return 2.5 + (double)(M + N) * (double)ld * 3.0 / 5.5e6; }
+inline double tiled_us(size_t M, size_t N, size_t K, size_t cus) {
+  const uint64_t rows = (M + 127) / 128, cols = (N + 63) / 64;
+  return (M + 63) / 64 * cols <= cus ? 3.0 + 0.00275 * (double)K : rows * cols <= cus ? 3.9 + 0.0038 * (double)K
+         : 4.0 + ((M < N ? M : N) <= 256 ? 0.0065 : 0.0055) * (double)K;
+}
 inline bool small_route(size_t M, size_t N, size_t K, bool codes, bool sqerr) {
-  if (small_problem(M, N, K, codes, sqerr)) return true;
+  const bool small = small_problem(M, N, K, codes, sqerr);
   const size_t s = M < N ? M : N, tiles = ((M + 127) / 128) * ((N + 127) / 128);
-  if (s <= (codes ? 32 : kSmallCodesRows) || tiles > (codes ? 512u : 256u) || K < 320 || sqerr) return false;  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
-  const double k = (double)K, tiled = codes ? 5 + (tiles <= 256 ? 0.021 : 0.026) * k : 4 + (s <= 256 ? 0.0065 : 0.0055) * k;
-  return SmallCost(M, N, K, codes).us(small_choice(M, N, K, codes)) < 0.85 * tiled;
+  if (s <= (codes ? 32 : kSmallCodesRows) || tiles > (codes ? 512u : 256u) || K < 320 || sqerr) return small;  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
+  const SmallPlan plan = small_choice(M, N, K, codes);
+  const double us = SmallCost(M, N, K, codes).us(plan);
+  if (codes) return small || us < 0.85 * (5 + (tiles <= 256 ? 0.021 : 0.026) * (double)K);
+  const double tiled = tiled_us(M, N, K, 256);
+  if (us <= 0.87 * tiled || us >= 1.15 * tiled || plan.waves < 4u) return us < tiled;
+  return SmallCost(M, N, K, true).us(small_choice(M, N, K, true, false, plan.waves)) < tiled + expand_us(M, N, K);
 }
 
 // A product through the workspace, of operands whose expansions would go to the small-tile kernel with more than kSmallCodesRows rows: straight from the codes with
@@ -367,8 +388,7 @@ inline uint32_t small_codes_waves(size_t M, size_t N, size_t K) {
   const size_t ld = (K + 63) / 64 * 64;
   const SmallPlan x = small_choice(M, N, ld, false);
   if (x.waves < 4u) return 0;
-  const double expand = 2.5 + (double)(M + N) * (double)ld * 3.0 / 5.5e6;
-  return SmallCost(M, N, K, true).us(small_choice(M, N, K, true, false, x.waves)) < SmallCost(M, N, ld, false).us(x) + expand ? x.waves : 0u;
+  return SmallCost(M, N, K, true).us(small_choice(M, N, K, true, false, x.waves)) < SmallCost(M, N, ld, false).us(x) + expand_us(M, N, ld) ? x.waves : 0u;
 }
 
 // Workgroup -> tile of the expanded-operand kernel.  The hardware deals consecutive workgroups round-robin over the

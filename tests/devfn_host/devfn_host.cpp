@@ -110,6 +110,10 @@ int devfn_small_route(size_t M, size_t N, size_t K, int codes, int sqerr) { retu
 uint32_t devfn_small_codes_waves(size_t M, size_t N, size_t K) { return hif8gemm::small_codes_waves(M, N, K); }
 int devfn_small_by_pairs(size_t K, uint32_t waves) { return hif8gemm::small_by_pairs(K, waves); }
 int devfn_small_problem(size_t M, size_t N, size_t K, int codes, int sqerr) { return hif8gemm::small_problem(M, N, K, codes != 0, sqerr != 0); }
+// the finest tile with which a launch of 128 x 128 tiles, one to a compute unit, keeps that: 0 = 128 x 128, 1 = 128 x 64, 2 = 64 x 64
+int devfn_fine_tile(size_t M, uint32_t begin, uint32_t end, size_t pairs, size_t cus) {
+  return hif8gemm::fine_tile(hif8gemm::TileProblem{M, end, 4096, pairs, 0}, hif8gemm::TileLaunch{hif8gemm::TILE_128, 4, begin, end}, cus);
+}
 // expanded-operand GEMM: the launches of its plan, 4 numbers each: tile (0 = 256 x 256, 1 = 256 x 192, 2 = 128 x 128), LDS
 // stages, first column, end; returns how many
 int devfn_tile_launches(size_t M, size_t N, size_t K, size_t pairs, size_t cus, int kind, uint32_t* out) {

@@ -280,16 +280,18 @@ def test_small_gemm_choice(dev):
         if min(M, N) <= 128:
             assert got[0][1] == got[1][1] or min(got[0][1], got[1][1]) >= -(-ld // 128)
         for codes, k in ((0, ld), (1, K)):
-            assert all(not small(M, N, k, codes, e) or route(M, N, k, codes, e) for e in (0, 1))
             assert route(M, N, k, codes, 1) == small(M, N, k, codes, 1)
+            if min(M, N) <= (32 if codes else 128) or k < 320 or -(-M // 128) * -(-N // 128) > (512 if codes else 256):
+                assert route(M, N, k, codes, 0) == small(M, N, k, codes, 0)
+            assert route(M, N, k, codes, 0) or not codes or not small(M, N, k, codes, 0)
         if min(M, N) > 128 and waves_of(M, N, K):
             assert waves_of(M, N, K) == got[0][1] >= 4
     assert seen == set(tiles)
     # both sides of the routes' lines: small tiles, tiled
     for codes, yes, no in ((1, [(700, 4177, 5136), (300, 9133, 6368)], [(1000, 7514, 5136), (512, 10419, 3392)]),
-                           (0, [(160, 1086, 448), (200, 2730, 640), (135, 1959, 1024)], [(256, 10456, 4672), (512, 3521, 4544), (256, 10236, 448)])):
+                           (0, [(200, 594, 4224), (512, 1000, 8000), (300, 520, 4096)], [(512, 2006, 4096), (256, 3163, 2048), (256, 10456, 4672), (520, 2578, 9920)])):
         assert all(route(*x, codes, 0) for x in yes) and not any(route(*x, codes, 0) for x in no)
-    assert waves_of(130, 1477, 2730) and not waves_of(1000, 1000, 100000)
+    assert waves_of(130, 900, 2730) and not waves_of(1000, 1000, 100000)
 
 
 # (M, N, K) measured faster in small tiles, then those measured faster in the tiled kernels, in the kernels' own time
@@ -518,6 +520,19 @@ def test_gemm_tile_forms(dev, tile_launches):
             short = tile == 1 and K <= 768 and -(-M // 256) * -(-(end - begin) // 192) * pairs <= cus
             assert got == (2 if short else 0 if tile != 2 else 4 if stages == 4 else 3 if paired else 2)
             assert got != 4 or ones <= cus
+
+
+def test_finest_tile_with_a_compute_unit_each(dev):
+    f = dev.devfn_fine_tile
+    f.argtypes = [ctypes.c_size_t, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_size_t, ctypes.c_size_t]
+    assert [f(m, b, e, p, 256) for m, b, e, p in ((1024, 0, 1024, 1), (1024, 0, 1025, 1), (1024, 64, 1088, 1), (1025, 0, 1024, 1), (1024, 0, 2048, 1), (1024, 0, 2049, 1), (1, 0, 1, 256),
+                                                 (1, 0, 1, 257), (4096, 0, 1024, 1))] == [2, 1, 2, 1, 1, 0, 2, 0, 0]
+    rng = np.random.default_rng(3)
+    for _ in range(1000):
+        M, begin, cols, pairs, cus = (int(2 ** rng.uniform(0, 13)) for _ in range(5))
+        got = f(M, begin, begin + cols, pairs, cus)
+        tiles = [-(-M // m) * -(-cols // n) * pairs for m, n in ((128, 128), (128, 64), (64, 64))]
+        assert (got == 0 or tiles[got] <= cus) and all(t > cus for t in tiles[got + 1:])
 
 
 def test_scale_search_launches_fit(dev, tile_launches):

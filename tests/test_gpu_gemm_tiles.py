@@ -388,3 +388,29 @@ def test_workspace_product_expands_both_operands(h):
         h.hif8_gemm_ws_f32(a, b, one, M, N, K, ws, 2.0, 4.0)
         h.hif8_gemm_expanded_f32(xa, xb, two, M, N, K, ld, 2.0, 4.0)
         assert torch.equal(ws.view(torch.int16), torch.cat([xa, xb]).view(torch.int16).reshape(-1)) and torch.equal(one, two)
+
+
+# tiles of 64 x 64 (one and four K steps more than its four stages, and fewer), 128 x 64 in six stages, and 128 x 128 where the finer ones are too many; edges of
+# their blocks, rows at unaligned addresses; pairs of a scale search
+@pytest.mark.parametrize("M,N,K", [(1, 1, 64), (66, 63, 128), (129, 190, 192), (700, 1227, 256), (513, 1003, 330), (64, 64, 520), (1000, 1023, 1000),
+                                   (520, 2578, 64), (1030, 1101, 256), (513, 2049, 320), (900, 1153, 384), (641, 3001, 450), (1024, 2048, 770),
+                                   (1500, 2003, 200), (1030, 4001, 330)])
+def test_finest_tiles_every_output(h, M, N, K):
+    rng = np.random.default_rng(M + 3 * N + 7 * K)
+    (a, ld), (b, _) = expand(h, random_codes(rng, (M, K), "cast_normal")), expand(h, random_codes(rng, (N, K), "cast_normal"))
+    outs = {d: torch.full((M * N + 8,), 7.0, dtype=d, device=dev()) for d in (torch.float32, torch.bfloat16, torch.float16)}
+    h.hif8_gemm_set_variant(9)
+    for call, o in zip((h.hif8_gemm_expanded_f32, h.hif8_gemm_expanded_bf16, h.hif8_gemm_expanded_f16), outs.values()):
+        call(a, b, o, M, N, K, ld, 8.0, 8.0)
+        assert torch.all(o[M * N:] == 7.0)
+    out = outs[torch.float32][:M * N].view(M, N)
+    x, y = a.view(torch.bfloat16).double(), b.view(torch.bfloat16).double()
+    assert torch.all((out.double() - x @ y.t() / 64.0).abs() <= K * 2.0 ** -23 * (x.abs() @ y.abs().t()) / 64.0)
+    for d in (torch.bfloat16, torch.float16):
+        assert torch.equal(outs[d][:M * N].view(M, N), out.to(d))
+    ref = (out * 1.01 + 0.5).contiguous()
+    err = torch.zeros(2, dtype=torch.float64, device=dev())
+    h.hif8_gemm_expanded_sqerr(a, b, ref, M, N, K, ld, 8.0, 8.0, err)
+    h.hif8_gemm_set_variant(0)
+    want = float(((out.double() - ref.double()) ** 2).sum())
+    assert err[1].item() == 0.0 and abs(err[0].item() - want) <= 1e-12 * want
