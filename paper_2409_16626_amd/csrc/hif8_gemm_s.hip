@@ -114,7 +114,7 @@ constexpr uint32_t kRowStage = 128;
 // wavefronts on a SIMD, which its work fills at the sizes it is for: aiming at seven, the compiler waits for look-ups one pair
 // after the other to save registers (4 x 4096 x 4096 7.1 us, 7.7 so; 5 x 7001 x 1999 7.6, 7.85).
 template <int OP, int TM, int TN, int HALF, int EPI>
-__global__ void __launch_bounds__(TM * TN <= 4 ? 1024 : 512) __attribute__((amdgpu_waves_per_eu(TM * TN <= 4 ? 4 : 2, HALF != 0 ? 6 : 8)))
+__global__ void __launch_bounds__(TM * TN <= 4 ? 1024 : TM * TN <= 8 ? 768 : 512) __attribute__((amdgpu_waves_per_eu(TM * TN <= 4 ? 4 : TM * TN <= 8 ? 3 : 2, HALF != 0 ? 6 : 8)))
 k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __restrict__ out,
          const float* __restrict__ ref, double* __restrict__ err, uint32_t M, uint32_t N, uint32_t K, float descale,
          uint32_t tiles_m, uint32_t tiles_n, uint32_t share) {

@@ -228,9 +228,9 @@ inline uint32_t small_resident_stored(const SmallPlan& p, bool codes) {
   const uint32_t by_regs = 4u * per_simd / p.waves, most = by_lds < by_regs ? by_lds : by_regs;
   return most == 0u ? 1u : most;
 }
-// What a kernel can be launched with: 1024 lanes up to four blocks, 512 above, and LDS for the wavefronts' areas.
+// What a kernel can be launched with: 1024 lanes up to four blocks, 768 up to eight, 512 above, and LDS for the wavefronts' areas.
 inline bool small_fits(const SmallPlan& p) {
-  return p.waves <= (p.tm * p.tn <= 4u ? 16u : 8u) && 512u + p.waves * (p.tm + p.tn) * 2048u <= 160u * 1024u;
+  return p.waves <= (p.tm * p.tn <= 4u ? 16u : p.tm * p.tn <= 8u ? 12u : 8u) && 512u + p.waves * (p.tm + p.tn) * 2048u <= 160u * 1024u;
 }
 // The wavefronts' shares of K in pairs of units of 64, 128 codes: whole cache lines for every wavefront, unless single units give the longest
 // share fewer of them (us, single units / pairs, the weight from memory, eight wavefronts: 2 x 4096 x 11008, 172 units, 14.7 / 14.4, 8 x 4096 x 2624, 41,
@@ -316,9 +316,18 @@ constexpr double kSmallGain = 0.93;
 // 16 wavefronts have to promise 12 % over 8 (here fourth powers): where they do less, codes gain nothing and expanded operands, which take over the
 // split, lose 8 to 10 % (24 x 3398 x 5600 12.9 / 13.0 and 9.0 / 10.0).
 constexpr double kSixteen = 1.6;
+// A ninth wavefront where that takes a quarter or more of the stages off the longest share: 17, 33 or 49 units of K and a few more, in tiles of six or eight blocks, of
+// which a compute unit has one (codes above kSmallCodesRows rows; us, eight / nine: 509 x 1003 x 1081 10.7 / 9.9, x 2049 15.2 / 14.0, x 3100 17.5 / 16.6, 700 x 1400 x 2100
+// 26.9 / 24.6; one stage of five less, x 4100, 20.8 / 21.2).
+constexpr double kNineGain = 0.92;
+inline bool ninth_wave(const SmallPlan& p, size_t K) {
+  auto stages = [&](size_t waves) { return ((K + 63) / 64 + 2 * waves - 1) / (2 * waves); };
+  return p.waves == 8u && p.tm * p.tn > 4u && p.tm * p.tn <= 8u && stages(9) * 4 <= stages(8) * 3;
+}
 // What the host takes for a launch: with less on the GPU nothing is gained, and the look at all tiles would come on top.
 // Up to 16 rows it pays from larger products on (16 x 4447 x 7104 16.9 us, now 14.7, 16 x 10257 x 10453 41.8, 33.5; 16 x 1131 x 4272 8.0, 8.0).
 constexpr double kLaunchBound = 5.2, kFewRowsBound = 9.0;
+constexpr uint32_t kSmallWaves[] = {16, 9, 8, 4};
 constexpr uint32_t kSmallTiles[][2] = {{1, 1}, {1, 2}, {1, 3}, {2, 2}, {2, 3}, {2, 4}, {3, 4}, {4, 3}, {4, 4}};
 inline double atomics(const SmallCost& c, const SmallPlan& p, size_t K) {  // of a squared error, see launch_s
   const double wgs = (double)c.tiles_m[p.tm] * c.tiles_n[p.tn];
@@ -342,8 +351,9 @@ inline SmallPlan small_choice(size_t M, size_t N, size_t K, bool codes, bool sqe
   double least = 1e300;
   for (const auto& t : kSmallTiles) {
     if (16u * (t[0] - 1u) >= M || 16u * (t[1] - 1u) >= N) continue;  // a block outside the matrix
-    for (uint32_t w = s <= 16 ? 8 : 16; w >= 4u; w /= 2u) {
+    for (const uint32_t w : kSmallWaves) {
       const SmallPlan p{t[0], t[1], w};
+      if (w == 9u ? waves != 9u : w == 16u && s <= 16) continue;
       if (waves != 0u ? w != waves : w > 4u && w / 2u * kShareK >= ld) continue;  // no wavefronts without a share
       if (!small_fits(p) || (sqerr && (p.tm == 3u || p.tn == 3u))) continue;
       const double c = (cost.score(p) + (sqerr ? SmallCost::fourth(0.01 * atomics(cost, p, K)) : 0.0)) * (w == 16u ? kSixteen : 1.0);
@@ -353,7 +363,10 @@ inline SmallPlan small_choice(size_t M, size_t N, size_t K, bool codes, bool sqe
       }
     }
   }
-  return may_stay && cost.us(best) > kSmallGain * base_us ? base : best;
+  const bool nine = codes && !sqerr && waves == 0u && s > kSmallCodesRows;
+  if (may_stay && cost.us(best) > kSmallGain * base_us * (nine && ninth_wave(base, K) ? kNineGain : 1.0)) best = base;
+  if (nine && ninth_wave(best, K)) best.waves = 9;
+  return best;
 }
 
 // Products that go to the small-tile kernel: small_problem()'s, whose lines were drawn with small_plan() and 128 x 128 tiles, but for the stored ones on the far side of

@@ -271,12 +271,13 @@ def test_small_gemm_choice(dev):
             assert checked[-1][1] == got[0][1]
         for t, w in checked:
             tm, tn = t // 100, t // 10 % 10
-            assert t in tiles and w in (1, 2, 4, 8, 16) and w <= (16 if tm * tn <= 4 else 8)
+            assert t in tiles and w in (1, 2, 4, 8, 9, 16) and w <= (16 if tm * tn <= 4 else 9 if tm * tn <= 8 else 8)
+            assert w != 9 or (tm * tn > 4 and min(M, N) > 128)
             assert 512 + w * (tm + tn) * 2048 <= 160 * 1024 and (w <= 4 or w // 2 < -(-ld // 128))
         seen.update(t for t, w in got)
         for (_, w), codes, k in zip(got, (0, 1), (ld, K)):  # the squared error of the stored product's bits
             t, we = plan(M, N, k, codes, 0, 1)
-            assert t in (110, 120, 220, 240, 440) and (we == w or min(w, we) >= -(-ld // 128)) and we <= (16 if t in (110, 120, 220) else 8)
+            assert t in (110, 120, 220, 240, 440) and (we == w or min(w, we) >= -(-ld // 128)) and we <= (16 if t in (110, 120, 220) else 9 if t == 240 else 8)
         if min(M, N) <= 128:
             assert got[0][1] == got[1][1] or min(got[0][1], got[1][1]) >= -(-ld // 128)
         for codes, k in ((0, ld), (1, K)):
@@ -291,6 +292,7 @@ def test_small_gemm_choice(dev):
     for codes, yes, no in ((1, [(700, 4177, 5136), (300, 9133, 6368)], [(1000, 7514, 5136), (512, 10419, 3392)]),
                            (0, [(200, 594, 4224), (512, 1000, 8000), (300, 520, 4096)], [(512, 2006, 4096), (256, 3163, 2048), (256, 10456, 4672), (520, 2578, 9920)])):
         assert all(route(*x, codes, 0) for x in yes) and not any(route(*x, codes, 0) for x in no)
+    assert [plan(509, 1003, k, 1) for k in (1081, 2049, 2304, 3100)] == [(240, 9)] * 4 and all(plan(509, 1003, k, 1)[1] == 8 for k in (1024, 2048, 2305, 4100)) and plan(509, 1003, 2049, 1, 0, 1)[1] == 9
     assert waves_of(130, 900, 2730) and not waves_of(1000, 1000, 100000)
 
 

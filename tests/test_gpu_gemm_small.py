@@ -184,3 +184,20 @@ def test_small_gemm_tiles_of_three_blocks(h, M, N, K):
     assert torch.equal(got["ws"].view(torch.int32), got["expanded"].view(torch.int32))
     if min(M, N) <= 128:
         assert torch.equal(got["codes"].view(torch.int32), got["ws"].view(torch.int32))
+
+
+# nine wavefronts: 17, 33, 36 and 54 units of K, the last of them of one element or whole; the squared error of the same bits
+@pytest.mark.parametrize("M,N,K", [(509, 1003, 1025), (509, 1000, 2049), (500, 1003, 2304), (512, 1024, 3456)])
+def test_small_gemm_nine_wavefronts(h, M, N, K):
+    rng = np.random.default_rng(K)
+    ca, cb = random_codes(rng, (M, K), "cast_normal"), random_codes(rng, (N, K), "cast_normal")
+    a, b = on_gpu(ca, 1), on_gpu(cb, 1)
+    out = torch.full((M * N + 8,), 7.0, dtype=torch.float32, device=dev())
+    h.hif8_gemm_f32(a, b, out, M, N, K, 8.0, 0.5)
+    assert torch.all(out[M * N:] == 7.0)
+    out = out[:M * N].view(M, N)
+    check(out.cpu().numpy(), ca, cb, 8.0, 0.5)
+    ref, err = (out * 1.01 + 0.5).contiguous(), torch.zeros(1, dtype=torch.float64, device=dev())
+    h.hif8_gemm_sqerr(a, b, ref, M, N, K, 8.0, 0.5, err)
+    want = float(((out.double() - ref.double()) ** 2).sum())
+    assert abs(err.item() - want) <= 1e-12 * want
