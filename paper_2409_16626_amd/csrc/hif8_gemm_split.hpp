@@ -317,7 +317,7 @@ constexpr double kSmallGain = 0.93;
 // split, lose 8 to 10 % (24 x 3398 x 5600 12.9 / 13.0 and 9.0 / 10.0).
 constexpr double kSixteen = 1.6;
 // A ninth wavefront where that takes a quarter or more of the stages off the longest share: 17, 33 or 49 units of K and a few more, in tiles of six or eight blocks, of
-// which a compute unit has one (codes above kSmallCodesRows rows; us, eight / nine: 509 x 1003 x 1081 10.7 / 9.9, x 2049 15.2 / 14.0, x 3100 17.5 / 16.6, 700 x 1400 x 2100
+// which a compute unit has one (codes above kSmallCodesRows rows; us, 2 x 4 tiles with eight / nine: 509 x 1003 x 1081 10.7 / 9.9, x 2049 15.2 / 14.0, x 3100 17.5 / 16.6, 700 x 1400 x 2100
 // 26.9 / 24.6; one stage of five less, x 4100, 20.8 / 21.2).
 constexpr double kNineGain = 0.92;
 inline bool ninth_wave(const SmallPlan& p, size_t K) {

@@ -292,7 +292,7 @@ def test_small_gemm_choice(dev):
     for codes, yes, no in ((1, [(700, 4177, 5136), (300, 9133, 6368)], [(1000, 7514, 5136), (512, 10419, 3392)]),
                            (0, [(200, 594, 4224), (512, 1000, 8000), (300, 520, 4096)], [(512, 2006, 4096), (256, 3163, 2048), (256, 10456, 4672), (520, 2578, 9920)])):
         assert all(route(*x, codes, 0) for x in yes) and not any(route(*x, codes, 0) for x in no)
-    assert [plan(509, 1003, k, 1) for k in (1081, 2049, 2304, 3100)] == [(240, 9)] * 4 and all(plan(509, 1003, k, 1)[1] == 8 for k in (1024, 2048, 2305, 4100)) and plan(509, 1003, 2049, 1, 0, 1)[1] == 9
+    assert [plan(509, 1003, k, 1) for k in (2049, 2200, 2304, 3100)] == [(240, 9)] * 4 and all(plan(509, 1003, k, 1)[1] == 8 for k in (1024, 2048, 2305, 4100)) and plan(509, 1003, 2049, 1, 0, 1)[1] == 9
     assert waves_of(130, 900, 2730) and not waves_of(1000, 1000, 100000)
 
 
