@@ -55,9 +55,9 @@ int hif8_get_tuning(int key); /* -1 for an unknown key */
 
 /*
  * Tile shape of the simulated HiF8 GEMMs, for benchmarking (default 0 = chosen by problem size).
- *   code-operand kernel (hif8_gemm_*):         5 = 256 x 256 x 32 workgroup tile, 8 wavefronts as 4 x 2 (the
- *                                              choice when there is such a tile for every compute unit);
- *                                              6 = 128 x 128 x 32, 4 wavefronts, two workgroups per CU
+ *   code-operand kernel (hif8_gemm_*):         5 = 256 x 256 x 32 workgroup tile; 6 = 128 x 128 x 64; 8 wavefronts each
+ *                                              (the choice, which has 256 x 128 and 128 x 256 tiles as well, is the one with
+ *                                              the shortest sum of rounds)
  *   expanded-operand kernel (hif8_gemm_expanded_*), 4 wavefronts as 2 x 2 each: 9 = 128 x 128 x 64, two workgroups
  *                                              per CU (from K = 4096 on in pairs, 256 x 128 x 64, where that needs no
  *                                              more rounds), or one with four LDS stages where there are no more tiles

@@ -12,7 +12,12 @@
 //
 // Tiling: a workgroup of WM x WN wavefronts owns a (WM TM 32) x (WN TN 32) tile of O; each
 // wavefront TM x TN blocks of v_mfma_f32_32x32x16_bf16; K advances in steps of BK through a
-// double-buffered LDS tile, with the next tile's codes in flight in registers during the MFMAs.
+// double-buffered LDS tile, with the next tile's codes in flight in registers during the MFMAs.  What bounds it is the LDS: of a
+// step of a 256 x 128 x 64 tile the table look-ups take 768 cycles, the fragments 512 and the expanded codes' stores 384, the MFMAs 1024 on
+// each SIMD and the vector instructions (3.7 a code) as much; 1024 x 8192 x 4096 keeps the LDS 54 %, the vector ALUs 46 % and the
+// matrix cores 33 % busy and takes 86 us.  A look-up is needed per row or column and K of a workgroup's tile, so a larger tile needs fewer per MFMA;
+// BK = 64 makes fewer, longer steps (256 x 128 with BK = 32: 120 us).  16 wavefronts do no better (93 us), two workgroups of 128 x 128 tiles
+// on a compute unit need a third more look-ups (121 us).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -46,32 +51,36 @@ __global__ void k_build_gemm_lut() {
   if (i < 256u) g_bf16_lut[i] = (uint16_t)(decode_bits(i) >> 16);
 }
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 // 16 codes (one 16-byte chunk) -> 16 bf16, written to LDS as two 16-byte stores.
 // lut16: this lane's column of the replicated table, indexed by code * (2 * kLutCopies).
-__device__ __forceinline__ void decode_chunk_to_lds(const uint4& c, const uint16_t* lut16, uint4* dst) {
-  const uint32_t w[4] = {c.x, c.y, c.z, c.w};
-  uint32_t o[8];
+__device__ __forceinline__ void decode_chunk_to_lds(const u32x4& c, const uint16_t* lut16, uint4* dst) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    u16x2 p0, p1;
-    p0.x = lut16[(w[j] & 0xFFu) * (2 * kLutCopies)];
-    p0.y = lut16[((w[j] >> 8) & 0xFFu) * (2 * kLutCopies)];
-    p1.x = lut16[((w[j] >> 16) & 0xFFu) * (2 * kLutCopies)];
-    p1.y = lut16[(w[j] >> 24) * (2 * kLutCopies)];
-    o[2 * j] = __builtin_bit_cast(uint32_t, p0);
-    o[2 * j + 1] = __builtin_bit_cast(uint32_t, p1);
+  for (int h = 0; h < 2; ++h) {
+    uint32_t o[4];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t w = c[2 * h + j];
+      u16x2 p0, p1;
+      p0.x = lut16[(w & 0xFFu) * (2 * kLutCopies)];
+      p0.y = lut16[((w >> 8) & 0xFFu) * (2 * kLutCopies)];
+      p1.x = lut16[((w >> 16) & 0xFFu) * (2 * kLutCopies)];
+      p1.y = lut16[(w >> 24) * (2 * kLutCopies)];
+      o[2 * j] = __builtin_bit_cast(uint32_t, p0);
+      o[2 * j + 1] = __builtin_bit_cast(uint32_t, p1);
+    }
+    dst[h] = make_uint4(o[0], o[1], o[2], o[3]);
   }
-  dst[0] = make_uint4(o[0], o[1], o[2], o[3]);
-  dst[1] = make_uint4(o[4], o[5], o[6], o[7]);
 }
 
-// 16 codes of row `row` at column k; rows / columns outside the matrix read as zero codes.  The
-// address is clamped instead of branching so that the loop body stays one basic block.
-__device__ __forceinline__ uint4 load_chunk(const uint8_t* __restrict__ P, uint32_t row, uint32_t rows,
-                                            uint32_t k, uint32_t K) {
-  const bool ok = row < rows && k < K;
-  const uint4 v = *reinterpret_cast<const uint4*>(P + (size_t)(ok ? row : 0u) * K + (ok ? k : 0u));
-  return ok ? v : make_uint4(0u, 0u, 0u, 0u);
+// 16 codes of row `row` at column k; rows / columns outside the matrix read as zero codes.  The address is selected, not the value:
+// a value that is selected behind its load gets loaded under a branch, which cut the K step into blocks, kept the look-ups of one
+// from the MFMAs of the next and made a step wait for the loads that it had just issued (3006 x 8074 x 7664 602 us, so 493).
+static __device__ __attribute__((aligned(16))) const uint8_t g_zero_codes[16] = {};
+__device__ __forceinline__ u32x4 load_chunk(const uint8_t* __restrict__ P, uint32_t row, uint32_t rows, uint32_t k, uint32_t K) {
+  const uint8_t* at = row < rows && k < K ? P + (size_t)row * K + k : g_zero_codes;
+  return *(const __attribute__((address_space(1))) u32x4*)(uintptr_t)at;  // global memory, which the compiler no longer sees
 }
 
 // Epilogue of one wavefront, straight from the accumulators: TM x TN blocks of v_mfma_f32_32x32x16_bf16 whose top-left
@@ -174,7 +183,7 @@ k_gemm_nt(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __
   auto chunk_col = [](uint32_t q) { return (q >> 3) % CPR; };
   // Two register sets: one holds the codes of the tile being expanded into LDS during this K step,
   // the other receives the loads for the tile after it, so a load has a whole K step to arrive.
-  uint4 ra[2][CA], rb[2][CB];
+  u32x4 ra[2][CA], rb[2][CB];
   auto load_tiles = [&](int set, uint32_t k0) {
 #pragma unroll
     for (int i = 0; i < CA; ++i) {
@@ -229,6 +238,19 @@ k_gemm_nt(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
     }
     store_tiles(set, buf ^ 1);
+    // The look-ups spread evenly over the MFMAs, so that neither the LDS nor the matrix core waits while the other works; left to itself
+    // the compiler puts half of them behind the last MFMA (256 x 128 tiles, us with / without: 1024 x 8192 x 4096 86 / 97, 3006 x 8074 x
+    // 7664 462 / 509).  128 x 128 tiles have four look-ups per MFMA and wave and a shorter step, where a fixed order costs (512 x 4096^2 65 / 59).
+    if constexpr (TM * TN * WM * WN > 16) {
+      constexpr int kMfma = TM * TN * (BK / 16), kFirst = TM + TN;
+      constexpr int kReads = (TM + TN) * (BK / 16) + 16 * (CA + CB);  // fragments and look-ups
+      __builtin_amdgcn_sched_group_barrier(0x100, kFirst, 0);
+#pragma unroll
+      for (int i = 0; i < kMfma; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, (kReads - kFirst + kMfma - 1) / kMfma, 0);
+      }
+    }
     __syncthreads();
   };
 
@@ -287,8 +309,7 @@ constexpr size_t smem_bytes() {
 template <int WM, int WN, int TM, int TN, int BK, int EPI>
 static hif8_status launch_tiled(const uint8_t* A, const uint8_t* B, void* out, const float* ref, double* err,
                                 uint32_t M, uint32_t N, uint32_t K, float descale, const uint16_t* lut,
-                                hipStream_t st, uint32_t col_begin = 0, uint32_t col_end = 0xFFFFFFFFu) {
-  if (col_end > N) col_end = N;
+                                hipStream_t st, uint32_t col_begin, uint32_t col_end) {
   if (col_begin >= col_end) return HIF8_OK;
   constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
   constexpr size_t smem = smem_bytes<WM, WN, TM, TN, BK>();
@@ -331,18 +352,18 @@ static hif8_status gemm_dispatch(const uint8_t* A, const uint8_t* B, void* out, 
   const bool fast = K != 0 && (K % 16) == 0 && aligned_to(A, 16) && aligned_to(B, 16);
   if (!fast || g_gemm_variant == 12 || (g_gemm_variant == 0 && small_route(M, N, K, true, EPI == EPI_ERR)))
     return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st);
-  int variant = g_gemm_variant;
-  uint32_t split = 0;
-  if (variant == 0 && ragged_round_split(M, N, (size_t)cus, &split)) {
-    // complete rounds of 256 x 256 tiles, then the remaining columns in 128 x 128 tiles (second launch)
-    s = launch_tiled<4, 2, 2, 4, 32, EPI>(A, B, out, ref, err, m, n, k, descale, lut, st, 0u, split);
-    if (s != HIF8_OK) return s;
-    return launch_tiled<2, 2, 2, 2, 32, EPI>(A, B, out, ref, err, m, n, k, descale, lut, st, split, n);
+  CodesLaunch launch[2] = {{g_gemm_variant == 5 ? CODES_256 : CODES_128, 0u, n}, {CODES_128, 0u, 0u}};
+  const int launches = g_gemm_variant == 0 ? codes_launches(M, N, K, (size_t)cus, launch) : 1;
+  for (int i = 0; i < launches && s == HIF8_OK; ++i) {
+    auto go = [&](auto launch_one) { return launch_one(A, B, out, ref, err, m, n, k, descale, lut, st, launch[i].begin, launch[i].end); };
+    switch (launch[i].tile) {
+      case CODES_256: s = go(launch_tiled<4, 2, 2, 4, 32, EPI>); break;
+      case CODES_TALL: s = go(launch_tiled<4, 2, 2, 2, 64, EPI>); break;
+      case CODES_WIDE: s = go(launch_tiled<2, 4, 2, 2, 64, EPI>); break;
+      default: s = go(launch_tiled<2, 4, 2, 1, 64, EPI>); break;
+    }
   }
-  if (variant == 0)  // 256 x 256 tiles once there is one for every compute unit, else 128 x 128 (two workgroups per CU)
-    variant = (((M + 255) / 256) * ((N + 255) / 256) >= (size_t)cus) ? 5 : 6;
-  if (variant == 5) return launch_tiled<4, 2, 2, 4, 32, EPI>(A, B, out, ref, err, m, n, k, descale, lut, st);
-  return launch_tiled<2, 2, 2, 2, 32, EPI>(A, B, out, ref, err, m, n, k, descale, lut, st);
+  return s;
 }
 
 // hif8_gemm_* through a workspace: expand both operands, then the expanded-operand kernel.

@@ -369,10 +369,45 @@ inline SmallPlan small_choice(size_t M, size_t N, size_t K, bool codes, bool sqe
   return best;
 }
 
+// Tiles of the code-operand kernel, one workgroup per compute unit: the shortest sum of rounds of 256 workgroups, a round at the price
+// below, fitted to 206 shapes with weights from memory (4 % rms error; from the caches a round at K = 4096 takes 59, 86 and 130 us).  Where
+// the complete rounds of 256 x 256 tiles leave some columns over, those may go to smaller tiles in a second launch.
+enum : int { CODES_128 = 0, CODES_TALL = 1, CODES_WIDE = 2, CODES_256 = 3 };  // 128 x 128, 256 x 128, 128 x 256, 256 x 256
+struct CodesLaunch {
+  int tile;
+  uint32_t begin, end;  // columns
+};
+inline double codes_tile_us(int tile, size_t M, size_t N, size_t K, size_t cus) {
+  const uint64_t bm = tile == CODES_TALL || tile == CODES_256 ? 256 : 128, bn = tile == CODES_WIDE || tile == CODES_256 ? 256 : 128;
+  const uint64_t rounds = (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + cus - 1) / cus;
+  const double k = (double)K;
+  return (double)rounds * (tile == CODES_128 ? 5.4 + 0.0152 * k : tile == CODES_256 ? 12.7 + 0.0332 * k : 10.2 + 0.0196 * k);
+}
+inline int codes_tile(size_t M, size_t N, size_t K, size_t cus, double* us) {
+  int best = CODES_128;
+  *us = codes_tile_us(CODES_128, M, N, K, cus);
+  for (int tile = CODES_TALL; tile <= CODES_256; ++tile) {
+    const double t = codes_tile_us(tile, M, N, K, cus);
+    if (t < *us) *us = t, best = tile;
+  }
+  return best;
+}
+inline int codes_launches(size_t M, size_t N, size_t K, size_t cus, CodesLaunch (&out)[2]) {
+  double us = 0.0, right = 0.0;
+  out[0] = CodesLaunch{codes_tile(M, N, K, cus, &us), 0u, (uint32_t)N};
+  uint32_t split = 0;
+  if (!ragged_round_split(M, N, cus, &split)) return 1;
+  const int tile = codes_tile(M, N - split, K, cus, &right);
+  if (codes_tile_us(CODES_256, M, split, K, cus) + right + 4.0 >= us) return 1;
+  out[0] = CodesLaunch{CODES_256, 0u, split};
+  out[1] = CodesLaunch{tile, split, (uint32_t)N};
+  return 2;
+}
+
 // Products that go to the small-tile kernel: small_problem()'s, whose lines were drawn with small_plan() and 128 x 128 tiles, but for the stored ones on the far side of
 // those lines whose price is below the tiled kernels'.
-// Codes: 15 % below what the tiled kernel takes at least while every 128 x 128 tile has half a compute unit to itself (us, weights from memory, tiled / small
-// tiles: 5 + 0.021 to 0.026 K at best, 300 x 9133 x 6368 165 / 112, 700 x 4177 x 5136 131 / 95, but 1000 x 7514 x 5136 171 / 211, 1375 x 2571 x 2240 51 / 58).
+// Codes: by price on either side (us, weights from memory, tiled / small tiles: 370 x 1071 x 6608 107 / 29, 300 x 9133 x 6368 150 / 112, but 1428 x
+// 2166 x 3792 66 / 75, 840 x 2996 x 6896 110 / 118); of 260 shapes the choice loses 0.2 % to the better one in the mean.
 // Expanded operands of more than kSmallCodesRows rows: by price on either side, that of the finest tiles that have a compute unit each (fine_tile: 64 x 64 3.0 + 0.00275 K us,
 // 128 x 64 3.9 + 0.0038 K, 128 x 128 4 + 0.0055 K; tiled / small tiles: 512 x 2006 x 4096 14.7 / 19.9, 256 x 3163 x 2048 8.9 / 13.0, but 512 x 1000 x 8000 24 / 21, 200 x
 // 594 x 4176 14 / 7.1).  Where the two are within 15 % the product through the workspace, which has to give the same bits, decides: from the codes, or expanded first.
@@ -388,7 +423,11 @@ inline bool small_route(size_t M, size_t N, size_t K, bool codes, bool sqerr) {
   if (s <= (codes ? 32 : kSmallCodesRows) || tiles > (codes ? 512u : 256u) || K < 320 || sqerr) return small;  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
   const SmallPlan plan = small_choice(M, N, K, codes);
   const double us = SmallCost(M, N, K, codes).us(plan);
-  if (codes) return small || us < 0.85 * (5 + (tiles <= 256 ? 0.021 : 0.026) * (double)K);
+  if (codes) {
+    double tiled = 0.0;
+    codes_tile(M, N, K, 256, &tiled);
+    return small || us < tiled;
+  }
   const double tiled = tiled_us(M, N, K, 256);
   if (us <= 0.87 * tiled || us >= 1.15 * tiled || plan.waves < 4u) return us < tiled;
   return SmallCost(M, N, K, true).us(small_choice(M, N, K, true, false, plan.waves)) < tiled + expand_us(M, N, K);

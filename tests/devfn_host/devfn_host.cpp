@@ -93,6 +93,19 @@ uint32_t devfn_ragged_round_split(size_t M, size_t N, size_t cus) {
   uint32_t split = 0;
   return hif8gemm::ragged_round_split(M, N, cus, &split) ? split : 0u;
 }
+// code-operand GEMM: the launches of its plan, 3 numbers each: tile (0 = 128 x 128, 1 = 256 x 128, 2 = 128 x 256, 3 = 256 x 256), first column,
+// end; returns how many
+int devfn_codes_launches(size_t M, size_t N, size_t K, size_t cus, uint32_t* out) {
+  hif8gemm::CodesLaunch l[2];
+  const int n = hif8gemm::codes_launches(M, N, K, cus, l);
+  for (int i = 0; i < n; ++i) {
+    out[3 * i] = (uint32_t)l[i].tile;
+    out[3 * i + 1] = l[i].begin;
+    out[3 * i + 2] = l[i].end;
+  }
+  return n;
+}
+double devfn_codes_tile_us(int tile, size_t M, size_t N, size_t K, size_t cus) { return hif8gemm::codes_tile_us(tile, M, N, K, cus); }
 // small-tile GEMM kernel: 100 * tile rows + 10 * tile columns (in blocks of 16) and wavefronts; whether a problem goes there
 uint32_t devfn_small_plan(size_t M, size_t N, size_t K, int codes, int sqerr, uint32_t* waves) {
   const hif8gemm::SmallPlan p = hif8gemm::small_plan(M, N, K, codes != 0, sqerr != 0);

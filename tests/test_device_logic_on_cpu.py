@@ -183,6 +183,34 @@ def test_gemm_ragged_round_split_plan(dev):
             assert tm * tn > cus and (tm * tn) % cus != 0
 
 
+def test_codes_gemm_launches(dev):
+    """Tiles of the code-operand kernel: every column in one launch, a second launch only where the large tiles of the first fill whole rounds, every tile
+    shape reached, and never a price above that of any single tile."""
+    f, us = dev.devfn_codes_launches, dev.devfn_codes_tile_us
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_size_t] * 4 + [ctypes.POINTER(ctypes.c_uint32)]
+    us.restype, us.argtypes = ctypes.c_double, [ctypes.c_int] + [ctypes.c_size_t] * 4
+
+    def plan(M, N, K, cus=256):
+        out = (ctypes.c_uint32 * 6)()
+        n = f(M, N, K, cus, out)
+        return [tuple(out[3 * i:3 * i + 3]) for i in range(n)]
+
+    assert plan(512, 4096, 4096) == [(0, 0, 4096)] and plan(1024, 8192, 4096) == [(1, 0, 8192)] and plan(100, 33000, 80) == [(2, 0, 33000)]
+    assert plan(4096, 4096, 4096) == [(3, 0, 4096)] and plan(2048, 11008, 4096) == [(3, 0, 8192), (1, 8192, 11008)]
+    rng = np.random.default_rng(8)
+    for _ in range(3000):
+        M, N, K = (int(2.0 ** rng.uniform(0, 15)) for _ in range(3))
+        cus = int(rng.choice([64, 256, 304]))
+        got = plan(M, N, K, cus)
+        assert got[0][1] == 0 and got[-1][2] == N and all(0 <= t <= 3 and b < e for t, b, e in got)
+        price = [us(t, M, N, K, cus) for t in range(4)]
+        if len(got) == 2:
+            assert got[0][0] == 3 and got[0][2] == got[1][1] and got[1][1] % 256 == 0
+            assert us(3, M, got[0][2], K, cus) + us(got[1][0], M, N - got[0][2], K, cus) < min(price)
+        else:
+            assert price[got[0][0]] == min(price)
+
+
 def test_gemm_tile_order_is_a_bijection_and_compact_per_die(dev):
     """Workgroup -> tile of the expanded-operand GEMM: every tile is taken exactly once, only workgroups at the
     end of the grid go without one, and the 32 workgroups that run together on one die (b = die + 8 s for 32
@@ -289,7 +317,7 @@ def test_small_gemm_choice(dev):
             assert waves_of(M, N, K) == got[0][1] >= 4
     assert seen == set(tiles)
     # both sides of the routes' lines: small tiles, tiled
-    for codes, yes, no in ((1, [(700, 4177, 5136), (300, 9133, 6368)], [(1000, 7514, 5136), (512, 10419, 3392)]),
+    for codes, yes, no in ((1, [(370, 1071, 6608), (512, 3328, 4096)], [(1000, 7514, 5136), (512, 10419, 3392), (700, 4177, 5136), (1428, 2166, 3792)]),
                            (0, [(200, 594, 4224), (512, 1000, 8000), (300, 520, 4096)], [(512, 2006, 4096), (256, 3163, 2048), (256, 10456, 4672), (520, 2578, 9920)])):
         assert all(route(*x, codes, 0) for x in yes) and not any(route(*x, codes, 0) for x in no)
     assert [plan(509, 1003, k, 1) for k in (2049, 2200, 2304, 3100)] == [(240, 9)] * 4 and all(plan(509, 1003, k, 1)[1] == 8 for k in (1024, 2048, 2305, 4100)) and plan(509, 1003, 2049, 1, 0, 1)[1] == 9

@@ -136,6 +136,29 @@ def test_gemm_special_codes_follow_ieee(h):
         assert np.all(bits[np.isnan(want)] == 0x7FC0) and np.array_equal(bits == 0x7F80, np.isposinf(want))
 
 
+# every tile of the code-operand kernel and its launches in two parts, at the ends of tiles and of K steps (64, or 32 for 256 x 256 tiles): 128 x 128,
+# 256 x 128, 128 x 256, 256 x 256, a split with the rest in 128 x 128 and in 256 x 128 tiles; a step and less, an odd and an even number of steps
+@pytest.mark.parametrize("M,N,K", [(1025, 3071, 16), (1025, 3071, 208), (2049, 2049, 128), (2177, 2175, 80), (100, 33001, 144), (4095, 4090, 48), (4095, 4090, 112),
+                                   (3001, 5500, 80), (2047, 11000, 272)])
+def test_gemm_code_tiles(h, M, N, K):
+    rng = np.random.default_rng(M + N + K)
+    ca, cb = random_codes(rng, (M, K), "cast_normal"), random_codes(rng, (N, K), "cast_normal")
+    a, b = torch.from_numpy(ca).to(dev()), torch.from_numpy(cb).to(dev())
+    o32 = torch.full((M * N + 8,), 7.0, dtype=torch.float32, device=dev())
+    ob, oh = (torch.full((M * N + 8,), 7.0, dtype=d, device=dev()) for d in (torch.bfloat16, torch.float16))
+    for call, o in ((h.hif8_gemm_f32, o32), (h.hif8_gemm_bf16, ob), (h.hif8_gemm_f16, oh)):
+        call(a, b, o, M, N, K, 8.0, 8.0)
+        assert torch.all(o[M * N:] == 7.0)
+    out = o32[:M * N].view(M, N)
+    check(out.cpu().numpy(), ca, cb, 8.0, 8.0)
+    assert torch.equal(ob[:M * N].view(M, N), out.to(torch.bfloat16)) and torch.equal(oh[:M * N].view(M, N), out.to(torch.float16))
+    ref = (out * 1.01 + 0.5).contiguous()
+    err = torch.zeros(2, dtype=torch.float64, device=dev())
+    h.hif8_gemm_sqerr(a, b, ref, M, N, K, 8.0, 8.0, err)
+    want = float(((out.double() - ref.double()) ** 2).sum())
+    assert err[1].item() == 0.0 and abs(err[0].item() - want) <= 1e-12 * want
+
+
 @pytest.mark.parametrize("M,N,K,off", [(40, 24, 17, 0), (5, 9, 100, 0), (64, 64, 64, 1), (3, 2, 1, 0)])
 def test_gemm_odd_k_and_alignment(h, M, N, K, off):
     rng = np.random.default_rng(8)
