@@ -392,6 +392,10 @@ k_encode_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t 
 constexpr int kQrBlock = 512;
 constexpr int kQrWaves = kQrBlock / 64;
 constexpr int kQrWaveVecs = 4;  // vectors of a lane up to which a wavefront takes a row by itself
+// and the rows that it takes for each vector of a lane beyond the first: with fewer a workgroup per row has more loads in flight (us,
+// workgroup / wavefront, from memory: 300 x 1024 2.77 / 2.89, 300 x 2048 2.82 / 3.61, 1000 x 2048 3.57 / 3.91, but 1000 x 1024 3.44 / 3.10,
+// 2746 x 2048 5.67 / 5.56)
+constexpr size_t kQrWaveRows = 512;
 
 template <int IMPL, int SRCK, int VPT, int LANES>
 __global__ void __launch_bounds__(kQrBlock)
@@ -833,7 +837,8 @@ hif8_status quantize_rows(const void* src, uint8_t* dst, size_t rows, size_t col
   }
   const uint64_t seed = sr_seed();
   // enough workgroups to fill the chip (four of 512 lanes per CU), each walking several rows (measured flat from 3 to 8 per CU)
-  const bool by_wave = cols_vec <= (size_t)64 * kQrWaveVecs;
+  const size_t wave_vecs = (cols_vec + 63) / 64;
+  const bool by_wave = wave_vecs <= (size_t)kQrWaveVecs && rows >= kQrWaveRows * (wave_vecs - 1);
   const size_t lanes = by_wave ? 64 : kQrBlock, want = by_wave ? (rows + kQrWaves - 1) / kQrWaves : rows;
   size_t wgs = (size_t)cus * 4;
   if (wgs > want) wgs = want;

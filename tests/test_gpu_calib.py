@@ -252,9 +252,9 @@ def test_per_channel_unaligned_base_and_special_values(h):
 
 
 # one below, at and above a vector (4 or 8 values); a wavefront's vectors of a row (64 to 256) and one more; a workgroup's (512 to 4096) and one more,
-# which takes the three launches; several chunks of a row; many short rows; strips of columns
+# which takes the three launches; several chunks of a row; many short rows; strips of columns; enough rows for a wavefront each at three and four vectors a lane
 @pytest.mark.parametrize("rows,cols", [(700, 1), (65, 3), (3000, 7), (33, 9), (40, 513), (9, 1021), (2500, 259), (17, 2047), (6, 2051), (5, 4099), (3, 16381),
-                                       (2, 32771), (300, 1547)])
+                                       (2, 32771), (300, 1547), (1100, 1099), (1540, 1001)])
 @pytest.mark.parametrize("off", [0, 1])
 def test_per_channel_any_columns_and_address(h, rows, cols, off):
     """Rows that start anywhere (odd numbers of columns, a base one element or one byte off): bit for bit the oracle's, nothing
