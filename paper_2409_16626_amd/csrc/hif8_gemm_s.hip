@@ -12,9 +12,10 @@
 // straight from global memory, 16 rows in 16 neighbouring lanes, ran at half the speed on rows that are not 16-byte
 // aligned), passes them through its own 2 KiB of LDS per 16-row block, with the loads of the next 128 bytes in flight
 // meanwhile, and expands codes on their way from there into the fragments of v_mfma_f32_16x16x32_bf16 through a
-// 256-entry table in LDS.  That table look-up, one LDS read and three vector instructions per element, is the larger part of
+// 256-entry table in LDS.  That table look-up, one LDS read and two vector instructions per element, is the larger part of
 // the code form: without it 8 x 11008 x 4096 takes 11 us, without the loads 14 us, as it is 14 us; the LDS is active 56 % of
-// the cycles, a fifth of them bank conflicts, the vector ALUs 55 %.  With one workgroup per compute unit (509 x 1003 x 2049) both
+// the cycles, a fifth of them bank conflicts, the vector ALUs half (with three vector instructions 55 %).  Conflicts weigh more than
+// instructions: without table_slots(), half an instruction less per element, it is 4 to 6 % slower.  With one workgroup per compute unit (509 x 1003 x 2049) both
 // are busy a quarter of the time, and the chain of loads, stages and the sum counts.  (8 x 11008 x 4096: 45 MB, 7.5 us at
 // the memory's rate); the tiled kernel took 85 us.  Measured against the tiled kernels (us per call, codes / expanded
 // operands): 8 x 4096 x 4096 7.9 / 9.3 (80 / 55), 64 x 4096 x 4096 14.2 / 14.9 (84 / 55), 256 x 4096 x 4096 33 / 23
@@ -84,20 +85,30 @@ __device__ __forceinline__ u32x4 load_short_row(const uint8_t* row, uint32_t k, 
 // their negatives (codes 0x40.., 0x60.., 0xC0.., 0xE0.. of values above 2^4) sit in different LDS banks.
 __device__ __forceinline__ uint32_t table_slots(uint32_t w) { return w ^ ((w >> 3) & 0x10101010u); }
 
-// Two neighbouring elements.  The table is the first thing in the kernel's only LDS, which is dynamic, at LDS address 0 (a CPU
-// test holds the kernel to that); with the address formed here an index costs one shift of a selected byte, from the array's own
-// address an addition more (3 % more instructions in the kernel).
+// Twice the lowest byte of w, the LDS address of that code's element: the table is the first thing in the kernel's only LDS, which is dynamic,
+// at LDS address 0 (a CPU test holds the kernel to that); from the array's own address an index costs an addition more (3 % more
+// instructions in the kernel).  The compiler takes one instruction for the other bytes of a word, but a shift and a mask for this one, a ninth
+// of all that an expansion takes (us: 64 x 11008 x 4096 26.0, so 25.6; 173 x 3951 x 6832 37.2, 36.3; 509 x 1003 x 2049 14.3, 14.0; with the eight rows'
+// words selected before the look-ups, not the elements behind them, 8 x 11008 x 4096 14.85, 14.6).
+__device__ __forceinline__ uint32_t twice_lowest(uint32_t w) {
+  uint32_t r;
+  asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(r) : "v"(1u), "v"(w));
+  return r;
+}
+
+// Two neighbouring elements, by their addresses
 __device__ __forceinline__ uint32_t lookup2(uint32_t lo, uint32_t hi) {
   typedef const __attribute__((address_space(3))) uint16_t* lds_u16;
-  return (uint32_t)*(lds_u16)(lo << 1) | ((uint32_t)*(lds_u16)(hi << 1) << 16);
+  return (uint32_t)*(lds_u16)lo | ((uint32_t)*(lds_u16)hi << 16);
 }
 
 // 8 codes -> one MFMA fragment
 __device__ __forceinline__ u32x4 expand8(uint32_t w0, uint32_t w1) {
   w0 = table_slots(w0);
   w1 = table_slots(w1);
-  return u32x4{lookup2(w0 & 0xFFu, (w0 >> 8) & 0xFFu), lookup2((w0 >> 16) & 0xFFu, w0 >> 24),
-               lookup2(w1 & 0xFFu, (w1 >> 8) & 0xFFu), lookup2((w1 >> 16) & 0xFFu, w1 >> 24)};
+  auto second = [](uint32_t w) { return ((w >> 8) & 0xFFu) << 1; };
+  auto upper = [](uint32_t w) { return lookup2(((w >> 16) & 0xFFu) << 1, (w >> 24) << 1); };
+  return u32x4{lookup2(twice_lowest(w0), second(w0)), upper(w0), lookup2(twice_lowest(w1), second(w1)), upper(w1)};
 }
 
 // 16 codes -> two fragments
@@ -226,7 +237,7 @@ k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __r
           static_assert(OP == OP_CODES && TM == 1, "one row block of codes");
           const uint32_t r8 = r16 & 7u;
           const u32x4 c = *reinterpret_cast<const u32x4*>(area + r8 * kRowStage + (((p * 4 + q) ^ (r8 >> 1)) * 16u));
-          const u32x4 own = r16 < 8u ? expand8(c[0], c[1]) : expand8(c[2], c[3]);
+          const u32x4 own = expand8(r16 < 8u ? c[0] : c[2], r16 < 8u ? c[1] : c[3]);
           u32x4 other;
 #pragma unroll
           for (int v = 0; v < 4; ++v) other[v] = __builtin_amdgcn_update_dpp(0, own[v], 0x128, 0xF, 0xF, true);  // row_ror:8
