@@ -17,9 +17,9 @@
 // the cycles, a fifth of them bank conflicts, the vector ALUs half (with three vector instructions 55 %).  Conflicts weigh more than
 // instructions: without table_slots(), half an instruction less per element, it is 4 to 6 % slower.  With one workgroup per compute unit (509 x 1003 x 2049) both
 // are busy a quarter of the time, and the chain of loads, stages and the sum counts.  (8 x 11008 x 4096: 45 MB, 7.5 us at
-// the memory's rate); the tiled kernel took 85 us.  Measured against the tiled kernels (us per call, codes / expanded
-// operands): 8 x 4096 x 4096 7.9 / 9.3 (80 / 55), 64 x 4096 x 4096 14.2 / 14.9 (84 / 55), 256 x 4096 x 4096 33 / 23
-// (85 / 55), 512 x 4096 x 11008 150 / 80 (231 / 143); odd K, 509 x 1003 x 2049: 15.5 (3810 with one output per lane).
+// the memory's rate); 128 x 128 tiles of the code-operand kernel take 67 us.  Measured against 128 x 128 and finer tiles (us per call, codes /
+// expanded operands): 8 x 4096 x 4096 6.5 / 5.9 (61 / 13), 64 x 4096 x 4096 13.5 / 10.2 (62 / 14), 256 x 4096 x 4096 26 / 20
+// (64 / 14), 512 x 4096 x 11008 107 / 74 (179 / 52); odd K, 509 x 1003 x 2049: 13.7 (3810 with one output per lane).
 //
 // The element order of a K share is the same for both operand kinds, so that one product gives the same bits whether
 // its operands come as codes or expanded.
