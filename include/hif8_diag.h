@@ -61,7 +61,8 @@ int hif8_get_tuning(int key); /* -1 for an unknown key */
  *   expanded-operand kernel (hif8_gemm_expanded_*), 4 wavefronts as 2 x 2 each: 9 = 128 x 128 x 64, two workgroups
  *                                              per CU (from K = 4096 on in pairs, 256 x 128 x 64, where that needs no
  *                                              more rounds), or one with four LDS stages where there are no more tiles
- *                                              than compute units; 10 = 256 x 256 x 64; 11 = 256 x 192 x 64, both in a
+ *                                              than compute units (there 128 x 64 or 64 x 64, where each
+ *                                              of those has a compute unit too); 10 = 256 x 256 x 64; 11 = 256 x 192 x 64, both in a
  *                                              ring of operand slots (a single round of 11 up to K = 768: two LDS stages)
  *                                              (the choice is the one with the shortest sum of rounds)
  *   both:                                      12 = the small-tile kernel that few output tiles and unaligned code

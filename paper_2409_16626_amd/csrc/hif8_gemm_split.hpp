@@ -147,15 +147,16 @@ inline uint32_t pairs_per_launch(int tile, size_t M, size_t N, size_t K, uint32_
 }
 
 // Products with at most this many rows on one side run straight from the codes in hif8_gemm_ws_* when the expanded operands
-// would go to the small-tile kernel: up to here both operand kinds have one plan (small_plan) and so the same bits.  Above it
-// the codes are expanded first, which is faster for large products (codes / expanded first, us: 512 x 2560 x 4096 50 / 38, 1024 x
-// 2560 x 2048 47 / 26) and slower for small ones (256 x 1280 x 4096 18 / 31, 512 x 2048 x 2048 19 / 23, 700 x 700 x 700 10 / 15.5).
+// would go to the small-tile kernel: up to here both operand kinds have one K split (small_choice) and so the same bits.  Above it
+// the codes are expanded first, which is faster for large products, or asked for the expanded operands' split, by price (small_codes_waves).
 constexpr size_t kSmallCodesRows = 128;
 
 // Which problems go to the small-tile kernel (hif8_gemm_s.hip) although the tiled kernels could run them.  The tiled kernels
-// walk all of K however few tiles there are, so their time is a few us plus K (up to 256 tiles of 128 x 128: 7.5 us + 0.018
+// walk all of K however few tiles there are, so their time is a few us plus K (up to 256 tiles of 128 x 128: 5.4 us + 0.015
 // us * K on codes, 3.8 us + 0.005 us * K on expanded operands with their four LDS stages); the small-tile kernel's goes with
-// M N K.  s: the shorter side, l: the longer one.  In us, small tiles / tiled, on either side of each line:
+// M N K.  s: the shorter side, l: the longer one.  These lines were drawn with small_plan()'s tiles against 128 x 128 tiles that took a quarter longer on
+// codes; both kernels are faster now, and small_route() moves products across them by price.  In us, small tiles / tiled, on either side
+// of each line, as it was drawn:
 //   codes        64 x 16384 x 64 8.2 / 8.2, 32000 9.6 / 8.9; 128 x 5120 x 64 7.8 / 8.2, 10240 13.4 / 8.4; 64 x 26624 x 512 14.7 /
 //                17.2; 256 x 10240 x 1024 36 / 28; 512 x 3328 x 4096 64 / 90, 5120 104 / 89; 32 x 200000 x 64 20 / 32
 //   expanded     256 x 4096 x 512 9.2 / 7.0, x 1024 10.1 / 9.4, x 2048 13.6 / 14.4, 5120 19.4 / 14.8; 128 x 2560 x 512
