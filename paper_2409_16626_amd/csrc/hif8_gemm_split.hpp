@@ -152,7 +152,7 @@ inline uint32_t pairs_per_launch(int tile, size_t M, size_t N, size_t K, uint32_
 constexpr size_t kSmallCodesRows = 128;
 
 // Which problems go to the small-tile kernel (hif8_gemm_s.hip) although the tiled kernels could run them.  The tiled kernels
-// walk all of K however few tiles there are, so their time is a few us plus K (up to 256 tiles of 128 x 128: 5.4 us + 0.015
+// walk all of K however few tiles there are, so their time is a few us plus K (up to 256 tiles of 128 x 128: 5.9 us + 0.013
 // us * K on codes, 3.8 us + 0.005 us * K on expanded operands with their four LDS stages); the small-tile kernel's goes with
 // M N K.  s: the shorter side, l: the longer one.  These lines were drawn with small_plan()'s tiles against 128 x 128 tiles that took a quarter longer on
 // codes; both kernels are faster now, and small_route() moves products across them by price.  In us, small tiles / tiled, on either side
@@ -371,7 +371,7 @@ inline SmallPlan small_choice(size_t M, size_t N, size_t K, bool codes, bool sqe
 }
 
 // Tiles of the code-operand kernel, one workgroup per compute unit: the shortest sum of rounds of 256 workgroups, a round at the price
-// below, fitted to 206 shapes with weights from memory (4 % rms error; from the caches a round at K = 4096 takes 59, 86 and 130 us).  Where
+// below, fitted to 206 shapes with weights from memory (4 % rms error; from the caches a round at K = 4096 takes 60, 86 and 126 us).  Where
 // the complete rounds of 256 x 256 tiles leave some columns over, those may go to smaller tiles in a second launch.
 enum : int { CODES_128 = 0, CODES_TALL = 1, CODES_WIDE = 2, CODES_256 = 3 };  // 128 x 128, 256 x 128, 128 x 256, 256 x 256
 struct CodesLaunch {
@@ -382,7 +382,7 @@ inline double codes_tile_us(int tile, size_t M, size_t N, size_t K, size_t cus) 
   const uint64_t bm = tile == CODES_TALL || tile == CODES_256 ? 256 : 128, bn = tile == CODES_WIDE || tile == CODES_256 ? 256 : 128;
   const uint64_t rounds = (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + cus - 1) / cus;
   const double k = (double)K;
-  return (double)rounds * (tile == CODES_128 ? 5.4 + 0.0152 * k : tile == CODES_256 ? 12.7 + 0.0332 * k : 10.2 + 0.0196 * k);
+  return (double)rounds * (tile == CODES_128 ? 5.9 + 0.013 * k : tile == CODES_256 ? 13.0 + 0.0303 * k : 10.2 + 0.0195 * k);
 }
 inline int codes_tile(size_t M, size_t N, size_t K, size_t cus, double* us) {
   int best = CODES_128;
@@ -407,8 +407,8 @@ inline int codes_launches(size_t M, size_t N, size_t K, size_t cus, CodesLaunch 
 
 // Products that go to the small-tile kernel: small_problem()'s, whose lines were drawn with small_plan() and 128 x 128 tiles, but for the stored ones on the far side of
 // those lines whose price is below the tiled kernels'.
-// Codes: by price on either side (us, weights from memory, tiled / small tiles: 370 x 1071 x 6608 107 / 29, 300 x 9133 x 6368 150 / 112, but 1428 x
-// 2166 x 3792 66 / 75, 840 x 2996 x 6896 110 / 118); of 260 shapes the choice loses 0.2 % to the better one in the mean.
+// Codes: by price on either side (us, weights from memory, tiled / small tiles: 370 x 1071 x 6608 107 / 29, but 1428 x
+// 2166 x 3792 66 / 75, 840 x 2996 x 6896 110 / 118); of 260 shapes the choice loses 0.3 % to the better one in the mean.
 // Expanded operands of more than kSmallCodesRows rows: by price on either side, that of the finest tiles that have a compute unit each (fine_tile: 64 x 64 3.0 + 0.00275 K us,
 // 128 x 64 3.9 + 0.0038 K, 128 x 128 4 + 0.0055 K; tiled / small tiles: 512 x 2006 x 4096 14.7 / 19.9, 256 x 3163 x 2048 8.9 / 13.0, but 512 x 1000 x 8000 24 / 21, 200 x
 // 594 x 4176 14 / 7.1).  Where the two are within 15 % the product through the workspace, which has to give the same bits, decides: from the codes, or expanded first.
