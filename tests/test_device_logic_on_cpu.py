@@ -630,6 +630,32 @@ def test_walking_gemm_kernels_store_as_often_as_they_count(tmp_path):
     assert seen == 8
 
 
+def test_gemm_accumulators_are_read_behind_wait_states(tmp_path):
+    """The matrix instructions of k_gemm_x are assembly, which the compiler takes for ordinary instructions: where it copied an accumulator between two of
+    them, the copy would not wait for the result.  In the built code no other instruction of a basic block names the accumulators that its matrix instructions
+    write, but for those behind the wait states."""
+    code = device_code("hif8_gemm_x.hip", tmp_path)
+    asm = subprocess.run([LLVM + "llvm-objdump", "-d", "--no-show-raw-insn", code], check=True, stdout=subprocess.PIPE, text=True).stdout
+
+    def registers(text):
+        return {k + str(i) for k, a, b, k1, one in re.findall(r"\b([av])\[(\d+):(\d+)\]|\b([av])(\d+)\b", text) for k, i in
+                ([(k, i) for i in range(int(a), int(b) + 1)] if k else [(k1, int(one))])}
+
+    seen = 0
+    for body in re.split(r"^[0-9a-f]+ <", asm, flags=re.M):
+        if not re.match(r"\w*k_gemm_xI", body):
+            continue
+        for block in re.split(r"\n[^\n]*\bs_c?branch[^\n]*", body):
+            lines = [line.split("//")[0].split(None, 1) for line in block.split("s_nop 15")[0].splitlines()]
+            lines = [line for line in lines if len(line) == 2]
+            written = set().union(*[registers(ops.split(",")[0]) for op, ops in lines if op.startswith("v_mfma")])
+            first = next((i for i, (op, _) in enumerate(lines) if op.startswith("v_mfma")), 0)
+            others = [(op, ops) for op, ops in lines[first:] if not op.startswith("v_mfma") and registers(ops) & written]
+            assert not others, (body[:60], others[:3])
+        seen += 1
+    assert seen == 36
+
+
 def test_small_gemm_kernel_has_no_static_lds(tmp_path):
     """k_gemm_s looks codes up in a table at LDS address 0, the start of its dynamic LDS: static LDS would come before it."""
     code = device_code("hif8_gemm_s.hip", tmp_path)

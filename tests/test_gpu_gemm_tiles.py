@@ -414,3 +414,28 @@ def test_finest_tiles_every_output(h, M, N, K):
     h.hif8_gemm_set_variant(0)
     want = float(((out.double() - ref.double()) ** 2).sum())
     assert err[1].item() == 0.0 and abs(err[0].item() - want) <= 1e-12 * want
+
+
+# 64 x 64 tiles from 16 K steps on: a part of K every two steps, unevenly, and with a remainder of K; 700 x 1227 and 512 x 2006 go there by price
+@pytest.mark.parametrize("M,N,K,variant", [(130, 190, 1024, 9), (66, 257, 1500, 9), (310, 2751, 2160, 0), (700, 1227, 4096, 0), (512, 2006, 8000, 0)])
+def test_finest_tiles_sum_over_parts_of_k(h, M, N, K, variant):
+    """No less exact than eight binary32 chains, one for each eighth of K, added one after the other (the sum of these products in the small-tile
+    kernel): the error against fp64 is the rounding of the chains, so the two agree to the noise of M N independent errors; one chain is 1.2
+    (K = 2160) to 1.6 times (8000) as far off."""
+    rng = np.random.default_rng(M + N + K)
+    (a, ld), (b, _) = expand(h, random_codes(rng, (M, K), "cast_normal")), expand(h, random_codes(rng, (N, K), "cast_normal"))
+    x, y = a.view(torch.bfloat16).double(), b.view(torch.bfloat16).double()
+    out = torch.empty(M, N, device=dev())
+    h.hif8_gemm_set_variant(variant)
+    h.hif8_gemm_expanded_f32(a, b, out, M, N, K, ld, 1.0, 1.0)
+    h.hif8_gemm_set_variant(0)
+    want, total = x @ y.t(), None
+    units = ld // 64
+    for p in range(8):
+        chain = torch.zeros(M, N, device=dev())
+        for k in range(units * p // 8 * 64, units * (p + 1) // 8 * 64, 32):  # a matrix instruction adds 32 products to the accumulator
+            chain = (chain.double() + x[:, k:k + 32] @ y[:, k:k + 32].t()).float()
+        total = chain if total is None else total + chain
+    off, split = ((o.double() - want).square().mean().sqrt() for o in (out, total))
+    print("%dx%dx%d: %.4g of eight chains' error" % (M, N, K, off / split))
+    assert off <= 1.05 * split
