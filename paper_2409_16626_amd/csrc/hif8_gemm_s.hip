@@ -5,7 +5,7 @@
 // aligned rows; with eight rows of activations their launch has one tile row, most of the chip idles and each
 // workgroup walks the whole of K alone, one memory round trip per step.  Here an output tile is small (16 TM x 16 TN)
 // and the wavefronts of a workgroup split K between them: no barrier in the K loop, a wavefront's loads only ever
-// wait for themselves, and the partial products meet in LDS once, added in wavefront order (the result does not
+// wait for themselves, and the partial products meet in LDS once, added in a fixed order (the result does not
 // depend on timing).
 //
 // A wavefront reads 128 bytes of 8 rows with one load (8 lanes x 16 bytes a row: whole cache lines; fragments taken
@@ -269,7 +269,9 @@ k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __r
     }
     __syncthreads();  // staging areas free: the reduction uses the same LDS
 
-    // the wavefronts' partial tiles, 16 rows at a time, added in wavefront order
+    // the wavefronts' partial tiles, 16 rows at a time, four by four in a fixed order: with more wavefronts, which a plan may take for its speed, a sum of
+    // one after the other has more roundings than it saves in their shorter chains (relative error of binary32 results, 20 x 1284 x 2614: eight wavefronts
+    // 4.6e-8, sixteen 4.9e-8, added so 4.2e-8; 612 x 788 x 785 from codes: four 2.5e-8, eight 2.6e-8, 2.4e-8; the times are the same)
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       if (i > 0) __syncthreads();
@@ -280,8 +282,9 @@ k_gemm_s(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __r
       __syncthreads();
       for (uint32_t e = tid; e < 16u * (TN * 16); e += threads) {
         const uint32_t r = e / (TN * 16), c = e % (TN * 16), row = m0 + i * 16u + r, col = n0 + c;
-        float sum = red[r * kPitch + c];
-        for (uint32_t w = 1; w < waves; ++w) sum += red[(w * 16u + r) * kPitch + c];
+        auto of = [&](uint32_t w) { return w < waves ? red[(w * 16u + r) * kPitch + c] : 0.0f; };
+        float sum = 0.0f;
+        for (uint32_t w = 0; w < waves; w += 4u) sum += (of(w) + of(w + 1u)) + (of(w + 2u) + of(w + 3u));
         if (row < M && col < N) {
           const float o = __fmul_rn(sum, descale);
           if constexpr (EPI == EPI_ERR) {

@@ -201,3 +201,29 @@ def test_small_gemm_nine_wavefronts(h, M, N, K):
     h.hif8_gemm_sqerr(a, b, ref, M, N, K, 8.0, 0.5, err)
     want = float(((out.double() - ref.double()) ** 2).sum())
     assert abs(err.item() - want) <= 1e-12 * want
+
+
+# more wavefronts than the lines of small_plan() give (16 for 8, 8 for 4, 9 for 8), the same number, and fewer (8 for 16)
+@pytest.mark.parametrize("M,N,K,chains", [(20, 1284, 2614, 8), (18, 5345, 2592, 8), (36, 6384, 832, 4), (612, 788, 785, 4), (509, 1003, 2049, 8), (578, 1056, 2849, 4),
+                                          (46, 1475, 10960, 16), (8, 4096, 4096, 8)])
+def test_small_gemm_sum_is_no_less_exact_with_other_wavefronts(h, M, N, K, chains):
+    """The error against fp64 is that of at most `chains` binary32 chains, one for each share of K, added one after the other; the two agree to the noise of
+    M N independent errors, 2 % here at most."""
+    rng = np.random.default_rng(M + N + K)
+    a, b, ld = on_gpu(random_codes(rng, (M, K), "cast_normal"), 1), on_gpu(random_codes(rng, (N, K), "cast_normal"), 1), h.hif8_expanded_ld(K)
+    xa, xb = (torch.empty(r, ld, dtype=torch.bfloat16, device=dev()) for r in (M, N))
+    h.hif8_expand_bf16(a, M, K, xa, ld)
+    h.hif8_expand_bf16(b, N, K, xb, ld)
+    x, y = xa.double(), xb.double()
+    want, total = x @ y.t(), None
+    units = ld // 64
+    for p in range(chains):
+        chain = torch.zeros(M, N, device=dev())
+        for k in range(units * p // chains * 64, units * (p + 1) // chains * 64, 32):  # a matrix instruction adds 32 products to the accumulator
+            chain = (chain.double() + x[:, k:k + 32] @ y[:, k:k + 32].t()).float()
+        total = chain if total is None else total + chain
+    out = torch.empty(M, N, device=dev())
+    h.hif8_gemm_f32(a, b, out, M, N, K, 1.0, 1.0)
+    off, split = ((o.double() - want).square().mean().sqrt() for o in (out, total))
+    print("%dx%dx%d: %.4g of %d chains' error" % (M, N, K, off / split, chains))
+    assert off <= 1.02 * split
