@@ -409,19 +409,17 @@ inline int codes_launches(size_t M, size_t N, size_t K, size_t cus, CodesLaunch 
 // those lines whose price is below the tiled kernels'.
 // Codes: by price on either side (us, weights from memory, tiled / small tiles: 370 x 1071 x 6608 107 / 29, but 1428 x
 // 2166 x 3792 66 / 75, 840 x 2996 x 6896 110 / 118); of 260 shapes the choice loses 0.3 % to the better one in the mean.
-// Expanded operands of more than kSmallCodesRows rows: by price on either side, that of the finest tiles that have a compute unit each (fine_tile: 64 x 64 3.0 + 0.00275 K us,
-// 128 x 64 3.9 + 0.0038 K, 128 x 128 4 + 0.0055 K; tiled / small tiles: 512 x 2006 x 4096 14.7 / 19.9, 256 x 3163 x 2048 8.9 / 13.0, but 512 x 1000 x 8000 24 / 21, 200 x
-// 594 x 4176 14 / 7.1).  Where the two are within 15 % the product through the workspace, which has to give the same bits, decides: from the codes, or expanded first.
+// Expanded operands of more than kSmallCodesRows rows: by price on either side where 64 x 64 tiles have a compute unit each (3.0 + 0.00275 K us; tiled / small
+// tiles: 512 x 2006 x 4096 14.7 / 19.9, 256 x 3163 x 2048 8.9 / 13.0, but 512 x 1000 x 8000 24 / 21, 200 x 594 x 4176 14 / 7.1).  Where the two are within 15 % the
+// product through the workspace, which has to give the same bits, decides: from the codes, or expanded first.  With more tiles the lines hold, beyond which
+// the small tiles' price is up to a third too low for tiles of six and more blocks (tiled / small tiles: 187 x 8860 x 400 7.7 / 10.2, 283 x 6438 x 3776 29.4 /
+// 36.1, 148 x 10790 x 5968 44.7 / 54.0, 258 x 4012 x 992 7.7 / 10.9, 582 x 1998 x 462 6.4 / 8.5).
 inline double expand_us(size_t M, size_t N, size_t ld) { return 2.5 + (double)(M + N) * (double)ld * 3.0 / 5.5e6; }
-inline double tiled_us(size_t M, size_t N, size_t K, size_t cus) {
-  const uint64_t rows = (M + 127) / 128, cols = (N + 63) / 64;
-  return (M + 63) / 64 * cols <= cus ? 3.0 + 0.00275 * (double)K : rows * cols <= cus ? 3.9 + 0.0038 * (double)K
-         : 4.0 + ((M < N ? M : N) <= 256 ? 0.0065 : 0.0055) * (double)K;
-}
 inline bool small_route(size_t M, size_t N, size_t K, bool codes, bool sqerr) {
   const bool small = small_problem(M, N, K, codes, sqerr);
-  const size_t s = M < N ? M : N, tiles = ((M + 127) / 128) * ((N + 127) / 128);
-  if (s <= (codes ? 32 : kSmallCodesRows) || tiles > (codes ? 512u : 256u) || K < 320 || sqerr) return small;  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
+  const size_t s = M < N ? M : N;
+  auto tiles = [&](size_t side) { return ((M + side - 1) / side) * ((N + side - 1) / side); };
+  if (s <= (codes ? 32 : kSmallCodesRows) || (codes ? tiles(128) > 512 : tiles(64) > 256) || K < 320 || sqerr) return small;  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
   const SmallPlan plan = small_choice(M, N, K, codes);
   const double us = SmallCost(M, N, K, codes).us(plan);
   if (codes) {
@@ -429,7 +427,7 @@ inline bool small_route(size_t M, size_t N, size_t K, bool codes, bool sqerr) {
     codes_tile(M, N, K, 256, &tiled);
     return small || us < tiled;
   }
-  const double tiled = tiled_us(M, N, K, 256);
+  const double tiled = 3.0 + 0.00275 * (double)K;
   if (us <= 0.87 * tiled || us >= 1.15 * tiled || plan.waves < 4u) return us < tiled;
   return SmallCost(M, N, K, true).us(small_choice(M, N, K, true, false, plan.waves)) < tiled + expand_us(M, N, K);
 }

@@ -552,6 +552,21 @@ def test_gemm_tile_forms(dev, tile_launches):
             assert got != 4 or ones <= cus
 
 
+def test_small_gemm_route_of_expanded_operands_beyond_64_x_64_tiles(dev):
+    """Where 64 x 64 tiles do not have a compute unit each, the lines of small_problem() hold for expanded operands (products that the price had moved, and
+    slowed down, then drawn ones)."""
+    route, small = dev.devfn_small_route, dev.devfn_small_problem
+    for f in (route, small):
+        f.restype, f.argtypes = ctypes.c_int, [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.c_int]
+    for M, N, K in ((187, 8860, 448), (146, 10754, 768), (283, 6438, 3776), (148, 10790, 6016), (258, 4012, 1024), (582, 1998, 512), (141, 6452, 5824)):
+        assert not small(M, N, K, 0, 0) and not route(M, N, K, 0, 0)
+    rng = np.random.default_rng(11)
+    for _ in range(4000):
+        M, N, K = (int(2.0 ** rng.uniform(lo, hi)) for lo, hi in ((5, 13), (5, 14), (0, 7)))
+        if -(-M // 64) * -(-N // 64) > 256:
+            assert route(M, N, 64 * K, 0, 0) == small(M, N, 64 * K, 0, 0)
+
+
 def test_finest_tile_with_a_compute_unit_each(dev):
     f = dev.devfn_fine_tile
     f.argtypes = [ctypes.c_size_t, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_size_t, ctypes.c_size_t]
