@@ -239,15 +239,33 @@ __device__ __forceinline__ uint32_t vec_begin(uint32_t c, uint32_t cols) {
   const uint32_t e = c * VE;
   return e <= cols - VE ? e : cols - VE;
 }
+// and its index in the matrix.  WHOLE: rows of whole vectors, where the index is a multiple of VE, which the compiler uses: a threshold of standard SR takes an
+// instruction less, and so does an address (11008 x 4096 bfloat16, standard SR by rows: 38.7 us, so 38.1).
+template <int VE, bool WHOLE>
+__device__ __forceinline__ size_t vec_elem(uint32_t row, uint32_t c, uint32_t cols, uint32_t cols_vec) {
+  if constexpr (WHOLE) return ((size_t)row * cols_vec + c) * VE;
+  else return (size_t)row * cols + vec_begin<VE>(c, cols);
+}
 template <int KIND>
 __device__ __forceinline__ const uint8_t* elem_ptr(const void* p, size_t e) {
   return reinterpret_cast<const uint8_t*>(p) + e * (KIND == kSrcF32 ? 4 : 2);
 }
-// one vector of values at element e -> codes
+// One vector of values at element e -> codes.  Standard SR draws its thresholds with one key for each 2^32 elements; a vector lies within one such block (see
+// plan_axis): looking for its end in every vector of a cast bound by the vector ALUs took 5 to 10 % (11008 x 4096 bfloat16 by rows, maximum and scale included,
+// 44.9 us, 48.5 so), selecting a key for every element by columns 154 us instead of 43.
 template <int IMPL, int SRCK>
 __device__ __forceinline__ void encode_vec_any(const uint4& v, float scale, const EncCtx& ctx, uint8_t* __restrict__ dst, size_t e) {
-  if constexpr (SRCK == kSrcF32) st_stream_any(dst + e, encode4_f32<IMPL>(v, scale, ctx, e));
-  else st_stream_any(dst + e, encode8_16<IMPL, SRCK>(v, scale, ctx, e));
+  const EncCtx c = keyed<IMPL>(ctx, e);
+  if constexpr (SRCK == kSrcF32) {
+    const uint32_t y[4] = {v.x, v.y, v.z, v.w};
+    uint32_t o = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o |= encode_one<IMPL, SRCK>(scaled_bits(y[j], scale), c, e + j) << (8 * j);
+    st_stream_any(dst + e, o);
+  } else {
+    st_stream_any(dst + e, make_uint2(encode2_16<IMPL, SRCK>(v.x, scale, c, e) | (encode2_16<IMPL, SRCK>(v.y, scale, c, e + 2) << 16),
+                                      encode2_16<IMPL, SRCK>(v.z, scale, c, e + 4) | (encode2_16<IMPL, SRCK>(v.w, scale, c, e + 6) << 16)));
+  }
 }
 
 template <int SRCK>
@@ -352,7 +370,7 @@ k_amax_axis_elem(const void* __restrict__ src, size_t rows, uint32_t cols, int a
   if (m) atomicMax(out + t % cols, m);
 }
 
-template <int IMPL, int SRCK>
+template <int IMPL, int SRCK, bool WHOLE>
 __global__ void __launch_bounds__(kAxBlock)
 k_encode_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t cols, uint32_t cols_vec, uint32_t chunks,
               const float* __restrict__ d_scale2, uint32_t mode, uint64_t seed,
@@ -362,12 +380,11 @@ k_encode_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t 
   const EncCtx ctx = make_ctx<IMPL>(lut, hrt.w, mode, seed);
   constexpr int VE = vec_elems<SRCK>();
   const uint32_t row = blockIdx.x / chunks, chunk = blockIdx.x - row * chunks;
-  const size_t rbase = (size_t)row * cols;
   uint4 v[kAxUnroll];
 #pragma unroll
   for (int j = 0; j < kAxUnroll; ++j) {
     const uint32_t c = (chunk * kAxUnroll + j) * kAxBlock + threadIdx.x;
-    if (c < cols_vec) v[j] = ld_stream_any<uint4>(elem_ptr<SRCK>(src, rbase + vec_begin<VE>(c, cols)));
+    if (c < cols_vec) v[j] = ld_stream_any<uint4>(elem_ptr<SRCK>(src, vec_elem<VE, WHOLE>(row, c, cols, cols_vec)));
   }
   const float scale = d_scale2[2 * (size_t)row];
   stage_enc_lut<IMPL, SRCK>(lut, g_lut, mode);
@@ -376,7 +393,7 @@ k_encode_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t 
 #pragma unroll
   for (int j = 0; j < kAxUnroll; ++j) {
     const uint32_t c = (chunk * kAxUnroll + j) * kAxBlock + threadIdx.x;
-    if (c < cols_vec) encode_vec_any<IMPL, SRCK>(v[j], scale, ctx, dst, rbase + vec_begin<VE>(c, cols));
+    if (c < cols_vec) encode_vec_any<IMPL, SRCK>(v[j], scale, ctx, dst, vec_elem<VE, WHOLE>(row, c, cols, cols_vec));
   }
 }
 
@@ -397,7 +414,7 @@ constexpr int kQrWaveVecs = 4;  // vectors of a lane up to which a wavefront tak
 // 2746 x 2048 5.67 / 5.56)
 constexpr size_t kQrWaveRows = 512;
 
-template <int IMPL, int SRCK, int VPT, int LANES>
+template <int IMPL, int SRCK, int VPT, int LANES, bool WHOLE>
 __global__ void __launch_bounds__(kQrBlock)
 k_quant_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t rows, uint32_t cols, uint32_t cols_vec, float target,
              int pow2, uint32_t* __restrict__ d_amax, float* __restrict__ d_scale2, uint32_t mode, uint64_t seed,
@@ -415,7 +432,7 @@ k_quant_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t r
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
       const uint32_t c = j * LANES + at;
-      nxt[j] = c < cols_vec ? ld_stream_any<uint4>(elem_ptr<SRCK>(src, (size_t)r * cols + vec_begin<VE>(c, cols))) : make_uint4(0u, 0u, 0u, 0u);
+      nxt[j] = c < cols_vec ? ld_stream_any<uint4>(elem_ptr<SRCK>(src, vec_elem<VE, WHOLE>(r, c, cols, cols_vec))) : make_uint4(0u, 0u, 0u, 0u);
     }
   };
   const uint32_t step = WAVE ? gridDim.x * kQrWaves : gridDim.x;
@@ -450,16 +467,15 @@ k_quant_rows(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t r
       d_scale2[2 * (size_t)r] = scale;
       d_scale2[2 * (size_t)r + 1] = 1.0f / scale;
     }
-    const size_t rbase = (size_t)r * cols;
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
       const uint32_t c = j * LANES + at;
-      if (c < cols_vec) encode_vec_any<IMPL, SRCK>(cur[j], scale, ctx, dst, rbase + vec_begin<VE>(c, cols));
+      if (c < cols_vec) encode_vec_any<IMPL, SRCK>(cur[j], scale, ctx, dst, vec_elem<VE, WHOLE>(r, c, cols, cols_vec));
     }
   }
 }
 
-template <int IMPL, int SRCK>
+template <int IMPL, int SRCK, bool WHOLE>
 __global__ void __launch_bounds__(kAxBlock)
 k_encode_cols(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t rows, uint32_t cols, uint32_t cols_vec,
               uint32_t strips, uint32_t rows_per_wg, const float* __restrict__ d_scale2, uint32_t mode,
@@ -475,19 +491,16 @@ k_encode_cols(const void* __restrict__ src, uint8_t* __restrict__ dst, uint32_t 
   const uint32_t rchunk = blockIdx.x / strips, strip = blockIdx.x - rchunk * strips;
   const uint32_t cv = strip * 64u + lane;
   if (cv >= cols_vec) return;
-  const uint32_t c0 = vec_begin<VE>(cv, cols);
+  const uint32_t c0 = WHOLE ? cv * VE : vec_begin<VE>(cv, cols);
   float sc[VE];
 #pragma unroll
   for (int j = 0; j < VE; ++j) sc[j] = d_scale2[2 * ((size_t)c0 + j)];
   const uint32_t r0 = rchunk * rows_per_wg;
   const uint32_t r1 = min(rows, r0 + rows_per_wg);
   auto encode_row = [&](uint32_t r, const uint4& v) {
-    const uint64_t e0 = (uint64_t)r * cols + c0;
-    const bool split = straddles_block<IMPL, VE>(e0);
-    const EncCtx k0 = keyed<IMPL>(ctx, e0);
-    auto code = [&](uint32_t bits, int j) {
-      return encode_one<IMPL, SRCK>(scaled_bits(bits, sc[j]), split ? keyed<IMPL>(ctx, e0 + j) : k0, e0 + j);
-    };
+    const uint64_t e0 = vec_elem<VE, WHOLE>(r, cv, cols, cols_vec);
+    const EncCtx kc = keyed<IMPL>(ctx, e0);
+    auto code = [&](uint32_t bits, int j) { return encode_one<IMPL, SRCK>(scaled_bits(bits, sc[j]), kc, e0 + j); };
     if constexpr (SRCK == kSrcF32) {
       const uint32_t b0 = code(v.x, 0);
       const uint32_t b1 = code(v.y, 1);
@@ -715,12 +728,18 @@ struct AxisPlan {
   uint32_t cols_vec, chunks, strips, rows_per_wg, row_chunks;
 };
 
+// Whether every vector of a cast lies within one 2^32-element block, as standard SR wants it in the vector kernels: those of rows that end with a whole vector
+// begin at multiples of the vector width; others may reach into the next block where there is one.
+template <int KIND>
+bool vectors_in_blocks(size_t rows, size_t cols, uint32_t mode) {
+  return (mode & 0xFu) != kRmSR || cols % vec_elems<KIND>() == 0 || rows * cols <= (size_t)1 << 32;
+}
 // shapes of the per-channel launches; sizes are limited to what 32-bit row / vector counts hold
 template <int KIND>
-bool plan_axis(size_t rows, size_t cols, int cus, AxisPlan* p) {
+bool plan_axis(size_t rows, size_t cols, int cus, AxisPlan* p, uint32_t mode = kRmTA) {
   constexpr size_t VE = vec_elems<KIND>();
   if (rows > 0x7FFFFFFFu || cols > 0x7FFFFFFFu) return false;
-  p->fast = cols >= VE;
+  p->fast = cols >= VE && vectors_in_blocks<KIND>(rows, cols, mode);
   p->cols_vec = (uint32_t)((cols + VE - 1) / VE);
   const uint32_t per_chunk = kAxBlock * kAxUnroll;
   p->chunks = (p->cols_vec + per_chunk - 1) / per_chunk;
@@ -793,7 +812,7 @@ hif8_status encode_axis(const void* src, uint8_t* dst, size_t rows, size_t cols,
   hif8_status s = ensure_init(&cus, &tb);
   if (s != HIF8_OK) return s;
   AxisPlan p;
-  if (!plan_axis<SRCK>(rows, cols, cus, &p)) return HIF8_ERR_ARG;
+  if (!plan_axis<SRCK>(rows, cols, cus, &p, mode)) return HIF8_ERR_ARG;
   const uint64_t seed = sr_seed();
   if (!p.fast) {
     hipLaunchKernelGGL(k_encode_axis_elem<SRCK>, dim3(grid_elem(rows * cols, cus)), dim3(256), 0, st, src, dst, rows,
@@ -802,12 +821,17 @@ hif8_status encode_axis(const void* src, uint8_t* dst, size_t rows, size_t cols,
   }
   dispatch_impl_only(impl_no_alu(mode), [&](auto impl_c) {
     constexpr int IMPL = decltype(impl_c)::value;
-    if (axis == 0)
-      hipLaunchKernelGGL((k_encode_rows<IMPL, SRCK>), dim3((unsigned)(rows * p.chunks)), dim3(kAxBlock), 0, st, src,
-                         dst, (uint32_t)cols, p.cols_vec, p.chunks, d_scale2, mode, seed, tb.enc_lut);
-    else
-      hipLaunchKernelGGL((k_encode_cols<IMPL, SRCK>), dim3(p.row_chunks * p.strips), dim3(kAxBlock), 0, st, src, dst,
-                         (uint32_t)rows, (uint32_t)cols, p.cols_vec, p.strips, p.rows_per_wg, d_scale2, mode, seed, tb.enc_lut);
+    auto go = [&](auto whole_c) {
+      constexpr bool WHOLE = decltype(whole_c)::value;
+      if (axis == 0)
+        hipLaunchKernelGGL((k_encode_rows<IMPL, SRCK, WHOLE>), dim3((unsigned)(rows * p.chunks)), dim3(kAxBlock), 0, st, src,
+                           dst, (uint32_t)cols, p.cols_vec, p.chunks, d_scale2, mode, seed, tb.enc_lut);
+      else
+        hipLaunchKernelGGL((k_encode_cols<IMPL, SRCK, WHOLE>), dim3(p.row_chunks * p.strips), dim3(kAxBlock), 0, st, src, dst,
+                           (uint32_t)rows, (uint32_t)cols, p.cols_vec, p.strips, p.rows_per_wg, d_scale2, mode, seed, tb.enc_lut);
+    };
+    if (cols % vec_elems<SRCK>() == 0) go(std::true_type{});
+    else go(std::false_type{});
   });
   return finish_launch();
 }
@@ -828,7 +852,7 @@ hif8_status quantize_rows(const void* src, uint8_t* dst, size_t rows, size_t col
   if (s != HIF8_OK) return s;
   constexpr size_t VE = vec_elems<SRCK>();
   const size_t cols_vec = (cols + VE - 1) / VE;
-  if (cols < VE || cols_vec > (size_t)kQrBlock * 8) {
+  if (cols < VE || cols_vec > (size_t)kQrBlock * 8 || !vectors_in_blocks<SRCK>(rows, cols, mode)) {
     s = amax_axis<SRCK>(src, rows, cols, 0, d_amax, st);
     if (s != HIF8_OK) return s;
     s = hif8host::launch_scale_from_amax(d_amax, d_scale2, (uint32_t)rows, target, pow2, st);
@@ -848,8 +872,12 @@ hif8_status quantize_rows(const void* src, uint8_t* dst, size_t rows, size_t col
     constexpr int IMPL = decltype(impl_c)::value;
     auto go = [&](auto vpt_c, auto lanes_c) {
       constexpr int VPT = decltype(vpt_c)::value, LANES = decltype(lanes_c)::value;
-      hipLaunchKernelGGL((k_quant_rows<IMPL, SRCK, VPT, LANES>), dim3((unsigned)wgs), dim3(kQrBlock), 0, st, src, dst, (uint32_t)rows,
-                         (uint32_t)cols, (uint32_t)cols_vec, target, pow2, am, d_scale2, mode, seed, tb.enc_lut);
+      auto launch = [&](auto whole_c) {
+        hipLaunchKernelGGL((k_quant_rows<IMPL, SRCK, VPT, LANES, decltype(whole_c)::value>), dim3((unsigned)wgs), dim3(kQrBlock), 0, st, src, dst,
+                           (uint32_t)rows, (uint32_t)cols, (uint32_t)cols_vec, target, pow2, am, d_scale2, mode, seed, tb.enc_lut);
+      };
+      if (IMPL == IMPL_SR && cols % VE == 0) launch(std::bool_constant<IMPL == IMPL_SR>{});
+      else launch(std::false_type{});
     };
     auto vecs = [&](auto lanes_c) {
       using std::integral_constant;

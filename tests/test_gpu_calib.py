@@ -295,3 +295,56 @@ def test_per_channel_any_columns_and_address(h, rows, cols, off):
             gd = f32_bits(out) if kind == "f32" else bits16(out)
             assert_same_bytes(gd[off:off + n], (wd.view(np.uint32) if kind == "f32" else wd).reshape(-1), "decode %s %d" % (kind, axis))
             assert torch.all(out[:off] == 7.0) and torch.all(out[off + n:] == 7.0)
+
+
+def test_standard_sr_rows_over_the_end_of_a_threshold_block(h):
+    """More than 2^32 elements in rows of an odd number of columns, so that a row, and in it a vector, reaches over element 2^32, where another key of the
+    thresholds begins: that row and its neighbours, cast by rows, by columns and in one pass, against the oracle's one-element entry point."""
+    cols = 32749
+    row = (1 << 32) // cols  # the row that reaches over the end
+    rows = row + 3
+    x = torch.zeros(rows * cols, dtype=torch.bfloat16, device=dev())
+    lo, hi = (row - 1) * cols, (row + 2) * cols
+    g = torch.Generator(device=dev()).manual_seed(3)
+    x[lo:hi] = (torch.randn(hi - lo, generator=g, device=dev()) * 40.0).to(torch.bfloat16)
+    assert lo < (1 << 32) - 8 and (1 << 32) - row * cols > 8 and hi > (1 << 32) + 8 and ((1 << 32) - row * cols) % 8 != 0
+    at = np.concatenate([np.arange(lo, lo + 64), np.arange(row * cols - 16, row * cols + 16), np.arange((1 << 32) - 64, (1 << 32) + 64),
+                         np.arange((row + 1) * cols - 16, (row + 1) * cols + 64), np.arange(hi - 64, hi)])
+    idx = torch.from_numpy(at).to(dev())
+    xs = bf16_bits(x[idx])
+    codes, am, sc = torch.empty(rows * cols, dtype=torch.uint8, device=dev()), torch.empty(rows, device=dev()), torch.ones(rows, 2, device=dev())
+    got = {}
+    h.hif8_encode_axis_bf16(x, codes, rows, cols, 0, sc, SR)
+    got["rows"] = codes[idx].cpu().numpy()
+    codes.fill_(0xAA)
+    h.hif8_encode_axis_bf16(x, codes, rows, cols, 1, torch.ones(cols, 2, device=dev()), SR)
+    got["columns"] = codes[idx].cpu().numpy()
+    want = [orc.encode_one(np.array([int(b) << 16], np.uint32).view(np.float32)[0], SR, orc.SRC_BF16, orc.sr_threshold(SEED, int(i))) for b, i in zip(xs, at)]
+    for name in got:
+        assert got[name].tolist() == want, name
+    codes.fill_(0xAA)
+    h.hif8_quantize_rows_bf16(x, codes, rows, cols, am, sc, 32768.0, 1, SR)
+    one = codes[idx].cpu().numpy()
+    h.hif8_encode_axis_bf16(x, codes, rows, cols, 0, sc, SR)
+    assert np.array_equal(one, codes[idx].cpu().numpy())
+
+
+def test_standard_sr_by_columns_costs_no_more_than_twice_by_rows(h):
+    """Both draw one threshold per element and read and write the same bytes (40 and 43 us for 11008 x 4096; a key selected for each element: 154)."""
+    rows, cols = 8192, 4096
+    x = torch.randn(rows, cols, device=dev()).to(torch.bfloat16)
+    codes = torch.empty(rows, cols, dtype=torch.uint8, device=dev())
+    best = []
+    for axis in (0, 1):
+        sc = torch.ones(rows if axis == 0 else cols, 2, device=dev())
+        took = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                h.hif8_encode_axis_bf16(x, codes, rows, cols, axis, sc, SR)
+            b.record()
+            b.synchronize()
+            took.append(a.elapsed_time(b))
+        best.append(min(took))
+    assert best[1] < 2 * best[0], best
