@@ -5,6 +5,7 @@
 //   per-channel ops   amax / encode / decode of a row-major matrix with one scale per row or per
 //                     column (Sec. 4.2 names per-channel weight scaling as a further method).
 // They reuse the element encoders and the streaming helpers of the conversion kernels.
+#include "hif8_axis_plan.hpp"
 #include "hif8_conv.hpp"
 
 namespace hif8calib {
@@ -218,7 +219,8 @@ k_cast_scales(const void* __restrict__ src, uint16_t* __restrict__ dst, size_t r
 // per-channel kernels.  Row-major [rows, cols]; axis 0: one scale per row, axis 1: one per column.
 // A row of at least one vector is covered by vectors that start at its first element, wherever that lies in memory; the
 // last one ends with the row, so that it shares elements with the one before where cols is not a multiple of the vector width
-// (a maximum does not mind, and a cast writes the same bytes twice).  Rows of fewer elements go to the element kernels.
+// (a maximum does not mind, and a cast writes the same bytes twice).  Shorter rows, and matrices that are narrow or small, go to the element kernels
+// (axis_by_elements).
 // Maximum, scale and codes in us, element by element with an atomic for each (until now) / now: 316 x 5267 bfloat16 3400 / 4.8, 11008 x
 // 4099 7190 / 30 (11008 x 4096 23.5), binary32 7310 / 40 (38.7).
 //
@@ -251,7 +253,7 @@ __device__ __forceinline__ const uint8_t* elem_ptr(const void* p, size_t e) {
   return reinterpret_cast<const uint8_t*>(p) + e * (KIND == kSrcF32 ? 4 : 2);
 }
 // One vector of values at element e -> codes.  Standard SR draws its thresholds with one key for each 2^32 elements; a vector lies within one such block (see
-// plan_axis): looking for its end in every vector of a cast bound by the vector ALUs took 5 to 10 % (11008 x 4096 bfloat16 by rows, maximum and scale included,
+// vectors_in_blocks): looking for its end in every vector of a cast bound by the vector ALUs took 5 to 10 % (11008 x 4096 bfloat16 by rows, maximum and scale included,
 // 44.9 us, 48.5 so), selecting a key for every element by columns 154 us instead of 43.
 template <int IMPL, int SRCK>
 __device__ __forceinline__ void encode_vec_any(const uint4& v, float scale, const EncCtx& ctx, uint8_t* __restrict__ dst, size_t e) {
@@ -348,8 +350,8 @@ k_amax_cols(const void* __restrict__ src, uint32_t rows, uint32_t cols, uint32_t
   }
 }
 
-// Rows shorter than a vector.  axis 0: a lane per row, which stores its maximum; axis 1: a lane stays in one column (the lanes
-// that walk are a multiple of cols), one atomic for each that found something.
+// Short rows.  axis 0: a lane per row, which stores its maximum; axis 1: a lane stays in one column (the lanes
+// that walk are a multiple of cols, fewer than a vector), one atomic for each that found something.
 template <int SRCK>
 __global__ void __launch_bounds__(256)
 k_amax_axis_elem(const void* __restrict__ src, size_t rows, uint32_t cols, int axis, uint32_t* __restrict__ out) {
@@ -728,18 +730,11 @@ struct AxisPlan {
   uint32_t cols_vec, chunks, strips, rows_per_wg, row_chunks;
 };
 
-// Whether every vector of a cast lies within one 2^32-element block, as standard SR wants it in the vector kernels: those of rows that end with a whole vector
-// begin at multiples of the vector width; others may reach into the next block where there is one.
-template <int KIND>
-bool vectors_in_blocks(size_t rows, size_t cols, uint32_t mode) {
-  return (mode & 0xFu) != kRmSR || cols % vec_elems<KIND>() == 0 || rows * cols <= (size_t)1 << 32;
-}
 // shapes of the per-channel launches; sizes are limited to what 32-bit row / vector counts hold
 template <int KIND>
-bool plan_axis(size_t rows, size_t cols, int cus, AxisPlan* p, uint32_t mode = kRmTA) {
+bool plan_axis(int what, int axis, size_t rows, size_t cols, int cus, AxisPlan* p, uint32_t mode = kRmTA) {
   constexpr size_t VE = vec_elems<KIND>();
   if (rows > 0x7FFFFFFFu || cols > 0x7FFFFFFFu) return false;
-  p->fast = cols >= VE && vectors_in_blocks<KIND>(rows, cols, mode);
   p->cols_vec = (uint32_t)((cols + VE - 1) / VE);
   const uint32_t per_chunk = kAxBlock * kAxUnroll;
   p->chunks = (p->cols_vec + per_chunk - 1) / per_chunk;
@@ -755,6 +750,7 @@ bool plan_axis(size_t rows, size_t cols, int cus, AxisPlan* p, uint32_t mode = k
   p->rows_per_wg = rpw;
   p->row_chunks = (uint32_t)((rows + rpw - 1) / rpw);
   if ((uint64_t)rows * p->chunks > 0x7FFFFFFFull || (uint64_t)p->row_chunks * p->strips > 0x7FFFFFFFull) return false;
+  p->fast = !axis_by_elements(what, axis, rows, cols, VE, axis == 0 ? (uint64_t)rows * p->chunks : (uint64_t)p->row_chunks * p->strips, mode);
   return true;
 }
 
@@ -768,9 +764,9 @@ hif8_status amax_axis(const void* src, size_t rows, size_t cols, int axis, float
   hif8_status s = ensure_init(&cus, nullptr);
   if (s != HIF8_OK) return s;
   AxisPlan p;
-  if (!plan_axis<SRCK>(rows, cols, cus, &p)) return HIF8_ERR_ARG;
+  if (!plan_axis<SRCK>(AXIS_AMAX, axis, rows, cols, cus, &p)) return HIF8_ERR_ARG;
   uint32_t* out = reinterpret_cast<uint32_t*>(d_amax);
-  const bool stores = axis == 0 && p.chunks == 1 && rows * cols != 0;  // k_amax_rows and k_amax_axis_elem write every row themselves
+  const bool stores = axis == 0 && (p.chunks == 1 || !p.fast) && rows * cols != 0;  // k_amax_rows and k_amax_axis_elem write every row themselves
   if (!stores) {
     s = launch_fill_u32(out, 0u, (uint32_t)nch, st);
     if (s != HIF8_OK || rows * cols == 0) return s;
@@ -812,7 +808,7 @@ hif8_status encode_axis(const void* src, uint8_t* dst, size_t rows, size_t cols,
   hif8_status s = ensure_init(&cus, &tb);
   if (s != HIF8_OK) return s;
   AxisPlan p;
-  if (!plan_axis<SRCK>(rows, cols, cus, &p, mode)) return HIF8_ERR_ARG;
+  if (!plan_axis<SRCK>(AXIS_CAST, axis, rows, cols, cus, &p, mode)) return HIF8_ERR_ARG;
   const uint64_t seed = sr_seed();
   if (!p.fast) {
     hipLaunchKernelGGL(k_encode_axis_elem<SRCK>, dim3(grid_elem(rows * cols, cus)), dim3(256), 0, st, src, dst, rows,
@@ -852,7 +848,7 @@ hif8_status quantize_rows(const void* src, uint8_t* dst, size_t rows, size_t col
   if (s != HIF8_OK) return s;
   constexpr size_t VE = vec_elems<SRCK>();
   const size_t cols_vec = (cols + VE - 1) / VE;
-  if (cols < VE || cols_vec > (size_t)kQrBlock * 8 || !vectors_in_blocks<SRCK>(rows, cols, mode)) {
+  if (cols < VE || cols_vec > (size_t)kQrBlock * 8 || !vectors_in_blocks(rows, cols, VE, mode)) {
     s = amax_axis<SRCK>(src, rows, cols, 0, d_amax, st);
     if (s != HIF8_OK) return s;
     s = hif8host::launch_scale_from_amax(d_amax, d_scale2, (uint32_t)rows, target, pow2, st);
@@ -903,7 +899,7 @@ hif8_status decode_axis(const uint8_t* src, void* dst, size_t rows, size_t cols,
   hif8_status s = ensure_init(&cus, &tb);
   if (s != HIF8_OK) return s;
   AxisPlan p;
-  if (!plan_axis<DSTK>(rows, cols, cus, &p)) return HIF8_ERR_ARG;
+  if (!plan_axis<DSTK>(AXIS_CAST, axis, rows, cols, cus, &p)) return HIF8_ERR_ARG;
   if (!p.fast) {
     hipLaunchKernelGGL(k_decode_axis_elem<DSTK>, dim3(grid_elem(rows * cols, cus)), dim3(256), 0, st, src, dst, rows,
                        cols, axis, d_scale2);

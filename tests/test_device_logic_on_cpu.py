@@ -567,6 +567,36 @@ def test_small_gemm_route_of_expanded_operands_beyond_64_x_64_tiles(dev):
             assert route(M, N, 64 * K, 0, 0) == small(M, N, 64 * K, 0, 0)
 
 
+def test_per_channel_calls_that_go_to_the_element_kernels(dev):
+    """Narrow and small matrices, both sides of each line; what the vector kernels cannot take: rows shorter than a vector, launches of 2^32 lanes and more, vectors
+    that may reach over the end of a standard SR block."""
+    f = dev.devfn_axis_by_elements
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t, ctypes.c_size_t, ctypes.c_uint64, ctypes.c_uint32]
+    AMAX, CAST, TA, HR, TE, SSR, SR = 0, 1, 0, 1, 2, 3, 4
+    for ve in (4, 8):
+        for what in (AMAX, CAST):
+            for axis in (0, 1):
+                assert f(what, axis, 1 << 22, ve - 1, ve, 100, TA) and f(what, axis, 1 << 23, 4096, ve, 1 << 24, TA)
+                assert not f(what, axis, 1 << 23, 4096, ve, (1 << 24) - 1, TA | 0x30)
+        # maxima: up to 32 columns by rows, 16 where there are few; by columns always in vectors
+        assert f(AMAX, 0, 1 << 20, 32, ve, 1, TA) and not f(AMAX, 0, 1 << 20, 33, ve, 1, TA) and not f(AMAX, 1, 1 << 20, 9, ve, 1, TA)
+        assert f(AMAX, 0, 100, 16, ve, 1, TA) and not f(AMAX, 0, 100, 17, ve, 1, TA)
+        for mode in (TA, TE, HR, SSR, SR):
+            drawn = mode in (HR, SSR, SR)
+            c, n = (400, 1 << 18) if drawn else (256, 1 << 17)
+            assert f(CAST, 0, 1 << 16, c - 1, ve, 1, mode) and not f(CAST, 0, 1 << 16, c, ve, 1, mode)
+            assert f(CAST, 0, n // 4096, 4096, ve, 1, mode) and not f(CAST, 0, n // 4096 + 1, 4096, ve, 1, mode)
+            c = {4: (32, 56), 8: (40, 96)}[ve][drawn]
+            assert f(CAST, 1, 1 << 20, c - 1, ve, 1, mode) and not f(CAST, 1, 1 << 20, c, ve, 1, mode)
+            n = ve << (18 if drawn else 17)
+            assert f(CAST, 1, n // 4096, 4096, ve, 1, mode) and not f(CAST, 1, n // 4096 + 1, 4096, ve, 1, mode)
+            n, cols = ve << (19 if drawn else 17), 64 * ve + 1  # one vector in the last wavefront of a row
+            assert f(CAST, 1, n // cols, cols, ve, 1, mode) and not f(CAST, 1, n // cols + 1, cols, ve, 1, mode)
+            # more than 2^32 elements: whole vectors to a row, or element by element under standard SR
+            assert not f(CAST, 0, 1 << 21, 4096, ve, 1, mode) and f(CAST, 0, 1 << 21, 4097, ve, 1, mode) == (mode == SR) == f(CAST, 1, 1 << 21, 4097, ve, 1, mode | 0x10)
+            assert not f(CAST, 0, (1 << 32) // 4097, 4097, ve, 1, mode)
+
+
 def test_finest_tile_with_a_compute_unit_each(dev):
     f = dev.devfn_fine_tile
     f.argtypes = [ctypes.c_size_t, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_size_t, ctypes.c_size_t]

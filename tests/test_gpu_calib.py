@@ -297,6 +297,14 @@ def test_per_channel_any_columns_and_address(h, rows, cols, off):
             assert torch.all(out[:off] == 7.0) and torch.all(out[off + n:] == 7.0)
 
 
+# the vector kernels, which matrices that are neither narrow nor small take (axis_by_elements): several chunks of a row and one, whole vectors to a row or not; strips with a
+# vector in the last wavefront; the fewest columns that go there by rows and by columns
+@pytest.mark.parametrize("rows,cols,off", [(1100, 4099, 1), (1030, 4096, 0), (70, 70001, 1), (9000, 515, 0), (16500, 263, 1), (16500, 256, 0), (45000, 97, 1), (110000, 41, 0),
+                                           (44000, 96, 1)])
+def test_per_channel_vector_kernels(h, rows, cols, off):
+    test_per_channel_any_columns_and_address(h, rows, cols, off)
+
+
 def test_standard_sr_rows_over_the_end_of_a_threshold_block(h):
     """More than 2^32 elements in rows of an odd number of columns, so that a row, and in it a vector, reaches over element 2^32, where another key of the
     thresholds begins: that row and its neighbours, cast by rows, by columns and in one pass, against the oracle's one-element entry point."""
