@@ -308,7 +308,7 @@ struct SmallCost {
 // 14.2 / 7.7, 46 x 5162 x 7536 38 / 28, 48 x 10642 x 8528 63 / 45, 106 x 6133 x 7600 61 / 41, 173 x 3951 x 6832 53 / 36; expanded 80 x 1644 x 2528 10.0 /
 // 6.9, 128 x 674 x 7456 18.8 / 10, 200 x 594 x 4176 18.6 / 7.1, 400 x 835 x 3456 16.9 / 10.  Over the shapes above it is 1.8 % (codes) and 3 %
 // (expanded) behind the best tile for each; small_plan 22 and 26 %.
-// The wavefronts decide the bits.  Up to kSmallCodesRows rows they are those of the code operands, for both kinds; the squared error takes the wavefronts of the stored product, with
+// The wavefronts decide the bits.  Up to kSmallCodesRows rows they are those of the code operands, for both kinds; the squared error takes the wavefronts that the stored product has here, with
 // the tiles of its kernels and 0.01 us for each workgroup's atomic.  With fewer than four wavefronts (more tiles than the chip holds, a short K)
 // small_plan() stands.  waves != 0: that number is asked for.
 // Another plan than small_plan()'s has to promise 7 % (the fit's own error; without that 12 of 296 shapes on codes lost 4 to 10 %, with it 2).  No 16
@@ -414,12 +414,17 @@ inline int codes_launches(size_t M, size_t N, size_t K, size_t cus, CodesLaunch 
 // product through the workspace, which has to give the same bits, decides: from the codes, or expanded first.  With more tiles the lines hold, beyond which
 // the small tiles' price is up to a third too low for tiles of six and more blocks (tiled / small tiles: 187 x 8860 x 400 7.7 / 10.2, 283 x 6438 x 3776 29.4 /
 // 36.1, 148 x 10790 x 5968 44.7 / 54.0, 258 x 4012 x 992 7.7 / 10.9, 582 x 1998 x 462 6.4 / 8.5).
+// The squared error leaves the small tiles where the stored product does: it is that of the same bits, and faster (expanded, small tiles / tiled: 762 x 1119 x
+// 5760 28.4 / 20.9, 1915 x 312 x 3136 19.1 / 13.2, 635 x 1081 x 8896 34.8 / 28.1, 2352 x 349 x 11200 49.6 / 49.8).  It does not follow into them, where its
+// atomics come on top (expanded 501 x 951 x 832 11.3 / 7.2, 618 x 338 x 832 7.6 / 6.3; codes 591 x 3051 x 624 22.6 / 15.8, 415 x 8977 x 9856 210 / 213), so there
+// it is the error of the tiled kernels' sum, whose rounding differs.
 inline double expand_us(size_t M, size_t N, size_t ld) { return 2.5 + (double)(M + N) * (double)ld * 3.0 / 5.5e6; }
 inline bool small_route(size_t M, size_t N, size_t K, bool codes, bool sqerr) {
   const bool small = small_problem(M, N, K, codes, sqerr);
   const size_t s = M < N ? M : N;
   auto tiles = [&](size_t side) { return ((M + side - 1) / side) * ((N + side - 1) / side); };
-  if (s <= (codes ? 32 : kSmallCodesRows) || (codes ? tiles(128) > 512 : tiles(64) > 256) || K < 320 || sqerr) return small;  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
+  if (s <= (codes ? 32 : kSmallCodesRows) || (codes ? tiles(128) > 512 : tiles(64) > 256) || K < 320) return small;  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
+  if (sqerr) return small && (!small_problem(M, N, K, codes, false) || small_route(M, N, K, codes, false));
   const SmallPlan plan = small_choice(M, N, K, codes);
   const double us = SmallCost(M, N, K, codes).us(plan);
   if (codes) {

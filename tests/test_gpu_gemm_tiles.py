@@ -439,3 +439,15 @@ def test_finest_tiles_sum_over_parts_of_k(h, M, N, K, variant):
     off, split = ((o.double() - want).square().mean().sqrt() for o in (out, total))
     print("%dx%dx%d: %.4g of eight chains' error" % (M, N, K, off / split))
     assert off <= 1.05 * split
+
+
+# products that the price takes from the small tiles to 64 x 64 tiles, and some that stay there; odd rows and a K with a remainder
+@pytest.mark.parametrize("M,N,K", [(700, 1227, 4096), (512, 2006, 4096), (512, 2006, 8000), (311, 1633, 5930), (512, 1000, 8000), (200, 594, 4176)])
+def test_squared_error_of_the_stored_bits(h, M, N, K):
+    """Where the squared error had run in the small-tile kernel as the stored product had, both take the same kernel: against the stored result it is zero."""
+    rng = np.random.default_rng(M + N + K)
+    (a, ld), (b, _) = expand(h, random_codes(rng, (M, K), "cast_normal")), expand(h, random_codes(rng, (N, K), "cast_normal"))
+    out, err = torch.empty(M, N, device=dev()), torch.zeros(1, dtype=torch.float64, device=dev())
+    h.hif8_gemm_expanded_f32(a, b, out, M, N, K, ld, 8.0, 0.5)
+    h.hif8_gemm_expanded_sqerr(a, b, out, M, N, K, ld, 8.0, 0.5, err)
+    assert err.item() == 0.0
