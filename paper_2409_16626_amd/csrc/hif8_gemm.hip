@@ -353,8 +353,12 @@ static hif8_status gemm_dispatch(const uint8_t* A, const uint8_t* B, void* out, 
   if (s != HIF8_OK) return s;
   const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
   const bool fast = K != 0 && (K % 16) == 0 && aligned_to(A, 16) && aligned_to(B, 16);
-  if (!fast || g_gemm_variant == 12 || (g_gemm_variant == 0 && small_route(M, N, K, true, EPI == EPI_ERR)))
-    return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st);
+  if (!fast || g_gemm_variant == 12)
+    return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, small_choice(M, N, K, true, EPI == EPI_ERR), descale, st);
+  if (g_gemm_variant == 0) {
+    const SmallRoute route = small_route(M, N, K, true, EPI == EPI_ERR);
+    if (route.small) return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, route.plan, descale, st);
+  }
   CodesLaunch launch[2] = {{g_gemm_variant == 5 ? CODES_256 : CODES_128, 0u, n}, {CODES_128, 0u, 0u}};
   const int launches = g_gemm_variant == 0 ? codes_launches(M, N, K, (size_t)cus, launch) : 1;
   for (int i = 0; i < launches && s == HIF8_OK; ++i) {
@@ -394,17 +398,22 @@ static hif8_status gemm_ws(const uint8_t* A, const uint8_t* B, void* out, const 
   if (EPI == EPI_ERR && !aligned_to(err, 8)) return HIF8_ERR_ARG;
   // few rows: straight from the codes, which gives the bits that the expanded operands would give (see small_plan)
   if (expanded_variant() == 0 && (M < N ? M : N) <= kSmallCodesRows && small_problem(M, N, expanded_ld(K), false, EPI == EPI_ERR))
-    return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st);
+    return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, small_choice(M, N, K, true, EPI == EPI_ERR), descale, st);
   const size_t ld = expanded_ld(K);
-  if (EPI != EPI_ERR && expanded_variant() == 0 && (M < N ? M : N) > kSmallCodesRows && small_route(M, N, ld, false, false)) {
-    const uint32_t waves = small_codes_waves(M, N, K);
-    if (waves != 0u) return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, descale, st, waves);
+  SmallRoute route{false, {0, 0, 0}, {0, 0, 0}};
+  const bool routed = EPI != EPI_ERR && expanded_variant() == 0;
+  if (routed) {
+    route = small_route(M, N, ld, false, false);
+    SmallPlan plan;
+    if (route.small && (M < N ? M : N) > kSmallCodesRows && small_from_codes(M, N, K, route, &plan))
+      return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, plan, descale, st);
   }
   uint16_t* xa = reinterpret_cast<uint16_t*>(ws);
   uint16_t* xb = xa + M * ld;  // M * ld * 2 bytes is a multiple of 128: still 16-byte aligned
   const hif8_status s = expand_rows(A, M, B, N, K, xa, ld, st);
   if (s != HIF8_OK) return s;
-  return gemm_expanded<EPI>(xa, xb, out, ref, err, M, N, ld, descale, st);
+  if (route.small) return gemm_small<EPI>(xa, xb, true, out, ref, err, M, N, ld, route.plan, descale, st);
+  return gemm_expanded<EPI>(xa, xb, out, ref, err, M, N, ld, descale, st, Batch{}, routed);
 }
 
 // position of the smallest finite entry of err[rows * cols] -> best[0] = e_row_lo + row,

@@ -313,16 +313,16 @@ hif8_status expand_rows(const uint8_t* a, size_t rows_a, const uint8_t* b, size_
                         hipStream_t st);
 hif8_status expand_cols(const uint8_t* codes, size_t rows, size_t cols, uint16_t* dst, size_t ld, hipStream_t st);
 
-// out = (A x B^T) * descale on operands of pitch ld (zero beyond K); batch.na != 0: the na x nb products of a scale search
+// out = (A x B^T) * descale on operands of pitch ld (zero beyond K); batch.na != 0: the na x nb products of a scale search; tiled: the caller has asked
+// small_route(), which said no
 template <int EPI>
 hif8_status gemm_expanded(const uint16_t* A, const uint16_t* B, void* out, const float* ref, double* err, size_t M,
-                          size_t N, size_t ld, float descale, hipStream_t st, const Batch& batch = Batch{});
+                          size_t N, size_t ld, float descale, hipStream_t st, const Batch& batch = Batch{}, bool tiled = false);
 
 // ---- few output tiles, any K and alignment of code operands (hif8_gemm_s.hip) ----
-// out = (A x B^T) * descale; expanded: operands are bfloat16 of pitch K (a multiple of 64), else codes of pitch K; waves: wavefronts that share K,
-// 0: the plan's
+// out = (A x B^T) * descale; expanded: operands are bfloat16 of pitch K (a multiple of 64), else codes of pitch K, in the tiles of `plan`
 template <int EPI>
 hif8_status gemm_small(const void* A, const void* B, bool expanded, void* out, const float* ref, double* err, size_t M,
-                       size_t N, size_t K, float descale, hipStream_t st, uint32_t waves = 0);
+                       size_t N, size_t K, const SmallPlan& plan, float descale, hipStream_t st);
 
 }  // namespace hif8gemm

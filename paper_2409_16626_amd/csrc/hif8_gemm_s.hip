@@ -362,12 +362,11 @@ static hif8_status launch_s(const void* A, const void* B, void* out, const float
 
 template <int OP, int EPI>
 static hif8_status gemm_small_op(const void* A, const void* B, void* out, const float* ref, double* err, size_t M, size_t N,
-                                 size_t K, float descale, hipStream_t st, uint32_t waves) {
+                                 size_t K, const SmallPlan& p, float descale, hipStream_t st) {
   const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
   int cus = 0;
   const hif8_status s = ensure_init(&cus, nullptr);
   if (s != HIF8_OK) return s;
-  const SmallPlan p = small_choice(M, N, K, OP == OP_CODES, EPI == EPI_ERR, waves);
   auto run = [&](auto launch) { return launch(A, B, out, ref, err, m, n, k, descale, p.waves, cus, st); };
   switch (p.tm * 10 + p.tn) {
     case 11:
@@ -393,14 +392,14 @@ static hif8_status gemm_small_op(const void* A, const void* B, void* out, const 
 
 template <int EPI>
 hif8_status gemm_small(const void* A, const void* B, bool expanded, void* out, const float* ref, double* err, size_t M, size_t N,
-                       size_t K, float descale, hipStream_t st, uint32_t waves) {
-  return expanded ? gemm_small_op<OP_BF16, EPI>(A, B, out, ref, err, M, N, K, descale, st, waves)
-                  : gemm_small_op<OP_CODES, EPI>(A, B, out, ref, err, M, N, K, descale, st, waves);
+                       size_t K, const SmallPlan& plan, float descale, hipStream_t st) {
+  return expanded ? gemm_small_op<OP_BF16, EPI>(A, B, out, ref, err, M, N, K, plan, descale, st)
+                  : gemm_small_op<OP_CODES, EPI>(A, B, out, ref, err, M, N, K, plan, descale, st);
 }
 
-template hif8_status gemm_small<EPI_F32>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t, uint32_t);
-template hif8_status gemm_small<EPI_BF16>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t, uint32_t);
-template hif8_status gemm_small<EPI_F16>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t, uint32_t);
-template hif8_status gemm_small<EPI_ERR>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, float, hipStream_t, uint32_t);
+template hif8_status gemm_small<EPI_F32>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, const SmallPlan&, float, hipStream_t);
+template hif8_status gemm_small<EPI_BF16>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, const SmallPlan&, float, hipStream_t);
+template hif8_status gemm_small<EPI_F16>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, const SmallPlan&, float, hipStream_t);
+template hif8_status gemm_small<EPI_ERR>(const void*, const void*, bool, void*, const float*, double*, size_t, size_t, size_t, const SmallPlan&, float, hipStream_t);
 
 }  // namespace hif8gemm

@@ -148,7 +148,7 @@ inline uint32_t pairs_per_launch(int tile, size_t M, size_t N, size_t K, uint32_
 
 // Products with at most this many rows on one side run straight from the codes in hif8_gemm_ws_* when the expanded operands
 // would go to the small-tile kernel: up to here both operand kinds have one K split (small_choice) and so the same bits.  Above it
-// the codes are expanded first, which is faster for large products, or asked for the expanded operands' split, by price (small_codes_waves).
+// the codes are expanded first, which is faster for large products, or asked for the expanded operands' split, by price (small_from_codes).
 constexpr size_t kSmallCodesRows = 128;
 
 // Which problems go to the small-tile kernel (hif8_gemm_s.hip) although the tiled kernels could run them.  The tiled kernels
@@ -223,14 +223,14 @@ inline size_t small_resident(uint32_t tm, uint32_t tn, uint32_t waves, bool code
 }
 // The same on one compute unit, for the kernels that store: by the registers that they take (a wavefront's, codes / expanded: 1 x 1 67 (half-row form 75) / 60, 1 x 2 87 / 76, 1 x 3 107 /
 // 96, 2 x 2 120 / 112, 2 x 3 140 / 130, 2 x 4 160 / 152, 3 x 4, 4 x 3 and 4 x 4 192 to 236).
-inline uint32_t small_resident_stored(const SmallPlan& p, bool codes) {
+constexpr uint32_t small_resident_stored(const SmallPlan& p, bool codes) {
   const uint32_t by_lds = 160u * 1024u / (512u + p.waves * (p.tm + p.tn) * 2048u), blocks = p.tm * p.tn;
   const uint32_t per_simd = blocks == 1u ? (codes ? 6u : 8u) : blocks == 2u ? (codes ? 5u : 6u) : blocks == 3u ? (codes ? 4u : 5u) : blocks == 4u ? 4u : blocks <= 8u ? 3u : 2u;
   const uint32_t by_regs = 4u * per_simd / p.waves, most = by_lds < by_regs ? by_lds : by_regs;
   return most == 0u ? 1u : most;
 }
 // What a kernel can be launched with: 1024 lanes up to four blocks, 768 up to eight, 512 above, and LDS for the wavefronts' areas.
-inline bool small_fits(const SmallPlan& p) {
+constexpr bool small_fits(const SmallPlan& p) {
   return p.waves <= (p.tm * p.tn <= 4u ? 16u : p.tm * p.tn <= 8u ? 12u : 8u) && 512u + p.waves * (p.tm + p.tn) * 2048u <= 160u * 1024u;
 }
 // The wavefronts' shares of K in pairs of units of 64, 128 codes: whole cache lines for every wavefront, unless single units give the longest
@@ -289,16 +289,23 @@ struct SmallCost {
     memory = fourth((double)(m + n) * units * (codes ? 64.0 : 128.0) / 6e6 * kSmallRates[c ? 1 : 0].memory);
   }
   static double fourth(double x) { return x * x * x * x; }
-  // what plans are compared by: the largest of the parts, more where two are close
-  double score(const SmallPlan& p) const {
-    const SmallRates& r = kSmallRates[codes ? 1 : 0];
-    const uint64_t tiles = (uint64_t)tiles_m[p.tm] * tiles_n[p.tn], of_unit = (tiles + 255u) / 256u;
-    const uint32_t turns = of_unit > 0xFFFFFF00u ? 0xFFFFFF00u : (uint32_t)of_unit, resident = small_resident_stored(p, codes);
-    const double rows = (codes && M <= 8 && p.tm * p.tn == 1u ? 0.5 : (double)p.tm) + p.tn;  // in blocks of 16; the half-row form
-    const double lds = (double)turns * units * rows * r.lds;
-    const double wave = (double)((turns + resident - 1) / resident) * ((units + p.waves - 1) / p.waves * (rows * r.wave + r.unit) + r.turn + r.add * p.waves * (p.tm * p.tn));
-    return fourth(lds) + fourth(wave) + memory;
+  // what plans are compared by: the largest of the parts, more where two are close.  In two steps, the tile's and the wavefronts'
+  struct Tile {
+    double rows, lds;  // in blocks of 16 (the half-row form); fourth power
+    uint32_t turns;
+  };
+  Tile tile(uint32_t tm, uint32_t tn) const {
+    const uint64_t tiles = (uint64_t)tiles_m[tm] * tiles_n[tn], of_unit = (tiles + 255u) / 256u;
+    const uint32_t turns = of_unit > 0xFFFFFF00u ? 0xFFFFFF00u : (uint32_t)of_unit;
+    const double rows = (codes && M <= 8 && tm * tn == 1u ? 0.5 : (double)tm) + tn;
+    return Tile{rows, fourth((double)turns * units * rows * kSmallRates[codes ? 1 : 0].lds), turns};
   }
+  double score(const Tile& t, const SmallPlan& p, uint32_t share, uint32_t resident) const {
+    const SmallRates& r = kSmallRates[codes ? 1 : 0];
+    const uint32_t rounds = t.turns <= resident ? 1u : (t.turns + resident - 1) / resident;
+    return t.lds + fourth((double)rounds * (share * (t.rows * r.wave + r.unit) + r.turn + r.add * p.waves * (p.tm * p.tn))) + memory;
+  }
+  double score(const SmallPlan& p) const { return score(tile(p.tm, p.tn), p, (units + p.waves - 1) / p.waves, small_resident_stored(p, codes)); }
   double us(const SmallPlan& p) const { return kSmallRates[codes ? 1 : 0].base + std::sqrt(std::sqrt(score(p))); }
 };
 
@@ -328,8 +335,21 @@ inline bool ninth_wave(const SmallPlan& p, size_t K) {
 // What the host takes for a launch: with less on the GPU nothing is gained, and the look at all tiles would come on top.
 // Up to 16 rows it pays from larger products on (16 x 4447 x 7104 16.9 us, now 14.7, 16 x 10257 x 10453 41.8, 33.5; 16 x 1131 x 4272 8.0, 8.0).
 constexpr double kLaunchBound = 5.2, kFewRowsBound = 9.0;
-constexpr uint32_t kSmallWaves[] = {16, 9, 8, 4};
-constexpr uint32_t kSmallTiles[][2] = {{1, 1}, {1, 2}, {1, 3}, {2, 2}, {2, 3}, {2, 4}, {3, 4}, {4, 3}, {4, 4}};
+constexpr uint32_t kSmallWaveCounts = 4, kSmallTileCount = 9;
+constexpr uint32_t kSmallWaves[kSmallWaveCounts] = {16, 9, 8, 4};
+constexpr uint32_t kSmallTiles[kSmallTileCount][2] = {{1, 1}, {1, 2}, {1, 3}, {2, 2}, {2, 3}, {2, 4}, {3, 4}, {4, 3}, {4, 4}};
+struct SmallResident {  // workgroups of a compute unit; 0: cannot be launched
+  uint32_t of[2][kSmallTileCount][kSmallWaveCounts];
+  constexpr SmallResident() : of{} {
+    for (uint32_t c = 0; c < 2; ++c)
+      for (uint32_t n = 0; n < kSmallTileCount; ++n)
+        for (uint32_t i = 0; i < kSmallWaveCounts; ++i) {
+          const SmallPlan p{kSmallTiles[n][0], kSmallTiles[n][1], kSmallWaves[i]};
+          of[c][n][i] = small_fits(p) ? small_resident_stored(p, c == 1) : 0u;
+        }
+  }
+};
+constexpr SmallResident kSmallResident;
 inline double atomics(const SmallCost& c, const SmallPlan& p, size_t K) {  // of a squared error, see launch_s
   const double wgs = (double)c.tiles_m[p.tm] * c.tiles_n[p.tn];
   return K < 4096 && wgs > 1024.0 ? 1024.0 : wgs;
@@ -350,14 +370,19 @@ inline SmallPlan small_choice(size_t M, size_t N, size_t K, bool codes, bool sqe
   if (may_stay && base_us < (s <= 16 ? kFewRowsBound : kLaunchBound)) return base;
   SmallPlan best = base;
   double least = 1e300;
-  for (const auto& t : kSmallTiles) {
-    if (16u * (t[0] - 1u) >= M || 16u * (t[1] - 1u) >= N) continue;  // a block outside the matrix
-    for (const uint32_t w : kSmallWaves) {
-      const SmallPlan p{t[0], t[1], w};
-      if (w == 9u ? waves != 9u : w == 16u && s <= 16) continue;
+  uint32_t share[kSmallWaveCounts];
+  for (uint32_t i = 0; i < kSmallWaveCounts; ++i) share[i] = (cost.units + kSmallWaves[i] - 1) / kSmallWaves[i];
+  for (uint32_t n = 0; n < kSmallTileCount; ++n) {
+    const uint32_t tm = kSmallTiles[n][0], tn = kSmallTiles[n][1];
+    if (16u * (tm - 1u) >= M || 16u * (tn - 1u) >= N || (sqerr && (tm == 3u || tn == 3u))) continue;  // a block outside the matrix; tiles not built
+    const SmallCost::Tile t = cost.tile(tm, tn);
+    if (t.lds + cost.memory >= least) continue;
+    for (uint32_t i = 0; i < kSmallWaveCounts; ++i) {
+      const uint32_t w = kSmallWaves[i], resident = kSmallResident.of[codes ? 1 : 0][n][i];
+      if (resident == 0u || (w == 9u ? waves != 9u : w == 16u && s <= 16)) continue;
       if (waves != 0u ? w != waves : w > 4u && w / 2u * kShareK >= ld) continue;  // no wavefronts without a share
-      if (!small_fits(p) || (sqerr && (p.tm == 3u || p.tn == 3u))) continue;
-      const double c = (cost.score(p) + (sqerr ? SmallCost::fourth(0.01 * atomics(cost, p, K)) : 0.0)) * (w == 16u ? kSixteen : 1.0);
+      const SmallPlan p{tm, tn, w};
+      const double c = (cost.score(t, p, share[i], resident) + (sqerr ? SmallCost::fourth(0.01 * atomics(cost, p, K)) : 0.0)) * (w == 16u ? kSixteen : 1.0);
       if (c < least) {
         best = p;
         least = c;
@@ -419,32 +444,50 @@ inline int codes_launches(size_t M, size_t N, size_t K, size_t cus, CodesLaunch 
 // atomics come on top (expanded 501 x 951 x 832 11.3 / 7.2, 618 x 338 x 832 7.6 / 6.3; codes 591 x 3051 x 624 22.6 / 15.8, 415 x 8977 x 9856 210 / 213), so there
 // it is the error of the tiled kernels' sum, whose rounding differs.
 inline double expand_us(size_t M, size_t N, size_t ld) { return 2.5 + (double)(M + N) * (double)ld * 3.0 / 5.5e6; }
-inline bool small_route(size_t M, size_t N, size_t K, bool codes, bool sqerr) {
+// The plan that the prices are of comes with the answer, so that a call searches once (0.15 to 0.3 us on the host, next to products of a few us).
+struct SmallRoute {
+  bool small;
+  SmallPlan plan;        // where small
+  SmallPlan from_codes;  // of the workspace's product, with the wavefronts of `plan`; waves 0: not looked for
+};
+inline SmallRoute small_route(size_t M, size_t N, size_t K, bool codes, bool sqerr) {
+  const SmallPlan none{0, 0, 0};
   const bool small = small_problem(M, N, K, codes, sqerr);
   const size_t s = M < N ? M : N;
   auto tiles = [&](size_t side) { return ((M + side - 1) / side) * ((N + side - 1) / side); };
-  if (s <= (codes ? 32 : kSmallCodesRows) || (codes ? tiles(128) > 512 : tiles(64) > 256) || K < 320) return small;  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
-  if (sqerr) return small && (!small_problem(M, N, K, codes, false) || small_route(M, N, K, codes, false));
-  const SmallPlan plan = small_choice(M, N, K, codes);
-  const double us = SmallCost(M, N, K, codes).us(plan);
+  auto by_lines = [&] { return small ? SmallRoute{true, small_choice(M, N, K, codes, sqerr), none} : SmallRoute{false, none, none}; };
+  if (s <= (codes ? 32 : kSmallCodesRows) || (codes ? tiles(128) > 512 : tiles(64) > 256) || K < 320) return by_lines();  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
+  if (sqerr) {
+    if (codes || !small || !small_problem(M, N, K, false, false) || small_route(M, N, K, false, false).small) return by_lines();
+    return SmallRoute{false, none, none};
+  }
+  SmallRoute r{true, small_choice(M, N, K, codes), none};
+  if (codes && small) return r;
+  const double us = SmallCost(M, N, K, codes).us(r.plan);
   if (codes) {
     double tiled = 0.0;
     codes_tile(M, N, K, 256, &tiled);
-    return small || us < tiled;
+    r.small = us < tiled;
+    return r;
   }
   const double tiled = 3.0 + 0.00275 * (double)K;
-  if (us <= 0.87 * tiled || us >= 1.15 * tiled || plan.waves < 4u) return us < tiled;
-  return SmallCost(M, N, K, true).us(small_choice(M, N, K, true, false, plan.waves)) < tiled + expand_us(M, N, K);
+  if (us <= 0.87 * tiled || us >= 1.15 * tiled || r.plan.waves < 4u) {
+    r.small = us < tiled;
+    return r;
+  }
+  r.from_codes = small_choice(M, N, K, true, false, r.plan.waves);
+  r.small = SmallCost(M, N, K, true).us(r.from_codes) < tiled + expand_us(M, N, K);
+  return r;
 }
 
-// A product through the workspace, of operands whose expansions would go to the small-tile kernel with more than kSmallCodesRows rows: straight from the codes with
+// A product through the workspace, of operands whose expansions would go to the small-tile kernel (x) with more than kSmallCodesRows rows: straight from the codes with
 // the expansions' wavefronts, which gives their bits, where that is faster than writing them (2.5 us and 3 bytes an element; us, expanded first / from
-// the codes: 130 x 1477 x 2730 20.2 / 11.4, 168 x 981 x 1216 14.6 / 8, 454 x 1143 x 5168 28 / 25).  Returns those wavefronts, 0: expand.
-inline uint32_t small_codes_waves(size_t M, size_t N, size_t K) {
+// the codes: 130 x 1477 x 2730 20.2 / 11.4, 168 x 981 x 1216 14.6 / 8, 454 x 1143 x 5168 28 / 25).  False: expand.
+inline bool small_from_codes(size_t M, size_t N, size_t K, const SmallRoute& x, SmallPlan* plan) {
+  if (x.plan.waves < 4u) return false;
   const size_t ld = (K + 63) / 64 * 64;
-  const SmallPlan x = small_choice(M, N, ld, false);
-  if (x.waves < 4u) return 0;
-  return SmallCost(M, N, K, true).us(small_choice(M, N, K, true, false, x.waves)) < SmallCost(M, N, ld, false).us(x) + expand_us(M, N, ld) ? x.waves : 0u;
+  *plan = x.from_codes.waves != 0u ? x.from_codes : small_choice(M, N, K, true, false, x.plan.waves);
+  return SmallCost(M, N, K, true).us(*plan) < SmallCost(M, N, ld, false).us(x.plan) + expand_us(M, N, ld);
 }
 
 // Workgroup -> tile of the expanded-operand kernel.  The hardware deals consecutive workgroups round-robin over the

@@ -4,6 +4,7 @@
 // tests.  Not part of the product and never loaded by it.
 #include <stdint.h>
 #include <stddef.h>
+#include <chrono>
 #define HIF8_DEVICE_HOST_SHIM 1
 #define __device__
 #define __host__
@@ -13,6 +14,19 @@ static inline int __clz(int x) { return x == 0 ? 32 : __builtin_clz((unsigned)x)
 #include "../../paper_2409_16626_amd/csrc/hif8_axis_plan.hpp"
 #include "../../paper_2409_16626_amd/csrc/hif8_gemm_split.hpp"
 #include "../../paper_2409_16626_amd/csrc/hif8_multi_plan.hpp"
+
+template <typename F>
+static double fastest(int rounds, F call) {  // ns a call
+  static volatile uint32_t sink;
+  double best = 1e300;
+  for (int r = 0; r < rounds; ++r) {
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int i = 0; i < 200; ++i) sink = call();
+    const double ns = std::chrono::duration<double, std::nano>(std::chrono::steady_clock::now() - t0).count() / 200;
+    if (ns < best) best = ns;
+  }
+  return best;
+}
 
 extern "C" {
 // per-tensor scale from an amax (the arithmetic of the scale kernels)
@@ -124,8 +138,30 @@ uint32_t devfn_small_choice(size_t M, size_t N, size_t K, int codes, int sqerr, 
   *waves = p.waves;
   return p.tm * 100 + p.tn * 10;
 }
-int devfn_small_route(size_t M, size_t N, size_t K, int codes, int sqerr) { return hif8gemm::small_route(M, N, K, codes != 0, sqerr != 0); }
-uint32_t devfn_small_codes_waves(size_t M, size_t N, size_t K) { return hif8gemm::small_codes_waves(M, N, K); }
+int devfn_small_route(size_t M, size_t N, size_t K, int codes, int sqerr) { return hif8gemm::small_route(M, N, K, codes != 0, sqerr != 0).small; }
+// the plan that comes with the route: as devfn_small_choice, 0 where the product does not go there
+uint32_t devfn_small_route_plan(size_t M, size_t N, size_t K, int codes, int sqerr, uint32_t* waves) {
+  const hif8gemm::SmallRoute r = hif8gemm::small_route(M, N, K, codes != 0, sqerr != 0);
+  *waves = r.plan.waves;
+  return r.small ? r.plan.tm * 100 + r.plan.tn * 10 : 0u;
+}
+uint32_t devfn_small_codes_waves(size_t M, size_t N, size_t K) {
+  const hif8gemm::SmallRoute r{true, hif8gemm::small_choice(M, N, (K + 63) / 64 * 64, false), {0, 0, 0}};
+  hif8gemm::SmallPlan p{0, 0, 0};
+  return hif8gemm::small_from_codes(M, N, K, r, &p) ? p.waves : 0u;
+}
+// shortest time of a call, ns, over `rounds` of 200: the route with its plan (of the product, and of the workspace's where it is taken from the codes) / one search
+double devfn_small_route_ns(size_t M, size_t N, size_t K, int codes, int rounds) {
+  return fastest(rounds, [&] {
+    const hif8gemm::SmallRoute r = hif8gemm::small_route(M, N, K, codes != 0, false);
+    hif8gemm::SmallPlan p = r.plan;
+    if (codes == 0 && r.small) hif8gemm::small_from_codes(M, N, K, r, &p);
+    return p.waves;
+  });
+}
+double devfn_small_choice_ns(size_t M, size_t N, size_t K, int codes, int rounds) {
+  return fastest(rounds, [&] { return hif8gemm::small_choice(M, N, K, codes != 0).waves; });
+}
 int devfn_small_by_pairs(size_t K, uint32_t waves) { return hif8gemm::small_by_pairs(K, waves); }
 int devfn_small_problem(size_t M, size_t N, size_t K, int codes, int sqerr) { return hif8gemm::small_problem(M, N, K, codes != 0, sqerr != 0); }
 // the finest tile with which a launch of 128 x 128 tiles, one to a compute unit, keeps that: 0 = 128 x 128, 1 = 128 x 64, 2 = 64 x 64

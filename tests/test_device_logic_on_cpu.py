@@ -326,6 +326,33 @@ def test_small_gemm_choice(dev):
     assert waves_of(130, 900, 2730) and not waves_of(1000, 1000, 100000)
 
 
+def test_small_gemm_route_brings_its_plan(dev):
+    """What the route says and what it took to say so: the plan of the kernel that is launched, so that a call searches once (and once more for the codes'
+    plan, where a product through the workspace is taken from them)."""
+    f, choice, route = dev.devfn_small_route_plan, dev.devfn_small_choice, dev.devfn_small_route
+    f.restype, f.argtypes = ctypes.c_uint32, [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_uint32)]
+    choice.restype, choice.argtypes = ctypes.c_uint32, [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.c_int, ctypes.c_uint32, ctypes.POINTER(ctypes.c_uint32)]
+    route.restype, route.argtypes = ctypes.c_int, [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.c_int]
+    rng = np.random.default_rng(12)
+    seen = set()
+    for i in range(4000):
+        M, N, K = (int(2.0 ** rng.uniform(0, 20 if i % 4 == 0 else 13)) for _ in range(3))
+        codes, sqerr = i // 4 % 2, i // 8 % 2
+        k = K if codes else -(-K // 64) * 64
+        w, want = ctypes.c_uint32(0), ctypes.c_uint32(0)
+        t = f(M, N, k, codes, sqerr, ctypes.byref(w))
+        assert (t != 0) == route(M, N, k, codes, sqerr)
+        if t:
+            assert (t, w.value) == (choice(M, N, k, codes, sqerr, 0, ctypes.byref(want)), want.value)
+        seen.add((codes, sqerr, t != 0))
+    assert len(seen) == 8
+    took, search = dev.devfn_small_route_ns, dev.devfn_small_choice_ns
+    for g in (took, search):
+        g.restype, g.argtypes = ctypes.c_double, [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.c_int]
+    for M, N, K, codes, most in ((40, 600, 400, 1, 1.7), (700, 700, 704, 1, 1.7), (509, 1003, 2112, 1, 1.7), (200, 400, 512, 0, 2.8), (700, 700, 704, 0, 2.8)):
+        assert any(took(M, N, K, codes, 30) <= most * search(M, N, K, codes, 30) for _ in range(5))  # the machine may be busy
+
+
 # (M, N, K) measured faster in small tiles, then those measured faster in the tiled kernels, in the kernels' own time
 SMALL_OR_TILED = {
     ("codes", "store"): ([(8, 11008, 4096), (1, 200000, 16), (32, 8192, 64), (32, 200000, 64), (64, 8000, 64), (128, 8192, 64), (512, 2048, 64),
