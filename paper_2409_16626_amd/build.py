@@ -2,11 +2,14 @@
 
 Every .hip / .cpp file under csrc/ is one translation unit; they are compiled in parallel
 into _build/ and linked into one shared library.  binding/native_call.cpp, the marshalling of Python arguments,
-becomes an extension module of its own (g++, Python's and torch's headers), _native_call.so.
+becomes an extension module of its own (g++, Python's and torch's headers), _native_call-*.so; the library does not need it.
 """
 import glob
+import hashlib
 import os
+import re
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -15,7 +18,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJDIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libhif8.so")
 NATIVE_SRC = os.path.join(PKG, "binding", "native_call.cpp")
-NATIVE = os.path.join(PKG, "_native_call.so")
+NATIVE_INPUTS = [NATIVE_SRC, os.path.join(ROOT, "include", "hif8.h")]
 
 
 def sources():
@@ -36,17 +39,27 @@ HIPCC_FLAGS = [
 ]
 
 
+def native_path() -> str:
+    """Where the extension module is for this torch and this Python, whose C++ and C interfaces it is compiled against, and for these sources; a module
+    for others is not found, and so not loaded."""
+    import torch
+    digest = hashlib.sha256()
+    for f in NATIVE_INPUTS:
+        with open(f, "rb") as src:
+            digest.update(src.read())
+    kind = re.sub(r"[^\w.]", "_", "%s-%s" % (torch.__version__, sysconfig.get_config_var("SOABI")))
+    return os.path.join(PKG, "_native_call-%s-%s.so" % (kind, digest.hexdigest()[:12]))
+
+
 def build_native(force: bool = True, verbose: bool = False) -> str:
     """The extension module that hif8.py calls the library through."""
-    inputs = [NATIVE_SRC, os.path.join(ROOT, "include", "hif8.h")]
-    if not force and os.path.exists(NATIVE) and all(os.path.getmtime(f) <= os.path.getmtime(NATIVE) for f in inputs):
-        return NATIVE
-    import sysconfig
-
+    path = native_path()
+    if not force and os.path.exists(path):
+        return path
     import torch
     from torch.utils import cpp_extension
     dirs = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"]] + cpp_extension.include_paths()
-    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    tmp = path + ".tmp.%d" % os.getpid()
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
     for d in dirs:
         cmd += ["-isystem", d]
@@ -59,8 +72,11 @@ def build_native(force: bool = True, verbose: bool = False) -> str:
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         raise RuntimeError("g++ failed on %s:\n%s" % (NATIVE_SRC, r.stdout))
-    os.replace(tmp, NATIVE)
-    return NATIVE
+    os.replace(tmp, path)
+    for old in glob.glob(glob.escape(path[:-len("-0123456789ab.so")]) + "-*.so"):  # of other sources
+        if old != path:
+            os.remove(old)
+    return path
 
 
 def is_stale() -> bool:
@@ -70,9 +86,11 @@ def is_stale() -> bool:
     return any(os.path.getmtime(f) > t for f in sources() + headers())
 
 
-def build(force: bool = True, verbose: bool = False, jobs: int = 8) -> str:
+def build(force: bool = True, verbose: bool = False, jobs: int = 8, native: bool = True) -> str:
+    """The library and, if `native`, the extension module."""
     if not force and not is_stale():
-        build_native(False, verbose)
+        if native:
+            build_native(False, verbose)
         return LIB
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJDIR, exist_ok=True)
@@ -94,9 +112,10 @@ def build(force: bool = True, verbose: bool = False, jobs: int = 8) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=jobs) as pool:
-        native = pool.submit(build_native, force, verbose)
+        extension = pool.submit(build_native, force, verbose) if native else None
         objs = list(pool.map(compile_one, sources()))
-        native.result()
+        if extension:
+            extension.result()
     tmp = LIB + ".tmp.%d" % os.getpid()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
     if verbose:

@@ -1,7 +1,7 @@
 """Thin binding over libhif8.so: same names as the C ABI in include/hif8.h.
 
 Argument marshalling only -- every step of the conversion runs in the HIP kernels.  The usual arguments of a launch are taken in native
-code (binding/native_call.cpp); what that does not take goes through ctypes, in the line below it.
+code (binding/native_call.cpp); what that does not take goes through ctypes, in the line below it, and so does every call where it cannot be built or loaded.
 Data arguments are torch tensors living on the GPU (or raw integer device pointers);
 bfloat16 / float16 tensors may be passed as such or as int16/uint16 views.  The HIP
 stream defaults to torch's current stream.  There is no CPU fallback: if the library
@@ -10,6 +10,7 @@ is missing or a call fails, an exception is raised.
 import ctypes
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -43,7 +44,7 @@ def _load():
     path = _build.LIB
     if not os.path.exists(path):
         # nothing built yet: build once (hipcc cross-compiles without a GPU); never fall back
-        _build.build(force=True)
+        _build.build(force=True, native=False)
     return ctypes.CDLL(path)
 
 
@@ -188,19 +189,34 @@ def _check(status):
         raise Hif8Error(status, lib.hif8_last_hip_error())
 
 
+class _NoNative:
+    """In place of the native marshalling where it cannot be had: everything is left to ctypes."""
+
+    def __getattr__(self, name):
+        return lambda *args: NotImplemented
+
+
 def _load_native():
     """The native marshalling, bound to the library that is loaded here: each of its functions returns None after a successful call and
-    NotImplemented for arguments it leaves to ctypes.  4 tokens x 4096, scaled and encoded: 6.1 us a call through ctypes, 4.45 so."""
-    if not os.path.exists(_build.NATIVE):
-        _build.build_native()
-    spec = importlib.util.spec_from_file_location("_native_call", _build.NATIVE)
-    native = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(native)
-    if _device is None or _raw_stream is None:
-        native.set_up(lib._handle, _check, torch.cuda.current_device, lambda device: torch.cuda.current_stream(device).cuda_stream)
-    else:
-        native.set_up(lib._handle, _check, _device, _raw_stream)
-    return native
+    NotImplemented for arguments it leaves to ctypes.  4 tokens x 4096, scaled and encoded: 6.1 us a call through ctypes, 4.45 so.  It needs a C++ compiler, once, and
+    this torch's interface; without them every call goes through ctypes."""
+    try:
+        path = _build.native_path()
+        if not os.path.exists(path):
+            if not os.access(os.path.dirname(path), os.W_OK):
+                raise OSError("%s is not there and cannot be written" % path)
+            _build.build_native()
+        spec = importlib.util.spec_from_file_location("_native_call", path)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
+        if _device is None or _raw_stream is None:
+            native.set_up(lib._handle, _check, torch.cuda.current_device, lambda device: torch.cuda.current_stream(device).cuda_stream)
+        else:
+            native.set_up(lib._handle, _check, _device, _raw_stream)
+        return native
+    except Exception as e:
+        warnings.warn("no native argument marshalling, calls go through ctypes and take 1.6 us longer: %s" % e, RuntimeWarning, stacklevel=3)
+        return _NoNative()
 
 
 _native = _load_native()

@@ -1,6 +1,9 @@
 """The native marshalling of launch arguments: what it leaves to ctypes, what it raises, and that it does what the ctypes line does."""
 import ctypes
+import os
 import re
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -56,6 +59,72 @@ def test_what_is_left_to_ctypes():
     with Mode():
         assert f(P, P, 0, 1.0, 0, 0) is NotImplemented
     assert not any(hasattr(hif8._native, n) for n in ("hif8_init", "hif8_calibrate_layer_f32", "hif8_multi_cast_f32"))
+
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(hif8.__file__)))
+IMPORT = """
+import os, sys, warnings
+from paper_2409_16626_amd import build
+%s
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    from paper_2409_16626_amd import hif8
+assert [w.category for w in seen if "native" in str(w.message)] == [RuntimeWarning], [str(w.message) for w in seen]
+hif8.hif8_encode_f32(0x1000, 0x1000, 0, 1.0, stream=0)
+for bad, status in ((dict(scale=0.0), -3), (dict(rounding_mode=5), -2)):
+    try:
+        hif8.hif8_encode_f32(0x1000, 0x1000, 16, stream=0, **bad)
+    except hif8.Hif8Error as e:
+        assert e.status == status
+    else:
+        assert False
+print("went through ctypes")
+"""
+
+
+# nothing built and no compiler; nowhere to put it; built for another torch, and no compiler; a module that does not load; a library without
+# one of its functions
+@pytest.mark.parametrize("what", ["no_compiler", "read_only", "other_torch", "broken", "other_library"])
+def test_package_without_native_marshalling(tmp_path, what):
+    """The library is all that the package needs: without the extension module it warns, and its calls go through ctypes."""
+    there = str(tmp_path / "_native_call.so")
+    setup = {
+        "no_compiler": "os.environ['PATH'] = '/nonexistent'; build.native_path = lambda: %r" % there,
+        "read_only": "build.native_path = lambda: '/nonexistent/_native_call.so'",
+        "other_torch": "os.environ['PATH'] = '/nonexistent'; import torch; torch.__version__ = '0.0.0'",
+        "broken": "build.native_path = lambda: %r; open(%r, 'w').write('no module')" % (there, there),
+        "other_library": """
+import ctypes, importlib.util
+class Loader:  # hands the module another library's handle
+    def __init__(self, spec): self.real = spec.loader
+    def create_module(self, spec): return self.real.create_module(spec)
+    def exec_module(self, module):
+        self.real.exec_module(module)
+        set_up = module.set_up
+        module.set_up = lambda handle, *rest: set_up(ctypes.CDLL('libc.so.6')._handle, *rest)
+from_file = importlib.util.spec_from_file_location
+def spec_of(name, path):
+    spec = from_file(name, path)
+    spec.loader = Loader(spec)
+    return spec
+importlib.util.spec_from_file_location = spec_of
+""",
+    }[what]
+    r = subprocess.run([sys.executable, "-c", IMPORT % setup], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert r.returncode == 0 and "went through ctypes" in r.stdout, r.stdout
+
+
+def test_native_module_is_of_this_torch_python_and_header(monkeypatch, tmp_path):
+    from paper_2409_16626_amd import build
+    path = build.native_path()
+    assert os.path.exists(path) and hif8._native.__file__ == path
+    monkeypatch.setattr(torch, "__version__", "0.0.0")
+    assert build.native_path() != path
+    monkeypatch.undo()
+    header = tmp_path / "hif8.h"
+    header.write_text(open(build.NATIVE_INPUTS[1]).read() + "\n")
+    monkeypatch.setattr(build, "NATIVE_INPUTS", [build.NATIVE_INPUTS[0], str(header)])
+    assert build.native_path() != path
 
 
 @pytest.mark.gpu
