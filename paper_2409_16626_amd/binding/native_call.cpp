@@ -3,9 +3,9 @@
 // encoded, 6.1 -> 4.45 us a call; an encode of 18,000 values 5.7 -> 4.4).
 //
 // Each function takes the arguments of the C call in its order.  Pointers: None, an int, or a torch.Tensor that lies on the GPU and is contiguous; a byte
-// count behind a workspace may be None, the size of that tensor; the stream is None (torch's current one) or an int.  What is of another kind (tensor
-// subclasses, CPU tensors, streams as objects, numbers that do not fit, an active torch function mode, ...) is not looked at here: the
-// function returns NotImplemented without having done anything, and hif8.py goes its own way, with its own errors.
+// count behind a workspace may be None, the size of that tensor; truth values are whole numbers; the stream is None (torch's current one), an int or an
+// object with the handle in `cuda_stream`.  What is of another kind (tensor subclasses, CPU tensors, numbers that do not fit, an active torch function mode
+// other than that of a default device, which has no part in these calls, ...) is not looked at here: the function returns NotImplemented without having done anything, and hif8.py goes its own way, with its own errors.
 // Success returns None; a status other than HIF8_OK raises through the checker that set_up() was given.  The GIL is released during the call,
 // as ctypes does: a launch may wait for the queue.
 #define PY_SSIZE_T_CLEAN
@@ -13,6 +13,7 @@
 
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <dlfcn.h>
+#include <torch/csrc/PyInterpreter.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
@@ -28,6 +29,7 @@ namespace {
 PyObject* g_check = nullptr;       // check(status): raises
 PyObject* g_device = nullptr;      // () -> index of the current device
 PyObject* g_raw_stream = nullptr;  // (device) -> handle of its current stream
+PyObject* g_device_mode = nullptr; // type of the function mode that a default device is, or None
 
 struct Seen {
   const at::Tensor* last = nullptr;  // tensor of the workspace argument just before
@@ -62,7 +64,7 @@ bool take_integer(PyObject* o, T* v, const Seen& seen) {
     *v = (T)(seen.last->numel() * seen.last->element_size());
     return true;
   }
-  if (!PyLong_CheckExact(o)) return false;
+  if (!PyLong_CheckExact(o) && !PyBool_Check(o)) return false;
   if (std::is_signed<T>::value) {
     const long long x = PyLong_AsLongLong(o);
     if (x == -1 && PyErr_Occurred()) {
@@ -103,10 +105,14 @@ bool take_stream(PyObject* o, void** p, const Seen& seen) {
     Seen none;
     return take_pointer(o, p, none);
   }
-  if (o != Py_None || !seen.any) return false;
-  PyObject* device = PyObject_CallNoArgs(g_device);
-  PyObject* handle = device ? PyObject_CallOneArg(g_raw_stream, device) : nullptr;
-  Py_XDECREF(device);
+  PyObject* handle = nullptr;
+  if (o != Py_None) {
+    handle = PyObject_GetAttrString(o, "cuda_stream");
+  } else if (seen.any) {
+    PyObject* device = PyObject_CallNoArgs(g_device);
+    handle = device ? PyObject_CallOneArg(g_raw_stream, device) : nullptr;
+    Py_XDECREF(device);
+  }
   Seen none;
   const bool ok = handle != nullptr && PyLong_CheckExact(handle) && take_pointer(handle, p, none);
   Py_XDECREF(handle);
@@ -135,12 +141,22 @@ bool take_all(PyObject* const* args, std::tuple<A...>& values, Seen& seen, std::
   return (take(args[I], &std::get<I>(values), seen, I + 1 == sizeof...(A)) && ...);  // the stream comes last in every call
 }
 
+// whether a function mode is active that may want to see what is done with the tensors
+bool seen_by_a_mode() {
+  if (!at::impl::torch_function_mode_enabled()) return false;
+  for (int64_t i = 0; i < at::impl::PythonTorchFunctionTLS::stack_len(); ++i) {
+    PyObject* mode = at::impl::PythonTorchFunctionTLS::get_stack_at(i)->ptr(getPyInterpreter());
+    if (reinterpret_cast<PyObject*>(Py_TYPE(mode)) != g_device_mode) return true;
+  }
+  return false;
+}
+
 template <typename... A>
 PyObject* run(hif8_status (*fn)(A...), PyObject* const* args, Py_ssize_t n) {
   std::tuple<A...> values{};
   Seen seen;
   try {
-    if (fn == nullptr || n != (Py_ssize_t)sizeof...(A) || at::impl::torch_function_mode_enabled() ||
+    if (fn == nullptr || n != (Py_ssize_t)sizeof...(A) || seen_by_a_mode() ||
         !take_all(args, values, seen, std::index_sequence_for<A...>{}))
       Py_RETURN_NOTIMPLEMENTED;
   } catch (...) {  // a tensor without storage
@@ -172,11 +188,11 @@ PyObject* run(hif8_status (*fn)(A...), PyObject* const* args, Py_ssize_t n) {
 FUNCTIONS(SLOT)
 #undef SLOT
 
-// set_up(handle of the loaded library, check, device, raw_stream)
+// set_up(handle of the loaded library, check, device, raw_stream, type of the default device's mode or None)
 PyObject* set_up(PyObject*, PyObject* const* args, Py_ssize_t n) {
-  void* handle = n == 4 ? PyLong_AsVoidPtr(args[0]) : nullptr;
+  void* handle = n == 5 ? PyLong_AsVoidPtr(args[0]) : nullptr;
   if (handle == nullptr) {
-    if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "set_up(library handle, check, device, raw_stream)");
+    if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "set_up(library handle, check, device, raw_stream, device_mode)");
     return nullptr;
   }
   const char* missing = nullptr;
@@ -189,8 +205,8 @@ PyObject* set_up(PyObject*, PyObject* const* args, Py_ssize_t n) {
     PyErr_Format(PyExc_ImportError, "libhif8 has no %s", missing);
     return nullptr;
   }
-  PyObject** const to[3] = {&g_check, &g_device, &g_raw_stream};
-  for (int i = 0; i < 3; ++i) {
+  PyObject** const to[4] = {&g_check, &g_device, &g_raw_stream, &g_device_mode};
+  for (int i = 0; i < 4; ++i) {
     Py_INCREF(args[i + 1]);
     Py_XDECREF(*to[i]);
     *to[i] = args[i + 1];

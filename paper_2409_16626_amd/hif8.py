@@ -209,10 +209,14 @@ def _load_native():
         spec = importlib.util.spec_from_file_location("_native_call", path)
         native = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(native)
+        try:
+            from torch.utils._device import DeviceContext as device_mode  # of torch.set_default_device
+        except ImportError:
+            device_mode = None
         if _device is None or _raw_stream is None:
-            native.set_up(lib._handle, _check, torch.cuda.current_device, lambda device: torch.cuda.current_stream(device).cuda_stream)
+            native.set_up(lib._handle, _check, torch.cuda.current_device, lambda device: torch.cuda.current_stream(device).cuda_stream, device_mode)
         else:
-            native.set_up(lib._handle, _check, _device, _raw_stream)
+            native.set_up(lib._handle, _check, _device, _raw_stream, device_mode)
         return native
     except Exception as e:
         warnings.warn("no native argument marshalling, calls go through ctypes and take 1.6 us longer: %s" % e, RuntimeWarning, stacklevel=3)

@@ -34,6 +34,32 @@ def test_usual_arguments_and_errors():
         hif8.hif8_encode_f32(P, P, 16, scale=0.0, stream=0)
 
 
+def test_truth_values_stream_objects_and_a_default_device():
+    """pow2=True, a torch.cuda.Stream and torch.set_default_device are ordinary arguments: none of them goes through both ways."""
+    f = hif8._native.hif8_encode_f32
+
+    class Stream:
+        cuda_stream = 0
+
+    class Other:
+        cuda_stream = "s"
+
+    assert f(P, P, False, 1.0, True, 0) is None and f(P, P, 0, 1.0, 0, Stream()) is None
+    assert f(P, P, 0, 1.0, 0, Other()) is NotImplemented and f(P, P, 0, 1.0, 0, Stream) is None and f(P, P, 0, 1.0, 0, True) is NotImplemented
+    with pytest.raises(hif8.Hif8Error) as e:
+        f(None, P, True, 1.0, 0, Stream())
+    assert e.value.status == -1
+    with torch.device("cpu"):
+        assert f(P, P, 0, 1.0, 0, 0) is None
+    torch.set_default_device("cpu")
+    try:
+        assert f(P, P, 0, 1.0, 0, 0) is None
+    finally:
+        torch.set_default_device(None)
+    with pytest.raises(AttributeError):
+        hif8.hif8_encode_f32(P, P, 0, stream="s")
+
+
 class Sub(torch.Tensor):
     pass
 
@@ -45,7 +71,6 @@ def test_what_is_left_to_ctypes():
                  (P, P, None, 1.0, 0, 0), (P, P, 0, None, 0, 0), (P, P, 0, 1.0, -1, 0), (P, P, 0, 1.0, 1 << 32, 0), (P, P, 0, 1.0, 0, None), (P, P, 0, 1.0, 0, "s"),
                  (1 << 70, P, 0, 1.0, 0, 0), ("p", P, 0, 1.0, 0, 0), (P, P, 0, 10 ** 400, 0, 0)):
         assert f(*args) is NotImplemented, args
-    assert q(P, P, P, 0, 1.0, True, 0, P, P, P, 16, 0) is NotImplemented  # a truth value for an int
     assert q(P, P, P, 0, 1.0, 1, 0, P, P, P, None, 0) is NotImplemented  # no tensor to take the bytes from
     with pytest.raises(ValueError):
         hif8.hif8_encode_f32(cpu, P, 0, stream=0)
@@ -58,6 +83,11 @@ def test_what_is_left_to_ctypes():
 
     with Mode():
         assert f(P, P, 0, 1.0, 0, 0) is NotImplemented
+        with torch.device("cpu"):
+            assert f(P, P, 0, 1.0, 0, 0) is NotImplemented
+    with torch.device("cpu"), Mode():
+        assert f(P, P, 0, 1.0, 0, 0) is NotImplemented
+    assert f(P, P, 0, 1.0, 0, 0) is None
     assert not any(hasattr(hif8._native, n) for n in ("hif8_init", "hif8_calibrate_layer_f32", "hif8_multi_cast_f32"))
 
 
