@@ -498,6 +498,7 @@ inline bool small_from_codes(size_t M, size_t N, size_t K, const SmallRoute& x, 
 // 2560, and a row of the first operand is asked for by fewer dies at a time (2048 x 4096 x 11008 from cold memory 159 us with groups of 8, 155
 // with 4).  The wider tiles stay with 8: groups of 4 gave 1 % at 8192^3, but a product with a short K right behind its expansions took
 // longer (with expansions, groups of 8 / 4: 1537 x 6197 x 688 31.5 / 34.5, 2011 x 4511 x 1168 38.7 / 42.5).
+// 128 x 64 tiles, one to a compute unit, take the same with either (60 drawn products, groups of 8 over 4: 0.94 to 1.03, 1.001 in the mean).
 // The launch has tile_order_grid() workgroups; returns false
 // for the few at the end of the last die's share that have no tile.
 constexpr uint32_t kXcds = 8;    // accelerator dies, each with an L2 of its own
