@@ -732,7 +732,7 @@ struct AxisPlan {
 
 // shapes of the per-channel launches; sizes are limited to what 32-bit row / vector counts hold
 template <int KIND>
-bool plan_axis(int what, int axis, size_t rows, size_t cols, int cus, AxisPlan* p, uint32_t mode = kRmTA) {
+bool plan_axis(int what, int axis, size_t rows, size_t cols, int cus, AxisPlan* p, uint32_t mode = kRmTA, bool aligned = true) {
   constexpr size_t VE = vec_elems<KIND>();
   if (rows > 0x7FFFFFFFu || cols > 0x7FFFFFFFu) return false;
   p->cols_vec = (uint32_t)((cols + VE - 1) / VE);
@@ -750,7 +750,7 @@ bool plan_axis(int what, int axis, size_t rows, size_t cols, int cus, AxisPlan* 
   p->rows_per_wg = rpw;
   p->row_chunks = (uint32_t)((rows + rpw - 1) / rpw);
   if ((uint64_t)rows * p->chunks > 0x7FFFFFFFull || (uint64_t)p->row_chunks * p->strips > 0x7FFFFFFFull) return false;
-  p->fast = !axis_by_elements(what, axis, rows, cols, VE, axis == 0 ? (uint64_t)rows * p->chunks : (uint64_t)p->row_chunks * p->strips, mode);
+  p->fast = !axis_by_elements(what, axis, rows, cols, VE, axis == 0 ? (uint64_t)rows * p->chunks : (uint64_t)p->row_chunks * p->strips, mode, aligned);
   return true;
 }
 
@@ -808,7 +808,7 @@ hif8_status encode_axis(const void* src, uint8_t* dst, size_t rows, size_t cols,
   hif8_status s = ensure_init(&cus, &tb);
   if (s != HIF8_OK) return s;
   AxisPlan p;
-  if (!plan_axis<SRCK>(AXIS_CAST, axis, rows, cols, cus, &p, mode)) return HIF8_ERR_ARG;
+  if (!plan_axis<SRCK>(AXIS_ENCODE, axis, rows, cols, cus, &p, mode, aligned_to(src, 16))) return HIF8_ERR_ARG;
   const uint64_t seed = sr_seed();
   if (!p.fast) {
     hipLaunchKernelGGL(k_encode_axis_elem<SRCK>, dim3(grid_elem(rows * cols, cus)), dim3(256), 0, st, src, dst, rows,
@@ -899,7 +899,7 @@ hif8_status decode_axis(const uint8_t* src, void* dst, size_t rows, size_t cols,
   hif8_status s = ensure_init(&cus, &tb);
   if (s != HIF8_OK) return s;
   AxisPlan p;
-  if (!plan_axis<DSTK>(AXIS_CAST, axis, rows, cols, cus, &p)) return HIF8_ERR_ARG;
+  if (!plan_axis<DSTK>(AXIS_DECODE, axis, rows, cols, cus, &p, kRmTA, aligned_to(dst, 16))) return HIF8_ERR_ARG;
   if (!p.fast) {
     hipLaunchKernelGGL(k_decode_axis_elem<DSTK>, dim3(grid_elem(rows * cols, cus)), dim3(256), 0, st, src, dst, rows,
                        cols, axis, d_scale2);

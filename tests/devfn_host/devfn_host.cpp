@@ -38,9 +38,9 @@ int devfn_sample_holds(uint32_t sample, uint32_t amax, float target, float* scal
 // first tile of the piece that a sample reads, and the number of tiles from which on a tensor is sampled
 uint64_t devfn_sampled_piece(uint64_t offset, uint64_t tiles) { return hif8conv::sampled_piece(offset, tiles); }
 uint32_t devfn_sample_period() { return hif8conv::kSamplePeriod; }
-// whether a per-channel call goes to the element kernels (what: 0 maxima, 1 casts)
-int devfn_axis_by_elements(int what, int axis, size_t rows, size_t cols, size_t ve, uint64_t grid, uint32_t mode) {
-  return hif8calib::axis_by_elements(what, axis, rows, cols, ve, grid, mode);
+// whether a per-channel call goes to the element kernels (what: 0 maxima, 1 encode, 2 decode)
+int devfn_axis_by_elements(int what, int axis, size_t rows, size_t cols, size_t ve, uint64_t grid, uint32_t mode, int aligned) {
+  return hif8calib::axis_by_elements(what, axis, rows, cols, ve, grid, mode, aligned != 0);
 }
 // which way a list is cast: 0 by sample, 1 in groups, 2 in four launches
 int devfn_multi_cast_way(size_t count, uint64_t tiles, int host, int pow2, uint32_t mode) {

@@ -21,12 +21,13 @@ SRC = os.path.join(HERE, "devfn_host", "devfn_host.cpp")
 HDR = os.path.join(HERE, "..", "paper_2409_16626_amd", "csrc", "hif8_device.hpp")
 HDR2 = os.path.join(HERE, "..", "paper_2409_16626_amd", "csrc", "hif8_gemm_split.hpp")
 HDR3 = os.path.join(HERE, "..", "paper_2409_16626_amd", "csrc", "hif8_multi_plan.hpp")
+HDR4 = os.path.join(HERE, "..", "paper_2409_16626_amd", "csrc", "hif8_axis_plan.hpp")
 LIB = os.path.join(HERE, "devfn_host", "libdevfn_host.so")
 
 
 @pytest.fixture(scope="module")
 def dev():
-    newest = max(os.path.getmtime(f) for f in (SRC, HDR, HDR2, HDR3))
+    newest = max(os.path.getmtime(f) for f in (SRC, HDR, HDR2, HDR3, HDR4))
     if not os.path.exists(LIB) or os.path.getmtime(LIB) < newest:
         subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", LIB, SRC], check=True)
     lib = ctypes.CDLL(LIB)
@@ -600,30 +601,42 @@ def test_per_channel_calls_that_go_to_the_element_kernels(dev):
     """Narrow and small matrices, both sides of each line; what the vector kernels cannot take: rows shorter than a vector, launches of 2^32 lanes and more, vectors
     that may reach over the end of a standard SR block."""
     f = dev.devfn_axis_by_elements
-    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t, ctypes.c_size_t, ctypes.c_uint64, ctypes.c_uint32]
-    AMAX, CAST, TA, HR, TE, SSR, SR = 0, 1, 0, 1, 2, 3, 4
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t, ctypes.c_size_t, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int]
+    AMAX, ENCODE, DECODE, TA, HR, TE, SSR, SR, Ki, Mi = 0, 1, 2, 0, 1, 2, 3, 4, 1 << 10, 1 << 20
+    # columns and values of each line, by axis, call, vectors at multiples of 16 bytes or not, and vector
+    lines = {(0, ENCODE, False, 0): ((384, 640 * Ki), (320, 640 * Ki)), (0, ENCODE, False, 1): ((384, 512 * Ki), (320, 512 * Ki)),
+             (0, ENCODE, True, 0): ((448, 704 * Ki), (448, 704 * Ki)), (0, ENCODE, True, 1): ((384, 512 * Ki), (288, 512 * Ki)),
+             (0, DECODE, False, 0): ((1024, 3 * Mi), (640, 5 * Mi // 2)), (0, DECODE, False, 1): ((704, 704 * Ki), (512, 5 * Mi // 4)),
+             (1, ENCODE, False, 0): ((48, 3 * Mi // 2), (64, 9 * Mi // 4)), (1, ENCODE, False, 1): ((48, 5 * Mi // 4), (56, 2 * Mi)),
+             (1, ENCODE, True, 0): ((80, 5 * Mi // 2), (128, 13 * Mi // 4)), (1, ENCODE, True, 1): ((80, 5 * Mi // 2), (96, 3 * Mi)),
+             (1, DECODE, False, 0): (None, (112, 15 * Mi // 4)), (1, DECODE, False, 1): ((80, 2 * Mi), (80, 5 * Mi // 2))}
     for ve in (4, 8):
-        for what in (AMAX, CAST):
+        for what in (AMAX, ENCODE, DECODE):
             for axis in (0, 1):
-                assert f(what, axis, 1 << 22, ve - 1, ve, 100, TA) and f(what, axis, 1 << 23, 4096, ve, 1 << 24, TA)
-                assert not f(what, axis, 1 << 23, 4096, ve, (1 << 24) - 1, TA | 0x30)
+                assert f(what, axis, 1 << 22, ve - 1, ve, 100, TA, 1) and f(what, axis, 1 << 23, 4096, ve, 1 << 24, TA, 1)
+                assert not f(what, axis, 1 << 23, 4096, ve, (1 << 24) - 1, TA | 0x30, 1)
         # maxima: up to 32 columns by rows, 16 where there are few; by columns always in vectors
-        assert f(AMAX, 0, 1 << 20, 32, ve, 1, TA) and not f(AMAX, 0, 1 << 20, 33, ve, 1, TA) and not f(AMAX, 1, 1 << 20, 9, ve, 1, TA)
-        assert f(AMAX, 0, 100, 16, ve, 1, TA) and not f(AMAX, 0, 100, 17, ve, 1, TA)
+        assert f(AMAX, 0, 1 << 20, 32, ve, 1, TA, 1) and not f(AMAX, 0, 1 << 20, 33, ve, 1, TA, 1) and not f(AMAX, 1, 1 << 20, 9, ve, 1, TA, 1)
+        assert f(AMAX, 0, 100, 16, ve, 1, TA, 1) and not f(AMAX, 0, 100, 17, ve, 1, TA, 1)
+        for (axis, what, drawn, aligned), of in lines.items():
+            line = of[ve == 8]
+            for mode in (HR, SR) + (SSR,) * (axis == 0 or not aligned) if drawn else (TA, TE) + (SSR,) * (axis == 1 and aligned):
+                if line is None:  # binary32 by columns at any address: elements
+                    assert f(what, axis, 1 << 16, 5000, ve, 1, mode, 0) and f(what, axis, 1 << 16, 5001, ve, 1, mode, 1) and not f(what, axis, 1 << 16, 5000, ve, 1, mode, 1)
+                    continue
+                c, n = line
+                least = -(-c // ve) * ve if aligned else c
+                assert f(what, axis, 1 << 17, least - (ve if aligned else 1), ve, 1, mode, aligned) and not f(what, axis, 1 << 17, least, ve, 1, mode, aligned)
+                assert f(what, axis, 1 << 17, c - 1, ve, 1, mode, 1) == f(what, axis, 1 << 17, c - 1, ve, 1, mode, aligned and (c - 1) % ve == 0)  # an odd number of columns alone
+                cols = 64 * ve * 16 + 32 * ve
+                assert f(what, axis, n // cols, cols, ve, 1, mode, aligned) and not f(what, axis, n // cols + 1, cols, ve, 1, mode, aligned)
+        for mode in (HR, SR):  # 16 bits by columns, one vector in the last wavefront of a row
+            cols, n = 64 * ve + 1, 4 * Mi if ve == 8 else 5 * Mi // 2
+            assert f(ENCODE, 1, n // cols, cols, ve, 1, mode, 1) and not f(ENCODE, 1, n // cols + 1, cols, ve, 1, mode, 1)
         for mode in (TA, TE, HR, SSR, SR):
-            drawn = mode in (HR, SSR, SR)
-            c, n = (400, 1 << 18) if drawn else (256, 1 << 17)
-            assert f(CAST, 0, 1 << 16, c - 1, ve, 1, mode) and not f(CAST, 0, 1 << 16, c, ve, 1, mode)
-            assert f(CAST, 0, n // 4096, 4096, ve, 1, mode) and not f(CAST, 0, n // 4096 + 1, 4096, ve, 1, mode)
-            c = {4: (32, 56), 8: (40, 96)}[ve][drawn]
-            assert f(CAST, 1, 1 << 20, c - 1, ve, 1, mode) and not f(CAST, 1, 1 << 20, c, ve, 1, mode)
-            n = ve << (18 if drawn else 17)
-            assert f(CAST, 1, n // 4096, 4096, ve, 1, mode) and not f(CAST, 1, n // 4096 + 1, 4096, ve, 1, mode)
-            n, cols = ve << (19 if drawn else 17), 64 * ve + 1  # one vector in the last wavefront of a row
-            assert f(CAST, 1, n // cols, cols, ve, 1, mode) and not f(CAST, 1, n // cols + 1, cols, ve, 1, mode)
             # more than 2^32 elements: whole vectors to a row, or element by element under standard SR
-            assert not f(CAST, 0, 1 << 21, 4096, ve, 1, mode) and f(CAST, 0, 1 << 21, 4097, ve, 1, mode) == (mode == SR) == f(CAST, 1, 1 << 21, 4097, ve, 1, mode | 0x10)
-            assert not f(CAST, 0, (1 << 32) // 4097, 4097, ve, 1, mode)
+            assert not f(ENCODE, 0, 1 << 21, 4096, ve, 1, mode, 1) and f(ENCODE, 0, 1 << 21, 4097, ve, 1, mode, 1) == (mode == SR) == f(ENCODE, 1, 1 << 21, 4097, ve, 1, mode | 0x10, 1)
+            assert not f(ENCODE, 0, (1 << 32) // 4097, 4097, ve, 1, mode, 1)
 
 
 def test_finest_tile_with_a_compute_unit_each(dev):

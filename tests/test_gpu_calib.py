@@ -299,8 +299,8 @@ def test_per_channel_any_columns_and_address(h, rows, cols, off):
 
 # the vector kernels, which matrices that are neither narrow nor small take (axis_by_elements): several chunks of a row and one, whole vectors to a row or not; strips with a
 # vector in the last wavefront; the fewest columns that go there by rows and by columns
-@pytest.mark.parametrize("rows,cols,off", [(1100, 4099, 1), (1030, 4096, 0), (70, 70001, 1), (9000, 515, 0), (16500, 263, 1), (16500, 256, 0), (45000, 97, 1), (110000, 41, 0),
-                                           (44000, 96, 1)])
+@pytest.mark.parametrize("rows,cols,off", [(1100, 4099, 1), (1030, 4096, 0), (70, 70001, 1), (9000, 515, 0), (14000, 321, 1), (10500, 449, 1), (16500, 288, 0), (45000, 97, 1),
+                                           (70000, 65, 0), (70000, 56, 0), (44000, 96, 0), (40000, 129, 1)])
 def test_per_channel_vector_kernels(h, rows, cols, off):
     test_per_channel_any_columns_and_address(h, rows, cols, off)
 
