@@ -55,4 +55,13 @@ inline bool axis_by_elements(int what, int axis, size_t rows, size_t cols, size_
   return cols < line.cols || n <= line.values;
 }
 
+// Maximum, scale and codes of rows in three launches by elements instead of one pass in vectors, in which a wavefront has a row and few lanes at work on a narrow one (us, one pass / three
+// launches: 223270 rows of 4 binary32 values TA 29 / 10, SR 61 / 11, of 16 32 / 22, 62 / 25, of 24 32.8 / 35.2; of 8 bfloat16 36 / 12, 93 / 15, of 24 39 / 26, of 32 38.8 / 37.7; 50000 rows of 8
+// bfloat16 TA 10.2 / 10.2, SR 23.9 / 10.2; 5000 4.5 / 10.5).
+inline bool rows_by_elements(size_t rows, size_t cols, size_t ve, uint32_t mode) {
+  const uint32_t rm = mode & 0xFu;
+  const bool drawn = rm == hif8dev::kRmHR || rm == hif8dev::kRmSSR || rm == hif8dev::kRmSR;
+  return cols <= (ve == 4 ? 16u : 24u) && rows >= (drawn ? 60000u : 100000u);
+}
+
 }  // namespace hif8calib

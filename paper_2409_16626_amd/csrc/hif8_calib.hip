@@ -832,7 +832,7 @@ hif8_status encode_axis(const void* src, uint8_t* dst, size_t rows, size_t cols,
   return finish_launch();
 }
 
-// Fused per-row path when a row has at least one vector and fits the registers of one workgroup;
+// Fused per-row path when a row has at least one vector and fits the registers of one workgroup, but for many narrow rows;
 // otherwise the three separate launches (same results).
 template <int SRCK>
 hif8_status quantize_rows(const void* src, uint8_t* dst, size_t rows, size_t cols, float target, int pow2, uint32_t mode,
@@ -848,7 +848,7 @@ hif8_status quantize_rows(const void* src, uint8_t* dst, size_t rows, size_t col
   if (s != HIF8_OK) return s;
   constexpr size_t VE = vec_elems<SRCK>();
   const size_t cols_vec = (cols + VE - 1) / VE;
-  if (cols < VE || cols_vec > (size_t)kQrBlock * 8 || !vectors_in_blocks(rows, cols, VE, mode)) {
+  if (cols < VE || cols_vec > (size_t)kQrBlock * 8 || !vectors_in_blocks(rows, cols, VE, mode) || rows_by_elements(rows, cols, VE, mode)) {
     s = amax_axis<SRCK>(src, rows, cols, 0, d_amax, st);
     if (s != HIF8_OK) return s;
     s = hif8host::launch_scale_from_amax(d_amax, d_scale2, (uint32_t)rows, target, pow2, st);
