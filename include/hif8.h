@@ -414,8 +414,10 @@ hif8_status hif8_scale_sweep_f16(const uint16_t* src, size_t n, int e_lo, int co
  *   hif8_encode_axis_*      dst[r, c] = code(Q(fl32(x[r, c] * scale[ch])))  (standard-SR thresholds
  *                           are indexed by the flat element index r * cols + c)
  *   hif8_decode_axis_*      dst[r, c] = narrow(fl32(value(src[r, c]) * fl32(1 / scale[ch])))
- * The fast paths need 16-byte aligned matrices (codes: 4 / 8 bytes as for hif8_encode_*) and
- * cols a multiple of 4 (FP32) or 8 (16-bit); anything else takes an element-per-lane path.
+ * Any cols and any address of the elements.  Rows of at least one 16-byte vector (4 FP32 or 8 16-bit
+ * values) are read in vectors wherever they begin, fastest at multiples of 16 bytes; narrow and small
+ * matrices take an element-per-lane path, chosen by size, which is the faster one there, and so do
+ * standard-SR casts of more than 2^32 elements with cols not a multiple of a vector.  The results are the same.
  * rows and cols must each be below 2^31.
  */
 hif8_status hif8_scale_from_amax_n(const float* d_amax, float* d_scale2, size_t count, float target,
@@ -450,9 +452,10 @@ hif8_status hif8_decode_axis_f16(const uint8_t* src, uint16_t* dst, size_t rows,
  *     d_scale2[2 r], [2 r + 1] = scale, fl32(1 / scale)    as hif8_scale_from_amax(d_amax[r], target, pow2)
  *     dst[r, c]  = code(Q(fl32(src[r, c] * scale)))
  * i.e. exactly what hif8_amax_axis_* (axis 0), hif8_scale_from_amax_n and hif8_encode_axis_* (axis 0)
- * produce in three launches and two reads of the source.  The single-pass form needs the fast-path
- * alignment of hif8_encode_axis_* and at most 16,384 (FP32) or 32,768 (16-bit) columns; other inputs
- * are handed to the three separate launches.  All pointers are device pointers owned by the caller;
+ * produce in three launches and two reads of the source.  The single-pass form takes rows of 4 to 16,384
+ * (FP32) or 8 to 32,768 (16-bit) columns at any address; other inputs, standard-SR casts of more than
+ * 2^32 elements with cols not a multiple of 4 or 8, and many rows (from 60,000 on) of at most 16 or 24
+ * columns are handed to the three separate launches.  All pointers are device pointers owned by the caller;
  * rows == 0 is a no-op; HIF8_ERR_NULL for a null d_amax or d_scale2 (or null data with rows * cols > 0),
  * HIF8_ERR_MODE / HIF8_ERR_ARG as for the separate calls.
  */
@@ -541,7 +544,8 @@ hif8_status hif8_als_update(hif8_als_state* st, int found_overflow);
  * operands.  M, N, K < 2^31.
  *   hif8_gemm_sqerr   no output matrix: *d_err += sum (out[m, n] - ref[m, n])^2 in fp64
  *                     (ref: [M, N] FP32; the caller clears *d_err) -- the "Quantization Error"
- *                     step of Algorithm 1.
+ *                     step of Algorithm 1.  Same error bound for out; its sums may be taken in another
+ *                     order than those of hif8_gemm_f32.
  */
 hif8_status hif8_gemm_f32(const uint8_t* a_codes, const uint8_t* b_codes, float* out, size_t M,
                           size_t N, size_t K, float scale_a, float scale_b, hif8_stream_t stream);

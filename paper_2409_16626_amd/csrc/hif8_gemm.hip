@@ -15,7 +15,7 @@
 // double-buffered LDS tile, with the next tile's codes in flight in registers during the MFMAs.  What bounds it is the LDS: of a
 // step of a 256 x 128 x 64 tile the table look-ups take 768 cycles, the fragments 512 and the expanded codes' stores 384, the MFMAs 1024 on
 // each SIMD and the vector instructions (3.7 a code) as much; 1024 x 8192 x 4096 keeps the LDS 54 %, the vector ALUs 46 % and the
-// matrix cores 33 % busy and takes 86 us.  A look-up is needed per row or column and K of a workgroup's tile, so a larger tile needs fewer per MFMA;
+// matrix cores 33 % busy and takes 86 to 105 us, by the clock of the chip.  A look-up is needed per row or column and K of a workgroup's tile, so a larger tile needs fewer per MFMA;
 // BK = 64 makes fewer, longer steps (256 x 128 with BK = 32: 120 us).  16 wavefronts do no better (93 us), two workgroups of 128 x 128 tiles
 // on a compute unit need a third more look-ups (121 us).
 #include <hip/hip_runtime.h>
@@ -396,7 +396,7 @@ static hif8_status gemm_ws(const uint8_t* A, const uint8_t* B, void* out, const 
   if (EPI == EPI_ERR ? (!ref || !err) : !out) return HIF8_ERR_NULL;
   if (ws_bytes < need || !aligned_to(ws, 16)) return HIF8_ERR_ARG;
   if (EPI == EPI_ERR && !aligned_to(err, 8)) return HIF8_ERR_ARG;
-  // few rows: straight from the codes, which gives the bits that the expanded operands would give (see small_plan)
+  // few rows: straight from the codes, which gives the bits that the expanded operands would give (see small_choice)
   if (expanded_variant() == 0 && (M < N ? M : N) <= kSmallCodesRows && small_problem(M, N, expanded_ld(K), false, EPI == EPI_ERR))
     return gemm_small<EPI>(A, B, false, out, ref, err, M, N, K, small_choice(M, N, K, true, EPI == EPI_ERR), descale, st);
   const size_t ld = expanded_ld(K);

@@ -13,7 +13,7 @@
 // aligned), passes them through its own 2 KiB of LDS per 16-row block, with the loads of the next 128 bytes in flight
 // meanwhile, and expands codes on their way from there into the fragments of v_mfma_f32_16x16x32_bf16 through a
 // 256-entry table in LDS.  That table look-up, one LDS read and two vector instructions per element, is the larger part of
-// the code form: without it 8 x 11008 x 4096 takes 11 us, without the loads 14 us, as it is 14 us; the LDS is active 56 % of
+// the code form: 8 x 11008 x 4096 took 14 us, without it 11, without the loads 14, and takes 12.6 with the shorter one; the LDS is active 56 % of
 // the cycles, a fifth of them bank conflicts, the vector ALUs half (with three vector instructions 55 %).  Conflicts weigh more than
 // instructions: without table_slots(), half an instruction less per element, it is 4 to 6 % slower.  With one workgroup per compute unit (509 x 1003 x 2049) both
 // are busy a quarter of the time, and the chain of loads, stages and the sum counts.  (8 x 11008 x 4096: 45 MB, 7.5 us at

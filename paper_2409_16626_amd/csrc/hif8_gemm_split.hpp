@@ -11,8 +11,9 @@ namespace hif8gemm {
 
 // A ragged last round of 256 x 256 tiles leaves most compute units idle for a whole tile time.  When that
 // round would be at most half full, the large tiles get as many whole tile columns as fill complete rounds
-// (columns [0, *split)) and the remaining columns go to 128 x 128 tiles -- a quarter of the work each, two
-// workgroups per compute unit, one round -- in a second launch.  Returns false where one launch is better.
+// (columns [0, *split)) and the remaining columns may go to smaller tiles in a second launch: of expanded operands 128 x 128 -- a quarter
+// of the work each, two workgroups per compute unit, one round --, of code operands the tile with the lowest price, one workgroup per compute unit
+// and one round or two.  Returns false where there is no such round; the callers compare prices.
 inline bool ragged_round_split(size_t M, size_t N, size_t cus, uint32_t* split) {
   const size_t tm = (M + 255) / 256, tn = (N + 255) / 256, tiles = tm * tn;
   if (cus == 0 || tiles <= cus || tiles % cus == 0) return false;
@@ -221,7 +222,8 @@ inline size_t small_resident(uint32_t tm, uint32_t tn, uint32_t waves, bool code
   const uint32_t by_regs = 4u * (blocks == 1u ? 6u : blocks == 2u ? 5u : blocks == 4u ? 4u : blocks == 8u && !codes ? 3u : 2u) / waves;
   return 256u * (by_lds < by_regs ? by_lds : by_regs);
 }
-// The same on one compute unit, for the kernels that store: by the registers that they take (a wavefront's, codes / expanded: 1 x 1 67 (half-row form 75) / 60, 1 x 2 87 / 76, 1 x 3 107 /
+// The same on one compute unit, for the price: by the registers of the kernels that store as they are built now.  small_plan()'s wavefronts, which are part
+// of a result's rounding, stay with the number above, from earlier kernels.  By the registers that they take (a wavefront's, codes / expanded: 1 x 1 67 (half-row form 75) / 60, 1 x 2 87 / 76, 1 x 3 107 /
 // 96, 2 x 2 120 / 112, 2 x 3 140 / 130, 2 x 4 160 / 152, 3 x 4, 4 x 3 and 4 x 4 192 to 236).
 constexpr uint32_t small_resident_stored(const SmallPlan& p, bool codes) {
   const uint32_t by_lds = 160u * 1024u / (512u + p.waves * (p.tm + p.tn) * 2048u), blocks = p.tm * p.tn;
@@ -267,6 +269,7 @@ inline SmallPlan small_plan(size_t M, size_t N, size_t K, bool codes, bool sqerr
 // K one stage after the other, and as many tiles as fit at a time go side by side; then the partial tiles are added.  The constants
 // are a least-squares fit, in the logarithm, to 296 shapes of 4 to 1000 rows on codes and 178 on expanded operands, weights from memory, each in up to 40
 // tiles and numbers of wavefronts: 13 and 12 % off on average.
+constexpr size_t kPricedUnits = 256;  // compute units of the chip that the prices of the small tiles, and of what they are compared with, were measured on
 struct SmallRates {
   double base, lds, wave, unit, turn, add, memory;
 };
@@ -295,7 +298,7 @@ struct SmallCost {
     uint32_t turns;
   };
   Tile tile(uint32_t tm, uint32_t tn) const {
-    const uint64_t tiles = (uint64_t)tiles_m[tm] * tiles_n[tn], of_unit = (tiles + 255u) / 256u;
+    const uint64_t tiles = (uint64_t)tiles_m[tm] * tiles_n[tn], of_unit = (tiles + (kPricedUnits - 1)) / kPricedUnits;
     const uint32_t turns = of_unit > 0xFFFFFF00u ? 0xFFFFFF00u : (uint32_t)of_unit;
     const double rows = (codes && M <= 8 && tm * tn == 1u ? 0.5 : (double)tm) + tn;
     return Tile{rows, fourth((double)turns * units * rows * kSmallRates[codes ? 1 : 0].lds), turns};
@@ -456,7 +459,7 @@ inline SmallRoute small_route(size_t M, size_t N, size_t K, bool codes, bool sqe
   const size_t s = M < N ? M : N;
   auto tiles = [&](size_t side) { return ((M + side - 1) / side) * ((N + side - 1) / side); };
   auto by_lines = [&] { return small ? SmallRoute{true, small_choice(M, N, K, codes, sqerr), none} : SmallRoute{false, none, none}; };
-  if (s <= (codes ? 32 : kSmallCodesRows) || (codes ? tiles(128) > 512 : tiles(64) > 256) || K < 320) return by_lines();  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
+  if (s <= (codes ? 32 : kSmallCodesRows) || (codes ? tiles(128) > 2 * kPricedUnits : tiles(64) > kPricedUnits) || K < 320) return by_lines();  // a shorter K gains little (256 x 1048 x 240 5.6 / 5.1)
   if (sqerr) {
     if (codes || !small || !small_problem(M, N, K, false, false) || small_route(M, N, K, false, false).small) return by_lines();
     return SmallRoute{false, none, none};
@@ -466,7 +469,7 @@ inline SmallRoute small_route(size_t M, size_t N, size_t K, bool codes, bool sqe
   const double us = SmallCost(M, N, K, codes).us(r.plan);
   if (codes) {
     double tiled = 0.0;
-    codes_tile(M, N, K, 256, &tiled);
+    codes_tile(M, N, K, kPricedUnits, &tiled);
     r.small = us < tiled;
     return r;
   }

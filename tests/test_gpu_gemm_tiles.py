@@ -204,8 +204,17 @@ def test_squared_error_of_more_tiles_than_workgroups(h):
 def test_scale_search_over_every_tile(h, variant):
     """Every pair of a 10 x 7 search meets its own operands, scale and place in the table (edge tiles; with 256 x 256 tiles
     420 tiles on at most 256 workgroups): each entry against the same product made alone."""
+    search_against_products_alone(h, variant, 300, 520, 130, 10, 7)
+
+
+# 24 tiles of 64 x 64 (a single chain over K, and a part of K every two steps) and 162 of 128 x 64, whose 64 x 64 tiles would be more than the compute units
+@pytest.mark.parametrize("M,N,K,na,nb", [(65, 40, 130, 4, 3), (65, 40, 1100, 4, 3), (128, 130, 200, 9, 6)])
+def test_scale_search_in_the_finest_tiles(h, M, N, K, na, nb):
+    search_against_products_alone(h, 9, M, N, K, na, nb)
+
+
+def search_against_products_alone(h, variant, M, N, K, na, nb):
     rng = np.random.default_rng(5)
-    M, N, K, na, nb = 300, 520, 130, 10, 7
     x = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).to(dev())
     w = torch.from_numpy((rng.standard_normal((N, K)) * 0.02).astype(np.float32)).to(dev())
     ref = (x.double() @ w.double().t()).float()
@@ -391,7 +400,7 @@ def test_workspace_product_expands_both_operands(h):
 
 
 # tiles of 64 x 64 (one and four K steps more than its four stages, and fewer), 128 x 64 in six stages, and 128 x 128 where the finer ones are too many; edges of
-# their blocks, rows at unaligned addresses; pairs of a scale search
+# their blocks, rows at unaligned addresses
 @pytest.mark.parametrize("M,N,K", [(1, 1, 64), (66, 63, 128), (129, 190, 192), (700, 1227, 256), (513, 1003, 330), (64, 64, 520), (1000, 1023, 1000),
                                    (520, 2578, 64), (1030, 1101, 256), (513, 2049, 320), (900, 1153, 384), (641, 3001, 450), (1024, 2048, 770),
                                    (1500, 2003, 200), (1030, 4001, 330)])
